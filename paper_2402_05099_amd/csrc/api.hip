@@ -24,6 +24,8 @@ struct hg_ctx {
     int opt_suffix_ipw;    // matrix-core suffix kernel: work items per wavefront (0 automatic)
     int opt_suffix_tile;   // matrix-core suffix kernel: query rows per tile (0 automatic, 16, 32)
     int opt_fused_kernel;  // fused call: 0 automatic, 1 separate kernels, 2 single launch whenever it applies
+    unsigned* arrivals;    // kArrivalCounters device counters, zero between calls (null: none left, calls are not split)
+    int arrivals_slot;
     hipStream_t aux;       // second stream for the overlap option
     hipEvent_t ev_fork, ev_join;
     // stage timing ring: slot = call % HG_TIMING_RING, 2 events (begin, end) per stage
@@ -40,6 +42,20 @@ struct hg_ctx {
 static __device__ __align__(256) unsigned char scratch[HG_STATIC_SCRATCH_BYTES];
 static unsigned char* g_scratch_ptr[64];   // per device, set by hg_create on that device
 static std::mutex g_scratch_mu;
+
+// Arrival counters of the kernels whose workgroups meet (fused_small.hip): a fixed array in the device image (zero when
+// the library is loaded, and every kernel leaves its counters at zero), handed out to contexts in slots.  A destroyed
+// context's last kernel may still be running, so its slot is used again only once all fresh ones are gone and after
+// the device has been waited for; a context that finds no slot works without.
+constexpr int kArrivalSlots = 1024;
+static __device__ unsigned arrival_counters[kArrivalSlots * hg::kArrivalCounters];
+struct ArrivalPool {
+    unsigned* base = nullptr;
+    int fresh = 0;                   // slots never handed out start here
+    int n_ready = 0, n_retired = 0;
+    int ready[kArrivalSlots], retired[kArrivalSlots];
+};
+static ArrivalPool* g_arrivals[64];   // per device, guarded by g_scratch_mu
 
 namespace {
 
@@ -340,6 +356,39 @@ int pick_wide_slots(double flops, double bytes, int T) {
     return best;
 }
 
+// A context's arrival counters on `device` (current), or null.
+unsigned* take_arrivals(int device, int* slot) {
+    *slot = -1;
+    if (device < 0 || device >= 64) return nullptr;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    ArrivalPool*& pool = g_arrivals[device];
+    if (!pool) {
+        void* p = nullptr;
+        if (hipGetSymbolAddress(&p, HIP_SYMBOL(arrival_counters)) != hipSuccess || !p) return nullptr;
+        pool = new (std::nothrow) ArrivalPool();
+        if (!pool) return nullptr;
+        pool->base = static_cast<unsigned*>(p);
+    }
+    if (pool->fresh < kArrivalSlots) {
+        *slot = pool->fresh++;
+    } else {
+        if (pool->n_ready == 0 && pool->n_retired > 0 && hipDeviceSynchronize() == hipSuccess) {
+            for (int i = 0; i < pool->n_retired; ++i) pool->ready[pool->n_ready++] = pool->retired[i];
+            pool->n_retired = 0;
+        }
+        if (pool->n_ready == 0) return nullptr;
+        *slot = pool->ready[--pool->n_ready];
+    }
+    return pool->base + (size_t)*slot * kArrivalCounters;
+}
+
+void give_arrivals(int device, int slot) {
+    if (slot < 0) return;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    ArrivalPool* const pool = g_arrivals[device];
+    pool->retired[pool->n_retired++] = slot;
+}
+
 int fill_empty(void* O, int o_dtype, float* LSE, int64_t rows, int D, hipStream_t s) {
     FillArgs f{};
     f.O = O; f.LSE = LSE; f.bf16 = (o_dtype == HG_BF16); f.rows = rows; f.D = D;
@@ -369,6 +418,7 @@ int hg_create(hg_ctx** out, int device, void* hip_stream, void* workspace, size_
     }
     hg_ctx* c = new (std::nothrow) hg_ctx();
     if (!c) return HG_ERR_HIP;
+    c->arrivals_slot = -1;
     c->device = device;
     c->stream = static_cast<hipStream_t>(hip_stream);
     c->ws = static_cast<unsigned char*>(workspace);
@@ -391,12 +441,14 @@ int hg_create(hg_ctx** out, int device, void* hip_stream, void* workspace, size_
         hg_destroy(c);
         return HG_ERR_HIP;
     }
+    c->arrivals = take_arrivals(device, &c->arrivals_slot);
     *out = c;
     return HG_OK;
 }
 
 void hg_destroy(hg_ctx* c) {
     if (!c) return;
+    give_arrivals(c->device, c->arrivals_slot);
     if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
     if (c->ev_join) (void)hipEventDestroy(c->ev_join);
     if (c->aux) (void)hipStreamDestroy(c->aux);
@@ -655,47 +707,62 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     const int64_t rows = (int64_t)B * nq * Hq;
     const int G = Hq / Hkv;
     const bool has_suffix = Ks != nullptr && max_len > 0;
+    const Ws ws = ws_override ? *ws_override : Ws{c->ws, c->ws_bytes};
 
-    // One launch for everything when that is the faster way (packed bf16 suffix rows only): a workgroup of four
-    // wavefronts per 32-row tile walks every shared block and the tile's suffixes and merges in LDS (fused_small.hip),
-    // against three launches, two event edges and a round trip of the partial results through HBM for the separate
-    // kernels.  Both durations are estimated, in microseconds, from fits to measurements on the shape of Sec. 4.2
-    // (eight query heads per KV head, B = 64 .. 2048, 256 .. 16384 shared keys, 128 and 512 suffix rows):
-    //   single launch: 9 + c x (stages of a tile / 4 wavefronts) x rounds of 256 workgroups, c = 1.24 us per 32-key
-    //                  stage while at most half the CUs are busy, 1.6 when the chip is full; never faster than the
-    //                  suffix rows stream in (5.5 TB/s);
-    //   separate:      24 for the launches and the merge + suffix rows at 5 TB/s + shared blocks at 1.1 PFLOP/s, 8 more
-    //                  once a block is long enough to be split.
-    // The host knows only an upper bound of the suffix lengths: the single launch is priced at that bound, the separate
-    // kernels at a mean of 0.75 of it.  The single launch is taken when its estimate is at most 130 us (beyond that the
-    // fit is optimistic: tiles of many short suffixes, 32 per tile with one query row per KV head, pay per segment) and
-    // below the other estimate, by a tenth once it exceeds 40 us.  With ragged lengths this errs towards the separate
-    // kernels (measured on the full-size configurations, single launch against separate kernels: 0.241 / 0.150 ms,
-    // 0.415 / 0.330, 0.578 / 0.370, 0.305 / 0.180, 0.712 / 0.577: there the separate kernels must be, and are, chosen).
-    if (!pg.table && !fmt.fp8 && c->opt_fused_kernel != 1 && !c->opt_timing) {
+    // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
+    // column of 32 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two
+    // event edges and a round trip of the partial results through HBM for the separate kernels.  Both durations are
+    // estimated, in microseconds, from fits to 82 shapes (B = 4 .. 2048, 0 .. 16K shared keys, every cache and head layout):
+    //   single launch: 4 + rounds x (4 + c x stages per wavefront), c = 1.6 us per 32-key stage while a quarter of the CUs
+    //                  are busy (the latency of one stage's K and V rows), 2.3 with all of them; 4.5 + 0.3 x splits more when
+    //                  a column's workgroups have to meet; never faster than the rows stream in (5 TB/s);
+    //   separate:      18, 6 and 10 more with one and two shared levels, 8 more once a block is long enough to be split,
+    //                  suffix rows at 5 TB/s, shared blocks at 1.1 PFLOP/s or 5 TB/s.
+    // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single
+    // launch is taken below the other estimate, from 60 us on only when it is 25 % below (the model of the separate kernels
+    // is pessimistic where suffixes and shared blocks overlap).  Measured single / separate: 12.4 / 25 us (72 sequences,
+    // 206 rows), 17.3 / 26 (2.5K shared keys, 16 sequences), 15.9 / 31.5 (256 sequences, 1K keys), 222 / 151 (256 x 40 heads, 2K
+    // keys: not taken), 257 / 203 (1024 x 40 heads at D = 64: not taken).
+    if (c->opt_fused_kernel != 1 && !c->opt_timing) {
         const int rps = nq * G;
         long long shared_keys = 0;
-        double flops = 0.0;
+        double flops = 0.0, shared_bytes = 0.0;
         bool any = has_suffix;
+        int nonempty = 0;
         for (int i = 0; i < n_levels; ++i) {
             const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B;
             if (levels[i].max_rows > 0 && seqs > 0) {
                 shared_keys += levels[i].max_rows;
                 flops += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * seqs * nq * Hq * D;
+                shared_bytes += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * Hkv * D;
                 any = true;
+                ++nonempty;
             }
         }
         const int seqs_per_tile = rps >= 32 ? 1 : (32 + rps - 1) / rps + (32 % rps ? 1 : 0);
-        const long long stages = (shared_keys + 31) / 32 + (has_suffix ? (long long)seqs_per_tile * ((max_len + 31) / 32) : 0);
+        const long long seqs_here = seqs_per_tile < B ? seqs_per_tile : B;
+        const double stages = (double)((shared_keys + 31) / 32) + (has_suffix ? seqs_here * ((0.75 * max_len + 16.0) / 32.0) : 0.0);
         const long long tiles = ((long long)B * rps + 31) / 32;
-        const double wgs = (double)(tiles * Hkv);
-        const double rounds = wgs > 256.0 ? wgs / 256.0 : 1.0;
-        const double suffix_us = has_suffix ? 4.0 * B * (double)max_len * Hkv * D / 5.0e6 : 0.0;      // at 5 TB/s
-        const double chain_us = 9.0 + (wgs <= 128.0 ? 1.24 : 1.6) * (double)((stages + 3) / 4) * rounds;
-        const double est_single = std::max(chain_us, suffix_us * (5.0 / 5.5) + 4.0);
-        const double est_separate = 24.0 + 0.75 * suffix_us + (shared_keys >= 1024 ? 8.0 : 0.0) + flops / 1.1e9;
-        const bool small = est_single <= 130.0 && est_single <= (est_single <= 40.0 ? 1.0 : 0.9) * est_separate;
-        if (any && tiles * Hkv < (1LL << 31) && (c->opt_fused_kernel == 2 || small)) {
+        const long long cols = tiles * Hkv;
+        const double per_round = D == 128 ? 256.0 : 512.0;       // workgroups that run at a time (LDS)
+        auto chain_at = [&](int S) {
+            const double wgs = (double)cols * S;
+            const double per_stage = 1.6 + 0.7 * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0));
+            return 4.0 + ceil(wgs / per_round) * (4.0 + per_stage * ceil(stages / (8.0 * S))) + (S > 1 ? 4.5 + 0.3 * S : 0.0);
+        };
+        int splits = 1;
+        if (c->arrivals && cols * 2 <= 256 && cols <= kArrivalCounters) {
+            const int most = (int)std::min<long long>(256 / cols, kSmallMaxSplits);
+            for (int S = 2; S <= most; ++S)
+                if (chain_at(S) < 0.95 * chain_at(splits) && small_part_floats((int)cols, S, D) * sizeof(float) <= ws.bytes) splits = S;
+        }
+        const double suffix_us = has_suffix ? (fmt.fp8 ? 2.0 : 4.0) * B * (0.75 * max_len) * Hkv * D / 5.0e6 : 0.0;      // at 5 TB/s
+        const double shared_us = shared_bytes / 5.0e6;
+        const double est_single = std::max(chain_at(splits), suffix_us + shared_us + 7.0);
+        const double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
+                                    suffix_us + std::max(flops / 1.1e9, shared_us);
+        const bool small = est_single <= (est_single <= 60.0 ? 1.0 : 0.75) * est_separate;
+        if (any && cols * splits < (1LL << 31) && (c->opt_fused_kernel == 2 || small)) {
             SmallArgs sa{};
             sa.Q = static_cast<const uint16_t*>(Q);
             sa.n_levels = 0;
@@ -708,15 +775,22 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
             sa.Vs = static_cast<const uint16_t*>(Vs);
             sa.offsets = offsets;
             sa.lengths = has_suffix ? lengths : nullptr;
+            sa.pg = has_suffix ? pg : PagedDev{};
+            sa.fp8 = has_suffix ? fmt.fp8 : 0;
+            sa.k_scale = fmt.k_scale; sa.v_scale = fmt.v_scale;
             sa.max_len = max_len;
             sa.B = B; sa.Hq = Hq; sa.Hkv = Hkv; sa.G = G; sa.nq = nq;
             sa.tiles = (int)tiles;
+            sa.cols = (int)cols;
+            sa.splits = splits;
+            sa.part = reinterpret_cast<float*>(ws.p);
+            sa.arrivals = c->arrivals;
             sa.scale = scale;
             sa.O = O_out; sa.LSE = LSE_out; sa.bf16 = (o_dtype == HG_BF16);
             return hip_rc(launch_fused_small(sa, D, c->stream));
         }
     }
-    const Parts parts = carve(ws_override ? *ws_override : Ws{c->ws, c->ws_bytes}, rows, D);
+    const Parts parts = carve(ws, rows, D);
 
     // plan: parts per level and for the suffix, shrunk to fit the workspace
     LevelDev lv[HG_MAX_LEVELS];

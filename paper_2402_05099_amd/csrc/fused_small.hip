@@ -1,20 +1,39 @@
 // The whole of Hydragen's attention (App. B's top-level routine: attention over every shared block, attention over each
 // sequence's own suffix, and the merge of the parts by their log-sum-exp, Eq. 5) in ONE launch, for calls with so
-// little work that three launches, a second stream and a pass over partial results in HBM cost more than the
-// arithmetic.  No workspace, no partial result leaves the chip.
+// little work that several launches and a pass over partial results cost more than the arithmetic.
 //
-// A workgroup owns 32 consecutive rows of the query rows of one KV head (Sec. 3.2's inter-sequence batching: row
-// r = sequence * nq * G + query * G + head-in-group).  Their keys are a list of segments: the block of every shared
-// level that covers their sequences (all rows of the tile attend to it, or those of the covered sequences when a
+// A column is 32 consecutive rows of the query rows of one KV head (Sec. 3.2's inter-sequence batching: row
+// r = sequence * nq * G + query * G + head-in-group).  Its keys are a list of segments: the block of every shared
+// level that covers its sequences (all rows of the tile attend to it, or those of the covered sequences when a
 // block boundary falls inside the tile), then the suffix of each of the tile's sequences (only that sequence's rows
 // attend).  Softmax over the union of all segments is one online softmax: a row that does not attend to a segment has
-// its scores masked.  The decomposition of Eq. 5 appears twice: the list is cut into four equal runs of 32-key
-// stages, one per wavefront, each with its own running maximum, sum and accumulator; at the end the four partial
-// results meet in LDS and are combined with the weights exp(LSE_i - max LSE) into the final (O, LSE).
+// its scores masked.  The decomposition of Eq. 5 appears twice: the list is cut into equal runs of 32-key stages, one
+// per wavefront of the column's workgroups, each with its own running maximum, sum and accumulator; the eight partial
+// results of a workgroup meet in LDS and are combined with the weights exp(LSE_i - max LSE).
 //
-// A wavefront streams its stages through a private ring of two 16 KiB slots (HBM -> LDS copies issued from inline
-// asm, counted s_waitcnt, one stage ahead) and multiplies on v_mfma_f32_32x32x16_bf16 with the transposed products,
-// XOR swizzles and lazy rescaling of the other kernels (prefix_wide.hip, decode_mfma.hip).
+// A column is worked on by `splits` workgroups (as many as leave the chip full: a small call has few columns, and one
+// workgroup per column would leave most CUs idle).  With more than one, each writes its combined result to the
+// workspace and counts itself in at the column's arrival counter; the last to arrive combines the column's results and
+// sets the counter back to zero for the next call.  No workgroup ever waits for another.
+//
+// A wavefront streams its stages through one K slot and one V slot of 8 KiB of its own (HBM -> LDS copies issued from
+// inline asm, counted s_waitcnt): the next stage's K rows are requested as soon as this stage's scores are done, its V
+// rows after the second product.  With eight wavefronts per workgroup (two per SIMD) that keeps as many bytes in
+// flight as four wavefronts with two slots for each, and the second wavefront fills the first one's waits.
+// Products, XOR swizzles and lazy rescaling are those of the other kernels (prefix_wide.hip, decode_mfma.hip).
+//
+// What bounds it: latency.  A call of one stage per wavefront takes about 10 us (launch 2, lengths, Q and the key list
+// 3, first rows 2, one stage 1.5, combination and output 1.5), every further stage 1.6 us (2.3 with all CUs busy), the
+// meeting of a column's workgroups 5.  Measured, four wavefronts and one workgroup per column before, this form after:
+// 256 sequences x 8 heads on one KV head, 1024 shared keys, 128 suffix rows 23.4 -> 15.9 us; 45 x 16 heads on two KV
+// heads, 515 keys, ragged up to 150 rows 19.2 -> 13.6; paged and 8-bit caches, which took the separate kernels:
+// 25-50 -> 15-25 us on calls of that size.
+//
+// PAGED: the suffix rows are found through a page table; FP8: they are E4M3 codes with one scale per tensor, expanded
+// in registers (exactly: every E4M3 value is a bf16 value); the K scale multiplies the scores of those stages, the V
+// scale their weights.
+#include <type_traits>
+
 #include "hg_internal.h"
 #include "prefix_common.h"
 
@@ -25,11 +44,12 @@ namespace hg {
 namespace {
 
 constexpr int KT = 32;                  // keys per stage
-constexpr int NWS = 4;                  // wavefronts per workgroup
-constexpr int NSL = 2;                  // ring slots per wavefront
+constexpr int NWS = 8;                  // wavefronts per workgroup
 constexpr float TAU = 8.0f;             // lazy-rescale threshold, log2 units
 
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+typedef int intx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 
@@ -50,37 +70,61 @@ typedef const __attribute__((address_space(4))) SmallArgs* kargs_ptr;
 
 // One segment of a tile's key list (uniform over the workgroup).
 struct Seg {
-    const unsigned char* K;   // the segment's tensor at this KV head (bytes)
+    const unsigned char* K;   // the segment's tensor at this KV head (bytes; a page pool's first row for paged suffixes)
     const unsigned char* V;
-    int ks, ke;               // key rows [ks, ke) of that tensor
+    int ks, ke;               // key rows [ks, ke) of that tensor (of the sequence when the suffix is paged)
     int rlo, rhi;             // rows [rlo, rhi) of the tile attend to it
     int vis_base;             // suffix: query t of the sequence sees rows below vis_base + t; shared block: INT_MAX / 2
     int nst;                  // stages of 32 keys
+    int sfx;                  // index of the suffix's sequence among the tile's (-1: shared block)
 };
 
-// Walks the segments of a tile in a fixed order: levels in order, within a level the blocks that cover sequences
-// b0 .. b1 in order, then the suffixes of b0 .. b1.  Segments without keys or without rows are skipped.
-struct SegIter {
-    int level, block, seq;    // position: level < n_levels: block index in that level (-1: not looked up yet); then the suffix of seq
-    __device__ void reset(int b0) { level = 0; block = -1; seq = b0; }
+// 8 E4M3 codes to 8 bf16 values (exact)
+__device__ __forceinline__ uintx4 expand8(unsigned lo, unsigned hi) {
+    uintx4 v;
+    v[0] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, false));
+    v[1] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, true));
+    v[2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, false));
+    v[3] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, true));
+    return v;
+}
+
+// Results that another workgroup of the same launch will read: relaxed stores and loads at agent scope go past the
+// caches that the XCDs do not share, so that nothing has to be flushed before the arrival is counted.
+__device__ __forceinline__ void st_agent(float* p, float a, float b) {
+    const uint64_t v = (uint64_t)__builtin_bit_cast(unsigned, a) | ((uint64_t)__builtin_bit_cast(unsigned, b) << 32);
+    __hip_atomic_store(reinterpret_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t ld_agent(const float* p) {
+    return __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int D>
+struct SmallGeo {
+    static constexpr int KS = D / 16, DB = D / 32;
+    static constexpr int CPR = D / 8, RPI = 64 / CPR, CPS = KT / RPI, ROWB = D * 2, STB = KT * ROWB;   // bf16 rows
+    static constexpr int CPR8 = D / 16, RPI8 = 64 / CPR8, CPS8 = KT / RPI8;                            // E4M3 rows
+    static constexpr int OW = KT * D * 4;                // combined result of a wavefront (32 rows, fp32); equals its ring
+    static constexpr int LDS = NWS * OW + NWS * 32 * 8 + 16;   // rings or results, maxima and sums, the "last" flag
+    static_assert(OW == 2 * STB, "a wavefront's result takes the place of its ring");
 };
 
 }  // namespace
 
-template <int D>
+template <int D, bool PAGED, bool FP8>
 __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
-    constexpr int KS = D / 16, DB = D / 32, CPR = D / 8, RPI = 64 / CPR, CPS = KT / RPI, ROWB = D * 2, STB = KT * ROWB;
-    constexpr int KVOPS = 2 * CPS;                  // copy instructions per stage
-    constexpr int WAVE_LDS = 2 * NSL * STB;         // ring of one wavefront: K slots, then V slots
-    static_assert(KVOPS <= 63, "the copies of a stage must fit the vmcnt counter");
+    using G_ = SmallGeo<D>;
+    constexpr int KS = G_::KS, DB = G_::DB, CPR = G_::CPR, RPI = G_::RPI, CPS = G_::CPS, ROWB = G_::ROWB, STB = G_::STB;
+    constexpr int CPR8 = G_::CPR8, RPI8 = G_::RPI8, CPS8 = G_::CPS8;
     unsigned char* const smem_all = fs_smem;
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = tid & 63, lq = l & 31, hl = l >> 5;
-    unsigned char* const smem = smem_all + w * WAVE_LDS;
+    unsigned char* const smem = smem_all + w * (2 * STB);      // this wavefront's K slot, then its V slot
     const kargs_ptr k = (kargs_ptr)__builtin_amdgcn_kernarg_segment_ptr();
 
-    const int tile = blockIdx.x % a.tiles, kvh = blockIdx.x / a.tiles;
+    const int col = blockIdx.x % a.cols, split = blockIdx.x / a.cols;
+    const int tile = col % a.tiles, kvh = col / a.tiles;
     const int rps = a.nq * a.G;                     // query rows of one sequence for this KV head
     const int R = a.B * rps;
     const int r0 = tile * 32;
@@ -92,6 +136,11 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     const int64_t qidx = ((int64_t)b_lane * a.nq + t_lane) * a.Hq + kvh * a.G + g_lane;   // (b*nq + t)*Hq + h
 
     // ---- Q operand (registers) and the tile's suffix lengths / offsets (lane i: sequence b0 + i), loaded before any copy ----
+    int len_v = 0, off_v = 0;
+    if (a.lengths != nullptr && b0 + l <= b1) {
+        len_v = a.lengths[b0 + l];
+        if (!PAGED) off_v = a.offsets[b0 + l];
+    }
     bf16x8 qf[KS];
     {
         const uint16_t* qp = a.Q + qidx * D;
@@ -102,94 +151,127 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
             qf[s] = __builtin_bit_cast(bf16x8, v);
         }
     }
-    int len_v = 0, off_v = 0;
-    if (a.lengths != nullptr && b0 + l <= b1) {
-        len_v = max(min(a.lengths[b0 + l], a.max_len), 0);
-        off_v = a.offsets[b0 + l];
-    }
-    // the loads above are the only ones the compiler sees; it waits for them here, before the first copy is issued
-    asm volatile("" : "+v"(len_v), "+v"(off_v));
-#pragma unroll
-    for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qf[s]));
-
-    // ---- segment enumeration ---------------------------------------------------------------------------------------------------
+    // ---- segment enumeration: shared blocks one by one, suffixes through a prefix sum over the lanes --------------------------
     const unsigned rstride_b = (unsigned)a.Hkv * D * 2u;
-    auto next_seg = [&](SegIter& it, Seg& s) -> bool {
+    const unsigned rstride_s = (unsigned)a.Hkv * D * (FP8 ? 1u : 2u);     // suffix rows
+    int it_level = 0, it_block = -1;                // next shared block (block -1: not looked up yet)
+    auto next_shared = [&](Seg& s) -> bool {        // the next shared block with keys and rows, if there is one
         for (;;) {
-            if (it.level < a.n_levels) {
-                const int L = it.level;
-                const const_i32_ptr seq_off = (const_i32_ptr)(uintptr_t)k->lv[L].seq_off;
-                const const_i32_ptr kv_off = (const_i32_ptr)(uintptr_t)k->lv[L].kv_off;
-                int sa = 0, sb = a.B, kv0 = 0, kv1 = k->lv[L].max_rows;
-                if (seq_off != nullptr) {
-                    const int nb = k->lv[L].n_blocks;
-                    if (it.block < 0) {
-                        // first block whose sequences end after b0
-                        int lo = 0, hi = nb;
-                        while (lo < hi) {
-                            const int mid = (lo + hi) >> 1;
-                            if (seq_off[mid + 1] <= b0) lo = mid + 1;
-                            else hi = mid;
-                        }
-                        it.block = lo;
+            if (it_level >= a.n_levels) return false;
+            const int L = it_level;
+            const const_i32_ptr seq_off = (const_i32_ptr)(uintptr_t)k->lv[L].seq_off;
+            const const_i32_ptr kv_off = (const_i32_ptr)(uintptr_t)k->lv[L].kv_off;
+            int sa = 0, sb = a.B, kv0 = 0, kv1 = k->lv[L].max_rows;
+            if (seq_off != nullptr) {
+                const int nb = k->lv[L].n_blocks;
+                if (it_block < 0) {
+                    // first block whose sequences end after b0
+                    int lo = 0, hi = nb;
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        if (seq_off[mid + 1] <= b0) lo = mid + 1;
+                        else hi = mid;
                     }
-                    if (it.block >= nb || seq_off[it.block] > b1) {   // no further block of this level touches the tile
-                        ++it.level;
-                        it.block = -1;
-                        continue;
-                    }
-                    sa = seq_off[it.block];
-                    sb = min(seq_off[it.block + 1], sa + k->lv[L].max_seqs);
-                    kv0 = kv_off[it.block];
-                    kv1 = min(kv_off[it.block + 1], kv0 + k->lv[L].max_rows);
-                    ++it.block;
-                } else {
-                    ++it.level;
-                    it.block = -1;
+                    it_block = lo;
                 }
-                s.K = reinterpret_cast<const unsigned char*>(k->lv[L].K + (int64_t)kvh * D);
-                s.V = reinterpret_cast<const unsigned char*>(k->lv[L].V + (int64_t)kvh * D);
-                s.ks = kv0;
-                s.ke = kv1;
-                s.rlo = max(max(sa, b0) * rps - r0, 0);
-                s.rhi = min(min(sb, b1 + 1) * rps - r0, 32);
-                s.vis_base = 0x3fffffff;
+                if (it_block >= nb || seq_off[it_block] > b1) {   // no further block of this level touches the tile
+                    ++it_level;
+                    it_block = -1;
+                    continue;
+                }
+                sa = seq_off[it_block];
+                sb = min(seq_off[it_block + 1], sa + k->lv[L].max_seqs);
+                kv0 = kv_off[it_block];
+                kv1 = min(kv_off[it_block + 1], kv0 + k->lv[L].max_rows);
+                ++it_block;
             } else {
-                if (a.lengths == nullptr || it.seq > b1) return false;
-                const int i = it.seq - b0;
-                const int cnt = __builtin_amdgcn_readlane(len_v, i), off = __builtin_amdgcn_readlane(off_v, i);
-                s.K = reinterpret_cast<const unsigned char*>(k->Ks + (int64_t)kvh * D);
-                s.V = reinterpret_cast<const unsigned char*>(k->Vs + (int64_t)kvh * D);
-                s.ks = off;
-                s.ke = off + cnt;
-                s.rlo = max(it.seq * rps - r0, 0);
-                s.rhi = min((it.seq + 1) * rps - r0, 32);
-                s.vis_base = off + cnt - (a.nq - 1);     // query t sees rows below off + cnt - (nq-1-t)
-                ++it.seq;
+                ++it_level;
+                it_block = -1;
             }
+            s.K = reinterpret_cast<const unsigned char*>(k->lv[L].K + (int64_t)kvh * D);
+            s.V = reinterpret_cast<const unsigned char*>(k->lv[L].V + (int64_t)kvh * D);
+            s.ks = kv0;
+            s.ke = kv1;
+            s.rlo = max(max(sa, b0) * rps - r0, 0);
+            s.rhi = min(min(sb, b1 + 1) * rps - r0, 32);
+            s.vis_base = 0x3fffffff;
+            s.sfx = -1;
             s.nst = (s.ke > s.ks && s.rhi > s.rlo) ? (s.ke - s.ks + KT - 1) / KT : 0;
             if (s.nst > 0) return true;
         }
     };
-
-    // total stages of the tile, and this wavefront's run [run_lo, run_hi) of them
-    int total = 0;
-    {
-        SegIter it;
-        it.reset(b0);
-        Seg s;
-        while (next_seg(it, s)) total += s.nst;
+    // the stages of the shared blocks are counted (scalar loads) while the loads above are on their way; those are the only
+    // vector loads the compiler sees, and it waits for them here, before the first copy is issued
+    Seg cs{};
+    int shared_total = 0;
+    while (next_shared(cs)) shared_total += cs.nst;
+    shared_total = __builtin_amdgcn_readfirstlane(shared_total);
+    asm volatile("" : "+v"(len_v), "+v"(off_v));
+#pragma unroll
+    for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qf[s]));
+    len_v = max(min(len_v, a.max_len), 0);
+    const int nst_v = (len_v + KT - 1) / KT;        // stages of the suffix of sequence b0 + l
+    int incl_v = nst_v;                             // ... of the suffixes of b0 .. b0 + l
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(incl_v, o);
+        if (l >= o) incl_v += up;
     }
-    total = __builtin_amdgcn_readfirstlane(total);
-    const int run_lo = (int)((long long)w * total / NWS), run_hi = (int)((long long)(w + 1) * total / NWS);
+    const uint64_t nonempty = __ballot(nst_v > 0);
+    auto load_suffix = [&](int i, Seg& s) {         // the suffix of sequence b0 + i (which has rows)
+        const int cnt = __builtin_amdgcn_readlane(len_v, i), off = PAGED ? 0 : __builtin_amdgcn_readlane(off_v, i);
+        s.K = reinterpret_cast<const unsigned char*>(k->Ks) + (int64_t)kvh * D * (FP8 ? 1 : 2);
+        s.V = reinterpret_cast<const unsigned char*>(k->Vs) + (int64_t)kvh * D * (FP8 ? 1 : 2);
+        s.ks = off;
+        s.ke = off + cnt;
+        s.rlo = max((b0 + i) * rps - r0, 0);
+        s.rhi = min((b0 + i + 1) * rps - r0, 32);
+        s.vis_base = off + cnt - (a.nq - 1);        // query t sees rows below off + cnt - (nq-1-t)
+        s.nst = (cnt + KT - 1) / KT;
+        s.sfx = i;
+    };
 
-    // ---- HBM -> LDS copies (as in decode_mfma.hip) -----------------------------------------------------------------------------------
+    // the column's stages, and this wavefront's run [run_lo, run_hi) of them
+    const int total = shared_total + __builtin_amdgcn_readlane(incl_v, 63);
+    const int runs = a.splits * NWS, run = split * NWS + w;
+    const int run_lo = (int)((long long)run * total / runs), run_hi = (int)((long long)(run + 1) * total / runs);
+    int ct = 0;                                     // current stage of segment cs
+    if (run_lo < run_hi) {
+        if (run_lo < shared_total) {
+            it_level = 0;
+            it_block = -1;
+            int base = 0;
+            while (next_shared(cs)) {
+                if (base + cs.nst > run_lo) break;
+                base += cs.nst;
+            }
+            ct = run_lo - base;
+        } else {
+            const int p = run_lo - shared_total;
+            const int i = __builtin_popcountll(__ballot(incl_v <= p));      // the first sequence whose stages reach past p
+            load_suffix(i, cs);
+            ct = p - (__builtin_amdgcn_readlane(incl_v, i) - cs.nst);
+        }
+    }
+    auto advance = [&](Seg& s, int& t) {            // one stage further (the caller knows that there is one)
+        if (++t < s.nst) return;
+        t = 0;
+        if (s.sfx < 0 && next_shared(s)) return;
+        const uint64_t rest = nonempty & (~0ull << (s.sfx + 1));
+        load_suffix(__builtin_ctzll(rest), s);
+    };
+
+    // ---- HBM -> LDS copies -----------------------------------------------------------------------------------------------------
     // Stage t of a segment holds rows [k0c, k0c + 32), k0c = min(ks + 32 t, kwin), kwin = max(ke - 32, 0): a partial last
     // stage re-reads the 32 rows that end the range; row i of a stage is a key of it iff ks + 32 t <= k0c + i < ke.
-    const int lrow = l / CPR, sch = l % CPR;
+    // Paged suffixes: a stage is 32 aligned logical rows and is never shifted; its two halves lie in one page each.
+    // 16-byte chunks are XOR-swizzled on the global side (bf16 rows: K chunk ^ row % 16, V chunk ^ 4 (row % 4) at D = 128, see
+    // decode_mfma.hip; codes: rows of 8 or 4 chunks, spread so that the reads below are free of bank conflicts).
     const unsigned ldsb = (unsigned)(uintptr_t)HG_LDS(smem);
     auto kswz = [](int row) { return D == 128 ? row % 16 : (row >> 1) & 7; };
     auto vswz = [](int row) { return D == 128 ? 4 * (row % 4) : 4 * ((row >> 1) & 1); };
+    auto kswz8 = [](int row) { return D == 128 ? (row >> 1) & 7 : (row >> 2) & 3; };
+    auto vswz8 = [](int row) { return D == 128 ? ((row >> 1) & 1) | (((row >> 3) & 1) << 1) : (row >> 2) & 3; };
     auto scalar_ptr = [&](const unsigned char* vbase) -> const unsigned char* {
         const uint64_t pv = reinterpret_cast<uint64_t>(vbase);
         const uint32_t plo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)pv);
@@ -199,70 +281,85 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     auto copy16 = [&](const unsigned char* sbase, unsigned voff, unsigned lds_dst) {
         asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_dst) : "memory", "m0");
     };
-
-    // A cursor over this wavefront's run: the segment it is in and the next stage of that segment.  Two of them walk
-    // the same run: the producer (copies) one stage ahead of the consumer (products).
-    struct Cursor {
-        SegIter it;
-        Seg s;
-        int base;     // stages of the tile before this segment
-        int t;        // next stage of the segment
-        int pos;      // its index in the tile's stage list
-    };
-    auto cursor_start = [&](Cursor& c) {        // on the stage run_lo (if the run is not empty)
-        c.it.reset(b0);
-        c.base = 0;
-        c.pos = run_lo;
-        c.s.nst = 0;
-        if (run_lo >= run_hi) return;
-        while (next_seg(c.it, c.s)) {
-            if (c.base + c.s.nst > run_lo) break;
-            c.base += c.s.nst;
-        }
-        c.t = run_lo - c.base;
-    };
-    auto cursor_step = [&](Cursor& c) {         // one stage further
-        ++c.pos;
-        if (++c.t == c.s.nst && c.pos < run_hi) {
-            c.base += c.s.nst;
-            c.t = 0;
-            next_seg(c.it, c.s);                // exists: the run ends within the tile's list
-        }
-    };
-
-    Cursor pc, cc;
-    cursor_start(pc);
-    cursor_start(cc);
-    int n_issued = 0;
-    auto produce_one = [&]() {
-        if (pc.pos >= run_hi) return;
-        const int kwin = max(pc.s.ke - KT, 0);
-        const int k0c = min(pc.s.ks + pc.t * KT, kwin);
-        const int rowclamp = min(pc.s.ke - 1 - kwin, KT - 1);     // < 31 only when the range ends before row 32 of the tensor
-        const unsigned char* const kg = scalar_ptr(pc.s.K + (int64_t)k0c * rstride_b);
-        const unsigned char* const vg = scalar_ptr(pc.s.V + (int64_t)k0c * rstride_b);
-        const unsigned dst = (unsigned)__builtin_amdgcn_readfirstlane(ldsb + (unsigned)(n_issued % NSL) * STB);
+    const int lrow = l / CPR, sch = l % CPR, lrow8 = l / CPR8, sch8 = l % CPR8;
+    unsigned voffK[CPS], voffV[CPS];                // this lane's byte offset in a bf16 stage (whole stages)
 #pragma unroll
-        for (int i = 0; i < CPS; ++i) {
-            const int srow = i * RPI + lrow;
-            const unsigned ro = (unsigned)min(srow, rowclamp) * rstride_b;
-            copy16(kg, ro + (unsigned)((sch ^ kswz(srow)) * 16), dst + i * 1024);
-        }
+    for (int i = 0; i < CPS; ++i) {
+        const int srow = i * RPI + lrow;
+        voffK[i] = (unsigned)srow * rstride_b + (unsigned)((sch ^ kswz(srow)) * 16);
+        voffV[i] = (unsigned)srow * rstride_b + (unsigned)((sch ^ vswz(srow)) * 16);
+    }
+    unsigned voffK8[FP8 ? CPS8 : 1], voffV8[FP8 ? CPS8 : 1];
+    if constexpr (FP8) {
 #pragma unroll
-        for (int i = 0; i < CPS; ++i) {
-            const int srow = i * RPI + lrow;
-            const unsigned ro = (unsigned)min(srow, rowclamp) * rstride_b;
-            copy16(vg, ro + (unsigned)((sch ^ vswz(srow)) * 16), dst + NSL * STB + i * 1024);
+        for (int i = 0; i < CPS8; ++i) {
+            const int srow = i * RPI8 + lrow8;
+            voffK8[i] = (unsigned)srow * rstride_s + (unsigned)((sch8 ^ kswz8(srow)) * 16);
+            voffV8[i] = (unsigned)srow * rstride_s + (unsigned)((sch8 ^ vswz8(srow)) * 16);
         }
-        ++n_issued;
-        cursor_step(pc);
+    }
+    auto copies_of = [&](const Seg& s) { return FP8 && s.sfx >= 0 ? CPS8 : CPS; };     // copy instructions per stage and tensor
+    // first row of stage t of segment s as it lies in LDS
+    auto row0_of = [&](const Seg& s, int t) { return PAGED && s.sfx >= 0 ? t * KT : min(s.ks + t * KT, max(s.ke - KT, 0)); };
+    auto issue = [&](const Seg& s, int t, auto is_v) {      // requests the K (or V) rows of stage t of segment s
+        constexpr bool V = decltype(is_v)::value;
+        const unsigned dst = (unsigned)__builtin_amdgcn_readfirstlane(ldsb + (V ? (unsigned)STB : 0u));
+        const bool codes = FP8 && s.sfx >= 0;
+        const unsigned rs = s.sfx >= 0 ? rstride_s : rstride_b;
+        const unsigned char* const tensor = V ? s.V : s.K;
+        const unsigned char *base0, *base1;         // of rows 0 .. 15 and 16 .. 31 (both relative to row 0)
+        int rowclamp = KT - 1;                      // < 31 only when the range ends before row 32 of the tensor
+        if (PAGED && s.sfx >= 0) {
+            const const_i32_ptr table = (const_i32_ptr)(uintptr_t)k->pg.table + (int64_t)(b0 + s.sfx) * k->pg.stride;
+            const int shift = k->pg.shift, mask = (1 << shift) - 1, last = k->pg.stride - 1, n_pages = k->pg.n_pages;
+            const int j0 = t * KT, j1 = j0 + KT / 2;
+            const int p0 = min(max(table[min(j0 >> shift, last)], 0), n_pages - 1);
+            const int p1 = min(max(table[min(j1 >> shift, last)], 0), n_pages - 1);
+            base0 = scalar_ptr(tensor + (((int64_t)p0 << shift) + (j0 & mask)) * rs);
+            base1 = scalar_ptr(tensor + (((int64_t)p1 << shift) + (j1 & mask) - KT / 2) * rs);
+        } else {
+            const int k0c = row0_of(s, t);
+            rowclamp = min(s.ke - 1 - k0c, KT - 1);
+            base0 = base1 = scalar_ptr(tensor + (int64_t)k0c * rs);
+        }
+        if (codes) {
+            if constexpr (FP8) {
+#pragma unroll
+                for (int i = 0; i < CPS8; ++i) {
+                    unsigned vo = V ? voffV8[i] : voffK8[i];
+                    if (rowclamp < KT - 1) {
+                        const int srow = i * RPI8 + lrow8;
+                        vo -= (unsigned)(srow - min(srow, rowclamp)) * rs;
+                    }
+                    copy16(i < CPS8 / 2 ? base0 : base1, vo, dst + i * 1024);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < CPS; ++i) {
+                unsigned vo = V ? voffV[i] : voffK[i];
+                if (rowclamp < KT - 1) {
+                    const int srow = i * RPI + lrow;
+                    vo -= (unsigned)(srow - min(srow, rowclamp)) * rs;
+                }
+                copy16(i < CPS / 2 ? base0 : base1, vo, dst + i * 1024);
+            }
+        }
     };
+    // wait until at most `younger` copy instructions are outstanding (those of one tensor of one stage, or none)
+    auto wait_for = [&](int younger) {
+        if (younger == CPS) wait_vm<CPS>();
+        else if (FP8 && younger == CPS8) wait_vm<CPS8>();
+        else wait_vm<0>();
+        asm volatile("" ::: "memory");
+    };
+    typedef std::integral_constant<bool, false> IsK;
+    typedef std::integral_constant<bool, true> IsV;
 
-    // ---- LDS fragment addresses (relative to the slot), as in prefix_wide.hip ------------------------------------------
-    unsigned kaddr[KS];
+    // ---- LDS fragment addresses (relative to the slot), as in decode_mfma.hip ---------------------------------------------------
+    unsigned kaddr[KS], vaddr[DB], kaddr8[FP8 ? KS : 1], vaddr8[FP8 ? DB : 1];
 #pragma unroll
     for (int s = 0; s < KS; ++s) kaddr[s] = (unsigned)(lq * ROWB + (((2 * s + hl) ^ kswz(lq)) * 16));
-    unsigned vaddr[DB];
     {
         const int i16 = l & 15, g1 = (l >> 4) & 1;
         const int keyq = 4 * hl + (i16 >> 2);
@@ -270,7 +367,17 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             const int chunk = 4 * db + 2 * g1 + ((i16 & 3) >> 1);
-            vaddr[db] = (unsigned)(keyq * ROWB + ((chunk ^ fv) * 16) + (i16 & 1) * 8);   // relative to the V stage
+            vaddr[db] = (unsigned)(STB + keyq * ROWB + ((chunk ^ fv) * 16) + (i16 & 1) * 8);
+        }
+        if constexpr (FP8) {
+            // codes: the 8 of K row lq, columns 16 s + 8 hl .. +7; V^T through ds_read_b64_tr_b8 (lane s of a group of 16 points
+            // at the key of k-slot s / 2 and columns 8 (s % 2) .. +7 of its 16-column block)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) kaddr8[s] = (unsigned)(lq * D + ((s ^ kswz8(lq)) * 16) + 8 * hl);
+            const int j = i16 >> 1, pp = i16 & 1;
+            const int row = 8 * (j >> 2) + 4 * hl + (j & 3);        // + 16 tt: the same swizzle
+#pragma unroll
+            for (int db = 0; db < DB; ++db) vaddr8[db] = (unsigned)(STB + row * D + (((2 * db + g1) ^ vswz8(row)) * 16) + 8 * pp);
         }
     }
 
@@ -286,45 +393,49 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     float mc = 0.f;             // m_used * c2, 0 while no key has been seen
     float lsum = 0.f;           // this lane's share of the row sum (unrounded exponentials)
 
-    produce_one();
-    int n_done = 0;
-    while (cc.pos < run_hi) {
-        n_done = __builtin_amdgcn_readfirstlane(n_done);
-        produce_one();                               // the stage after this one, into the other slot
-        if (n_issued > n_done + 1) wait_vm<KVOPS>();      // the stage after this one may stay in flight
-        else wait_vm<0>();
-        asm volatile("" ::: "memory");
-        const unsigned char* const sb = smem + (n_done % NSL) * STB;
-        unsigned char* const vstage = smem + (n_done % NSL) * STB + NSL * STB;
-        ++n_done;
-        const Seg& s = cc.s;
-        const int kwin = max(s.ke - KT, 0);
-        const int key0 = s.ks + cc.t * KT;
-        const int k0c = min(key0, kwin);
-        if (k0c != key0 || s.ke - kwin < KT) {
-            // stage rows that are not keys of this stage (re-read from below the range, or past a range that ends before
-            // row 32 of the tensor) may hold anything: their probabilities are zero, but 0 * NaN is NaN in the second
-            // product, so their V rows are cleared in LDS
-            const int nlo = key0 - k0c, nhi = s.ke - k0c;
-#pragma unroll
-            for (int i = 0; i < CPS; ++i) {
-                const int row = i * RPI + lrow;
-                if (row < nlo || row >= nhi) *reinterpret_cast<uintx4*>(vstage + row * ROWB + sch * 16) = uintx4{0u, 0u, 0u, 0u};
-            }
-        }
+    if (run_lo < run_hi) {
+        issue(cs, ct, IsK{});
+        issue(cs, ct, IsV{});
+    }
+    for (int pos = run_lo; pos < run_hi; ++pos) {
+        const bool more = pos + 1 < run_hi;
+        Seg ns = cs;
+        int nt = ct;
+        if (more) advance(ns, nt);
+        const bool codes = FP8 && cs.sfx >= 0;
+        wait_for(copies_of(cs));                    // this stage's K rows are here, its V rows may still be on their way
         // S^T = K Q^T
         floatx16 S;
 #pragma unroll
         for (int i = 0; i < 16; ++i) S[i] = 0.f;
+        if (codes) {
+            if constexpr (FP8) {
 #pragma unroll
-        for (int q = 0; q < KS; ++q) {
-            const uintx4 kv = *reinterpret_cast<const uintx4*>(sb + kaddr[q]);
-            S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kv), qf[q], S, 0, 0, 0);
+                for (int q = 0; q < KS; ++q) {
+                    const uintx2 kc = *reinterpret_cast<const uintx2*>(smem + kaddr8[q]);
+                    S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, expand8(kc[0], kc[1])), qf[q], S, 0, 0, 0);
+                }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) S[i] *= a.k_scale;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < KS; ++q) {
+                const uintx4 kv = *reinterpret_cast<const uintx4*>(smem + kaddr[q]);
+                S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kv), qf[q], S, 0, 0, 0);
+            }
         }
+        // the scores depend on every fragment read: once they are pinned here the K slot may be overwritten
+        asm volatile("" : "+v"(S));
+        asm volatile("" ::: "memory");
+        if (more) issue(ns, nt, IsK{});
+        const int key0 = cs.ks + ct * KT;
+        const int k0c = row0_of(cs, ct);
+        const bool partial = k0c != key0 || cs.ke - k0c < KT;      // some stage rows are not keys of this stage
         // masks: keys outside the stage's range, keys this lane's query does not see yet, rows that do not attend
-        {
-            const bool attends = lq >= s.rlo && lq < s.rhi;
-            const int vis_end = min(s.ke, s.vis_base + t_lane);
+        if (partial || cs.rlo > 0 || cs.rhi < 32 || key0 + KT > cs.vis_base) {
+            const bool attends = lq >= cs.rlo && lq < cs.rhi;
+            const int vis_end = min(cs.ke, cs.vis_base + t_lane);
             const int lo_i = key0 - k0c - 4 * hl, hi_i = (attends ? vis_end : k0c) - k0c - 4 * hl;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -348,6 +459,7 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
 #pragma unroll
                 for (int j = 0; j < 16; ++j) Oacc[i][j] *= alpha;
         }
+        const float vs = codes ? a.v_scale : 1.0f;
         uintx4 pb[2];
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt) {
@@ -356,40 +468,69 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
             for (int i = 0; i < 8; ++i) {
                 p[i] = __builtin_amdgcn_exp2f(fmaf(S[8 * tt + i], c2, -mc));
                 lsum += p[i];
+                if constexpr (FP8) p[i] *= vs;
             }
             pb[tt] = uintx4{pack_pair(p[0], p[1]), pack_pair(p[2], p[3]), pack_pair(p[4], p[5]), pack_pair(p[6], p[7])};
+        }
+        wait_for(more ? copies_of(ns) : 0);         // this stage's V rows are here, the next K rows may still be on their way
+        if (partial) {
+            // stage rows that are not keys of this stage (re-read from below the range, or past a range that ends before
+            // row 32 of the tensor, or a page's unwritten tail) may hold anything: their probabilities are zero, but 0 * NaN
+            // is NaN in the second product, so their V rows are cleared in LDS
+            const int nlo = key0 - k0c, nhi = cs.ke - k0c;
+            if (codes) {
+#pragma unroll
+                for (int i = 0; i < CPS8; ++i) {
+                    const int row = i * RPI8 + lrow8;
+                    if (row < nlo || row >= nhi) *reinterpret_cast<uintx4*>(smem + STB + i * 1024 + l * 16) = uintx4{0u, 0u, 0u, 0u};
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < CPS; ++i) {
+                    const int row = i * RPI + lrow;
+                    if (row < nlo || row >= nhi) *reinterpret_cast<uintx4*>(smem + STB + i * 1024 + l * 16) = uintx4{0u, 0u, 0u, 0u};
+                }
+            }
         }
         // O^T += V^T P^T
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt) {
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
-                const unsigned char* vp = vstage + vaddr[db] + tt * 16 * ROWB;
-                const shortx4 vlo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)HG_LDS(vp));
-                const shortx4 vhi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)HG_LDS(vp + 8 * ROWB));
-                const shortx8 vv = __builtin_shufflevector(vlo, vhi, 0, 1, 2, 3, 4, 5, 6, 7);
-                Oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv), __builtin_bit_cast(bf16x8, pb[tt]), Oacc[db], 0, 0, 0);
+                bf16x8 vv;
+                if (codes) {
+                    if constexpr (FP8) {
+                        const intx2 vc = __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) intx2*)HG_LDS(smem + vaddr8[db] + tt * 16 * D));
+                        vv = __builtin_bit_cast(bf16x8, expand8((unsigned)vc[0], (unsigned)vc[1]));
+                    }
+                } else {
+                    const unsigned char* vp = smem + vaddr[db] + tt * 16 * ROWB;
+                    const shortx4 vlo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)HG_LDS(vp));
+                    const shortx4 vhi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)HG_LDS(vp + 8 * ROWB));
+                    vv = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vlo, vhi, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+                Oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, __builtin_bit_cast(bf16x8, pb[tt]), Oacc[db], 0, 0, 0);
             }
         }
-        // the accumulators depend on every fragment read of this stage: once they are pinned here the reads have
-        // completed, and the next produce_one() may overwrite the slot
+        // the accumulators depend on every fragment read of this stage: once they are pinned here the V slot may be overwritten
 #pragma unroll
         for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(Oacc[db]));
         asm volatile("" ::: "memory");
-        cursor_step(cc);
+        if (more) issue(ns, nt, IsV{});
+        cs = ns;
+        ct = nt;
     }
-    wait_vm<0>();
 
-    // ---- the four partial results meet in LDS (Eq. 5) -------------------------------------------------------------------------------
-    // Layout (the rings are free now): O of wavefront v at v * 32 * D * 4, row-major [32][D] fp32 with the 16-byte chunk c of
-    // row r at chunk c ^ (r % (D / 4)); then the maxima and sums [NWS][32].
-    constexpr int OW = 32 * D * 4;
+    // ---- the workgroup's partial results meet in LDS (Eq. 5) -------------------------------------------------------------------------
+    // O of wavefront v takes the place of its ring: row-major [32][D] fp32 with the 16-byte chunk c of row r at chunk
+    // c ^ (r % (D / 4)); behind the eight of them the maxima and sums [NWS][32].
+    constexpr int OW = G_::OW;
     constexpr int CH = D / 4;                       // 16-byte chunks per row
     float* const Mw = reinterpret_cast<float*>(smem_all + NWS * OW);
     float* const Lw = Mw + NWS * 32;
+    int* const last_flag = reinterpret_cast<int*>(Lw + NWS * 32);
     const float ltot = half_sum(lsum);
-    __syncthreads();
-    {
+    {                                               // (own ring only: nothing to wait for)
         unsigned char* const ow = smem_all + w * OW;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -405,64 +546,151 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
         }
     }
     __syncthreads();
+    // wavefront w finishes rows 4w .. 4w+3: lane -> row 4w + l/16, 16-byte chunks (l%16) * CPL .. + CPL - 1
+    constexpr int CPL = CH / 16;                    // D = 128: 2, D = 64: 1
+    const int row = 4 * w + (l >> 4), c0 = (l & 15) * CPL;
+    float4 acc[CPL];
+    float M = -INFINITY, Lsum = 0.f;
     {
-        // wavefront w finishes rows 8w .. 8w+7: lane -> row 8w + l/8, columns (l%8) * D/8 .. + D/8 - 1
-        constexpr int CPL = CH / 8;                  // 16-byte chunks per lane (D = 128: 4, D = 64: 2)
-        const int row = 8 * w + (l >> 3), c0 = (l & 7) * CPL;
-        float mv[NWS], M = -INFINITY;
+        float mv[NWS];
 #pragma unroll
         for (int v = 0; v < NWS; ++v) {
             mv[v] = Mw[v * 32 + row];
             M = fmaxf(M, mv[v]);
         }
-        float f[NWS], Lsum = 0.f;
+        float f[NWS];
 #pragma unroll
         for (int v = 0; v < NWS; ++v) {
             f[v] = (mv[v] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((mv[v] - M) * c2);
             Lsum += f[v] * Lw[v * 32 + row];
         }
         const float inv = Lsum > 0.f ? 1.0f / Lsum : 0.f;     // a row without any key: O = 0, LSE = -inf
-        const int rg = r0 + row;                                // the row this lane finishes
-        const bool ok = rg < R;
-        const int rrg = ok ? rg : r0;
-        const int64_t oidx = ((int64_t)(rrg / rps) * a.nq + (rrg % rps) / a.G) * a.Hq + kvh * a.G + rrg % a.G;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+            acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
             for (int v = 0; v < NWS; ++v) {
                 const float4 o = *reinterpret_cast<const float4*>(smem_all + v * OW + row * (D * 4) + (((c0 + c) ^ (row & (CH - 1))) * 16));
-                acc.x += f[v] * o.x; acc.y += f[v] * o.y; acc.z += f[v] * o.z; acc.w += f[v] * o.w;
+                acc[c].x += f[v] * o.x; acc[c].y += f[v] * o.y; acc[c].z += f[v] * o.z; acc[c].w += f[v] * o.w;
             }
-            acc.x *= inv; acc.y *= inv; acc.z *= inv; acc.w *= inv;
-            if (ok) {
-                const int d = 4 * (c0 + c);
-                if (a.bf16) *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.O) + oidx * D + d) = make_uint2(pack_bf16(acc.x, acc.y), pack_bf16(acc.z, acc.w));
-                else *reinterpret_cast<float4*>(static_cast<float*>(a.O) + oidx * D + d) = acc;
+            acc[c].x *= inv; acc[c].y *= inv; acc[c].z *= inv; acc[c].w *= inv;
+        }
+    }
+    float lse = Lsum > 0.f ? M * a.scale + __logf(Lsum) : -INFINITY;
+
+    if (a.splits > 1) {
+        // ---- the column's results meet in the workspace ----------------------------------------------------------------------------------
+        const int S = a.splits;
+        float* const cO = a.part + (int64_t)col * S * (32 * D);                       // [S][32][D], then [S][32] behind all columns
+        float* const cL = a.part + (int64_t)a.cols * S * (32 * D) + (int64_t)col * S * 32 * 2;   // (LSE, unused) pairs
+        float* const mine = cO + (int64_t)split * (32 * D) + row * D + 4 * c0;
+        if (r0 + row < R) {
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                st_agent(mine + 4 * c, acc[c].x, acc[c].y);
+                st_agent(mine + 4 * c + 2, acc[c].z, acc[c].w);
+            }
+            if ((l & 15) == 0) st_agent(cL + (split * 32 + row) * 2, lse, 0.f);
+        }
+        wait_vm<0>();                               // this wavefront's results are where every XCD sees them
+        __syncthreads();
+        if (tid == 0) {
+            const unsigned before = __hip_atomic_fetch_add(a.arrivals + col, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int last = before == (unsigned)(S - 1);
+            if (last) __hip_atomic_store(a.arrivals + col, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
+            *last_flag = last;
+        }
+        __syncthreads();
+        if (!*last_flag || r0 + row >= R) return;
+        M = -INFINITY;
+        Lsum = 0.f;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+        constexpr int U = 8;                        // results in flight per lane
+        for (int i0 = 0; i0 < S; i0 += U) {
+            uint64_t lw[U], ow[U][2 * CPL];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = min(i0 + u, S - 1);
+                lw[u] = ld_agent(cL + (i * 32 + row) * 2);
+#pragma unroll
+                for (int c = 0; c < 2 * CPL; ++c) ow[u][c] = ld_agent(cO + (int64_t)i * (32 * D) + row * D + 4 * c0 + 2 * c);
+            }
+            float li[U], gm = M;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                li[u] = i0 + u < S ? __builtin_bit_cast(float, (unsigned)lw[u]) : -INFINITY;
+                gm = fmaxf(gm, li[u]);
+            }
+            const float gs = gm == -INFINITY ? 0.f : gm;        // nothing but empty results so far: every weight is 0
+            const float re = __builtin_amdgcn_exp2f((M - gs) * kLog2e);
+            M = gm;
+            Lsum *= re;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) { acc[c].x *= re; acc[c].y *= re; acc[c].z *= re; acc[c].w *= re; }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float f = __builtin_amdgcn_exp2f((li[u] - gs) * kLog2e);
+                Lsum += f;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    acc[c].x = fmaf(f, __builtin_bit_cast(float, (unsigned)ow[u][2 * c]), acc[c].x);
+                    acc[c].y = fmaf(f, __builtin_bit_cast(float, (unsigned)(ow[u][2 * c] >> 32)), acc[c].y);
+                    acc[c].z = fmaf(f, __builtin_bit_cast(float, (unsigned)ow[u][2 * c + 1]), acc[c].z);
+                    acc[c].w = fmaf(f, __builtin_bit_cast(float, (unsigned)(ow[u][2 * c + 1] >> 32)), acc[c].w);
+                }
             }
         }
-        if (ok && (l & 7) == 0 && a.LSE != nullptr) a.LSE[oidx] = Lsum > 0.f ? M * a.scale + __logf(Lsum) : -INFINITY;
+        const float inv = Lsum > 0.f ? 1.0f / Lsum : 0.f;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) { acc[c].x *= inv; acc[c].y *= inv; acc[c].z *= inv; acc[c].w *= inv; }
+        lse = Lsum > 0.f ? M + __logf(Lsum) : -INFINITY;
+    }
+
+    const int rg = r0 + row;                        // the row this lane finishes
+    if (rg < R) {
+        const int64_t oidx = ((int64_t)(rg / rps) * a.nq + (rg % rps) / a.G) * a.Hq + kvh * a.G + rg % a.G;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            const int d = 4 * (c0 + c);
+            if (a.bf16) *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.O) + oidx * D + d) = make_uint2(pack_bf16(acc[c].x, acc[c].y), pack_bf16(acc[c].z, acc[c].w));
+            else *reinterpret_cast<float4*>(static_cast<float*>(a.O) + oidx * D + d) = acc[c];
+        }
+        if ((l & 15) == 0 && a.LSE != nullptr) a.LSE[oidx] = lse;
     }
 }
 
-hipError_t launch_fused_small(const SmallArgs& a, int D, hipStream_t s) {
-    if (a.tiles < 1 || a.Hkv < 1 || (D != 64 && D != 128)) return hipErrorInvalidValue;
-    const long long grid = (long long)a.tiles * a.Hkv;
-    if (grid >= (1LL << 31)) return hipErrorInvalidValue;
-    static bool attr_set[64][2] = {};
+template <int D, bool PAGED, bool FP8>
+static hipError_t launch_small_t(const SmallArgs& a, hipStream_t s) {
+    constexpr int lds = SmallGeo<D>::LDS;
+    static bool attr_set[64] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    const int lds = D == 128 ? NWS * 2 * NSL * KT * 256 : NWS * 2 * NSL * KT * 128;   // the rings; the merge area fits inside
-    const void* fn = D == 128 ? reinterpret_cast<const void*>(&fused_small_kernel<128>) : reinterpret_cast<const void*>(&fused_small_kernel<64>);
-    if (dev >= 0 && dev < 64 && !attr_set[dev][D == 128]) {
-        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (dev >= 0 && dev < 64 && !attr_set[dev]) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_small_kernel<D, PAGED, FP8>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
-        attr_set[dev][D == 128] = true;
+        attr_set[dev] = true;
     }
-    if (D == 128) fused_small_kernel<128><<<(unsigned)grid, 64 * NWS, lds, s>>>(a);
-    else fused_small_kernel<64><<<(unsigned)grid, 64 * NWS, lds, s>>>(a);
+    fused_small_kernel<D, PAGED, FP8><<<(unsigned)(a.cols * a.splits), 64 * NWS, lds, s>>>(a);
     return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_small_d(const SmallArgs& a, hipStream_t s) {
+    if (a.fp8) return a.pg.table ? launch_small_t<D, true, true>(a, s) : launch_small_t<D, false, true>(a, s);
+    return a.pg.table ? launch_small_t<D, true, false>(a, s) : launch_small_t<D, false, false>(a, s);
+}
+
+// Workspace floats the splits of a call need: [cols][splits][32][D] results, [cols][splits][32] pairs of (LSE, unused)
+size_t small_part_floats(int cols, int splits, int D) { return (size_t)cols * splits * 32 * (D + 2); }
+
+hipError_t launch_fused_small(const SmallArgs& a, int D, hipStream_t s) {
+    if (a.tiles < 1 || a.Hkv < 1 || a.splits < 1 || (D != 64 && D != 128)) return hipErrorInvalidValue;
+    if ((long long)a.tiles * a.Hkv != a.cols || (long long)a.cols * a.splits >= (1LL << 31)) return hipErrorInvalidValue;
+    if (a.splits > 1 && (!a.part || !a.arrivals)) return hipErrorInvalidValue;
+    if (a.pg.table && (a.pg.shift < 4 || a.pg.stride < 1 || a.pg.n_pages < 1)) return hipErrorInvalidValue;
+    return D == 128 ? launch_small_d<128>(a, s) : launch_small_d<64>(a, s);
 }
 
 }  // namespace hg

@@ -104,6 +104,8 @@ struct DecodeArgs {
 };
 
 // The single-launch fused kernel (fused_small.hip): every level, the suffix and the merge for 32-row tiles of query rows.
+constexpr int kArrivalCounters = 256;         // arrival counters a context owns (one per column of a call that is split)
+constexpr int kSmallMaxSplits = 32;           // workgroups per column at most
 struct SmallArgs {
     const uint16_t* Q;
     int n_levels;
@@ -112,10 +114,17 @@ struct SmallArgs {
     const uint16_t* Vs;
     const int32_t* offsets;
     const int32_t* lengths;   // null: no suffix
+    PagedDev pg;              // suffix read through a page table when pg.table != null
+    int fp8;                  // suffix rows are E4M3 codes: value = code * scale
+    float k_scale, v_scale;
     int max_len;
     int B, Hq, Hkv, G;
     int nq;
     int tiles;                // 32-row tiles of the B * nq * G query rows of one KV head
+    int cols;                 // tiles * Hkv columns
+    int splits;               // workgroups per column
+    float* part;              // splits > 1: partial results (small_part_floats)
+    unsigned* arrivals;       // splits > 1: [cols] arrival counters, zero between calls
     float scale;
     void* O;                  // final results: [B, nq, Hq, D] bf16 or fp32, LSE [B, nq, Hq] (may be null)
     float* LSE;
@@ -160,6 +169,7 @@ hipError_t launch_decode(const DecodeArgs& a, int D, int GT, hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeArgs& a, int D, hipStream_t s);   // matrix-core per-sequence kernel (8-bit rows: D = 128 only)
 hipError_t launch_merge(const MergeArgs& a, int D, bool in_bf16, bool out_bf16, hipStream_t s);
 hipError_t launch_fused_small(const SmallArgs& a, int D, hipStream_t s);
+size_t small_part_floats(int cols, int splits, int D);   // workspace floats of a split single launch
 hipError_t launch_mfma_loop(int iters, int random_operands, unsigned long long* clocks, float* sink, hipStream_t s);
 hipError_t launch_stream_read(const void* src, size_t bytes, float* sink, hipStream_t s);
 hipError_t launch_xcd_probe(int n_workgroups, int* out, hipStream_t s);

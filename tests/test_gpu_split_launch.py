@@ -1,0 +1,79 @@
+"""The single launch with several workgroups per 32-row column (they meet through arrival counters and the workspace)
+and over every suffix cache: packed, paged, 8-bit, paged 8-bit.  Seeded random trees against the fp64 oracle; every
+call runs twice in a row (the first must leave its arrival counters at zero) with the same bits, with and without room
+for partial results."""
+import sys
+
+import pytest
+import torch
+
+import oracle
+from oracle import fp8
+from paper_2402_05099_amd import binding as hb
+from paper_2402_05099_amd import device as dev
+from paper_2402_05099_amd import workloads as wl
+from parity import check, to_np
+from test_gpu_random_shapes import random_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def reference(w, cache):
+    """(O, LSE, caller of the fused entry point) of workload w with its suffix in the given cache."""
+    if cache == "packed":
+        O, L = oracle.attention(w)
+        return O, L, lambda c, dw, o, l: hb.hg_hydragen_attn(c, dw.Q, dw.levels, dw.Ks, dw.Vs, dw.offsets, dw.lengths, dw.max_len, o, l, dw.scale)
+    if cache == "paged":
+        O, L = oracle.attention(w)
+        kv = dev.paged_to_device(wl.make_paged(w, 16))
+        return O, L, lambda c, dw, o, l: hb.hg_hydragen_attn_paged(c, dw.Q, dw.levels, kv, dw.lengths, dw.max_len, o, l, dw.scale)
+    f8 = wl.make_fp8(w, reserve=2)
+    O, L = fp8.suffix_attention_fp8(w.Q, w.Hkv, f8.Ks8, f8.Vs8, f8.k_scale, f8.v_scale, f8.offsets, w.lengths, w.scale)
+    if w.levels:
+        Op, Lp = oracle.attention(w, suffix=False)
+        O, L = oracle.merge([Op, O], [Lp, L])
+    if cache == "fp8":
+        Ks8, Vs8, off = (torch.from_numpy(x).cuda() for x in (f8.Ks8, f8.Vs8, f8.offsets))
+        return O, L, lambda c, dw, o, l: hb.hg_hydragen_attn_fp8(c, dw.Q, dw.levels, Ks8, Vs8, f8.k_scale, f8.v_scale, off, dw.lengths,
+                                                                dw.max_len, o, l, dw.scale)
+    pg, ks, vs = wl.make_paged_fp8(w, 32)
+    kv = hb.PagedKV(K=torch.from_numpy(pg.K).cuda(), V=torch.from_numpy(pg.V).cuda(), page_table=torch.from_numpy(pg.table).cuda(),
+                    page_size=pg.page_size, kv_format=hb.HG_KV_E4M3, k_scale=ks, v_scale=vs)
+    return O, L, lambda c, dw, o, l: hb.hg_hydragen_attn_paged(c, dw.Q, dw.levels, kv, dw.lengths, dw.max_len, o, l, dw.scale)
+
+
+def calls(w, cache, what):
+    if w.max_len == 0:
+        pytest.skip("no suffix rows: the caches do not differ")
+    dw = dev.to_device(w)
+    Oref, Lref, call = reference(w, cache)
+    for parts in (32, 0):                     # room for partial results (split columns), none (one workgroup per column)
+        ctx = dev.make_context(dw, parts=parts) if parts else hb.Context(0, 0)
+        ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 2)
+        got = []
+        for _ in range(2):
+            O = torch.full(dw.lead + (dw.D,), float("nan"), dtype=torch.float32, device="cuda:0")
+            L = torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0")
+            call(ctx, dw, O, L)
+            got.append((O, L))
+        torch.cuda.synchronize()
+        check(to_np(got[0][0]), to_np(got[0][1]), Oref, Lref, f"{what} parts={parts}")
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), f"{what}: the second call differs"
+        ctx.close()
+
+
+@pytest.mark.parametrize("cache", ["packed", "paged", "fp8", "paged_fp8"])
+@pytest.mark.parametrize("seed", range(16))
+def test_split_launch_random_trees(seed, cache):
+    w = random_workload(seed)
+    print(f"split launch: random shape {seed} {cache}: B={w.B} Hq={w.Hq} Hkv={w.Hkv} D={w.D} nq={w.nq} "
+          f"levels={[(l.Gn, l.max_rows) for l in w.levels]} max_len={w.max_len}", file=sys.stderr, flush=True)
+    calls(w, cache, f"random {seed} {cache}")
+
+
+@pytest.mark.parametrize("cache", ["packed", "paged_fp8"])
+@pytest.mark.parametrize("D", [64, 128])
+def test_split_launch_long_block(D, cache):
+    """One column, a block long enough for the largest number of workgroups per column."""
+    print(f"split launch: long block D={D} {cache}", file=sys.stderr, flush=True)
+    calls(wl.make_workload("long", 41, 3, 4, 1, D, [(1, 9001, 3)], 1, 70), cache, f"long block D={D} {cache}")

@@ -178,9 +178,7 @@ LevelPlan plan_level(const hg_ctx* c, const LevelDev& lv, int Hkv, int G, int D,
     return p;
 }
 
-// enqueue the shared-block kernel for one level with `ns` splits writing to `out` (part = split)
-int run_level(const void* Q, const LevelDev& lv, LevelPlan plan, int B, int nq, int Hq, int Hkv, int D, float scale,
-              const OutDev& out, hipStream_t s) {
+PrefixArgs level_args(const void* Q, const LevelDev& lv, const LevelPlan& plan, int B, int nq, int Hq, int Hkv, float scale, const OutDev& out) {
     PrefixArgs a{};
     a.Q = static_cast<const uint16_t*>(Q);
     a.lv = lv;
@@ -188,10 +186,15 @@ int run_level(const void* Q, const LevelDev& lv, LevelPlan plan, int B, int nq, 
     a.nq = nq;
     a.scale = scale;
     a.out = out;
-    if (plan.wide) {
-        a.wide = plan.wp;
-        return hip_rc(launch_prefix_wide(a, D, s));
-    }
+    if (plan.wide) a.wide = plan.wp;
+    return a;
+}
+
+// enqueue the shared-block kernel for one level with `ns` splits writing to `out` (part = split)
+int run_level(const void* Q, const LevelDev& lv, const LevelPlan& plan, int B, int nq, int Hq, int Hkv, int D, float scale,
+              const OutDev& out, hipStream_t s) {
+    PrefixArgs a = level_args(Q, lv, plan, B, nq, Hq, Hkv, scale, out);
+    if (plan.wide) return hip_rc(launch_prefix_wide(a, D, s));
     a.mtiles = ceil_div(lv.max_seqs * a.G * nq, kPrefixRowsNarrow);
     a.nsplit = plan.ns;
     a.chunk = round_up(ceil_div(lv.max_rows > 0 ? lv.max_rows : 1, plan.ns), kPrefixKeys);
@@ -255,18 +258,15 @@ SuffixPlan plan_suffix(const hg_ctx* c, int max_len, int G, int B, int nq, int H
     return p;
 }
 
-int run_decode(const void* Q, int n_levels, const LevelDev* lv, const void* Ks, const void* Vs, const int32_t* offsets,
-               const int32_t* lengths, int max_len, int B, int nq, int Hq, int Hkv, int D, float scale, int chunk, int nchunks,
-               int gt, const OutDev& out, hipStream_t s, const PagedDev& pg = PagedDev{}, bool mfma = false, int mfma_ipw = 0, bool seg = false,
-               const KvFmt& fmt = KvFmt{}, int mfma_tile = 0) {
+DecodeArgs suffix_args(const void* Q, const void* Ks, const void* Vs, const int32_t* offsets, const int32_t* lengths, int max_len, int B,
+                       int nq, int Hq, int Hkv, float scale, int chunk, int nchunks, int gt, const OutDev& out, const PagedDev& pg,
+                       const KvFmt& fmt) {
     DecodeArgs a{};
     a.pg = pg;
     a.fp8 = fmt.fp8;
     a.k_scale = fmt.k_scale;
     a.v_scale = fmt.v_scale;
     a.Q = static_cast<const uint16_t*>(Q);
-    a.n_levels = n_levels;
-    for (int i = 0; i < n_levels; ++i) a.lv[i] = lv[i];
     a.Ks = static_cast<const uint16_t*>(Ks);
     a.Vs = static_cast<const uint16_t*>(Vs);
     a.offsets = offsets;
@@ -279,6 +279,16 @@ int run_decode(const void* Q, int n_levels, const LevelDev* lv, const void* Ks, 
     a.units = (int64_t)B * nq * nchunks * Hkv * (a.G / gt);
     a.scale = scale;
     a.out = out;
+    return a;
+}
+
+int run_decode(const void* Q, int n_levels, const LevelDev* lv, const void* Ks, const void* Vs, const int32_t* offsets,
+               const int32_t* lengths, int max_len, int B, int nq, int Hq, int Hkv, int D, float scale, int chunk, int nchunks,
+               int gt, const OutDev& out, hipStream_t s, const PagedDev& pg = PagedDev{}, bool mfma = false, int mfma_ipw = 0, bool seg = false,
+               const KvFmt& fmt = KvFmt{}, int mfma_tile = 0) {
+    DecodeArgs a = suffix_args(Q, Ks, Vs, offsets, lengths, max_len, B, nq, Hq, Hkv, scale, chunk, nchunks, gt, out, pg, fmt);
+    a.n_levels = n_levels;
+    for (int i = 0; i < n_levels; ++i) a.lv[i] = lv[i];
     if (mfma) {
         a.seg = seg ? 1 : 0;
         // up to 16 rows per KV head and sequence fit a 16-row tile: half the matrix and softmax work per stage
@@ -354,6 +364,22 @@ int pick_wide_slots(double flops, double bytes, int T) {
         if (t < best_t * 0.995) { best_t = t; best = eff; }
     }
     return best;
+}
+
+// The same choice for the combined launch, where every CU goes on with suffix work when its shared-block pieces are done:
+// the fewest CUs per XCD that finish the shared block before the end of the call, with a margin.  Fewer CUs pay the
+// persistent kernel's start-up and write its partial results; but the end of the launch must not wait for them.
+// Fitted (us): the call takes ts + 0.65 (tp + 13), ts = the suffix alone, tp = the shared block alone on the whole chip;
+// beside the suffix the shared block takes 1.1 times as long as alone on the same CUs.  Measured calls at 4 / 8 / 12 / 16 / 20 / 24 CUs:
+// 1024 x 40 heads, 16K keys: - / - / 587 / 505 / 484 / 509; 4K keys, 8-bit cache: 428 / 243 / 214 / 218 / 225 / 237;
+// 256 x 40 heads, 2K keys: 135 / 140 / 142 / 144 / 147 / 150; 4K keys at D = 64: 319 / 180 / 180 / 184 / 186 / 196.
+int pick_combined_slots(double flops, double bytes, int T, int D) {
+    static const double rate[] = {0.18, 0.36, 0.543, 0.693, 0.823, 0.895, 0.964, 1.0};      // on 4, 8, .., 32 CUs per XCD
+    const double tp = flops / (D == 128 ? 1.14e15 : 0.63e15) * 1e6, ts = bytes / 6.0e12 * 1e6;
+    const double end = ts + 0.65 * (tp + 13.0);
+    for (int s = 4; s < 32; s += 4)
+        if (s >= T && s % T == 0 && 1.1 * tp / rate[s / 4 - 1] + 13.0 <= 0.85 * end) return s;
+    return T <= 20 ? 20 / T * T : 32 / T * T;
 }
 
 // A context's arrival counters on `device` (current), or null.
@@ -798,6 +824,10 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     int ns[HG_MAX_LEVELS];
     int nlev = 0;
     int wide_slots = 32;
+    // Shared block and suffix in one launch (combined_impl.h): calls with a level on the persistent kernel and one query row
+    // per KV head.  The stage timings need separate kernels.
+    const bool may_combine = c->opt_overlap == 0 && !c->opt_timing && has_suffix && c->arrivals && nq == 1 && G == 1 &&
+                             !plan_suffix(c, max_len, G, B, nq, Hkv, D, pg.table != nullptr, 1 << 30, fmt.fp8 != 0).mfma;
     bool tiny = false;   // so little work that the event edges between two streams cost more than overlap can gain
     if (has_suffix && c->opt_overlap != 1) {
         double flops = 0.0;
@@ -816,6 +846,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         wide_slots = pick_wide_slots(flops, bytes, T);
         tiny = c->opt_overlap == 0 && flops / 1.14e15 + bytes / 6.0e12 < 60e-6;
         if (tiny) wide_slots = 32;
+        if (may_combine) wide_slots = pick_combined_slots(flops, bytes, T, D);
     }
     for (int i = 0; i < n_levels; ++i) {
         LevelDev d = to_dev(levels[i], B);
@@ -860,6 +891,32 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     if (np == 0) return fill_empty(O_out, o_dtype, LSE_out, rows, D, s);
 
     // (grouped levels may leave sequences uncovered: the level's kernel marks their partial results empty)
+
+    // The level on the persistent kernel with the most work shares its launch with the suffix; the other levels go before it.
+    int joint = -1;
+    if (may_combine && (int64_t)B * sp.nchunks * Hkv < (1LL << 30)) {
+        for (int i = 0; i < nlev; ++i)
+            if (plan[i].wide && (joint < 0 || (double)lv[i].max_rows * lv[i].max_seqs > (double)lv[joint].max_rows * lv[joint].max_seqs)) joint = i;
+    }
+    if (joint >= 0) {
+        CombinedArgs ca{};
+        int part = 0;
+        for (int i = 0; i < nlev; ++i) {
+            if (i == joint) {
+                ca.p = level_args(Q, lv[i], plan[i], B, nq, Hq, Hkv, scale, parts_out(parts, part));
+            } else {
+                rc = run_level(Q, lv[i], plan[i], B, nq, Hq, Hkv, D, scale, parts_out(parts, part), s);
+                if (rc) return rc;
+            }
+            part += ns[i];
+        }
+        ca.d = suffix_args(Q, Ks, Vs, offsets, lengths, max_len, B, nq, Hq, Hkv, scale, sp.chunk, sp.nchunks, 1, parts_out(parts, part), pg, fmt);
+        ca.tickets = c->arrivals;
+        ca.long_runs = ((int)ca.d.units - std::min((int)ca.d.units, kTailItems)) / kLongRun;
+        rc = hip_rc(launch_combined(ca, D, s));
+        if (rc) return rc;
+        return run_merge(np, parts, 0, D, O_out, o_dtype, LSE_out, s);
+    }
 
     // Two streams unless asked for one.  In automatic mode a call whose levels all run in the persistent kernel on
     // the whole chip stays on one stream (there is no CU left for the suffix kernel to run beside it), and so does a

@@ -149,12 +149,14 @@ struct WidePiece {
     int has_rows;        // row0 < nrows
 };
 
-__global__ __launch_bounds__(64 * NW, 1) void HG_WIDE_KERNEL(PrefixArgs a) {
+// What one workgroup of the persistent kernel does.  `a` is the kernel's argument, at the start of the kernarg segment;
+// the first 8 * a.wide.slots workgroups of the launch call this.
+__device__ __forceinline__ void wide_role(const PrefixArgs& a) {
     HG_T(0);
 #ifdef HG_TRACE
     if (threadIdx.x == 0) hg_wide_trace[blockIdx.x * kTraceSlots + 28] = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u;   // XCC_ID
 #endif
-    mark_uncovered(a, D, a.wide.nparts, blockIdx.x, gridDim.x);
+    mark_uncovered(a, D, a.wide.nparts, blockIdx.x, 8 * a.wide.slots);
     unsigned char* const smem = wide_smem;
     const WidePlan& p = a.wide;
     const int pid = blockIdx.x;
@@ -749,6 +751,9 @@ __global__ __launch_bounds__(64 * NW, 1) void HG_WIDE_KERNEL(PrefixArgs a) {
     HG_T(15);
 }
 
+#ifdef HG_WIDE_KERNEL
+__global__ __launch_bounds__(64 * NW, 1) void HG_WIDE_KERNEL(PrefixArgs a) { wide_role(a); }
+
 #if defined(HG_TRACE) && HG_WIDE_D == 128
 }  // namespace hg
 // Copies the phase time stamps of the most recent prefix_kernel_wide launches to `out` (HOST, 256 * 32 values) after
@@ -927,5 +932,6 @@ hipError_t launch_prefix_wide_d64(const PrefixArgs& a, hipStream_t s) {
     HG_WIDE_KERNEL<<<8 * a.wide.slots, 64 * NW, LDS_BYTES, s>>>(a);
     return hipGetLastError();
 }
+#endif   // HG_WIDE_KERNEL
 
 }  // namespace hg

@@ -367,19 +367,26 @@ int pick_wide_slots(double flops, double bytes, int T) {
 }
 
 // The same choice for the combined launch, where every CU goes on with suffix work when its shared-block pieces are done:
-// the fewest CUs per XCD that finish the shared block before the end of the call, with a margin.  Fewer CUs pay the
-// persistent kernel's start-up and write its partial results; but the end of the launch must not wait for them.
-// Fitted (us): the call takes ts + 0.65 (tp + 13), ts = the suffix alone, tp = the shared block alone on the whole chip;
-// beside the suffix the shared block takes 1.1 times as long as alone on the same CUs.  Measured calls at 4 / 8 / 12 / 16 / 20 / 24 CUs:
-// 1024 x 40 heads, 16K keys: - / - / 587 / 505 / 484 / 509; 4K keys, 8-bit cache: 428 / 243 / 214 / 218 / 225 / 237;
-// 256 x 40 heads, 2K keys: 135 / 140 / 142 / 144 / 147 / 150; 4K keys at D = 64: 319 / 180 / 180 / 184 / 186 / 196.
-int pick_combined_slots(double flops, double bytes, int T, int D) {
+// the fewest CUs per XCD that finish the shared block before the end of the call.  Fewer CUs pay the persistent kernel's
+// start-up and write its partial results; but the end of the launch must not wait for them.  Fitted (us): the launch
+// takes ts + 0.65 (tp + 13), ts = the suffix alone, tp = the shared block alone on the whole chip; beside the suffix the shared
+// block takes 1.2 times as long as alone on the same CUs, plus its start-up and 7 for every further 256-row tile (pieces)
+// a CU has.  The tile role (tiles) gets a margin of a
+// tenth: it is the slower to catch up.  Measured calls at 4 / 8 / 12 / 16 / 20 / 24 CUs: 1024 x 40 heads, 16K keys:
+// - / 819 / 599 / 516 / 484 / 510; 4K keys, 8-bit cache: 433 / 245 / 219 / 223 / 229 / 246; 256 x 40 heads, 2K keys:
+// 132 / 138 / 139 / 141 / 147 / 150; 512 x 64/8 heads, 4K keys: 349 / 186 / 153 / 134 / 157 / 166; 128 x 32/8 heads, 2K keys, paged:
+// 46 / 52 / 55 / 60 / 64 / 69.
+int pick_combined_slots(double flops, double bytes, double pieces, int D, bool tiles) {
     static const double rate[] = {0.18, 0.36, 0.543, 0.693, 0.823, 0.895, 0.964, 1.0};      // on 4, 8, .., 32 CUs per XCD
     const double tp = flops / (D == 128 ? 1.14e15 : 0.63e15) * 1e6, ts = bytes / 6.0e12 * 1e6;
     const double end = ts + 0.65 * (tp + 13.0);
+    auto shared_us = [&](int s) { return 1.2 * tp / rate[s / 4 - 1] + 13.0 + 7.0 * std::max(0.0, pieces / (8.0 * s) - 1.0); };
     for (int s = 4; s < 32; s += 4)
-        if (s >= T && s % T == 0 && 1.1 * tp / rate[s / 4 - 1] + 13.0 <= 0.85 * end) return s;
-    return T <= 20 ? 20 / T * T : 32 / T * T;
+        if (shared_us(s) <= (tiles ? 0.9 * end + 5.0 : end)) return s;
+    // the shared block decides: the most CUs that leave enough for the suffix meanwhile
+    for (int s = 28; s > 16; s -= 4)
+        if (ts <= 1.3 * (32 - s) / 32.0 * shared_us(s)) return s;
+    return 16;
 }
 
 // A context's arrival counters on `device` (current), or null.
@@ -735,15 +742,24 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     const bool has_suffix = Ks != nullptr && max_len > 0;
     const Ws ws = ws_override ? *ws_override : Ws{c->ws, c->ws_bytes};
 
+    // Shared block and suffix in one launch (combined_impl.h): calls with a level on the persistent kernel and a suffix on the
+    // matrix cores or with one query row per KV head.  The stage timings need separate kernels.
+    // (8-bit codes in 32-row tiles stay on separate kernels: half the bytes in flight per wavefront do not cover the longer
+    // stage; 215 sequences, 64/8 heads, 4 queries: 83 against 76 us.)
+    const bool may_combine = c->opt_overlap == 0 && !c->opt_timing && has_suffix && c->arrivals && !(fmt.fp8 && (nq * G > 16 || c->opt_suffix_tile == 32)) &&
+                             ((nq == 1 && G == 1) || plan_suffix(c, max_len, G, B, nq, Hkv, D, pg.table != nullptr, 1 << 30, fmt.fp8 != 0).mfma);
+
     // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
     // column of 32 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two
     // event edges and a round trip of the partial results through HBM for the separate kernels.  Both durations are
     // estimated, in microseconds, from fits to 82 shapes (B = 4 .. 2048, 0 .. 16K shared keys, every cache and head layout):
     //   single launch: 4 + rounds x (4 + c x stages per wavefront), c = 1.6 us per 32-key stage while a quarter of the CUs
     //                  are busy (the latency of one stage's K and V rows), 2.3 with all of them; 4.5 + 0.3 x splits more when
-    //                  a column's workgroups have to meet; never faster than the rows stream in (5 TB/s);
+    //                  a column's workgroups have to meet; never faster than the suffix rows stream in (5 TB/s, 3.3 through a page table)
+    //                  and the shared rows, which every column reads for itself, at 8 TB/s once they do not fit the L2;
     //   separate:      18, 6 and 10 more with one and two shared levels, 8 more once a block is long enough to be split,
-    //                  suffix rows at 5 TB/s, shared blocks at 1.1 PFLOP/s or 5 TB/s.
+    //                  suffix rows at 5 TB/s, shared blocks at 1.1 PFLOP/s or 5 TB/s; with many suffix rows and one launch for
+    //                  both (below) 25, and 0.8 of the suffix time.
     // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single
     // launch is taken below the other estimate, from 60 us on only when it is 25 % below (the model of the separate kernels
     // is pessimistic where suffixes and shared blocks overlap).  Measured single / separate: 12.4 / 25 us (72 sequences,
@@ -784,9 +800,14 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         }
         const double suffix_us = has_suffix ? (fmt.fp8 ? 2.0 : 4.0) * B * (0.75 * max_len) * Hkv * D / 5.0e6 : 0.0;      // at 5 TB/s
         const double shared_us = shared_bytes / 5.0e6;
-        const double est_single = std::max(chain_at(splits), suffix_us + shared_us + 7.0);
-        const double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
+        // every column reads the shared rows for itself: from its XCD's L2 (4 MB; an XCD works on its share of the KV heads)
+        // while they fit there, at 8 TB/s beyond
+        const double restream_us = shared_bytes / std::min(8, Hkv) > 4.0e6
+                                       ? (double)cols * ((shared_keys + 31) / 32) * 128.0 * D / 8.0e6 + suffix_us + 13.0 : 0.0;
+        const double est_single = std::max({chain_at(splits), (pg.table ? 1.5 : 1.0) * suffix_us + shared_us + 7.0, restream_us});
+        double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
                                     suffix_us + std::max(flops / 1.1e9, shared_us);
+        if (suffix_us >= 30.0 && may_combine && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
         const bool small = est_single <= (est_single <= 60.0 ? 1.0 : 0.75) * est_separate;
         if (any && cols * splits < (1LL << 31) && (c->opt_fused_kernel == 2 || small)) {
             SmallArgs sa{};
@@ -824,19 +845,17 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     int ns[HG_MAX_LEVELS];
     int nlev = 0;
     int wide_slots = 32;
-    // Shared block and suffix in one launch (combined_impl.h): calls with a level on the persistent kernel and one query row
-    // per KV head.  The stage timings need separate kernels.
-    const bool may_combine = c->opt_overlap == 0 && !c->opt_timing && has_suffix && c->arrivals && nq == 1 && G == 1 &&
-                             !plan_suffix(c, max_len, G, B, nq, Hkv, D, pg.table != nullptr, 1 << 30, fmt.fp8 != 0).mfma;
     bool tiny = false;   // so little work that the event edges between two streams cost more than overlap can gain
     if (has_suffix && c->opt_overlap != 1) {
         double flops = 0.0;
         int T = 1;
+        double pieces = 0.0;     // 256-row tiles of the largest level on the persistent kernel, all blocks and KV heads
         for (int i = 0; i < n_levels; ++i) {
             const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B;
             flops += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * seqs * nq * Hq * D;
             const long long tiles = (seqs * nq * G + kPrefixRowsWide - 1) / kPrefixRowsWide;
             if (seqs * nq * G > kPrefixRowsNarrow && tiles <= 32 && tiles > T) T = (int)tiles;
+            if (seqs * nq * G > kPrefixRowsNarrow) pieces = std::max(pieces, (double)tiles * levels[i].n_blocks * Hkv);
         }
         // K and V, bf16 (or 8-bit codes; on the matrix cores their expansion costs about a third of the saving); the
         // vector-ALU kernel reads them once per query; mean length taken as 0.75 max_len
@@ -846,7 +865,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         wide_slots = pick_wide_slots(flops, bytes, T);
         tiny = c->opt_overlap == 0 && flops / 1.14e15 + bytes / 6.0e12 < 60e-6;
         if (tiny) wide_slots = 32;
-        if (may_combine) wide_slots = pick_combined_slots(flops, bytes, T, D);
+        if (may_combine) wide_slots = pick_combined_slots(flops, 0.8 * bytes, pieces, D, sfx_mfma);     // (here the mean is taken as 0.6 max_len)
     }
     for (int i = 0; i < n_levels; ++i) {
         LevelDev d = to_dev(levels[i], B);
@@ -858,6 +877,15 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     }
     const int max_chunk = pg.table ? 32 << pg.shift : 1 << 30;
     SuffixPlan sp = plan_suffix(c, max_len, G, B, nq, Hkv, D, pg.table != nullptr, max_chunk, fmt.fp8 != 0);
+    // (the combined launch has 2048 wavefronts: items for all of them, equal shares of the longest suffix)
+    if (may_combine && sp.mfma && c->opt_suffix_chunk == 0) {
+        const long long whole = (long long)B * Hkv * ceil_div(nq * G, 32);
+        const int n = (int)std::min<long long>({(2047 + whole) / whole, 4, std::max(1, max_len / 128)});
+        if (n > sp.nchunks) {
+            sp.chunk = round_up(ceil_div(max_len, n), 32);
+            sp.nchunks = ceil_div(max_len, sp.chunk);
+        }
+    }
     if (!has_suffix) sp.nchunks = 0;
     auto total_parts = [&]() { int t = sp.nchunks; for (int i = 0; i < nlev; ++i) t += ns[i]; return t; };
     if (nlev + (has_suffix ? 1 : 0) > parts.cap) return HG_ERR_WORKSPACE;
@@ -894,7 +922,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
 
     // The level on the persistent kernel with the most work shares its launch with the suffix; the other levels go before it.
     int joint = -1;
-    if (may_combine && (int64_t)B * sp.nchunks * Hkv < (1LL << 30)) {
+    if (may_combine && (int64_t)B * nq * G * sp.nchunks * Hkv < (1LL << 30)) {
         for (int i = 0; i < nlev; ++i)
             if (plan[i].wide && (joint < 0 || (double)lv[i].max_rows * lv[i].max_seqs > (double)lv[joint].max_rows * lv[joint].max_seqs)) joint = i;
     }
@@ -912,8 +940,16 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         }
         ca.d = suffix_args(Q, Ks, Vs, offsets, lengths, max_len, B, nq, Hq, Hkv, scale, sp.chunk, sp.nchunks, 1, parts_out(parts, part), pg, fmt);
         ca.tickets = c->arrivals;
-        ca.long_runs = ((int)ca.d.units - std::min((int)ca.d.units, kTailItems)) / kLongRun;
-        rc = hip_rc(launch_combined(ca, D, s));
+        if (sp.mfma) {
+            ca.d.tile_rows = (nq * G <= 16 && c->opt_suffix_tile != 32) ? 16 : 32;
+            ca.d.units = (int64_t)B * sp.nchunks * ceil_div(nq * G, ca.d.tile_rows) * Hkv;
+        }
+        const int units = (int)ca.d.units, tail = units - std::max(0, units - kTailItems) / kLongRun * kLongRun;
+        ca.long_runs = (units - tail) / kLongRun;
+        ca.tail_run = units <= kTailItems ? ceil_div(units, 256) : 2;
+        ca.n_tickets = ca.long_runs + ceil_div(tail, ca.tail_run);
+        if (sp.mfma) rc = hip_rc(D == 128 ? launch_combined_tiles(ca, s) : launch_combined_tiles_d64(ca, s));
+        else rc = hip_rc(D == 128 ? launch_combined_vector(ca, s) : launch_combined_vector_d64(ca, s));
         if (rc) return rc;
         return run_merge(np, parts, 0, D, O_out, o_dtype, LSE_out, s);
     }

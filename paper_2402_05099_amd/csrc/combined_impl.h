@@ -11,20 +11,87 @@
 // 4K keys with an 8-bit cache 258 -> 233, 4K keys at D = 64 205 -> 183.  What bounds it: HBM and the board's power while the
 // shared block runs, HBM afterwards (5.6 TB/s over the launch at 2K keys).
 //
-// Suffix role (one query row per KV head, vector ALU, the arithmetic of decode.hip): a CU holds eight wavefronts here where
+// Suffix role, one query row per KV head (SuffixStream; vector ALU, the arithmetic of decode.hip): a CU holds eight wavefronts here where
 // decode.hip runs about twenty, so each has to keep more bytes in flight: a wavefront streams the batches (16 keys; 32 at
 // D = 64) of its work items as one sequence, NB - 1 batches ahead of the one it multiplies, across the ends of work
 // items.  Every batch is loaded by the same unconditional instructions (lanes past an item's last key re-read its
 // first; a wavefront without further work re-reads its last batch's first key), so that the compiler's wait counts stay
 // exact, and carries the item's query row along.
+//
+// Suffix role, several query rows per KV head (SuffixTiles; matrix cores, the arithmetic of decode_mfma.hip): decode_mfma.hip
+// runs four wavefronts with two 16 KiB slots each on a CU; eight here have one K and one V slot of 8 KiB: the next stage's K
+// rows are requested as soon as this stage's scores are done, its V rows after the value product, and across items the
+// next item's first K rows during the last stage, its query tile (through the V slot) while the results are stored.
 #include "decode_core.h"
+#include "decode_mfma_core.h"
 #include "prefix_wide_impl.h"
+
+#pragma clang diagnostic ignored "-Winline-asm"
 
 namespace hg {
 
 namespace {
 
 typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
+
+// The workgroup's other LDS, behind the ring: the queue, two counters, and the order of the sequences.
+constexpr int kQueueOffset = LDS_RING_BYTES, kDoneOffset = kQueueOffset + 16, kCountsOffset = kQueueOffset + 64;
+constexpr int kOrderOffset = kQueueOffset + 512, kMaxOrdered = (LDS_BYTES - kOrderOffset) / 2 / 1024 * 1024;
+constexpr int kLengthClasses = 8;
+static_assert(kLengthClasses * NW == 64, "one lane per class and wavefront");
+
+// order[0 .. B): the sequences in descending order of their length class (eighths of max_len), by number within a class, so
+// that the last items handed out are the short ones.  Every workgroup computes it for itself (3 us, 512 lengths per round)
+// and all come to the same order.  Longest first against order of the sequences: 512 x 64/8 heads with suffixes of 1..512
+// rows 148 -> 131 us, 256 x 40 heads, 1..256 rows 135 -> 127.
+__device__ __forceinline__ void order_by_length(const DecodeArgs& a, unsigned char* smem) {
+    uint16_t* const order = reinterpret_cast<uint16_t*>(smem + kOrderOffset);
+    unsigned* const counts = reinterpret_cast<unsigned*>(smem + kCountsOffset);      // [class][wavefront]
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int seg = (a.B + 64 * NW - 1) / (64 * NW) * 64;           // sequences of one wavefront, a contiguous range
+    const int b0 = min(w * seg, a.B), b1 = min(b0 + seg, a.B);
+    const float per = (float)kLengthClasses / (float)(a.max_len + 1);
+    auto class_of = [&](int b) -> int {
+        const int n = b < b1 ? max(min(a.lengths[b], a.max_len), 0) : 0;
+        return b < b1 ? kLengthClasses - 1 - min((int)((float)n * per), kLengthClasses - 1) : kLengthClasses;
+    };
+    int cnt[kLengthClasses] = {};
+    for (int b = b0; b < b1; b += 64) {
+        const int k = class_of(b + lane);
+#pragma unroll
+        for (int i = 0; i < kLengthClasses; ++i) cnt[i] += __popcll(__ballot(k == i));
+    }
+    if (lane == 0)
+#pragma unroll
+        for (int i = 0; i < kLengthClasses; ++i) counts[i * NW + w] = cnt[i];
+    __syncthreads();
+    unsigned at = counts[lane];
+    const unsigned own = at;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {          // exclusive prefix sum over (class, wavefront)
+        const unsigned below = __shfl_up(at, d);
+        if (lane >= d) at += below;
+    }
+    at -= own;
+    int base[kLengthClasses];
+#pragma unroll
+    for (int i = 0; i < kLengthClasses; ++i) base[i] = __builtin_amdgcn_readlane((int)at, i * NW + w);
+    for (int b = b0; b < b1; b += 64) {
+        const int k = class_of(b + lane);
+#pragma unroll
+        for (int i = 0; i < kLengthClasses; ++i) {
+            const unsigned long long m = __ballot(k == i);
+            if (k == i) order[base[i] + __popcll(m & ((1ull << lane) - 1))] = (uint16_t)(b + lane);
+            base[i] += __popcll(m);
+        }
+    }
+    __syncthreads();
+}
+// the sequence at position p of that order
+__device__ __forceinline__ int sequence_at(const DecodeArgs& a, const unsigned char* smem, int p) {
+    if (a.B > kMaxOrdered) return p;
+    return __builtin_amdgcn_readfirstlane((int)reinterpret_cast<const uint16_t*>(smem + kOrderOffset)[p]);
+}
 
 // A workgroup's queue of work items, in LDS: items [pos, end) are left of the run it holds, pos in the low word.  pos
 // beyond end: the run is used up and a wavefront is fetching the next one; end = 0: there are no more.
@@ -35,9 +102,19 @@ constexpr queue_word kQueueFinished = 0x40000000u;
 // The items of ticket t: [base, stop), stop not beyond the last item.
 __device__ __forceinline__ unsigned run_of(const CombinedArgs& ca, unsigned t, unsigned& stop) {
     const unsigned nl = (unsigned)ca.long_runs;
-    const unsigned base = t < nl ? t * kLongRun : nl * kLongRun + (t - nl) * kTailRun;
-    stop = min(base + (t < nl ? kLongRun : kTailRun), (unsigned)ca.d.units);
+    const unsigned size = t < nl ? (unsigned)kLongRun : (unsigned)ca.tail_run;
+    const unsigned base = t < nl ? t * kLongRun : nl * kLongRun + (t - nl) * size;
+    stop = min(base + size, (unsigned)ca.d.units);
     return base;
+}
+
+// Tickets handed out without a draw (256 draws at one address take 3 us): a workgroup without shared-block work starts with
+// ticket blockIdx.x - 8 * wide.slots; where every workgroup has shared-block work, so that all would draw at the same time
+// after it, each starts with ticket blockIdx.x.
+__device__ __forceinline__ unsigned first_ticket(const CombinedArgs& ca, unsigned& given) {
+    const unsigned wide = 8 * ca.p.wide.slots;
+    given = wide == gridDim.x ? wide : gridDim.x - wide;
+    return wide == gridDim.x ? blockIdx.x : blockIdx.x - wide;      // (beyond `given` for a workgroup that starts without one)
 }
 
 // Next work item for this wavefront (-1: none left).  The wavefront that finds the run just used up draws the next
@@ -54,14 +131,17 @@ __device__ __forceinline__ int take_item(const CombinedArgs& ca, queue_word* que
         if (end == 0) return -1;
         if (pos < end) return (int)pos;
         if (pos == end) {
-            unsigned t = 0;
-            if (lane0) t = __hip_atomic_fetch_add(ca.tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            t = (unsigned)__builtin_amdgcn_readfirstlane((int)t);
-            t += (unsigned)(gridDim.x - 8 * ca.p.wide.slots);      // tickets handed out in advance, see the kernel
+            unsigned given;
+            first_ticket(ca, given);
+            unsigned t = (unsigned)ca.n_tickets;
+            if (given < t) {
+                t = 0;
+                if (lane0) t = __hip_atomic_fetch_add(ca.tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                t = (unsigned)__builtin_amdgcn_readfirstlane((int)t) + given;
+            }
+            const bool any = t < (unsigned)ca.n_tickets;
             unsigned stop;
             const unsigned base = run_of(ca, t, stop);
-            const unsigned units = (unsigned)ca.d.units;
-            const bool any = base < units;
             if (lane0)
                 __hip_atomic_store(queue, any ? ((queue_word)stop << 32) | (base + 1) : kQueueFinished, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             return any ? (int)base : -1;
@@ -85,7 +165,7 @@ struct SuffixStream {
         KVBatch<D, U, FP8, EPL> kv;
         unsigned q[QW];
         int left;      // keys of the item from this batch on (0: no batch)
-        int unit;      // the item, and bit 31: this is its first batch
+        int unit;      // the item's index in the results (query row * nchunks + chunk), and bit 31: this is its first batch
     };
 
     const CombinedArgs& ca;
@@ -93,6 +173,7 @@ struct SuffixStream {
     const int lane, sub;
     const unsigned rstride_b, colb, subrow;
     // the item whose batches are being loaded
+    unsigned char* const smem;
     queue_word* const queue;
     int no_more;              // the queue has been seen empty for good
     int left, first;          // keys not yet requested; the next batch is the item's first
@@ -102,9 +183,9 @@ struct SuffixStream {
     const unsigned char* vb;
     const unsigned char* qp;  // the item's query row
 
-    __device__ __forceinline__ SuffixStream(const CombinedArgs& c, queue_word* qu, int l)
+    __device__ __forceinline__ SuffixStream(const CombinedArgs& c, unsigned char* sm, int l)
         : ca(c), a(c.d), lane(l), sub(l / LPR), rstride_b((unsigned)c.d.Hkv * D * ES), colb((unsigned)(l % LPR) * EPL * ES),
-          subrow((unsigned)(l / LPR) * ((unsigned)c.d.Hkv * D * ES) + (unsigned)(l % LPR) * EPL * ES), queue(qu) {
+          subrow((unsigned)(l / LPR) * ((unsigned)c.d.Hkv * D * ES) + (unsigned)(l % LPR) * EPL * ES), smem(sm), queue(reinterpret_cast<queue_word*>(sm + kQueueOffset)) {
         no_more = 0;
         left = 0;
         first = 0;
@@ -134,7 +215,7 @@ struct SuffixStream {
             const int u = take_item(ca, queue);
             if (u < 0) { no_more = 1; return; }
             const int kvh = __builtin_amdgcn_readfirstlane(u % a.Hkv), bc = __builtin_amdgcn_readfirstlane(u / a.Hkv);
-            const int c = __builtin_amdgcn_readfirstlane(bc % a.nchunks), b = __builtin_amdgcn_readfirstlane(bc / a.nchunks);
+            const int c = __builtin_amdgcn_readfirstlane(bc % a.nchunks), b = sequence_at(a, smem, __builtin_amdgcn_readfirstlane(bc / a.nchunks));
             const int count = min(lengths[b], a.max_len);
             const int lo = c * a.chunk;
             const int n = __builtin_amdgcn_readfirstlane(min(count - lo, a.chunk));
@@ -142,7 +223,7 @@ struct SuffixStream {
                 if (lane == 0) a.out.LSE[(int64_t)c * a.out.part_stride_L + (int64_t)b * a.Hq + kvh] = -INFINITY;
                 continue;
             }
-            cur_unit = u;
+            cur_unit = (b * a.Hq + kvh) * a.nchunks + c;
             cur_kvh = kvh;
             left = n;
             first = 1;
@@ -253,8 +334,7 @@ struct SuffixStream {
                     consume_batch<D, 1, U, FP8, EPL>(st, cb.kv, sub, cb.left);
                     if (cb.left <= STEP) {
                         const int u = cb.unit & 0x7fffffff;
-                        const int kvh = u % a.Hkv, bc = u / a.Hkv;
-                        decode_finish<D, 1, FP8, EPL>(st, a, bc / a.nchunks, kvh, bc % a.nchunks, lane);
+                        decode_finish<D, 1, FP8, EPL>(st, a, 0, u / a.nchunks, u % a.nchunks, lane);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -263,7 +343,232 @@ struct SuffixStream {
     }
 };
 
+// Several query rows per KV head: a work item is (sequence, KV head, tile of TR query rows, key chunk), as in decode_mfma.hip.
+template <bool PAGED, bool FP8, int TR>
+struct SuffixTiles {
+    using Tile = dm::MfmaTile<D, FP8, TR>;
+    using G_ = dm::Geo<D>;
+    static constexpr int KEYS = dm::KT, CPSG = Tile::CPSG, RPIG = Tile::RPIG, CPRG = Tile::CPRG, QOPS = Tile::QOPS, ES = Tile::ES;
+    static constexpr int kSlot = 8192;               // K slot, then V slot, per wavefront
+    static_assert(KEYS * D * ES <= kSlot && TR * D * 2 <= kSlot, "a stage's rows and a query tile fit a slot");
+    static_assert(NW * 2 * kSlot <= LDS_RING_BYTES, "the slots lie in the ring's memory");
+
+    struct Item {
+        int b, c, rt, kvh;
+        int off, count;      // first suffix row of the sequence in Ks/Vs; suffix rows the newest query sees
+        int ks, ke;          // absolute rows [ks, ke) of this item's keys
+        int kwin, nst;       // first row of the last full window of the range (packed rows); stages
+    };
+
+    const CombinedArgs& ca;
+    const DecodeArgs& a;
+    unsigned char* const smem;
+    queue_word* const queue;
+    const int l, R, RT;
+    const unsigned rstride_b;
+    unsigned char* const lds;
+    unsigned ldsb;
+    int no_more;
+    unsigned voffK[CPSG], voffV[CPSG], voffQ[QOPS];      // lane offsets of the copies: K/V stage rows, query tile rows
+    int voff_clamp, voff_rt;                             // the row clamp / row tile they were computed for
+    int pg0, pg1;                                        // paged: pages of the stage whose K rows were requested last
+    int lane_rt, lane_tq, lane_g;                        // this lane's row of tile lane_rt: query, head in the group
+    bool rv;
+
+    __device__ __forceinline__ SuffixTiles(const CombinedArgs& c, unsigned char* sm)
+        : ca(c), a(c.d), smem(sm), queue(reinterpret_cast<queue_word*>(sm + kQueueOffset)), l(threadIdx.x & 63), R(c.d.nq * c.d.G), RT((c.d.nq * c.d.G + TR - 1) / TR),
+          rstride_b((unsigned)c.d.Hkv * D * ES), lds(sm + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (2 * kSlot)) {
+        ldsb = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)HG_LDS(lds));
+        no_more = 0;
+        voff_clamp = voff_rt = lane_rt = -1;
+        pg0 = pg1 = 0;
+        lane_tq = lane_g = 0;
+        rv = false;
+    }
+
+    __device__ __forceinline__ void lane_of(const Item& it) {
+        if (it.rt != lane_rt) {
+            lane_rt = it.rt;
+            const int r = it.rt * TR + (TR == 16 ? (l & 15) : (l & 31));
+            rv = r < R;
+            const int rr = rv ? r : 0;
+            lane_tq = rr / a.G;
+            lane_g = rr % a.G;
+        }
+    }
+    __device__ __forceinline__ int64_t row_of(const Item& it) const { return ((int64_t)it.b * a.nq + lane_tq) * a.Hq + it.kvh * a.G + lane_g; }
+
+    // the next item with keys (false: none left) and the lane offsets of its copies; items without keys get their empty result
+    __device__ __forceinline__ bool next_item(Item& it) {
+        const const_i32_ptr lengths = (const_i32_ptr)(uintptr_t)a.lengths;
+        const const_i32_ptr offsets = (const_i32_ptr)(uintptr_t)a.offsets;
+        for (;;) {
+            if (no_more) return false;
+            int u = take_item(ca, queue);
+            if (u < 0) { no_more = 1; return false; }
+            it.kvh = __builtin_amdgcn_readfirstlane(u % a.Hkv); u = __builtin_amdgcn_readfirstlane(u / a.Hkv);
+            it.rt = __builtin_amdgcn_readfirstlane(u % RT); u = __builtin_amdgcn_readfirstlane(u / RT);
+            it.c = __builtin_amdgcn_readfirstlane(u % a.nchunks);
+            it.b = sequence_at(a, smem, __builtin_amdgcn_readfirstlane(u / a.nchunks));
+            it.count = __builtin_amdgcn_readfirstlane(max(min(lengths[it.b], a.max_len), 0));
+            it.off = PAGED ? 0 : __builtin_amdgcn_readfirstlane(offsets[it.b]);
+            const int lo = it.c * a.chunk, hi = min(lo + a.chunk, it.count);
+            if (lo < hi) {
+                it.ks = __builtin_amdgcn_readfirstlane(it.off + lo);
+                it.ke = __builtin_amdgcn_readfirstlane(it.off + hi);
+                break;
+            }
+            lane_of(it);
+            if (rv && l < TR) a.out.LSE[(int64_t)it.c * a.out.part_stride_L + row_of(it)] = -INFINITY;
+        }
+        it.kwin = PAGED ? 0x3fffffff : max(it.ke - KEYS, 0);     // paged: stages stay where they are, rows past ke are masked
+        it.nst = (it.ke - it.ks + KEYS - 1) / KEYS;
+        const int rowclamp = PAGED ? KEYS - 1 : min(it.ke - 1 - it.kwin, KEYS - 1);   // < 31 only when the range ends before row 32 of the tensor
+        if (rowclamp != voff_clamp) {
+            voff_clamp = rowclamp;
+#pragma unroll
+            for (int i = 0; i < CPSG; ++i) {
+                const int srow = i * RPIG + l / CPRG, ch = l % CPRG;
+                const unsigned ro = (unsigned)min(srow, rowclamp) * rstride_b;
+                if (FP8) {
+                    voffK[i] = ro + (unsigned)((ch ^ ((srow >> 1) & 7)) * 16);
+                    voffV[i] = ro + (unsigned)((ch ^ (((srow >> 1) & 1) | (((srow >> (TR == 16 ? 4 : 3)) & 1) << 1))) * 16);
+                } else {
+                    voffK[i] = ro + (unsigned)((ch ^ G_::kswz(srow)) * 16);
+                    voffV[i] = ro + (unsigned)((ch ^ G_::vswz(srow)) * 16);
+                }
+            }
+        }
+        if (it.rt != voff_rt) {
+            voff_rt = it.rt;
+#pragma unroll
+            for (int i = 0; i < QOPS; ++i) {
+                const int srow = i * G_::RPI + l / G_::CPR;
+                int r = it.rt * TR + srow;
+                if (r >= R) r = 0;
+                voffQ[i] = (unsigned)((r / a.G) * a.Hq + r % a.G) * G_::ROWB + (unsigned)(((l % G_::CPR) ^ G_::kswz(srow)) * 16);
+            }
+        }
+        return true;
+    }
+
+    // ---- copies, issued from inline asm and waited for with counted s_waitcnt (see decode_mfma.hip) ----
+    __device__ __forceinline__ void copy16(const unsigned char* sbase, unsigned voff, unsigned lds_dst) const {
+        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(sbase), "s"(lds_dst) : "memory", "m0");
+    }
+    __device__ __forceinline__ void issue_rows(const Item& it, int t, const uint16_t* base, const unsigned (&voff)[CPSG], unsigned dst) const {
+        const unsigned char* const bp = reinterpret_cast<const unsigned char*>(base);
+        if constexpr (PAGED) {
+            const int r0 = it.ks + t * KEYS, ps_mask = (1 << a.pg.shift) - 1;
+#pragma unroll
+            for (int i = 0; i < CPSG; ++i) {
+                const int jr = r0 + i * RPIG;
+                const int64_t prow = ((int64_t)(i < CPSG / 2 ? pg0 : pg1) << a.pg.shift) + (jr & ps_mask);
+                copy16(uniform_ptr(bp + prow * rstride_b + (int64_t)it.kvh * (D * ES)), voff[i] - (unsigned)(i * RPIG) * rstride_b, dst + i * 1024);
+            }
+        } else {
+            const int k0c = min(it.ks + t * KEYS, it.kwin);
+            const unsigned char* const g = uniform_ptr(bp + (int64_t)k0c * rstride_b + (int64_t)it.kvh * (D * ES));
+#pragma unroll
+            for (int i = 0; i < CPSG; ++i) copy16(g, voff[i], dst + i * 1024);
+        }
+    }
+    __device__ __forceinline__ void issue_k(const Item& it, int t) {
+        if constexpr (PAGED) {     // the four or eight rows of one copy lie in one page (pages hold a power of two >= 16 rows)
+            const const_i32_ptr table = (const_i32_ptr)(uintptr_t)a.pg.table;
+            const int64_t trow = (int64_t)it.b * a.pg.stride;
+            const int r0 = it.ks + t * KEYS;
+            pg0 = __builtin_amdgcn_readfirstlane(min(max(table[trow + min(r0 >> a.pg.shift, a.pg.stride - 1)], 0), a.pg.n_pages - 1));
+            pg1 = __builtin_amdgcn_readfirstlane(min(max(table[trow + min((r0 + KEYS / 2) >> a.pg.shift, a.pg.stride - 1)], 0), a.pg.n_pages - 1));
+        }
+        issue_rows(it, t, a.Ks, voffK, ldsb);
+    }
+    __device__ __forceinline__ void issue_v(const Item& it, int t) const { issue_rows(it, t, a.Vs, voffV, ldsb + kSlot); }
+    __device__ __forceinline__ void issue_q(const Item& it) const {
+        const unsigned char* const q = uniform_ptr(reinterpret_cast<const unsigned char*>(a.Q + ((int64_t)it.b * a.nq * a.Hq + it.kvh * a.G) * D));
+#pragma unroll
+        for (int i = 0; i < QOPS; ++i) copy16(q, voffQ[i], ldsb + kSlot + i * (G_::RPI * G_::ROWB));
+    }
+
+    __device__ __forceinline__ void run() {
+        Item nx{};
+        if (!next_item(nx)) return;
+        Tile tile(FP8 ? a.scale * a.k_scale : a.scale, l);
+        unsigned char* const vslot = lds + kSlot;
+        // K rows of the first stage, query tile (through the V slot), V rows of the first stage
+        auto begin = [&]() {
+            dm::wait_vm<0>();                     // the query tile, and the K rows requested before it
+            asm volatile("" ::: "memory");
+            tile.load_q(vslot);
+            issue_v(nx, 0);
+        };
+        issue_k(nx, 0);
+        issue_q(nx);
+        begin();
+        for (bool more = true; more;) {
+            const Item it = nx;
+            lane_of(it);
+            const int vis_end = it.off + it.count - (a.nq - 1 - lane_tq);     // this lane's query sees absolute rows below vis_end
+            const int causal_from = it.off + it.count - (a.nq - 1);           // below this row every query sees every key
+            tile.clear();
+            for (int t = 0; t < it.nst; ++t) {
+                const bool last = t + 1 == it.nst;
+                if (t > 0) {
+                    dm::wait_vm<CPSG>();          // at most this stage's V rows are outstanding: its K rows are there
+                    asm volatile("" ::: "memory");
+                }
+                typename Tile::Scores S;
+                uintx4 pb[2];
+                tile.scores(lds, S);
+                if constexpr (TR == 16) asm volatile("" : "+v"(S.S4[0]), "+v"(S.S4[1]));     // the K rows have been read
+                else asm volatile("" : "+v"(S.S));
+                asm volatile("" ::: "memory");
+                if (!last) {
+                    issue_k(it, t + 1);
+                } else {
+                    more = next_item(nx);
+                    if (more) issue_k(nx, 0);
+                }
+                const int key0 = it.ks + t * KEYS, k0c = min(key0, it.kwin);
+                // stage rows before the stage's first key (window clamp), past the range, and not visible to this lane's query yet
+                if (k0c != key0 || key0 + KEYS > it.ke || key0 + KEYS > causal_from) tile.mask(S, key0 - k0c, min(it.ke, vis_end) - k0c);
+                tile.softmax(S, pb);
+                if (!last || more) dm::wait_vm<CPSG>();     // at most the K rows just requested are outstanding
+                else dm::wait_vm<0>();
+                asm volatile("" ::: "memory");
+                // rows that are nobody's keys may hold anything
+                if (PAGED && key0 + KEYS > it.ke) tile.clear_v_rows(vslot, 0, it.ke - key0);
+                if (k0c != key0) tile.clear_v_rows(vslot, key0 - k0c, KEYS);
+                tile.values(vslot, pb);
+                if (!last) issue_v(it, t + 1);
+            }
+            if (more) {
+                issue_q(nx);
+                begin();
+            }
+            // (the stores follow the next item's first V rows: nothing waits for them before those have landed)
+            lane_of(it);
+            tile.store(a.out, it.c, row_of(it), rv, a.v_scale);
+        }
+    }
+};
+
 template <bool PAGED, bool FP8>
+struct VectorRole {
+    static __device__ __forceinline__ void run(const CombinedArgs& c, unsigned char* smem) {
+        SuffixStream<PAGED, FP8> s(c, smem, threadIdx.x & 63);
+        s.run();
+    }
+};
+template <bool PAGED, bool FP8, int TR>
+struct TileRole {
+    static __device__ __forceinline__ void run(const CombinedArgs& c, unsigned char* smem) {
+        SuffixTiles<PAGED, FP8, TR> s(c, smem);
+        s.run();
+    }
+};
+
+template <class Role>
 __global__ __launch_bounds__(64 * NW, 1) void combined_kernel(CombinedArgs c) {
     unsigned char* const smem = wide_smem;
     if (blockIdx.x < 8 * c.p.wide.slots) {
@@ -271,24 +576,23 @@ __global__ __launch_bounds__(64 * NW, 1) void combined_kernel(CombinedArgs c) {
         __builtin_amdgcn_s_waitcnt(0x0F70);      // copies that nobody consumed have landed
         __syncthreads();
     }
-    queue_word* const queue = reinterpret_cast<queue_word*>(smem);
-    unsigned* const done = reinterpret_cast<unsigned*>(smem + 16);     // wavefronts of this workgroup that are done
+    queue_word* const queue = reinterpret_cast<queue_word*>(smem + kQueueOffset);
+    unsigned* const done = reinterpret_cast<unsigned*>(smem + kDoneOffset);     // wavefronts of this workgroup that are done
     if (threadIdx.x == 0) {
-        // a workgroup without shared-block work has its first ticket without a draw (256 draws at once take 3 us)
         queue_word first = kQueueEmpty;
-        if (blockIdx.x >= 8 * c.p.wide.slots) {
+        unsigned given;
+        const unsigned t = first_ticket(c, given);
+        if (t < given && t < (unsigned)c.n_tickets) {
             unsigned stop;
-            const unsigned base = run_of(c, blockIdx.x - 8 * c.p.wide.slots, stop);
-            if (base < stop) first = ((queue_word)stop << 32) | base;
+            const unsigned base = run_of(c, t, stop);
+            first = ((queue_word)stop << 32) | base;
         }
         *queue = first;
         *done = 0;
     }
+    if (c.d.B <= kMaxOrdered) order_by_length(c.d, smem);
     __syncthreads();
-    {
-        SuffixStream<PAGED, FP8> s(c, queue, threadIdx.x & 63);
-        s.run();
-    }
+    Role::run(c, smem);
     // no wavefront of this workgroup draws any more once all eight are here: the last workgroup of the launch sets the
     // counters back to zero for the next call
     if ((threadIdx.x & 63) == 0) {
@@ -303,31 +607,47 @@ __global__ __launch_bounds__(64 * NW, 1) void combined_kernel(CombinedArgs c) {
     }
 }
 
-template <bool PAGED, bool FP8>
-hipError_t launch_combined_t(const CombinedArgs& c, hipStream_t s) {
+template <class Role>
+hipError_t launch_role(const CombinedArgs& c, hipStream_t s) {
     static bool attr_set[64] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64 && !attr_set[dev]) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&combined_kernel<PAGED, FP8>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&combined_kernel<Role>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_set[dev] = true;
     }
-    combined_kernel<PAGED, FP8><<<256, 64 * NW, LDS_BYTES, s>>>(c);
+    combined_kernel<Role><<<256, 64 * NW, LDS_BYTES, s>>>(c);
     return hipGetLastError();
 }
 
 }  // namespace
 
-#if HG_WIDE_D == 128
-hipError_t launch_combined(const CombinedArgs& c, int head_dim, hipStream_t s) {
-    if (head_dim == 64) return launch_combined_d64(c, s);
+// One translation unit per head dimension and kind of suffix role.
+#if HG_WIDE_D == 128 && defined(HG_COMBINED_TILES)
+hipError_t launch_combined_tiles(const CombinedArgs& c, hipStream_t s) {
+#elif HG_WIDE_D == 128
+hipError_t launch_combined_vector(const CombinedArgs& c, hipStream_t s) {
+#elif defined(HG_COMBINED_TILES)
+hipError_t launch_combined_tiles_d64(const CombinedArgs& c, hipStream_t s) {
 #else
-hipError_t launch_combined_d64(const CombinedArgs& c, hipStream_t s) {
+hipError_t launch_combined_vector_d64(const CombinedArgs& c, hipStream_t s) {
 #endif
-    if (c.d.pg.table) return c.d.fp8 ? launch_combined_t<true, true>(c, s) : launch_combined_t<true, false>(c, s);
-    return c.d.fp8 ? launch_combined_t<false, true>(c, s) : launch_combined_t<false, false>(c, s);
+    const bool paged = c.d.pg.table != nullptr;
+#ifndef HG_COMBINED_TILES
+    if (paged) return c.d.fp8 ? launch_role<VectorRole<true, true>>(c, s) : launch_role<VectorRole<true, false>>(c, s);
+    return c.d.fp8 ? launch_role<VectorRole<false, true>>(c, s) : launch_role<VectorRole<false, false>>(c, s);
+#else
+#if HG_WIDE_D == 128
+    if (c.d.fp8 && c.d.tile_rows == 16) return paged ? launch_role<TileRole<true, true, 16>>(c, s) : launch_role<TileRole<false, true, 16>>(c, s);
+    if (c.d.fp8) return hipErrorInvalidValue;      // (the caller keeps 8-bit codes in 32-row tiles on the separate kernels)
+#else
+    if (c.d.fp8) return hipErrorInvalidValue;      // 8-bit rows on the matrix cores: D = 128 only
+#endif
+    if (c.d.tile_rows == 16) return paged ? launch_role<TileRole<true, false, 16>>(c, s) : launch_role<TileRole<false, false, 16>>(c, s);
+    return paged ? launch_role<TileRole<true, false, 32>>(c, s) : launch_role<TileRole<false, false, 32>>(c, s);
+#endif
 }
 
 }  // namespace hg

@@ -104,17 +104,19 @@ struct DecodeArgs {
 };
 
 // Shared block and suffix in one launch (combined_impl.h): `p` (first: the shared-block role reads it from the kernarg
-// segment) for one level on the persistent kernel, `d` for the suffix (one query row per KV head).
+// segment) for one level on the persistent kernel, `d` for the suffix; d.units counts its work items.
 struct CombinedArgs {
     PrefixArgs p;
     DecodeArgs d;
     unsigned* tickets;    // [0]: work counter, [32]: workgroups that are done; both zero between calls
-    int long_runs;        // tickets that stand for kLongRun work items; the rest stand for kTailRun
+    int long_runs;        // tickets that stand for kLongRun work items; the rest stand for tail_run
+    int tail_run;
+    int n_tickets;
 };
 // The last kTailItems items go out in short runs so that the workgroups end together: a run of eight 256-row items keeps a
 // CU busy for 45 us.  (256 x 40 heads with suffixes of 1..256 rows: runs of 32 and 8 150 us, 32 / 8 / 2 150, 16 / 4 / 2 134,
 // 8 / 2 135, 4 138.)
-constexpr int kLongRun = 8, kTailRun = 2, kTailItems = 1024;
+constexpr int kLongRun = 8, kTailItems = 1024;
 
 // The single-launch fused kernel (fused_small.hip): every level, the suffix and the merge for 32-row tiles of query rows.
 constexpr int kArrivalCounters = 256;         // arrival counters a context owns (one per column of a call that is split)
@@ -177,8 +179,10 @@ struct FillArgs {
 hipError_t launch_prefix_narrow(const PrefixArgs& a, int D, hipStream_t s);
 hipError_t launch_prefix_wide(const PrefixArgs& a, int D, hipStream_t s);   // a.wide from plan_prefix_wide with the same D
 hipError_t launch_prefix_wide_d64(const PrefixArgs& a, hipStream_t s);      // (the D = 64 kernel lives in its own translation unit)
-hipError_t launch_combined(const CombinedArgs& c, int D, hipStream_t s);    // 256 workgroups
-hipError_t launch_combined_d64(const CombinedArgs& c, hipStream_t s);
+hipError_t launch_combined_vector(const CombinedArgs& c, hipStream_t s);      // 256 workgroups; one query row per KV head
+hipError_t launch_combined_vector_d64(const CombinedArgs& c, hipStream_t s);
+hipError_t launch_combined_tiles(const CombinedArgs& c, hipStream_t s);       // several query rows per KV head, tiles of d.tile_rows
+hipError_t launch_combined_tiles_d64(const CombinedArgs& c, hipStream_t s);   // (bf16 rows only)
 bool plan_prefix_wide(const LevelDev& lv, int Hkv, int G, int D, int max_parts, int slots_per_xcd, WidePlan* out);
 hipError_t launch_decode(const DecodeArgs& a, int D, int GT, hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeArgs& a, int D, hipStream_t s);   // matrix-core per-sequence kernel (8-bit rows: D = 128 only)

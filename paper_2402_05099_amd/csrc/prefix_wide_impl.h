@@ -779,8 +779,23 @@ bool plan_prefix_wide(const LevelDev& lv, int Hkv, int G, int D, int max_parts, 
     if (mtiles < 1 || lv.max_rows < 1) return false;
     if (slots_per_xcd < 1 || slots_per_xcd > 32) return false;
     p.slots = slots_per_xcd;
-    p.rowgroups = (mtiles + p.slots - 1) / p.slots;         // the workgroups of a team run on one XCD
-    p.T = (mtiles + p.rowgroups - 1) / p.rowgroups;
+    // Row groups: the workgroups of a team run on one XCD, so T <= slots, and slots % T CUs stay idle.  More, smaller
+    // groups can fill them at the price of reading the block once more per group.  Both in units of the products' time on
+    // all of the slots (a K/V row of 4 D bytes costs as much as multiplying it with 190 query rows: 4 D / 6 TB/s against
+    // 4 D / 1.14 PFLOP/s per row): 4096 query rows on 24 CUs per XCD run as two teams of 8 tiles on 24 of them, not 16 on 16.
+    {
+        const int r0 = (mtiles + p.slots - 1) / p.slots;
+        double best = 0.0;
+        for (int r = r0; r <= mtiles && (r == r0 || (mtiles >= 8 && r <= 8 * r0)); ++r) {      // (few tiles: nothing to gain)
+            const int T = (mtiles + r - 1) / r;
+            const double cost = (double)r * T / mtiles * p.slots / (p.slots / T * T) + 190.0 * r / ((double)mtiles * kPrefixRowsWide);
+            if (r == r0 || cost < 0.97 * best) {
+                best = cost;
+                p.rowgroups = r;
+                p.T = T;
+            }
+        }
+    }
     p.tpx = p.slots / p.T;
     p.n_c = (lv.max_rows + KT - 1) / KT;
     const long long ncols = (long long)lv.n_blocks * Hkv * p.rowgroups;

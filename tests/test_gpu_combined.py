@@ -28,14 +28,34 @@ SHAPES = {
 }
 
 
+# several query rows per KV head; name: (B, query heads, KV heads, D, queries per sequence, levels, suffix lengths)
+TILE_SHAPES = {
+    "g8": (40, 16, 2, 128, 1, [(1, 97, 40)], 0, 70),
+    "g16": (33, 16, 1, 128, 1, [(1, 64, 33)], 31, 65),              # a full 16-row tile
+    "g3_nq6": (24, 6, 2, 128, 6, [(1, 40, 24)], 0, 45),             # 18 rows: a 32-row tile, causal among the new tokens
+    "two_tiles": (9, 40, 1, 128, 1, [(1, 70, 9)], 1, 40),           # 40 rows: two 32-row tiles, the second partly filled
+    "nq2": (150, 3, 3, 128, 2, [(1, 130, 150)], 0, 34),
+    "g8_d64": (40, 16, 2, 64, 1, [(1, 97, 40)], 0, 70),
+    "nq5_d64": (60, 8, 2, 64, 5, [(1, 97, 60)], 0, 50),
+    "one_row": (400, 1, 1, 128, 1, [(1, 70, 400)], 0, 390),         # long suffixes with one row per KV head
+    "tile_chunks": (70, 8, 2, 128, 1, [(2, 60, 35)], 0, 1100),
+    "tile_levels": (200, 8, 2, 128, 1, [(1, 200, 200), (8, 33, 25)], 0, 20),
+    "tile_items": (1100, 8, 4, 128, 1, [(1, 40, 1100)], 1, 24),
+}
+
+
 @pytest.mark.parametrize("cache", ["packed", "paged", "fp8", "paged_fp8"])
-@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("shape", [*SHAPES, *TILE_SHAPES])
 def test_combined(shape, cache):
-    B, H, D, levels, lo, hi = SHAPES[shape]
-    print(f"combined: {shape} {cache} {SHAPES[shape]}", file=sys.stderr, flush=True)
-    w = wl.make_workload(shape, 77, B, H, H, D, levels, lo, hi)
+    if shape in SHAPES:
+        B, H, D, levels, lo, hi = SHAPES[shape]
+        Hkv, nq = H, 1
+    else:
+        B, H, Hkv, D, nq, levels, lo, hi = TILE_SHAPES[shape]
+    print(f"combined: {shape} {cache} B={B} {H}/{Hkv} D={D} nq={nq} {levels} {lo}..{hi}", file=sys.stderr, flush=True)
+    w = wl.make_workload(shape, 77, B, H, Hkv, D, levels, lo, hi, nq=nq)
     w.lengths[:2] = (hi, lo)           # the longest and the shortest are there
-    w = wl.make_workload(shape, 77, B, H, H, D, levels, lo, hi, lengths=np.ascontiguousarray(w.lengths))
+    w = wl.make_workload(shape, 77, B, H, Hkv, D, levels, lo, hi, lengths=np.ascontiguousarray(w.lengths), nq=nq)
     dw = dev.to_device(w)
     Oref, Lref, call = reference(w, cache)
     ctx = dev.make_context(dw, parts=32)

@@ -1,6 +1,7 @@
 // Host side of libhydragen: argument checks, work partitioning, kernel sequencing.  No device allocation,
 // no host synchronisation, no copies: every entry point only enqueues kernels on the context's stream.
 #include <math.h>
+#include <string.h>
 #include <algorithm>
 #include <mutex>
 #include <new>
@@ -143,7 +144,8 @@ struct LevelPlan { bool wide; int ns; WidePlan wp; };
 // HG_OPT_PREFIX_KERNEL = 1 forces the 128-row kernel, 2 the 256-row kernel.  max_parts bounds the
 // partial results the plan may use.
 // G: query rows per sequence and KV head (queries per sequence x query heads per KV head).
-LevelPlan plan_level(const hg_ctx* c, const LevelDev& lv, int Hkv, int G, int D, int max_parts, int wide_slots = 32) {
+LevelPlan plan_level(const hg_ctx* c, const LevelDev& lv, int Hkv, int G, int D, int max_parts, int wide_slots = 32,
+                     int wide_above = kPrefixRowsNarrow, bool table = true) {
     LevelPlan p{};
     const long long rows = (long long)lv.max_seqs * G;
     p.wide = false;
@@ -151,8 +153,8 @@ LevelPlan plan_level(const hg_ctx* c, const LevelDev& lv, int Hkv, int G, int D,
     if (lv.max_rows <= 0) return p;
     if (max_parts < 1) max_parts = 1;
     if (max_parts > HG_MAX_PARTS) max_parts = HG_MAX_PARTS;
-    const bool want_wide = c->opt_prefix_kernel != 1 && (c->opt_prefix_kernel == 2 || rows > kPrefixRowsNarrow);
-    if (want_wide && plan_prefix_wide(lv, Hkv, G, D, max_parts, c->opt_wide_slots > 0 ? c->opt_wide_slots : wide_slots, &p.wp)) {
+    const bool want_wide = c->opt_prefix_kernel != 1 && (c->opt_prefix_kernel == 2 || rows > wide_above);
+    if (want_wide && plan_prefix_wide(lv, Hkv, G, D, max_parts, c->opt_wide_slots > 0 ? c->opt_wide_slots : wide_slots, &p.wp, table)) {
         p.wide = true;
         p.ns = p.wp.nparts;
         return p;
@@ -842,20 +844,35 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     // plan: parts per level and for the suffix, shrunk to fit the workspace
     LevelDev lv[HG_MAX_LEVELS];
     LevelPlan plan[HG_MAX_LEVELS];
-    int ns[HG_MAX_LEVELS];
+    int ns[HG_MAX_LEVELS], index[HG_MAX_LEVELS];
     int nlev = 0;
+    // In the combined launch levels of more than 64 query rows run on the persistent kernel as well, provided that one has more
+    // than 128: it costs no launch of its own there.  Only the level with the most work may use the plan with a table.
+    int main_level = -1;
+    bool combine = false;
+    for (int i = 0; i < n_levels; ++i) {
+        const double seqs = levels[i].kv_off ? levels[i].max_seqs : B;
+        if (may_combine && levels[i].max_rows > 0 && seqs * nq * G > kPrefixRowsNarrow) combine = true;
+        if (main_level < 0 || (double)levels[i].max_rows * levels[i].n_blocks * seqs >
+                                  (double)levels[main_level].max_rows * levels[main_level].n_blocks * (levels[main_level].kv_off ? levels[main_level].max_seqs : B))
+            main_level = i;
+    }
+    const int combined_above = combine ? 64 : kPrefixRowsNarrow;
     int wide_slots = 32;
     bool tiny = false;   // so little work that the event edges between two streams cost more than overlap can gain
     if (has_suffix && c->opt_overlap != 1) {
         double flops = 0.0;
         int T = 1;
-        double pieces = 0.0;     // 256-row tiles of the largest level on the persistent kernel, all blocks and KV heads
+        double pieces = 0.0, padded = 0.0;     // 256-row tiles of all levels, blocks and KV heads; flops with whole tiles
         for (int i = 0; i < n_levels; ++i) {
             const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B;
             flops += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * seqs * nq * Hq * D;
             const long long tiles = (seqs * nq * G + kPrefixRowsWide - 1) / kPrefixRowsWide;
             if (seqs * nq * G > kPrefixRowsNarrow && tiles <= 32 && tiles > T) T = (int)tiles;
-            if (seqs * nq * G > kPrefixRowsNarrow) pieces = std::max(pieces, (double)tiles * levels[i].n_blocks * Hkv);
+            if (levels[i].max_rows > 0 && seqs * nq * G > combined_above) {
+                pieces += (double)tiles * levels[i].n_blocks * Hkv;
+                padded += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * tiles * kPrefixRowsWide * Hkv * D;
+            }
         }
         // K and V, bf16 (or 8-bit codes; on the matrix cores their expansion costs about a third of the saving); the
         // vector-ALU kernel reads them once per query; mean length taken as 0.75 max_len
@@ -865,13 +882,14 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         wide_slots = pick_wide_slots(flops, bytes, T);
         tiny = c->opt_overlap == 0 && flops / 1.14e15 + bytes / 6.0e12 < 60e-6;
         if (tiny) wide_slots = 32;
-        if (may_combine) wide_slots = pick_combined_slots(flops, 0.8 * bytes, pieces, D, sfx_mfma);     // (here the mean is taken as 0.6 max_len)
+        if (may_combine) wide_slots = pick_combined_slots(padded, 0.8 * bytes, pieces, D, sfx_mfma);     // (here the mean is taken as 0.6 max_len)
     }
     for (int i = 0; i < n_levels; ++i) {
         LevelDev d = to_dev(levels[i], B);
         if (d.max_rows == 0 || d.max_seqs == 0) continue;  // empty level contributes nothing
         lv[nlev] = d;
-        plan[nlev] = plan_level(c, d, Hkv, nq * G, D, parts.cap, wide_slots);
+        index[nlev] = i;
+        plan[nlev] = plan_level(c, d, Hkv, nq * G, D, parts.cap, wide_slots, combined_above, i == main_level);
         ns[nlev] = plan[nlev].ns;
         ++nlev;
     }
@@ -897,7 +915,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
             sp.chunk = round_up(ceil_div(max_len, sp.nchunks), 32);
             sp.nchunks = ceil_div(max_len, sp.chunk);
         } else if (big >= 0) {
-            plan[big] = plan_level(c, lv[big], Hkv, nq * G, D, ns[big] - 1, wide_slots);
+            plan[big] = plan_level(c, lv[big], Hkv, nq * G, D, ns[big] - 1, wide_slots, combined_above, index[big] == main_level);
             ns[big] = plan[big].ns;
         } else {
             return HG_ERR_WORKSPACE;
@@ -920,20 +938,24 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
 
     // (grouped levels may leave sequences uncovered: the level's kernel marks their partial results empty)
 
-    // The level on the persistent kernel with the most work shares its launch with the suffix; the other levels go before it.
+    // The levels on the persistent kernel share the suffix's launch; the others, and more than a few, go before it.
     int joint = -1;
-    if (may_combine && (int64_t)B * nq * G * sp.nchunks * Hkv < (1LL << 30)) {
+    if (combine && (int64_t)B * nq * G * sp.nchunks * Hkv < (1LL << 30)) {
         for (int i = 0; i < nlev; ++i)
-            if (plan[i].wide && (joint < 0 || (double)lv[i].max_rows * lv[i].max_seqs > (double)lv[joint].max_rows * lv[joint].max_seqs)) joint = i;
+            if (plan[i].wide && (joint < 0 || index[i] == main_level)) joint = i;
     }
     if (joint >= 0) {
         CombinedArgs ca{};
         int part = 0;
         for (int i = 0; i < nlev; ++i) {
+            const OutDev out = parts_out(parts, part);
             if (i == joint) {
-                ca.p = level_args(Q, lv[i], plan[i], B, nq, Hq, Hkv, scale, parts_out(parts, part));
+                ca.p = level_args(Q, lv[i], plan[i], B, nq, Hq, Hkv, scale, out);
+            } else if (plan[i].wide && plan[i].wp.mode != 2 && plan[i].wp.slots == plan[joint].wp.slots && ca.n_more < kMoreLevels) {
+                const PrefixArgs pa = level_args(Q, lv[i], plan[i], B, nq, Hq, Hkv, scale, out);
+                memcpy(ca.more[ca.n_more++].args, &pa, kShortPrefixArgs);
             } else {
-                rc = run_level(Q, lv[i], plan[i], B, nq, Hq, Hkv, D, scale, parts_out(parts, part), s);
+                rc = run_level(Q, lv[i], plan[i], B, nq, Hq, Hkv, D, scale, out, s);
                 if (rc) return rc;
             }
             part += ns[i];

@@ -38,6 +38,7 @@ typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
 constexpr int kQueueOffset = LDS_RING_BYTES, kDoneOffset = kQueueOffset + 16, kCountsOffset = kQueueOffset + 64;
 constexpr int kOrderOffset = kQueueOffset + 512, kMaxOrdered = (LDS_BYTES - kOrderOffset) / 2 / 1024 * 1024;
 constexpr int kLengthClasses = 8;
+static_assert(offsetof(CombinedArgs, p) == 0 && sizeof(CombinedArgs) <= 4096, "the kernarg segment");
 static_assert(kLengthClasses * NW == 64, "one lane per class and wavefront");
 
 // order[0 .. B): the sequences in descending order of their length class (eighths of max_len), by number within a class, so
@@ -572,9 +573,13 @@ template <class Role>
 __global__ __launch_bounds__(64 * NW, 1) void combined_kernel(CombinedArgs c) {
     unsigned char* const smem = wide_smem;
     if (blockIdx.x < 8 * c.p.wide.slots) {
-        wide_role(c.p);
-        __builtin_amdgcn_s_waitcnt(0x0F70);      // copies that nobody consumed have landed
-        __syncthreads();
+        const wide_args_ptr first = (wide_args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+        for (int i = 0; i <= c.n_more; ++i) {
+            const size_t at = i == 0 ? 0 : offsetof(CombinedArgs, more) + (i - 1) * sizeof(MoreLevel);
+            wide_role((wide_args_ptr)((const __attribute__((address_space(4))) unsigned char*)first + at));
+            __builtin_amdgcn_s_waitcnt(0x0F70);      // copies that nobody consumed have landed
+            __syncthreads();
+        }
     }
     queue_word* const queue = reinterpret_cast<queue_word*>(smem + kQueueOffset);
     unsigned* const done = reinterpret_cast<unsigned*>(smem + kDoneOffset);     // wavefronts of this workgroup that are done

@@ -1,6 +1,7 @@
 // Internal declarations shared by the HIP translation units of libhydragen (gfx950 only).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "hydragen.h"
@@ -104,10 +105,15 @@ struct DecodeArgs {
 };
 
 // Shared block and suffix in one launch (combined_impl.h): `p` (first: the shared-block role reads it from the kernarg
-// segment) for one level on the persistent kernel, `d` for the suffix; d.units counts its work items.
+// segment) for the largest level on the persistent kernel, `d` for the suffix; d.units counts its work items.
+constexpr int kMoreLevels = 3;
+constexpr size_t kShortPrefixArgs = offsetof(PrefixArgs, wide) + offsetof(WidePlan, starts);      // a level without its tables
+struct alignas(16) MoreLevel { unsigned char args[(kShortPrefixArgs + 15) / 16 * 16]; };
 struct CombinedArgs {
     PrefixArgs p;
     DecodeArgs d;
+    int n_more;                     // further levels, one after another on the same workgroups
+    MoreLevel more[kMoreLevels];
     unsigned* tickets;    // [0]: work counter, [32]: workgroups that are done; both zero between calls
     int long_runs;        // tickets that stand for kLongRun work items; the rest stand for tail_run
     int tail_run;
@@ -183,7 +189,8 @@ hipError_t launch_combined_vector(const CombinedArgs& c, hipStream_t s);      //
 hipError_t launch_combined_vector_d64(const CombinedArgs& c, hipStream_t s);
 hipError_t launch_combined_tiles(const CombinedArgs& c, hipStream_t s);       // several query rows per KV head, tiles of d.tile_rows
 hipError_t launch_combined_tiles_d64(const CombinedArgs& c, hipStream_t s);   // (bf16 rows only)
-bool plan_prefix_wide(const LevelDev& lv, int Hkv, int G, int D, int max_parts, int slots_per_xcd, WidePlan* out);
+bool plan_prefix_wide(const LevelDev& lv, int Hkv, int G, int D, int max_parts, int slots_per_xcd, WidePlan* out,
+                      bool table = true);
 hipError_t launch_decode(const DecodeArgs& a, int D, int GT, hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeArgs& a, int D, hipStream_t s);   // matrix-core per-sequence kernel (8-bit rows: D = 128 only)
 hipError_t launch_merge(const MergeArgs& a, int D, bool in_bf16, bool out_bf16, hipStream_t s);

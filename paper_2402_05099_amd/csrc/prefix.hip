@@ -48,7 +48,7 @@ __global__ __launch_bounds__(256, 2) void prefix_kernel(PrefixArgs a) {
     __shared__ __attribute__((aligned(1024))) unsigned char sV0[TILEB];
     __shared__ __attribute__((aligned(1024))) unsigned char sV1[TILEB];
 
-    mark_uncovered(a, D, a.nsplit, blockIdx.x, gridDim.x);
+    mark_uncovered(UncoveredArgs{a.lv, a.B, a.Hq, a.nq, a.out}, D, a.nsplit, blockIdx.x, gridDim.x);
 
     // ---- which tile -------------------------------------------------------------------------------
     const int pid = blockIdx.x;

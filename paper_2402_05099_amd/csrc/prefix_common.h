@@ -29,7 +29,12 @@ __device__ __forceinline__ float half_sum(float x) { return x + other_half(x); }
 // level's `nparts` parts (the merge never reads the O of such a part), and O = 0 as well when the level's result is
 // written in place (one part, no stride).  The level's n_blocks + 2 candidate ranges are dealt out to the launch's
 // workgroups (range r to workgroup r % nwg); the kernels that call this write those rows nowhere else.
-__device__ __forceinline__ void mark_uncovered(const PrefixArgs& a, int D, int nparts, int wg, int nwg) {
+struct UncoveredArgs {
+    LevelDev lv;
+    int B, Hq, nq;
+    OutDev out;
+};
+__device__ __forceinline__ void mark_uncovered(const UncoveredArgs& a, int D, int nparts, int wg, int nwg) {
     if (!a.lv.seq_off) return;     // a level of one block covers every sequence
     const int n = a.lv.n_blocks;
     const int per_seq = a.nq * a.Hq;

@@ -149,16 +149,26 @@ struct WidePiece {
     int has_rows;        // row0 < nrows
 };
 
-// What one workgroup of the persistent kernel does.  `a` is the kernel's argument, at the start of the kernarg segment;
-// the first 8 * a.wide.slots workgroups of the launch call this.
-__device__ __forceinline__ void wide_role(const PrefixArgs& a) {
+// What one workgroup of the persistent kernel does with one level: the first 8 * wide.slots workgroups of the launch call
+// this.  `ka` points at the level's arguments in the kernarg segment (without the tables at its end unless they are used).
+typedef const __attribute__((address_space(4))) PrefixArgs* wide_args_ptr;
+__device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     HG_T(0);
 #ifdef HG_TRACE
     if (threadIdx.x == 0) hg_wide_trace[blockIdx.x * kTraceSlots + 28] = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u;   // XCC_ID
 #endif
-    mark_uncovered(a, D, a.wide.nparts, blockIdx.x, 8 * a.wide.slots);
+    if (ka->lv.seq_off) {
+        UncoveredArgs u;
+        u.lv.kv_off = ka->lv.kv_off; u.lv.seq_off = ka->lv.seq_off;
+        u.lv.n_blocks = ka->lv.n_blocks; u.lv.max_rows = ka->lv.max_rows; u.lv.max_seqs = ka->lv.max_seqs;
+        u.lv.K = ka->lv.K; u.lv.V = ka->lv.V;
+        u.B = ka->B; u.Hq = ka->Hq; u.nq = ka->nq;
+        u.out.O = ka->out.O; u.out.LSE = ka->out.LSE; u.out.bf16 = ka->out.bf16;
+        u.out.part_stride_O = ka->out.part_stride_O; u.out.part_stride_L = ka->out.part_stride_L;
+        mark_uncovered(u, D, ka->wide.nparts, blockIdx.x, 8 * ka->wide.slots);
+    }
     unsigned char* const smem = wide_smem;
-    const WidePlan& p = a.wide;
+    const auto& p = ka->wide;
     const int pid = blockIdx.x;
     const int xcd = pid & 7, cu_slot = pid >> 3;         // workgroups whose ids are equal modulo 8 run on one XCD (which one varies by launch)
     const int team_local = cu_slot / p.T, member = cu_slot % p.T;
@@ -197,7 +207,7 @@ __device__ __forceinline__ void wide_role(const PrefixArgs& a) {
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = tid & 63, lq = l & 31, hl = l >> 5;
-    const unsigned rstride_b = (unsigned)a.Hkv * D * 2u;
+    const unsigned rstride_b = (unsigned)ka->Hkv * D * 2u;
 
     // block offsets are read through the constant address space: nothing writes them while the kernel runs, and the
     // loads then stay on the scalar unit (a vector load would make the compiler wait for vmcnt(0) and drain the ring)
@@ -206,9 +216,9 @@ __device__ __forceinline__ void wide_role(const PrefixArgs& a) {
     // Everything that happens once per piece reads the kernel's arguments again from the kernarg segment (through a
     // pointer the compiler cannot see through) instead of keeping them in scalar registers across the pipeline
     // steps: the steps need those registers themselves, and what does not fit is parked in vector-register lanes.
-    typedef const __attribute__((address_space(4))) PrefixArgs* kargs_ptr;
+    typedef wide_args_ptr kargs_ptr;
     auto kargs = [&]() -> kargs_ptr {
-        kargs_ptr k = (kargs_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+        kargs_ptr k = ka;
         asm volatile("" : "+s"(k));
         return k;
     };
@@ -455,7 +465,7 @@ __device__ __forceinline__ void wide_role(const PrefixArgs& a) {
     float m_used;               // raw-score maximum the exponentials are taken against
     float lsum[2];              // this lane's share of the row sum (of the unrounded exponentials), two chains
     float mc;                   // m_used * c2
-    const float c2 = a.scale * kLog2e;
+    const float c2 = ka->scale * kLog2e;
     const float tau_raw = TAU / c2;
     auto maybe_rescale = [&](float tmax) {
         if (__any(tmax > m_used + tau_raw)) {
@@ -752,7 +762,7 @@ __device__ __forceinline__ void wide_role(const PrefixArgs& a) {
 }
 
 #ifdef HG_WIDE_KERNEL
-__global__ __launch_bounds__(64 * NW, 1) void HG_WIDE_KERNEL(PrefixArgs a) { wide_role(a); }
+__global__ __launch_bounds__(64 * NW, 1) void HG_WIDE_KERNEL(PrefixArgs) { wide_role((wide_args_ptr)__builtin_amdgcn_kernarg_segment_ptr()); }
 
 #if defined(HG_TRACE) && HG_WIDE_D == 128
 }  // namespace hg
@@ -768,8 +778,9 @@ namespace hg {
 
 #if HG_WIDE_D == 128
 // Work partition of the persistent kernel for a level (host side).  Returns false when the level does not fit
-// (more than max_parts partial results per row would be needed).  A stage is 32 keys at D = 128 and 64 keys at D = 64.
-bool plan_prefix_wide(const LevelDev& lv, int Hkv, int G, int D, int max_parts, int slots_per_xcd, WidePlan* out) {
+// (more than max_parts partial results per row would be needed).  table: the plan may use mode 2.  A stage is 32 keys at D = 128 and 64 keys at D = 64.
+bool plan_prefix_wide(const LevelDev& lv, int Hkv, int G, int D, int max_parts, int slots_per_xcd, WidePlan* out,
+                      bool table) {
     if (D != 128 && D != 64) return false;
     const int KT = D == 128 ? 32 : 64;
     // G here is the number of query rows per sequence and KV head (queries per sequence x heads per group)
@@ -864,7 +875,7 @@ bool plan_prefix_wide(const LevelDev& lv, int Hkv, int G, int D, int max_parts, 
     // Equal ranges, some with a column boundary inside and some without: the teams with a boundary finish later by what
     // a second piece costs.  Ranges of equal cost instead (cost = stages + kWideBoundaryCost per boundary inside): the
     // smallest cost C for which the teams, each taking the longest range that costs at most C, cover the space.
-    if (p.mode == 0 && nteams <= kWideMaxTeams) {
+    if (table && p.mode == 0 && nteams <= kWideMaxTeams) {
         const long long nc = p.n_c, kappa = kWideBoundaryCost;
         auto end_of = [&](long long a, long long C) {      // the largest b <= total with (b - a) + kappa * boundaries inside (a, b) <= C
             long long best = a + 1;

@@ -23,6 +23,7 @@ SHAPES = {
     "chunks": (140, 2, 128, [(1, 257, 140)], 0, 383),
     "chunks_d64": (140, 2, 64, [(1, 257, 140)], 0, 700),
     "two_levels": (320, 2, 128, [(1, 200, 320), (4, 65, 80)], 0, 20),
+    "four_levels": (300, 1, 128, [(1, 40, 300), (2, 65, 150), (3, 33, 100), (1, 64, 280)], 0, 20),
     "several_blocks": (600, 2, 64, [(3, 90, 200)], 0, 50),
     "many_items": (1300, 10, 128, [(1, 40, 1300)], 1, 24),
 }

@@ -36,7 +36,7 @@ CSRC = os.path.join(ROOT, "paper_2402_05099_amd", "csrc")
 # the source files each kernel's counters depend on (a stored counter reading is only quoted while they are unchanged)
 KERNEL_SOURCES = {
     "prefix_level": ["prefix_wide_impl.h", "prefix_wide.hip", "prefix_wide_step.inc", "prefix.hip", "prefix_common.h", "hg_internal.h"],
-    "suffix": ["decode.hip", "decode_mfma.hip", "hg_internal.h"],
+    "suffix": ["decode.hip", "decode_core.h", "decode_mfma.hip", "decode_mfma_core.h", "hg_internal.h"],
 }
 
 

@@ -757,21 +757,22 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     // estimated, in microseconds, from fits to 82 shapes (B = 4 .. 2048, 0 .. 16K shared keys, every cache and head layout):
     //   single launch: 4 + rounds x (4 + c x stages per wavefront), c = 1.6 us per 32-key stage while a quarter of the CUs
     //                  are busy (the latency of one stage's K and V rows), 2.3 with all of them; 4.5 + 0.3 x splits more when
-    //                  a column's workgroups have to meet; never faster than the suffix rows stream in (5 TB/s, 3.3 through a page table)
+    //                  a column's workgroups have to meet; never faster than the suffix rows stream in (5 TB/s, 4 on blocks of few rows, 3.3 through a page table)
     //                  and the shared rows, which every column reads for itself, at 8 TB/s once they do not fit the L2;
     //   separate:      18, 6 and 10 more with one and two shared levels, 8 more once a block is long enough to be split,
     //                  suffix rows at 5 TB/s, shared blocks at 1.1 PFLOP/s or 5 TB/s; with many suffix rows and one launch for
     //                  both (below) 25, and 0.8 of the suffix time.
-    // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single
-    // launch is taken below the other estimate, from 60 us on only when it is 25 % below (the model of the separate kernels
-    // is pessimistic where suffixes and shared blocks overlap).  Measured single / separate: 12.4 / 25 us (72 sequences,
-    // 206 rows), 17.3 / 26 (2.5K shared keys, 16 sequences), 15.9 / 31.5 (256 sequences, 1K keys), 222 / 151 (256 x 40 heads, 2K
-    // keys: not taken), 257 / 203 (1024 x 40 heads at D = 64: not taken).
+    // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single launch is
+    // taken below the other estimate; from 60 us on (45 where the other way is two launches side by side) only when it is 25 %
+    // below (the model of the separate kernels is pessimistic where suffixes and shared blocks overlap).  Measured single /
+    // other way: 12.4 / 25 us (72 sequences, 206 rows), 17.3 / 26 (2.5K shared keys, 16 sequences), 15.9 / 24 (256
+    // sequences, 1K keys), 59 / 46 (128 x 32/8 heads, 2K keys, paged, with the cache update: not taken), 74 / 59 (53 x 32/8
+    // heads, 12K + 12 x 276 keys, 8-bit: not taken), 222 / 131 (256 x 40 heads, 2K keys: not taken).
     if (c->opt_fused_kernel != 1 && !c->opt_timing) {
         const int rps = nq * G;
         long long shared_keys = 0;
         double flops = 0.0, shared_bytes = 0.0;
-        bool any = has_suffix;
+        bool any = has_suffix, joins = false;      // joins: shared block and suffix would share a launch otherwise
         int nonempty = 0;
         for (int i = 0; i < n_levels; ++i) {
             const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B;
@@ -780,6 +781,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
                 flops += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * seqs * nq * Hq * D;
                 shared_bytes += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * Hkv * D;
                 any = true;
+                joins = joins || (may_combine && seqs * rps > kPrefixRowsNarrow);
                 ++nonempty;
             }
         }
@@ -796,7 +798,8 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         };
         int splits = 1;
         if (c->arrivals && cols * 2 <= 256 && cols <= kArrivalCounters) {
-            const int most = (int)std::min<long long>(256 / cols, kSmallMaxSplits);
+            // (more workgroups than one stage per wavefront asks for only meet later)
+            const int most = (int)std::min<long long>({256 / cols, kSmallMaxSplits, (long long)ceil(stages / 8.0)});
             for (int S = 2; S <= most; ++S)
                 if (chain_at(S) < 0.95 * chain_at(splits) && small_part_floats((int)cols, S, D) * sizeof(float) <= ws.bytes) splits = S;
         }
@@ -806,11 +809,11 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         // while they fit there, at 8 TB/s beyond
         const double restream_us = shared_bytes / std::min(8, Hkv) > 4.0e6
                                        ? (double)cols * ((shared_keys + 31) / 32) * 128.0 * D / 8.0e6 + suffix_us + 13.0 : 0.0;
-        const double est_single = std::max({chain_at(splits), (pg.table ? 1.5 : 1.0) * suffix_us + shared_us + 7.0, restream_us});
+        const double est_single = std::max({chain_at(splits), (pg.table ? 1.5 : joins ? 1.0 : 1.2) * suffix_us + shared_us + 7.0, restream_us});
         double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
                                     suffix_us + std::max(flops / 1.1e9, shared_us);
-        if (suffix_us >= 30.0 && may_combine && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
-        const bool small = est_single <= (est_single <= 60.0 ? 1.0 : 0.75) * est_separate;
+        if (suffix_us >= 30.0 && joins && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
+        const bool small = est_single <= (est_single <= (joins ? 60.0 : 45.0) ? 1.0 : 0.75) * est_separate;
         if (any && cols * splits < (1LL << 31) && (c->opt_fused_kernel == 2 || small)) {
             SmallArgs sa{};
             sa.Q = static_cast<const uint16_t*>(Q);

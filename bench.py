@@ -410,7 +410,7 @@ def main() -> int:
     ap.add_argument("--naive-steps", type=int, default=3)
     ap.add_argument("--cpu-sample", type=int, default=256, help="sequences the CPU oracle is timed on (0 = skip)")
     ap.add_argument("--splits", type=int, default=0)
-    ap.add_argument("--overlap", type=int, default=0, help="HG_OPT_OVERLAP: 0 library default (two streams), 1 one stream, 2 two streams, shared blocks first")
+    ap.add_argument("--overlap", type=int, default=0, help="HG_OPT_OVERLAP: 0 library default (one launch where it applies, else two streams), 1 one stream, 2 two streams, shared blocks first")
     ap.add_argument("--suffix-chunk", type=int, default=0)
     ap.add_argument("--parts", type=int, default=24)
     ap.add_argument("--calibration-copy-mib", type=int, default=0,

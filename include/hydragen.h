@@ -76,7 +76,7 @@ enum { HG_STATIC_SCRATCH_BYTES = 67108864 }; /* 64 MiB: partial-result memory of
 enum {
     HG_OPT_PREFIX_SPLITS = 1, /* number of key-range splits of each shared block (>=1) */
     HG_OPT_SUFFIX_CHUNK = 2,  /* keys per work item of the suffix kernel (multiple of 32) */
-    HG_OPT_OVERLAP = 3,       /* fused call: 0 shared-block and suffix kernels overlap on two streams, 1 one stream, 2 two streams with the shared-block kernels enqueued first */
+    HG_OPT_OVERLAP = 3,       /* fused call: 0 shared blocks and suffix side by side (in one launch where it applies, else on two streams), 1 one kernel after another on one stream, 2 two streams with the shared-block kernels enqueued first */
     HG_OPT_NAIVE_CHUNK = 4,   /* keys per work item of the non-decomposed comparison kernel */
     HG_OPT_STAGE_TIMING = 5,  /* 1: hg_hydragen_attn brackets each of its kernels with timing events */
     HG_OPT_PREFIX_KERNEL = 6, /* shared-block kernel: 0 automatic (persistent 256-row kernel for blocks with more than 128 query rows, else the 128-row kernel), 1 always 128-row, 2 always 256-row */

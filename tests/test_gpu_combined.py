@@ -73,3 +73,42 @@ def test_combined(shape, cache):
         check(to_np(got[0][0]), to_np(got[0][1]), Oref, Lref, f"{shape} {cache} slots={slots}")
         assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), f"{shape} {cache}: the second call differs"
     ctx.close()
+
+
+@pytest.mark.parametrize("shape", ["many_items", "tile_items"])
+def test_combined_capture(shape):
+    """Captured once, replayed with eager calls and other inputs in between: every replay leaves its counters at zero."""
+    if shape in SHAPES:
+        B, H, D, levels, lo, hi = SHAPES[shape]
+        Hkv, nq = H, 1
+    else:
+        B, H, Hkv, D, nq, levels, lo, hi = TILE_SHAPES[shape]
+    print(f"combined, captured: {shape}", file=sys.stderr, flush=True)
+    dw = dev.to_device(wl.make_workload(shape, 78, B, H, Hkv, D, levels, lo, hi, nq=nq))
+    ctx = dev.make_context(dw, parts=32)
+    ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 1)
+    O = torch.empty(dw.lead + (dw.D,), dtype=torch.float32, device="cuda:0")
+    L = torch.empty(dw.lead, dtype=torch.float32, device="cuda:0")
+
+    def call(o, l):
+        hb.hg_hydragen_attn(ctx, dw.Q, dw.levels, dw.Ks, dw.Vs, dw.offsets, dw.lengths, dw.max_len, o, l, dw.scale)
+
+    call(O, L)
+    torch.cuda.synchronize()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        ctx.set_stream(side)
+        call(O, L)
+    ctx.set_stream(None)
+    for _ in range(3):
+        dw.Q.copy_(torch.randn_like(dw.Q))
+        Oe, Le = torch.empty_like(O), torch.empty_like(L)
+        call(Oe, Le)
+        torch.cuda.synchronize()
+        O.fill_(float("nan"))
+        L.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(O, Oe) and torch.equal(L, Le), f"{shape}: a replay differs from the eager call"
+    ctx.close()

@@ -759,7 +759,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     //                  are busy (the latency of one stage's K and V rows), 2.3 with all of them; 4.5 + 0.3 x splits more when
     //                  a column's workgroups have to meet; never faster than the suffix rows stream in (5 TB/s, 4 on blocks of few rows, 3.3 through a page table)
     //                  and the shared rows, which every column reads for itself, at 8 TB/s once they do not fit the L2;
-    //   separate:      18, 6 and 10 more with one and two shared levels, 8 more once a block is long enough to be split,
+    //   separate:      10.5 and 0.7 of the suffix time without a shared block; else 18, 6 and 10 more with one and two shared levels, 8 more once a block is long enough to be split,
     //                  suffix rows at 5 TB/s, shared blocks at 1.1 PFLOP/s or 5 TB/s; with many suffix rows and one launch for
     //                  both (below) 25, and 0.8 of the suffix time.
     // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single launch is
@@ -771,13 +771,16 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     if (c->opt_fused_kernel != 1 && !c->opt_timing) {
         const int rps = nq * G;
         long long shared_keys = 0;
-        double flops = 0.0, shared_bytes = 0.0;
+        double flops = 0.0, shared_bytes = 0.0, shared_stages = 0.0;
         bool any = has_suffix, joins = false;      // joins: shared block and suffix would share a launch otherwise
         int nonempty = 0;
         for (int i = 0; i < n_levels; ++i) {
             const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B;
             if (levels[i].max_rows > 0 && seqs > 0) {
                 shared_keys += levels[i].max_rows;
+                // blocks that a column of 32 rows meets: all of a small block's neighbours as well
+                const double met = std::min((double)levels[i].n_blocks, levels[i].n_blocks > 1 ? 1.0 + 31.0 / (double)(seqs * rps) : 1.0);
+                shared_stages += met * ((levels[i].max_rows + 31) / 32);
                 flops += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * seqs * nq * Hq * D;
                 shared_bytes += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * Hkv * D;
                 any = true;
@@ -787,7 +790,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         }
         const int seqs_per_tile = rps >= 32 ? 1 : (32 + rps - 1) / rps + (32 % rps ? 1 : 0);
         const long long seqs_here = seqs_per_tile < B ? seqs_per_tile : B;
-        const double stages = (double)((shared_keys + 31) / 32) + (has_suffix ? seqs_here * ((0.75 * max_len + 16.0) / 32.0) : 0.0);
+        const double stages = shared_stages + (has_suffix ? seqs_here * ((0.75 * max_len + 16.0) / 32.0) : 0.0);
         const long long tiles = ((long long)B * rps + 31) / 32;
         const long long cols = tiles * Hkv;
         const double per_round = D == 128 ? 256.0 : 512.0;       // workgroups that run at a time (LDS)
@@ -808,10 +811,11 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         // every column reads the shared rows for itself: from its XCD's L2 (4 MB; an XCD works on its share of the KV heads)
         // while they fit there, at 8 TB/s beyond
         const double restream_us = shared_bytes / std::min(8, Hkv) > 4.0e6
-                                       ? (double)cols * ((shared_keys + 31) / 32) * 128.0 * D / 8.0e6 + suffix_us + 13.0 : 0.0;
+                                       ? (double)cols * shared_stages * 128.0 * D / 8.0e6 + suffix_us + 13.0 : 0.0;
         const double est_single = std::max({chain_at(splits), (pg.table ? 1.5 : joins ? 1.0 : 1.2) * suffix_us + shared_us + 7.0, restream_us});
         double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
                                     suffix_us + std::max(flops / 1.1e9, shared_us);
+        if (nonempty == 0) est_separate = 10.5 + 0.7 * suffix_us;      // the suffix kernel alone: no event edges, hardly a merge
         if (suffix_us >= 30.0 && joins && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
         const bool small = est_single <= (est_single <= (joins ? 60.0 : 45.0) ? 1.0 : 0.75) * est_separate;
         if (any && cols * splits < (1LL << 31) && (c->opt_fused_kernel == 2 || small)) {

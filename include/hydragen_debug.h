@@ -39,12 +39,23 @@ extern "C" {
  * suffix rows, nq queries each, Hq / Hkv heads of dimension D (page_size > 0: paged cache).  Fills out[4] = { keys per
  * work item, work items per row (= partial results), 1 if the matrix-core kernel runs, query heads per vector-ALU
  * work item } and returns 1, or 0 on invalid arguments.
+ *
+ * hg_debug_fused_plan: how a fused call would run.  options: n_options pairs (option, value) for hg_set_option, the rest at
+ * their defaults (HG_OPT_STAGE_TIMING is not taken; nq is an argument of its own).  levels: as in hg_hydragen_attn, but no pointer is
+ * followed (kv_off only tells whether there are block arrays).  max_len 0: no suffix; page_size > 0: paged cache; fp8: 8-bit
+ * codes; workspace_bytes: room for partial results.  Returns what the call would return before it enqueues anything, and on
+ * HG_OK fills out[8] = { way: 0 single launch, 1 shared blocks and suffix in one launch, 2 one kernel after another on one
+ * stream, 3 on two streams, 4 no keys at all; workgroups per column (way 0, else 0); partial results per row (0 for way 0); keys
+ * per work item of the suffix kernel; work items per row; 1 if the suffix runs on the matrix cores; levels on the persistent
+ * kernel (bit i: levels[i]); CUs per XCD of the persistent kernel, 0 if it does not run }.
  */
 int hg_debug_wide_plan(int n_blocks, int max_rows, int max_seqs, int Hkv, int rows_per_seq, int max_parts,
                        int slots_per_xcd, int D, int out[9]);
 int hg_debug_wide_ranges(int n_blocks, int max_rows, int max_seqs, int Hkv, int rows_per_seq, int max_parts,
                          int slots_per_xcd, int D, int starts[257], int first_part[256]);
 int hg_debug_suffix_plan(int B, int nq, int Hq, int Hkv, int D, int max_len, int page_size, int out[4]);
+int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const hg_level* levels, int B, int nq, int Hq, int Hkv, int D,
+                        int max_len, int page_size, int fp8, size_t workspace_bytes, int out[8]);
 
 /*
  * What the chip sustains on the two resources the attention kernels are priced against (Sec. 4.2 and App. D.2 time

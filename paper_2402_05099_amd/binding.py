@@ -35,7 +35,7 @@ EXPORTS = (
     "hg_create", "hg_destroy", "hg_set_stream", "hg_set_option", "hg_workspace_bytes", "hg_prefix_attn",
     "hg_prefix_attn_grouped", "hg_suffix_attn", "hg_merge", "hg_hydragen_attn", "hg_naive_attn", "hg_read_stage_timings",
     "hg_strerror", "hg_suffix_attn_paged", "hg_hydragen_attn_paged", "hg_kv_append", "hg_kv_append_paged",
-    "hg_debug_wide_plan", "hg_debug_wide_ranges", "hg_debug_suffix_plan", "hg_suffix_attn_fp8", "hg_hydragen_attn_fp8", "hg_kv_append_fp8",
+    "hg_debug_wide_plan", "hg_debug_wide_ranges", "hg_debug_suffix_plan", "hg_debug_fused_plan", "hg_suffix_attn_fp8", "hg_hydragen_attn_fp8", "hg_kv_append_fp8",
     "hg_hydragen_attn_static", "hg_debug_mfma_loop", "hg_debug_stream_read", "hg_debug_xcd_of_workgroups",
 )
 
@@ -120,6 +120,8 @@ def lib() -> ctypes.CDLL:
         L.hg_debug_wide_ranges.restype = ci
         L.hg_debug_suffix_plan.argtypes = [ci] * 7 + [ctypes.POINTER(ci)]
         L.hg_debug_suffix_plan.restype = ci
+        L.hg_debug_fused_plan.argtypes = [ctypes.POINTER(ci), ci, ci, ctypes.POINTER(hg_level)] + [ci] * 8 + [cs, ctypes.POINTER(ci)]
+        L.hg_debug_fused_plan.restype = ci
         L.hg_debug_mfma_loop.argtypes = [vp, ci, ci, vp, vp]
         L.hg_debug_mfma_loop.restype = ci
         L.hg_debug_stream_read.argtypes = [vp, vp, cs, vp]
@@ -483,6 +485,23 @@ def hg_debug_suffix_plan(B: int, nq: int, Hq: int, Hkv: int, D: int, max_len: in
     if not lib().hg_debug_suffix_plan(B, nq, Hq, Hkv, D, max_len, page_size, out):
         return None
     return dict(zip(("chunk", "nchunks", "mfma", "gt"), list(out)))
+
+
+def hg_debug_fused_plan(levels, B: int, nq: int, Hq: int, Hkv: int, D: int, max_len: int, page_size: int = 0, fp8: bool = False,
+                        workspace_bytes: int = 1 << 40, options: Optional[dict] = None):
+    """dict of how a fused call would run, or the error code it would return (host only).  levels: (blocks, rows, sequences
+    per block) triples; options: {option: value}."""
+    arr = (hg_level * max(len(levels), 1))(*[hg_level(None, None, n, 1 if n > 1 or seqs != B else None, 1 if n > 1 or seqs != B else None,
+                                                      rows, seqs) for n, rows, seqs in levels])
+    flat = [x for item in (options or {}).items() for x in item]
+    out = (ctypes.c_int * 8)()
+    rc = lib().hg_debug_fused_plan((ctypes.c_int * max(len(flat), 1))(*flat), len(flat) // 2, len(levels), arr, B, nq, Hq, Hkv, D, max_len,
+                                   page_size, int(fp8), workspace_bytes, out)
+    if rc != HG_OK:
+        return rc
+    plan = dict(zip(("way", "splits", "parts", "chunk", "nchunks", "mfma", "wide_levels", "slots"), list(out)))
+    plan["way"] = ("single", "combined", "one_stream", "two_streams", "fill")[plan["way"]]
+    return plan
 
 
 def hg_debug_mfma_loop(ctx: Context, random_operands: bool, iters: int, clocks: torch.Tensor, sink: torch.Tensor) -> None:

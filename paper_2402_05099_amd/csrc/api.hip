@@ -77,14 +77,18 @@ struct Parts {   // fp32 partial results carved out of the workspace
 
 struct Ws { unsigned char* p; size_t bytes; };   // device memory that holds the partial results of one call
 
+// partial results that fit `bytes` of such memory
+int parts_cap(size_t bytes, int64_t rows, int D) {
+    const size_t per = (size_t)rows * (D + 1) * sizeof(float);
+    const size_t cap = per ? bytes / per : 0;
+    return cap > HG_MAX_PARTS ? HG_MAX_PARTS : (int)cap;
+}
+
 Parts carve(const Ws& ws, int64_t rows, int D) {
     Parts p{};
     p.rows = rows;
     p.D = D;
-    const size_t per = (size_t)rows * (D + 1) * sizeof(float);
-    size_t cap = (ws.p && per) ? ws.bytes / per : 0;
-    if (cap > HG_MAX_PARTS) cap = HG_MAX_PARTS;
-    p.cap = (int)cap;
+    p.cap = ws.p ? parts_cap(ws.bytes, rows, D) : 0;
     p.O = reinterpret_cast<float*>(ws.p);
     p.L = p.O + (int64_t)p.cap * rows * D;
     return p;
@@ -727,29 +731,49 @@ static int check_fused(hg_ctx* c, const void* Q, int n_levels, const hg_level* l
     return HG_OK;
 }
 
-// hg_hydragen_attn and hg_hydragen_attn_paged (pg.table set, offsets unused)
-static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* levels, const void* Ks, const void* Vs,
-                      const int32_t* offsets, const int32_t* lengths, int max_len, int B, int Hq, int Hkv, int D,
-                      float scale, void* O_out, int o_dtype, float* LSE_out, const hg::PagedDev& pg, const KvFmt& fmt = KvFmt{},
-                      const Ws* ws_override = nullptr) {
-    int rc = check_fused(c, Q, n_levels, levels, Ks, Vs, offsets, lengths, max_len, B, Hq, Hkv, D, O_out, o_dtype,
-                         pg.table != nullptr);
-    if (rc) return rc;
-    if (B == 0) return HG_OK;
-    if (hipSetDevice(c->device) != hipSuccess) return HG_ERR_HIP;
-    scale = eff_scale(scale, D);
-    const int nq = c->opt_nq;
-    const int64_t rows = (int64_t)B * nq * Hq;
-    const int G = Hq / Hkv;
-    const bool has_suffix = Ks != nullptr && max_len > 0;
-    const Ws ws = ws_override ? *ws_override : Ws{c->ws, c->ws_bytes};
+// How a fused call runs: everything that is decided from host values (shapes, options, room for partial results).
+enum { kWaySingle = 0, kWayCombined = 1, kWayOneStream = 2, kWayTwoStreams = 3, kWayFill = 4 };
+struct FusedPlan {
+    int way;
+    int splits;                     // single launch: workgroups per column
+    int nlev;                       // levels that hold keys
+    LevelDev lv[HG_MAX_LEVELS];
+    LevelPlan plan[HG_MAX_LEVELS];
+    int ns[HG_MAX_LEVELS], index[HG_MAX_LEVELS];      // partial results of a level, its place in the caller's list
+    int main_level, joint;          // the level with the most work (caller's list); combined launch: the level it is launched for
+    SuffixPlan sp;
+    int np;                         // partial results altogether
+};
+// What a fused call is asked to do, as far as the host knows it.
+struct FusedShape {
+    int n_levels;
+    const hg_level* levels;
+    bool has_suffix;
+    int max_len;
+    int page_shift;                 // -1: packed rows
+    bool fp8;
+    int B, Hq, Hkv, D;
+    size_t ws_bytes;                // room for partial results
+    bool counters;                  // the context has its device counters
+};
+
+static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
+    FusedPlan& p = *out;
+    p.way = kWaySingle;
+    p.splits = 1;
+    p.nlev = 0;
+    p.main_level = p.joint = -1;
+    const int n_levels = f.n_levels, max_len = f.max_len, B = f.B, Hq = f.Hq, Hkv = f.Hkv, D = f.D, nq = c->opt_nq, G = Hq / Hkv;
+    const hg_level* const levels = f.levels;
+    const bool has_suffix = f.has_suffix, paged = f.page_shift >= 0;
+    const int cap = parts_cap(f.ws_bytes, (int64_t)B * nq * Hq, D);
 
     // Shared block and suffix in one launch (combined_impl.h): calls with a level on the persistent kernel and a suffix on the
     // matrix cores or with one query row per KV head.  The stage timings need separate kernels.
     // (8-bit codes in 32-row tiles stay on separate kernels: half the bytes in flight per wavefront do not cover the longer
     // stage; 215 sequences, 64/8 heads, 4 queries: 83 against 76 us.)
-    const bool may_combine = c->opt_overlap == 0 && !c->opt_timing && has_suffix && c->arrivals && !(fmt.fp8 && (nq * G > 16 || c->opt_suffix_tile == 32)) &&
-                             ((nq == 1 && G == 1) || plan_suffix(c, max_len, G, B, nq, Hkv, D, pg.table != nullptr, 1 << 30, fmt.fp8 != 0).mfma);
+    const bool may_combine = c->opt_overlap == 0 && !c->opt_timing && has_suffix && f.counters && !(f.fp8 && (nq * G > 16 || c->opt_suffix_tile == 32)) &&
+                             ((nq == 1 && G == 1) || plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8).mfma);
 
     // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
     // column of 32 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two
@@ -799,63 +823,37 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
             const double per_stage = 1.6 + 0.7 * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0));
             return 4.0 + ceil(wgs / per_round) * (4.0 + per_stage * ceil(stages / (8.0 * S))) + (S > 1 ? 4.5 + 0.3 * S : 0.0);
         };
-        int splits = 1;
-        if (c->arrivals && cols * 2 <= 256 && cols <= kArrivalCounters) {
+        int& splits = p.splits;
+        if (f.counters && cols * 2 <= 256 && cols <= kArrivalCounters) {
             // (more workgroups than one stage per wavefront asks for only meet later)
             const int most = (int)std::min<long long>({256 / cols, kSmallMaxSplits, (long long)ceil(stages / 8.0)});
             for (int S = 2; S <= most; ++S)
-                if (chain_at(S) < 0.95 * chain_at(splits) && small_part_floats((int)cols, S, D) * sizeof(float) <= ws.bytes) splits = S;
+                if (chain_at(S) < 0.95 * chain_at(splits) && small_part_floats((int)cols, S, D) * sizeof(float) <= f.ws_bytes) splits = S;
         }
-        const double suffix_us = has_suffix ? (fmt.fp8 ? 2.0 : 4.0) * B * (0.75 * max_len) * Hkv * D / 5.0e6 : 0.0;      // at 5 TB/s
+        const double suffix_us = has_suffix ? (f.fp8 ? 2.0 : 4.0) * B * (0.75 * max_len) * Hkv * D / 5.0e6 : 0.0;      // at 5 TB/s
         const double shared_us = shared_bytes / 5.0e6;
         // every column reads the shared rows for itself: from its XCD's L2 (4 MB; an XCD works on its share of the KV heads)
         // while they fit there, at 8 TB/s beyond
         const double restream_us = shared_bytes / std::min(8, Hkv) > 4.0e6
                                        ? (double)cols * shared_stages * 128.0 * D / 8.0e6 + suffix_us + 13.0 : 0.0;
-        const double est_single = std::max({chain_at(splits), (pg.table ? 1.5 : joins ? 1.0 : 1.2) * suffix_us + shared_us + 7.0, restream_us});
+        const double est_single = std::max({chain_at(splits), (paged ? 1.5 : joins ? 1.0 : 1.2) * suffix_us + shared_us + 7.0, restream_us});
         double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
                                     suffix_us + std::max(flops / 1.1e9, shared_us);
         if (nonempty == 0) est_separate = 10.5 + 0.7 * suffix_us;      // the suffix kernel alone: no event edges, hardly a merge
         if (suffix_us >= 30.0 && joins && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
         const bool small = est_single <= (est_single <= (joins ? 60.0 : 45.0) ? 1.0 : 0.75) * est_separate;
         if (any && cols * splits < (1LL << 31) && (c->opt_fused_kernel == 2 || small)) {
-            SmallArgs sa{};
-            sa.Q = static_cast<const uint16_t*>(Q);
-            sa.n_levels = 0;
-            for (int i = 0; i < n_levels; ++i) {
-                const LevelDev d = to_dev(levels[i], B);
-                if (d.max_rows == 0 || d.max_seqs == 0) continue;
-                sa.lv[sa.n_levels++] = d;
-            }
-            sa.Ks = static_cast<const uint16_t*>(Ks);
-            sa.Vs = static_cast<const uint16_t*>(Vs);
-            sa.offsets = offsets;
-            sa.lengths = has_suffix ? lengths : nullptr;
-            sa.pg = has_suffix ? pg : PagedDev{};
-            sa.fp8 = has_suffix ? fmt.fp8 : 0;
-            sa.k_scale = fmt.k_scale; sa.v_scale = fmt.v_scale;
-            sa.max_len = max_len;
-            sa.B = B; sa.Hq = Hq; sa.Hkv = Hkv; sa.G = G; sa.nq = nq;
-            sa.tiles = (int)tiles;
-            sa.cols = (int)cols;
-            sa.splits = splits;
-            sa.part = reinterpret_cast<float*>(ws.p);
-            sa.arrivals = c->arrivals;
-            sa.scale = scale;
-            sa.O = O_out; sa.LSE = LSE_out; sa.bf16 = (o_dtype == HG_BF16);
-            return hip_rc(launch_fused_small(sa, D, c->stream));
+            return HG_OK;
         }
     }
-    const Parts parts = carve(ws, rows, D);
 
     // plan: parts per level and for the suffix, shrunk to fit the workspace
-    LevelDev lv[HG_MAX_LEVELS];
-    LevelPlan plan[HG_MAX_LEVELS];
-    int ns[HG_MAX_LEVELS], index[HG_MAX_LEVELS];
-    int nlev = 0;
+    LevelDev* const lv = p.lv;
+    LevelPlan* const plan = p.plan;
+    int *const ns = p.ns, *const index = p.index;
+    int &nlev = p.nlev, &main_level = p.main_level;
     // In the combined launch levels of more than 64 query rows run on the persistent kernel as well, provided that one has more
     // than 128: it costs no launch of its own there.  Only the level with the most work may use the plan with a table.
-    int main_level = -1;
     bool combine = false;
     for (int i = 0; i < n_levels; ++i) {
         const double seqs = levels[i].kv_off ? levels[i].max_seqs : B;
@@ -883,8 +881,8 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         }
         // K and V, bf16 (or 8-bit codes; on the matrix cores their expansion costs about a third of the saving); the
         // vector-ALU kernel reads them once per query; mean length taken as 0.75 max_len
-        const bool sfx_mfma = plan_suffix(c, max_len, G, B, nq, Hkv, D, pg.table != nullptr, 1 << 30, fmt.fp8 != 0).mfma;
-        const double per_elem = fmt.fp8 ? (sfx_mfma ? 2.6 : 2.0) : 4.0;
+        const bool sfx_mfma = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8).mfma;
+        const double per_elem = f.fp8 ? (sfx_mfma ? 2.6 : 2.0) : 4.0;
         const double bytes = per_elem * B * (sfx_mfma ? 1 : nq) * (0.75 * max_len) * Hkv * D;
         wide_slots = pick_wide_slots(flops, bytes, T);
         tiny = c->opt_overlap == 0 && flops / 1.14e15 + bytes / 6.0e12 < 60e-6;
@@ -896,12 +894,13 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         if (d.max_rows == 0 || d.max_seqs == 0) continue;  // empty level contributes nothing
         lv[nlev] = d;
         index[nlev] = i;
-        plan[nlev] = plan_level(c, d, Hkv, nq * G, D, parts.cap, wide_slots, combined_above, i == main_level);
+        plan[nlev] = plan_level(c, d, Hkv, nq * G, D, cap, wide_slots, combined_above, i == main_level);
         ns[nlev] = plan[nlev].ns;
         ++nlev;
     }
-    const int max_chunk = pg.table ? 32 << pg.shift : 1 << 30;
-    SuffixPlan sp = plan_suffix(c, max_len, G, B, nq, Hkv, D, pg.table != nullptr, max_chunk, fmt.fp8 != 0);
+    const int max_chunk = paged ? 32 << f.page_shift : 1 << 30;
+    SuffixPlan& sp = p.sp;
+    sp = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, max_chunk, f.fp8);
     // (the combined launch has 2048 wavefronts: items for all of them, equal shares of the longest suffix)
     if (may_combine && sp.mfma && c->opt_suffix_chunk == 0) {
         const long long whole = (long long)B * Hkv * ceil_div(nq * G, 32);
@@ -913,8 +912,8 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     }
     if (!has_suffix) sp.nchunks = 0;
     auto total_parts = [&]() { int t = sp.nchunks; for (int i = 0; i < nlev; ++i) t += ns[i]; return t; };
-    if (nlev + (has_suffix ? 1 : 0) > parts.cap) return HG_ERR_WORKSPACE;
-    while (total_parts() > parts.cap) {  // shrink the largest split count first
+    if (nlev + (has_suffix ? 1 : 0) > cap) return HG_ERR_WORKSPACE;
+    while (total_parts() > cap) {  // shrink the largest split count first
         int big = -1, bigv = 1;
         for (int i = 0; i < nlev; ++i) if (ns[i] > bigv) { bigv = ns[i]; big = i; }
         if (sp.nchunks > bigv) {
@@ -939,19 +938,93 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         const int tile_rows = (nq * G <= 16 && c->opt_suffix_tile != 32) ? 16 : 32;
         if ((int64_t)B * sp.nchunks * ceil_div(nq * G, tile_rows) * Hkv >= (1LL << 31)) return HG_ERR_UNSUPPORTED;
     }
-    const int np = total_parts();
-    hipStream_t s = c->stream;
-    if (np == 0) return fill_empty(O_out, o_dtype, LSE_out, rows, D, s);
-
-    // (grouped levels may leave sequences uncovered: the level's kernel marks their partial results empty)
+    p.np = total_parts();
+    if (p.np == 0) {
+        p.way = kWayFill;
+        return HG_OK;
+    }
 
     // The levels on the persistent kernel share the suffix's launch; the others, and more than a few, go before it.
-    int joint = -1;
+    int& joint = p.joint;
     if (combine && (int64_t)B * nq * G * sp.nchunks * Hkv < (1LL << 30)) {
         for (int i = 0; i < nlev; ++i)
             if (plan[i].wide && (joint < 0 || index[i] == main_level)) joint = i;
     }
     if (joint >= 0) {
+        p.way = kWayCombined;
+        return HG_OK;
+    }
+
+    // Two streams unless asked for one.  In automatic mode a call whose levels all run in the persistent kernel on
+    // the whole chip stays on one stream (there is no CU left for the suffix kernel to run beside it), and so does a
+    // call with less than about 60 us of work (forking and joining streams costs more than it can gain).
+    bool all_wide_full = nlev > 0;
+    for (int i = 0; i < nlev; ++i) all_wide_full = all_wide_full && plan[i].wide && plan[i].wp.slots == 32;
+    const bool two = c->opt_overlap != 1 && has_suffix && nlev > 0 && !(c->opt_overlap == 0 && (all_wide_full || tiny));
+    p.way = two ? kWayTwoStreams : kWayOneStream;
+    return HG_OK;
+}
+
+// hg_hydragen_attn and hg_hydragen_attn_paged (pg.table set, offsets unused)
+static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* levels, const void* Ks, const void* Vs,
+                      const int32_t* offsets, const int32_t* lengths, int max_len, int B, int Hq, int Hkv, int D,
+                      float scale, void* O_out, int o_dtype, float* LSE_out, const hg::PagedDev& pg, const KvFmt& fmt = KvFmt{},
+                      const Ws* ws_override = nullptr) {
+    int rc = check_fused(c, Q, n_levels, levels, Ks, Vs, offsets, lengths, max_len, B, Hq, Hkv, D, O_out, o_dtype,
+                         pg.table != nullptr);
+    if (rc) return rc;
+    if (B == 0) return HG_OK;
+    if (hipSetDevice(c->device) != hipSuccess) return HG_ERR_HIP;
+    scale = eff_scale(scale, D);
+    const int nq = c->opt_nq;
+    const int64_t rows = (int64_t)B * nq * Hq;
+    const int G = Hq / Hkv;
+    const bool has_suffix = Ks != nullptr && max_len > 0;
+    const Ws ws = ws_override ? *ws_override : Ws{c->ws, c->ws_bytes};
+
+    FusedPlan p;
+    rc = plan_fused(c, FusedShape{n_levels, levels, has_suffix, max_len, pg.table ? pg.shift : -1, fmt.fp8 != 0, B, Hq, Hkv, D,
+                                  ws.p ? ws.bytes : 0, c->arrivals != nullptr}, &p);
+    if (rc) return rc;
+    hipStream_t s = c->stream;
+    if (p.way == kWayFill) return fill_empty(O_out, o_dtype, LSE_out, rows, D, s);
+    if (p.way == kWaySingle) {
+        SmallArgs sa{};
+        sa.Q = static_cast<const uint16_t*>(Q);
+        sa.n_levels = 0;
+        for (int i = 0; i < n_levels; ++i) {
+            const LevelDev d = to_dev(levels[i], B);
+            if (d.max_rows == 0 || d.max_seqs == 0) continue;
+            sa.lv[sa.n_levels++] = d;
+        }
+        sa.Ks = static_cast<const uint16_t*>(Ks);
+        sa.Vs = static_cast<const uint16_t*>(Vs);
+        sa.offsets = offsets;
+        sa.lengths = has_suffix ? lengths : nullptr;
+        sa.pg = has_suffix ? pg : PagedDev{};
+        sa.fp8 = has_suffix ? fmt.fp8 : 0;
+        sa.k_scale = fmt.k_scale; sa.v_scale = fmt.v_scale;
+        sa.max_len = max_len;
+        sa.B = B; sa.Hq = Hq; sa.Hkv = Hkv; sa.G = G; sa.nq = nq;
+        sa.tiles = (B * nq * G + 31) / 32;
+        sa.cols = sa.tiles * Hkv;
+        sa.splits = p.splits;
+        sa.part = reinterpret_cast<float*>(ws.p);
+        sa.arrivals = c->arrivals;
+        sa.scale = scale;
+        sa.O = O_out; sa.LSE = LSE_out; sa.bf16 = (o_dtype == HG_BF16);
+        return hip_rc(launch_fused_small(sa, D, c->stream));
+    }
+    const Parts parts = carve(ws, rows, D);
+    const LevelDev* const lv = p.lv;
+    const LevelPlan* const plan = p.plan;
+    const int *const ns = p.ns;
+    const int nlev = p.nlev, np = p.np;
+    const SuffixPlan& sp = p.sp;
+
+    // (grouped levels may leave sequences uncovered: the level's kernel marks their partial results empty)
+    if (p.way == kWayCombined) {
+        const int joint = p.joint;
         CombinedArgs ca{};
         int part = 0;
         for (int i = 0; i < nlev; ++i) {
@@ -983,12 +1056,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         return run_merge(np, parts, 0, D, O_out, o_dtype, LSE_out, s);
     }
 
-    // Two streams unless asked for one.  In automatic mode a call whose levels all run in the persistent kernel on
-    // the whole chip stays on one stream (there is no CU left for the suffix kernel to run beside it), and so does a
-    // call with less than about 60 us of work (forking and joining streams costs more than it can gain).
-    bool all_wide_full = nlev > 0;
-    for (int i = 0; i < nlev; ++i) all_wide_full = all_wide_full && plan[i].wide && plan[i].wp.slots == 32;
-    const bool overlap = c->opt_overlap != 1 && has_suffix && nlev > 0 && !(c->opt_overlap == 0 && (all_wide_full || tiny));
+    const bool overlap = p.way == kWayTwoStreams;
     hipStream_t ssfx = s;
     if (overlap) {
         if (hipEventRecord(c->ev_fork, s) != hipSuccess) return HG_ERR_HIP;
@@ -1299,6 +1367,40 @@ int hg_debug_suffix_plan(int B, int nq, int Hq, int Hkv, int D, int max_len, int
     const SuffixPlan p = plan_suffix(&c, max_len, Hq / Hkv, B, nq, Hkv, D, page_size > 0, page_size > 0 ? 32 * page_size : 1 << 30);
     out[0] = p.chunk; out[1] = p.nchunks; out[2] = p.mfma ? 1 : 0; out[3] = p.gt;
     return 1;
+}
+
+int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const hg_level* levels, int B, int nq, int Hq, int Hkv, int D,
+                        int max_len, int page_size, int fp8, size_t workspace_bytes, int out[8]) {
+    if (!out || n_options < 0 || (n_options > 0 && !options) || n_levels < 0 || n_levels > HG_MAX_LEVELS || (n_levels > 0 && !levels)) return HG_ERR_INVALID_ARG;
+    if (B < 1 || nq < 1 || nq > 64 || max_len < 0 || page_size < 0 || page_size > 1024) return HG_ERR_INVALID_ARG;
+    const int rc = check_shape(B, Hq, Hkv, D, nq);
+    if (rc) return rc;
+    hg_ctx c{};
+    for (int i = 0; i < n_options; ++i) {
+        const int set = options[2 * i] == HG_OPT_STAGE_TIMING ? HG_ERR_INVALID_ARG : hg_set_option(&c, options[2 * i], options[2 * i + 1]);
+        if (set) return set;
+    }
+    c.opt_nq = nq;
+    int shift = -1;
+    if (page_size > 0)
+        for (shift = 0; (1 << shift) < page_size;) ++shift;
+    FusedPlan p;
+    const int r = plan_fused(&c, FusedShape{n_levels, levels, max_len > 0, max_len, shift, fp8 != 0, B, Hq, Hkv, D, workspace_bytes, true}, &p);
+    if (r) return r;
+    const bool single = p.way == kWaySingle;
+    out[0] = p.way;
+    out[1] = single ? p.splits : 0;
+    out[2] = single ? 0 : p.np;
+    out[3] = single ? 0 : p.sp.chunk;
+    out[4] = single ? 0 : p.sp.nchunks;
+    out[5] = !single && p.sp.nchunks > 0 && p.sp.mfma ? 1 : 0;
+    out[6] = out[7] = 0;
+    for (int i = 0; !single && i < p.nlev; ++i) {
+        if (!p.plan[i].wide) continue;
+        out[6] |= 1 << p.index[i];
+        if (p.index[i] == p.main_level || !out[7]) out[7] = p.plan[i].wp.slots;
+    }
+    return HG_OK;
 }
 
 int hg_debug_mfma_loop(hg_ctx* c, int random_operands, int iters, unsigned long long* clocks, float* sink) {

@@ -145,3 +145,21 @@ def test_suffix_plan_rejects_bad_arguments():
     assert hb.hg_debug_suffix_plan(4, 1, 6, 4, 128, 10) is None     # Hq not a multiple of Hkv
     assert hb.hg_debug_suffix_plan(4, 1, 4, 4, 96, 10) is None      # unsupported head dimension
     assert hb.hg_debug_suffix_plan(0, 1, 4, 4, 128, 10) is None
+
+
+# ---- which way a fused call runs (hg_debug_fused_plan) ------------------------------------------------------------------------
+
+
+def test_fused_plan_names_the_way():
+    plan = hb.hg_debug_fused_plan
+    assert plan([(1, 128, 4)], 4, 1, 4, 4, 64, 16)["way"] == "single"
+    big = plan([(1, 16384, 1024)], 1024, 1, 40, 40, 128, 128)
+    assert big["way"] == "combined" and big["wide_levels"] == 1 and big["mfma"] == 0 and 4 <= big["slots"] <= 32
+    assert plan([(1, 4096, 512)], 512, 1, 64, 8, 128, 512)["mfma"] == 1
+    assert plan([(1, 16384, 1024)], 1024, 1, 40, 40, 128, 128, options={hb.HG_OPT_OVERLAP: 1})["way"] == "one_stream"
+    assert plan([(1, 16384, 1024)], 1024, 1, 40, 40, 128, 128, options={hb.HG_OPT_OVERLAP: 2})["way"] == "two_streams"
+    assert plan([(1, 0, 4)], 4, 1, 4, 4, 64, 0, options={hb.HG_OPT_FUSED_KERNEL: 1}, workspace_bytes=1 << 20)["way"] == "fill"
+    assert plan([(1, 16384, 1024)], 1024, 1, 40, 40, 128, 128, workspace_bytes=0) == hb.HG_ERR_WORKSPACE
+    assert plan([], 4, 1, 6, 4, 128, 10) == hb.HG_ERR_UNSUPPORTED
+    assert plan([], 0, 1, 4, 4, 128, 10) == hb.HG_ERR_INVALID_ARG
+    assert plan([], 4, 1, 4, 4, 128, 10, options={hb.HG_OPT_STAGE_TIMING: 1}) == hb.HG_ERR_INVALID_ARG

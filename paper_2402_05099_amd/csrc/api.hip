@@ -768,12 +768,14 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     const bool has_suffix = f.has_suffix, paged = f.page_shift >= 0;
     const int cap = parts_cap(f.ws_bytes, (int64_t)B * nq * Hq, D);
 
+    const bool sfx_mfma = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8).mfma;
+
     // Shared block and suffix in one launch (combined_impl.h): calls with a level on the persistent kernel and a suffix on the
     // matrix cores or with one query row per KV head.  The stage timings need separate kernels.
     // (8-bit codes in 32-row tiles stay on separate kernels: half the bytes in flight per wavefront do not cover the longer
     // stage; 215 sequences, 64/8 heads, 4 queries: 83 against 76 us.)
     const bool may_combine = c->opt_overlap == 0 && !c->opt_timing && has_suffix && f.counters && !(f.fp8 && (nq * G > 16 || c->opt_suffix_tile == 32)) &&
-                             ((nq == 1 && G == 1) || plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8).mfma);
+                             ((nq == 1 && G == 1) || sfx_mfma);
 
     // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
     // column of 32 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two
@@ -792,7 +794,10 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // other way: 12.4 / 25 us (72 sequences, 206 rows), 17.3 / 26 (2.5K shared keys, 16 sequences), 15.9 / 24 (256
     // sequences, 1K keys), 59 / 46 (128 x 32/8 heads, 2K keys, paged, with the cache update: not taken), 74 / 59 (53 x 32/8
     // heads, 12K + 12 x 276 keys, 8-bit: not taken), 222 / 131 (256 x 40 heads, 2K keys: not taken).
-    if (c->opt_fused_kernel != 1 && !c->opt_timing) {
+    // 8-bit rows that the vector-ALU kernel would read stay with it unless the caller asks for the single launch: that kernel
+    // keeps fp32 weights, this one rounds them to bf16 (error of O without a shared block 1.3e-7 against 1.1e-3).
+    const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma;
+    if (c->opt_fused_kernel != 1 && !c->opt_timing && !(fp32_weights && c->opt_fused_kernel != 2)) {
         const int rps = nq * G;
         long long shared_keys = 0;
         double flops = 0.0, shared_bytes = 0.0, shared_stages = 0.0;
@@ -881,7 +886,6 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         }
         // K and V, bf16 (or 8-bit codes; on the matrix cores their expansion costs about a third of the saving); the
         // vector-ALU kernel reads them once per query; mean length taken as 0.75 max_len
-        const bool sfx_mfma = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8).mfma;
         const double per_elem = f.fp8 ? (sfx_mfma ? 2.6 : 2.0) : 4.0;
         const double bytes = per_elem * B * (sfx_mfma ? 1 : nq) * (0.75 * max_len) * Hkv * D;
         wide_slots = pick_wide_slots(flops, bytes, T);

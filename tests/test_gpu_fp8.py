@@ -461,3 +461,46 @@ def test_fp8_decode_steps_in_a_graph(idx):
         check(to_np(O), to_np(L), Oref, Lref, f"fp8 graph decode step {k}")
     assert np.array_equal(Lh, w.lengths + steps)
     ctx.close()
+
+
+# ---- precision of small fused calls -----------------------------------------------------------------------------------------------
+
+
+def small_fp8_call(w, paged, ctx, f8=None):
+    """(fp32 O of the fused call over an 8-bit cache, fp64 O of the decoded values)"""
+    f8 = f8 or wl.make_fp8(w, reserve=2)
+    Oref, Lref = fp8.suffix_attention_fp8(w.Q, w.Hkv, f8.Ks8, f8.Vs8, f8.k_scale, f8.v_scale, f8.offsets, w.lengths, w.scale)
+    if w.levels:
+        Op, Lp = oracle.attention(w, suffix=False)
+        Oref, _ = oracle.merge([Op, Oref], [Lp, Lref])
+    dw = dev.to_device(w)
+    O = torch.full(dw.lead + (dw.D,), float("nan"), dtype=torch.float32, device="cuda:0")
+    L = torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0")
+    if paged:
+        pg, ks, vs = wl.make_paged_fp8(w, 16)
+        kv = hb.PagedKV(K=u8(pg.K), V=u8(pg.V), page_table=i32(pg.table), page_size=pg.page_size, kv_format=hb.HG_KV_E4M3,
+                        k_scale=ks, v_scale=vs)
+        hb.hg_hydragen_attn_paged(ctx, dw.Q, dw.levels, kv, dw.lengths, dw.max_len, O, L, dw.scale)
+    else:
+        hb.hg_hydragen_attn_fp8(ctx, dw.Q, dw.levels, u8(f8.Ks8), u8(f8.Vs8), f8.k_scale, f8.v_scale, i32(f8.offsets), dw.lengths,
+                                dw.max_len, O, L, dw.scale)
+    torch.cuda.synchronize()
+    return to_np(O), Oref
+
+
+@pytest.mark.parametrize("paged", [False, True], ids=["packed", "paged"])
+@pytest.mark.parametrize("heads", [(4, 4, 128), (4, 2, 128), (4, 4, 64), (16, 2, 64)], ids=lambda h: f"{h[0]}_{h[1]}_{h[2]}")
+def test_small_fused_call_keeps_the_vector_kernels_precision(heads, paged):
+    """8-bit rows that the vector-ALU kernel reads (few rows per KV head, or D = 64): fp32 weights against fp32 values, so
+    a call without shared blocks is off by fp32 rounding only.  Gate 2e-5: about 100 products and weights of relative error
+    2^-22 each; weights rounded to bf16 (2^-9) would give about 1e-3."""
+    Hq, Hkv, D = heads
+    say(f"fp8 small fused call, vector kernel's precision: {heads} paged={paged}")
+    w = wl.make_workload("fp8 small", 51, 6, Hq, Hkv, D, [], 20, 60)
+    ctx = hb.Context(0, hb.hg_workspace_bytes(w.B, Hq, D, 24))
+    ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 0)
+    O, Oref = small_fp8_call(w, paged, ctx)
+    err = np.linalg.norm(O - Oref) / np.linalg.norm(Oref)
+    say(f"   rel-L2 {err:.2e}")
+    assert err <= 2e-5
+    ctx.close()

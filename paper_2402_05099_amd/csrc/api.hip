@@ -752,6 +752,7 @@ struct FusedShape {
     int max_len;
     int page_shift;                 // -1: packed rows
     bool fp8;
+    float v_scale;
     int B, Hq, Hkv, D;
     size_t ws_bytes;                // room for partial results
     bool counters;                  // the context has its device counters
@@ -797,7 +798,9 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // 8-bit rows that the vector-ALU kernel would read stay with it unless the caller asks for the single launch: that kernel
     // keeps fp32 weights, this one rounds them to bf16 (error of O without a shared block 1.3e-7 against 1.1e-3).
     const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma;
-    if (c->opt_fused_kernel != 1 && !c->opt_timing && !(fp32_weights && c->opt_fused_kernel != 2)) {
+    // (the single launch divides sums by the V scale and multiplies them again: not with scales near the ends of fp32)
+    const bool odd_scale = f.fp8 && has_suffix && !(f.v_scale >= 0x1p-60f && f.v_scale <= 0x1p60f);
+    if (c->opt_fused_kernel != 1 && !c->opt_timing && !odd_scale && !(fp32_weights && c->opt_fused_kernel != 2)) {
         const int rps = nq * G;
         long long shared_keys = 0;
         double flops = 0.0, shared_bytes = 0.0, shared_stages = 0.0;
@@ -987,7 +990,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     const Ws ws = ws_override ? *ws_override : Ws{c->ws, c->ws_bytes};
 
     FusedPlan p;
-    rc = plan_fused(c, FusedShape{n_levels, levels, has_suffix, max_len, pg.table ? pg.shift : -1, fmt.fp8 != 0, B, Hq, Hkv, D,
+    rc = plan_fused(c, FusedShape{n_levels, levels, has_suffix, max_len, pg.table ? pg.shift : -1, fmt.fp8 != 0, fmt.v_scale, B, Hq, Hkv, D,
                                   ws.p ? ws.bytes : 0, c->arrivals != nullptr}, &p);
     if (rc) return rc;
     hipStream_t s = c->stream;
@@ -1389,7 +1392,7 @@ int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const h
     if (page_size > 0)
         for (shift = 0; (1 << shift) < page_size;) ++shift;
     FusedPlan p;
-    const int r = plan_fused(&c, FusedShape{n_levels, levels, max_len > 0, max_len, shift, fp8 != 0, B, Hq, Hkv, D, workspace_bytes, true}, &p);
+    const int r = plan_fused(&c, FusedShape{n_levels, levels, max_len > 0, max_len, shift, fp8 != 0, 1.0f, B, Hq, Hkv, D, workspace_bytes, true}, &p);
     if (r) return r;
     const bool single = p.way == kWaySingle;
     out[0] = p.way;

@@ -31,7 +31,9 @@
 //
 // PAGED: the suffix rows are found through a page table; FP8: they are E4M3 codes with one scale per tensor, expanded
 // in registers (exactly: every E4M3 value is a bf16 value); the K scale multiplies the scores of those stages, the V
-// scale their weights.
+// scale finished sums: a wavefront whose run goes on from shared rows to codes divides its accumulators by it once and
+// goes on in units of it, and multiplies them by it at its end (on the weights it would be rounded to bf16 with them:
+// one key per sequence, whose weight is 1, came out 1.9e-3 off instead of exact).
 #include <type_traits>
 
 #include "hg_internal.h"
@@ -392,6 +394,7 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     float m_used = -INFINITY;   // raw-score maximum the exponentials are taken against (-inf: no key seen yet)
     float mc = 0.f;             // m_used * c2, 0 while no key has been seen
     float lsum = 0.f;           // this lane's share of the row sum (unrounded exponentials)
+    bool code_units = false;    // the accumulators hold sums of codes, to be multiplied by the V scale
 
     if (run_lo < run_hi) {
         issue(cs, ct, IsK{});
@@ -459,7 +462,6 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
 #pragma unroll
                 for (int j = 0; j < 16; ++j) Oacc[i][j] *= alpha;
         }
-        const float vs = codes ? a.v_scale : 1.0f;
         uintx4 pb[2];
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt) {
@@ -468,7 +470,6 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
             for (int i = 0; i < 8; ++i) {
                 p[i] = __builtin_amdgcn_exp2f(fmaf(S[8 * tt + i], c2, -mc));
                 lsum += p[i];
-                if constexpr (FP8) p[i] *= vs;
             }
             pb[tt] = uintx4{pack_pair(p[0], p[1]), pack_pair(p[2], p[3]), pack_pair(p[4], p[5]), pack_pair(p[6], p[7])};
         }
@@ -490,6 +491,16 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
                     const int row = i * RPI + lrow;
                     if (row < nlo || row >= nhi) *reinterpret_cast<uintx4*>(smem + STB + i * 1024 + l * 16) = uintx4{0u, 0u, 0u, 0u};
                 }
+            }
+        }
+        if constexpr (FP8) {
+            if (codes && !code_units) {             // (once per wavefront: the shared blocks come first; the host bounds the scale)
+                const float rs = 1.0f / a.v_scale;
+#pragma unroll
+                for (int i = 0; i < DB; ++i)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) Oacc[i][j] *= rs;
+                code_units = true;
             }
         }
         // O^T += V^T P^T
@@ -530,6 +541,14 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     float* const Lw = Mw + NWS * 32;
     int* const last_flag = reinterpret_cast<int*>(Lw + NWS * 32);
     const float ltot = half_sum(lsum);
+    if constexpr (FP8) {
+        if (code_units) {
+#pragma unroll
+            for (int i = 0; i < DB; ++i)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) Oacc[i][j] *= a.v_scale;
+        }
+    }
     {                                               // (own ring only: nothing to wait for)
         unsigned char* const ow = smem_all + w * OW;
 #pragma unroll

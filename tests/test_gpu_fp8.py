@@ -504,3 +504,36 @@ def test_small_fused_call_keeps_the_vector_kernels_precision(heads, paged):
     say(f"   rel-L2 {err:.2e}")
     assert err <= 2e-5
     ctx.close()
+
+
+@pytest.mark.parametrize("paged", [False, True], ids=["packed", "paged"])
+def test_small_fused_call_scales_values_after_the_sum(paged):
+    """Single launch over 8-bit rows (several query rows per KV head): the V scale multiplies finished sums, not the bf16
+    weights.  One key per sequence has weight 1 exactly, so O is code * v_scale up to fp32 rounding of the combination."""
+    say(f"fp8 small fused call, one key each, paged={paged}")
+    assert hb.hg_debug_fused_plan([], 6, 1, 32, 8, 128, 1, 16 if paged else 0, True)["way"] == "single"
+    w = wl.make_workload("fp8 one key", 52, 6, 32, 8, 128, [], 1, 1)
+    ctx = hb.Context(0, hb.hg_workspace_bytes(w.B, w.Hq, w.D, 24))
+    ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 0)
+    O, Oref = small_fp8_call(w, paged, ctx)
+    err = np.linalg.norm(O - Oref) / np.linalg.norm(Oref)
+    say(f"   rel-L2 {err:.2e}")
+    assert err <= 1e-6
+    ctx.close()
+
+
+@pytest.mark.parametrize("P", [33, 300])
+def test_small_fused_call_changes_from_shared_to_8_bit_rows(P):
+    """Wavefronts of the single launch whose stages begin in the shared block and end in the 8-bit suffix: no further from
+    the fp64 result than the separate kernels (a tenth more allowed: the two round other weights)."""
+    say(f"fp8 small fused call, P={P}")
+    w = wl.make_workload("fp8 mixed", 53, 9, 32, 8, 128, [(1, P, 9)], 5, 90)
+    errs = []
+    for kernel in (2, 1):
+        ctx = hb.Context(0, hb.hg_workspace_bytes(w.B, w.Hq, w.D, 24))
+        ctx.set_option(hb.HG_OPT_FUSED_KERNEL, kernel)
+        O, Oref = small_fp8_call(w, False, ctx)
+        errs.append(np.linalg.norm(O - Oref) / np.linalg.norm(Oref))
+        ctx.close()
+    say(f"   rel-L2 single {errs[0]:.2e}, separate {errs[1]:.2e}")
+    assert errs[0] <= 1.1 * errs[1]

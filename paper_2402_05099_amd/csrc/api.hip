@@ -753,6 +753,7 @@ struct FusedShape {
     int page_shift;                 // -1: packed rows
     bool fp8;
     float v_scale;
+    bool wants_lse;
     int B, Hq, Hkv, D;
     size_t ws_bytes;                // room for partial results
     bool counters;                  // the context has its device counters
@@ -831,8 +832,21 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             const double per_stage = 1.6 + 0.7 * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0));
             return 4.0 + ceil(wgs / per_round) * (4.0 + per_stage * ceil(stages / (8.0 * S))) + (S > 1 ? 4.5 + 0.3 * S : 0.0);
         };
+        // Small calls on packed rows touch nothing but their inputs and outputs: one workgroup per column, no workspace, no
+        // counters.  A program may have several in flight for one context (streams, graph replays, branches of a graph) or run
+        // them without a workspace, so which calls these are is fixed here and does not follow the estimates.  (Splitting their
+        // columns too gained 1 % over 200 drawn calls of this kind, 30 % where few columns meet 2K shared keys.)
+        bool own_memory = false;
+        if (any && !paged && !f.fp8 && cols < (1LL << 31)) {
+            const double suffix = has_suffix ? 4.0 * B * (double)max_len * Hkv * D / 5.0e6 : 0.0;
+            const long long walked = (shared_keys + 31) / 32 + (has_suffix ? (long long)seqs_per_tile * ((max_len + 31) / 32) : 0);
+            const double walk = 9.0 + (cols <= 128 ? 1.24 : 1.6) * (double)((walked + 3) / 4) * std::max(1.0, cols / 256.0);
+            const double one = std::max(walk, suffix * (5.0 / 5.5) + 4.0);
+            const double other = 24.0 + 0.75 * suffix + (shared_keys >= 1024 ? 8.0 : 0.0) + flops / 1.1e9;
+            own_memory = c->opt_fused_kernel == 2 || (one <= 130.0 && one <= (one <= 40.0 ? 1.0 : 0.9) * other);
+        }
         int& splits = p.splits;
-        if (f.counters && cols * 2 <= 256 && cols <= kArrivalCounters) {
+        if (!own_memory && f.counters && cols * 2 <= 256 && cols <= kArrivalCounters) {
             // (more workgroups than one stage per wavefront asks for only meet later)
             const int most = (int)std::min<long long>({256 / cols, kSmallMaxSplits, (long long)ceil(stages / 8.0)});
             for (int S = 2; S <= most; ++S)
@@ -850,6 +864,16 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         if (nonempty == 0) est_separate = 10.5 + 0.7 * suffix_us;      // the suffix kernel alone: no event edges, hardly a merge
         if (suffix_us >= 30.0 && joins && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
         const bool small = est_single <= (est_single <= (joins ? 60.0 : 45.0) ? 1.0 : 0.75) * est_separate;
+        if (own_memory) {
+            // (a suffix alone, in one work item per row, goes from its kernel straight to the outputs: 782 x 4 heads, 21 rows
+            // 14 us against 18 for the single launch)
+            if (small || c->opt_fused_kernel == 2 || nonempty > 0 || !f.wants_lse) return HG_OK;
+            p.sp = plan_suffix(c, max_len, G, B, nq, Hkv, D, false);
+            if (p.sp.nchunks > 1) return HG_OK;
+            p.way = kWayOneStream;
+            p.np = 1;
+            return HG_OK;
+        }
         if (any && cols * splits < (1LL << 31) && (c->opt_fused_kernel == 2 || small)) {
             return HG_OK;
         }
@@ -990,7 +1014,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
     const Ws ws = ws_override ? *ws_override : Ws{c->ws, c->ws_bytes};
 
     FusedPlan p;
-    rc = plan_fused(c, FusedShape{n_levels, levels, has_suffix, max_len, pg.table ? pg.shift : -1, fmt.fp8 != 0, fmt.v_scale, B, Hq, Hkv, D,
+    rc = plan_fused(c, FusedShape{n_levels, levels, has_suffix, max_len, pg.table ? pg.shift : -1, fmt.fp8 != 0, fmt.v_scale, LSE_out != nullptr, B, Hq, Hkv, D,
                                   ws.p ? ws.bytes : 0, c->arrivals != nullptr}, &p);
     if (rc) return rc;
     hipStream_t s = c->stream;
@@ -1062,6 +1086,11 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         if (rc) return rc;
         return run_merge(np, parts, 0, D, O_out, o_dtype, LSE_out, s);
     }
+
+    // one part, no timing events to place: straight to the outputs
+    if (nlev == 0 && np == 1 && LSE_out && !c->opt_timing)
+        return run_decode(Q, 0, nullptr, Ks, Vs, offsets, lengths, max_len, B, nq, Hq, Hkv, D, scale, sp.chunk, 1, sp.gt,
+                          direct_out(O_out, o_dtype, LSE_out), s, pg, sp.mfma, sp.ipw, false, fmt, c->opt_suffix_tile);
 
     const bool overlap = p.way == kWayTwoStreams;
     hipStream_t ssfx = s;
@@ -1392,7 +1421,7 @@ int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const h
     if (page_size > 0)
         for (shift = 0; (1 << shift) < page_size;) ++shift;
     FusedPlan p;
-    const int r = plan_fused(&c, FusedShape{n_levels, levels, max_len > 0, max_len, shift, fp8 != 0, 1.0f, B, Hq, Hkv, D, workspace_bytes, true}, &p);
+    const int r = plan_fused(&c, FusedShape{n_levels, levels, max_len > 0, max_len, shift, fp8 != 0, 1.0f, true, B, Hq, Hkv, D, workspace_bytes, true}, &p);
     if (r) return r;
     const bool single = p.way == kWaySingle;
     out[0] = p.way;

@@ -121,3 +121,54 @@ def test_tiny_call_takes_the_single_launch_by_itself():
         dev.hydragen(ctx, dw, torch.float32)
     assert e.value.code == hb.HG_ERR_WORKSPACE
     ctx.close()
+
+
+@pytest.mark.parametrize("shape", ["columns", "few_columns", "suffix_alone"])
+def test_one_context_with_several_small_calls_in_flight(shape):
+    """Small calls on packed rows touch only their inputs and outputs: one context enqueues them on two streams without
+    any order between them, and replays a captured one beside them.  Every result has the bits of a call made alone."""
+    say(f"single launch: several calls of one context in flight, {shape}")
+    w = {"columns": wl.make_workload("columns", 61, 45, 16, 2, 128, [(1, 515, 45)], 1, 150),
+         "few_columns": wl.make_workload("few", 62, 16, 16, 2, 128, [(1, 1509, 16)], 1, 217, nq=2),
+         "suffix_alone": wl.make_workload("alone", 63, 360, 16, 2, 128, [], 1, 33, nq=2)}[shape]
+    dw = dev.to_device(w)
+    ctx = hb.Context(0, 0)
+    ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 0)
+
+    def call(q, o, l):
+        hb.hg_hydragen_attn(ctx, q, dw.levels, dw.Ks, dw.Vs, dw.offsets, dw.lengths, dw.max_len, o, l, dw.scale)
+
+    def out():
+        return (torch.full(dw.lead + (dw.D,), float("nan"), dtype=torch.float32, device="cuda:0"),
+                torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0"))
+
+    queries = [dw.Q] + [torch.randn_like(dw.Q) for _ in range(2)]
+    alone = [out() for _ in queries]
+    for q, (o, l) in zip(queries, alone):
+        call(q, o, l)
+        torch.cuda.synchronize()
+    check(to_np(alone[0][0]), to_np(alone[0][1]), *oracle.attention(w), f"{shape} alone")
+    streams = [torch.cuda.Stream() for _ in queries]
+    Og, Lg = out()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=streams[2]):
+        ctx.set_stream(streams[2])
+        call(queries[2], Og, Lg)
+    for _ in range(3):
+        runs = [[out() for _ in range(20)] for _ in range(2)]
+        Og.fill_(float("nan"))
+        Lg.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for i in range(20):
+            for k in range(2):
+                ctx.set_stream(streams[k])
+                call(queries[k], *runs[k][i])
+            with torch.cuda.stream(streams[2]):
+                graph.replay()
+        torch.cuda.synchronize()
+        for k in range(2):
+            for o, l in runs[k]:
+                assert torch.equal(o, alone[k][0]) and torch.equal(l, alone[k][1]), f"{shape}: stream {k}"
+        assert torch.equal(Og, alone[2][0]) and torch.equal(Lg, alone[2][1]), f"{shape}: graph replay"
+    ctx.close()

@@ -180,3 +180,29 @@ def test_fused_plan_reads_8_bit_rows_with_the_suffix_kernels_arithmetic(page):
         assert not (vector and plan["way"] == "single"), (B, nq, Hkv, G, D, max_len, P, plan)
         seen += not vector and plan["way"] == "single"
     assert seen > 20
+
+
+# small calls on packed rows: (levels, B, nq, Hq, Hkv, D, max_len)
+OWN_MEMORY = [
+    ([(1, 128, 4)], 4, 1, 4, 4, 64, 16), ([(1, 515, 45)], 45, 1, 16, 2, 128, 150), ([(1, 1024, 256)], 256, 1, 8, 1, 128, 128),
+    ([(1, 441, 72)], 72, 1, 32, 8, 128, 233), ([(1, 1509, 16)], 16, 2, 64, 8, 128, 217), ([(1, 656, 37), (10, 302, 4)], 37, 2, 40, 40, 128, 28),
+    ([(13, 840, 4)], 48, 2, 8, 1, 64, 183), ([(1, 927, 265)], 265, 1, 32, 8, 128, 18), ([(1, 211, 1808)], 1808, 2, 8, 1, 128, 21),
+    ([(1, 189, 773)], 773, 4, 16, 2, 128, 30), ([(1, 1477, 357), (7, 131, 51)], 357, 1, 40, 40, 128, 92),
+    ([], 4, 1, 16, 2, 64, 178), ([], 360, 2, 64, 8, 128, 33), ([], 395, 1, 64, 8, 64, 38), ([], 6, 1, 40, 40, 128, 23),
+]
+
+
+@pytest.mark.parametrize("shape", OWN_MEMORY, ids=str)
+def test_small_packed_calls_share_no_memory(shape):
+    """One workgroup per column (or the suffix kernel straight to the outputs), whatever the workspace: such calls are accepted
+    without one and may be in flight side by side."""
+    levels, B, nq, Hq, Hkv, D, max_len = shape
+    plans = [hb.hg_debug_fused_plan(levels, B, nq, Hq, Hkv, D, max_len, workspace_bytes=n) for n in (0, 1 << 20, 1 << 34)]
+    assert plans[0] == plans[1] == plans[2], plans
+    if levels or plans[0]["way"] == "single":
+        assert plans[0]["way"] == "single" and plans[0]["splits"] == 1, plans[0]
+    else:
+        assert plans[0]["way"] == "one_stream" and plans[0]["parts"] == 1
+    # the caller's explicit single launch is such a call at any size
+    big = hb.hg_debug_fused_plan([(1, 9001, 3)], 3, 1, 4, 1, 128, 70, options={hb.HG_OPT_FUSED_KERNEL: 2})
+    assert big["way"] == "single" and big["splits"] == 1

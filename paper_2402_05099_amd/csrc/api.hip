@@ -736,6 +736,7 @@ enum { kWaySingle = 0, kWayCombined = 1, kWayOneStream = 2, kWayTwoStreams = 3, 
 struct FusedPlan {
     int way;
     int splits;                     // single launch: workgroups per column
+    bool sfx_mfma;                  // the suffix kernel's choice for these rows is the matrix cores
     int nlev;                       // levels that hold keys
     LevelDev lv[HG_MAX_LEVELS];
     LevelPlan plan[HG_MAX_LEVELS];
@@ -770,7 +771,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     const bool has_suffix = f.has_suffix, paged = f.page_shift >= 0;
     const int cap = parts_cap(f.ws_bytes, (int64_t)B * nq * Hq, D);
 
-    const bool sfx_mfma = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8).mfma;
+    const bool sfx_mfma = p.sfx_mfma = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8).mfma;
 
     // Shared block and suffix in one launch (combined_impl.h): calls with a level on the persistent kernel and a suffix on the
     // matrix cores or with one query row per KV head.  The stage timings need separate kernels.
@@ -796,12 +797,9 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // other way: 12.4 / 25 us (72 sequences, 206 rows), 17.3 / 26 (2.5K shared keys, 16 sequences), 15.9 / 24 (256
     // sequences, 1K keys), 59 / 46 (128 x 32/8 heads, 2K keys, paged, with the cache update: not taken), 74 / 59 (53 x 32/8
     // heads, 12K + 12 x 276 keys, 8-bit: not taken), 222 / 131 (256 x 40 heads, 2K keys: not taken).
-    // 8-bit rows that the vector-ALU kernel would read stay with it unless the caller asks for the single launch: that kernel
-    // keeps fp32 weights, this one rounds them to bf16 (error of O without a shared block 1.3e-7 against 1.1e-3).
-    const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma;
     // (the single launch divides sums by the V scale and multiplies them again: not with scales near the ends of fp32)
     const bool odd_scale = f.fp8 && has_suffix && !(f.v_scale >= 0x1p-60f && f.v_scale <= 0x1p60f);
-    if (c->opt_fused_kernel != 1 && !c->opt_timing && !odd_scale && !(fp32_weights && c->opt_fused_kernel != 2)) {
+    if (c->opt_fused_kernel != 1 && !c->opt_timing && !odd_scale) {
         const int rps = nq * G;
         long long shared_keys = 0;
         double flops = 0.0, shared_bytes = 0.0, shared_stages = 0.0;
@@ -1035,6 +1033,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         sa.pg = has_suffix ? pg : PagedDev{};
         sa.fp8 = has_suffix ? fmt.fp8 : 0;
         sa.k_scale = fmt.k_scale; sa.v_scale = fmt.v_scale;
+        sa.fp32_weights = sa.fp8 && !p.sfx_mfma;
         sa.max_len = max_len;
         sa.B = B; sa.Hq = Hq; sa.Hkv = Hkv; sa.G = G; sa.nq = nq;
         sa.tiles = (B * nq * G + 31) / 32;

@@ -29,11 +29,14 @@
 // heads, 515 keys, ragged up to 150 rows 19.2 -> 13.6; paged and 8-bit caches, which took the separate kernels:
 // 25-50 -> 15-25 us on calls of that size.
 //
-// PAGED: the suffix rows are found through a page table; FP8: they are E4M3 codes with one scale per tensor, expanded
+// PAGED: the suffix rows are found through a page table; CODES: they are E4M3 codes with one scale per tensor, expanded
 // in registers (exactly: every E4M3 value is a bf16 value); the K scale multiplies the scores of those stages, the V
 // scale finished sums: a wavefront whose run goes on from shared rows to codes divides its accumulators by it once and
 // goes on in units of it, and multiplies them by it at its end (on the weights it would be rounded to bf16 with them:
-// one key per sequence, whose weight is 1, came out 1.9e-3 off instead of exact).
+// one key per sequence, whose weight is 1, came out 1.9e-3 off instead of exact).  Rows that the vector-ALU kernel would
+// read with fp32 weights keep that precision (CODES = 2): a weight is taken as the sum of three bf16 values, which hold
+// all 24 bits of it, in three products.  Error of O without a shared block 1.0e-7 (vector-ALU kernel 1.3e-7, one bf16 value
+// per weight 1.1e-3); 5 x 40 heads, 269 keys, 1..37 codes: 11.0 us (10.3 with one value; separate kernels 19.8).
 #include <type_traits>
 
 #include "hg_internal.h"
@@ -91,6 +94,12 @@ __device__ __forceinline__ uintx4 expand8(unsigned lo, unsigned hi) {
     return v;
 }
 
+// elements 8 tt .. 8 tt + 7 of a stage's weights, rounded to bf16
+__device__ __forceinline__ uintx4 pack8(const floatx16& p, int tt) {
+    return uintx4{pack_pair(p[8 * tt], p[8 * tt + 1]), pack_pair(p[8 * tt + 2], p[8 * tt + 3]),
+                  pack_pair(p[8 * tt + 4], p[8 * tt + 5]), pack_pair(p[8 * tt + 6], p[8 * tt + 7])};
+}
+
 // Results that another workgroup of the same launch will read: relaxed stores and loads at agent scope go past the
 // caches that the XCDs do not share, so that nothing has to be flushed before the arrival is counted.
 __device__ __forceinline__ void st_agent(float* p, float a, float b) {
@@ -113,11 +122,14 @@ struct SmallGeo {
 
 }  // namespace
 
-template <int D, bool PAGED, bool FP8>
+// CODES: the suffix rows are bf16 (0), E4M3 codes (1), E4M3 codes whose weights keep fp32 precision (2)
+template <int D, bool PAGED, int CODES>
 __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
+    constexpr bool FP8 = CODES != 0;
     using G_ = SmallGeo<D>;
     constexpr int KS = G_::KS, DB = G_::DB, CPR = G_::CPR, RPI = G_::RPI, CPS = G_::CPS, ROWB = G_::ROWB, STB = G_::STB;
     constexpr int CPR8 = G_::CPR8, RPI8 = G_::RPI8, CPS8 = G_::CPS8;
+    constexpr int NP = CODES == 2 ? 3 : 1;          // bf16 pieces of a code's weight
     unsigned char* const smem_all = fs_smem;
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -462,16 +474,28 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
 #pragma unroll
                 for (int j = 0; j < 16; ++j) Oacc[i][j] *= alpha;
         }
-        uintx4 pb[2];
+        uintx4 pb[NP][2];
 #pragma unroll
-        for (int tt = 0; tt < 2; ++tt) {
-            float p[8];
+        for (int i = 0; i < 16; ++i) {
+            S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], c2, -mc));
+            lsum += S[i];
+        }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                p[i] = __builtin_amdgcn_exp2f(fmaf(S[8 * tt + i], c2, -mc));
-                lsum += p[i];
+        for (int tt = 0; tt < 2; ++tt) pb[0][tt] = pack8(S, tt);
+        if constexpr (NP > 1) {
+            if (codes) {                            // what the first piece left out, and what the second one did (both differences are exact)
+#pragma unroll
+                for (int n = 1; n < NP; ++n)
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            S[8 * tt + 2 * i] -= bf16_lo(pb[n - 1][tt][i]);
+                            S[8 * tt + 2 * i + 1] -= bf16_hi(pb[n - 1][tt][i]);
+                        }
+                        pb[n][tt] = pack8(S, tt);
+                    }
             }
-            pb[tt] = uintx4{pack_pair(p[0], p[1]), pack_pair(p[2], p[3]), pack_pair(p[4], p[5]), pack_pair(p[6], p[7])};
         }
         wait_for(more ? copies_of(ns) : 0);         // this stage's V rows are here, the next K rows may still be on their way
         if (partial) {
@@ -520,7 +544,14 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
                     const shortx4 vhi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)HG_LDS(vp + 8 * ROWB));
                     vv = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vlo, vhi, 0, 1, 2, 3, 4, 5, 6, 7));
                 }
-                Oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, __builtin_bit_cast(bf16x8, pb[tt]), Oacc[db], 0, 0, 0);
+                if constexpr (NP > 1) {
+                    if (codes) {
+#pragma unroll
+                        for (int n = NP - 1; n > 0; --n)
+                            Oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, __builtin_bit_cast(bf16x8, pb[n][tt]), Oacc[db], 0, 0, 0);
+                    }
+                }
+                Oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, __builtin_bit_cast(bf16x8, pb[0][tt]), Oacc[db], 0, 0, 0);
             }
         }
         // the accumulators depend on every fragment read of this stage: once they are pinned here the V slot may be overwritten
@@ -679,7 +710,7 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     }
 }
 
-template <int D, bool PAGED, bool FP8>
+template <int D, bool PAGED, int CODES>
 static hipError_t launch_small_t(const SmallArgs& a, hipStream_t s) {
     constexpr int lds = SmallGeo<D>::LDS;
     static bool attr_set[64] = {};
@@ -687,18 +718,20 @@ static hipError_t launch_small_t(const SmallArgs& a, hipStream_t s) {
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64 && !attr_set[dev]) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_small_kernel<D, PAGED, FP8>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_small_kernel<D, PAGED, CODES>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         attr_set[dev] = true;
     }
-    fused_small_kernel<D, PAGED, FP8><<<(unsigned)(a.cols * a.splits), 64 * NWS, lds, s>>>(a);
+    fused_small_kernel<D, PAGED, CODES><<<(unsigned)(a.cols * a.splits), 64 * NWS, lds, s>>>(a);
     return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_small_d(const SmallArgs& a, hipStream_t s) {
-    if (a.fp8) return a.pg.table ? launch_small_t<D, true, true>(a, s) : launch_small_t<D, false, true>(a, s);
-    return a.pg.table ? launch_small_t<D, true, false>(a, s) : launch_small_t<D, false, false>(a, s);
+    if constexpr (D == 128)      // (at D = 64 the vector-ALU kernel reads all 8-bit rows)
+        if (a.fp8 && !a.fp32_weights) return a.pg.table ? launch_small_t<D, true, 1>(a, s) : launch_small_t<D, false, 1>(a, s);
+    if (a.fp8) return a.pg.table ? launch_small_t<D, true, 2>(a, s) : launch_small_t<D, false, 2>(a, s);
+    return a.pg.table ? launch_small_t<D, true, 0>(a, s) : launch_small_t<D, false, 0>(a, s);
 }
 
 // Workspace floats the splits of a call need: [cols][splits][32][D] results, [cols][splits][32] pairs of (LSE, unused)

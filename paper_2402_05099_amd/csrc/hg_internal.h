@@ -138,6 +138,7 @@ struct SmallArgs {
     PagedDev pg;              // suffix read through a page table when pg.table != null
     int fp8;                  // suffix rows are E4M3 codes: value = code * scale
     float k_scale, v_scale;
+    int fp32_weights;         // the weights of codes are not rounded to bf16
     int max_len;
     int B, Hq, Hkv, G;
     int nq;

@@ -497,13 +497,15 @@ def test_small_fused_call_keeps_the_vector_kernels_precision(heads, paged):
     Hq, Hkv, D = heads
     say(f"fp8 small fused call, vector kernel's precision: {heads} paged={paged}")
     w = wl.make_workload("fp8 small", 51, 6, Hq, Hkv, D, [], 20, 60)
-    ctx = hb.Context(0, hb.hg_workspace_bytes(w.B, Hq, D, 24))
-    ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 0)
-    O, Oref = small_fp8_call(w, paged, ctx)
-    err = np.linalg.norm(O - Oref) / np.linalg.norm(Oref)
-    say(f"   rel-L2 {err:.2e}")
-    assert err <= 2e-5
-    ctx.close()
+    errs = []
+    for kernel in (0, 2, 1):
+        ctx = hb.Context(0, hb.hg_workspace_bytes(w.B, Hq, D, 24))
+        ctx.set_option(hb.HG_OPT_FUSED_KERNEL, kernel)
+        O, Oref = small_fp8_call(w, paged, ctx)
+        errs.append(np.linalg.norm(O - Oref) / np.linalg.norm(Oref))
+        ctx.close()
+    say(f"   rel-L2 automatic {errs[0]:.2e}, single launch {errs[1]:.2e}, separate kernels {errs[2]:.2e}")
+    assert max(errs) <= 2e-5
 
 
 @pytest.mark.parametrize("paged", [False, True], ids=["packed", "paged"])

@@ -165,23 +165,6 @@ def test_fused_plan_names_the_way():
     assert plan([], 4, 1, 4, 4, 128, 10, options={hb.HG_OPT_STAGE_TIMING: 1}) == hb.HG_ERR_INVALID_ARG
 
 
-@pytest.mark.parametrize("page", [0, 16])
-def test_fused_plan_reads_8_bit_rows_with_the_suffix_kernels_arithmetic(page):
-    """The vector-ALU kernel multiplies 8-bit values with fp32 weights: calls whose suffix it reads do not move to a kernel that
-    rounds the weights to bf16, however small they are.  (A caller may still ask for the single launch.)"""
-    rng = np.random.default_rng(3)
-    seen = 0
-    for _ in range(400):
-        Hkv, G, D = int(rng.choice([1, 2, 4, 8])), int(rng.choice([1, 2, 4, 8])), int(rng.choice([64, 128]))
-        B, nq, max_len, P = int(rng.integers(1, 60)), int(rng.choice([1, 1, 2])), int(rng.integers(1, 300)), int(rng.choice([0, 40, 700]))
-        levels = [(1, P, B)] if P else []
-        plan = hb.hg_debug_fused_plan(levels, B, nq, Hkv * G, Hkv, D, max_len, page, True)
-        vector = D == 64 or (nq == 1 and (G == 1 or (G == 2 and max_len < 256)))
-        assert not (vector and plan["way"] == "single"), (B, nq, Hkv, G, D, max_len, P, plan)
-        seen += not vector and plan["way"] == "single"
-    assert seen > 20
-
-
 # small calls on packed rows: (levels, B, nq, Hq, Hkv, D, max_len)
 OWN_MEMORY = [
     ([(1, 128, 4)], 4, 1, 4, 4, 64, 16), ([(1, 515, 45)], 45, 1, 16, 2, 128, 150), ([(1, 1024, 256)], 256, 1, 8, 1, 128, 128),

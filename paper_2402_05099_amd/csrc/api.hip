@@ -799,6 +799,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // heads, 12K + 12 x 276 keys, 8-bit: not taken), 222 / 131 (256 x 40 heads, 2K keys: not taken).
     // (the single launch divides sums by the V scale and multiplies them again: not with scales near the ends of fp32)
     const bool odd_scale = f.fp8 && has_suffix && !(f.v_scale >= 0x1p-60f && f.v_scale <= 0x1p60f);
+    bool take_single = false;
     if (c->opt_fused_kernel != 1 && !c->opt_timing && !odd_scale) {
         const int rps = nq * G;
         long long shared_keys = 0;
@@ -872,8 +873,9 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             p.np = 1;
             return HG_OK;
         }
-        if (any && cols * splits < (1LL << 31) && (c->opt_fused_kernel == 2 || small)) {
-            return HG_OK;
+        if (any && cols * splits < (1LL << 31)) {
+            if (c->opt_fused_kernel == 2) return HG_OK;
+            take_single = small;
         }
     }
 
@@ -967,6 +969,8 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const int tile_rows = (nq * G <= 16 && c->opt_suffix_tile != 32) ? 16 : 32;
         if ((int64_t)B * sp.nchunks * ceil_div(nq * G, tile_rows) * Hkv >= (1LL << 31)) return HG_ERR_UNSUPPORTED;
     }
+    // (up to here also for the single launch: a call is refused for its shape and workspace, not for what the estimates say)
+    if (take_single) return HG_OK;
     p.np = total_parts();
     if (p.np == 0) {
         p.way = kWayFill;

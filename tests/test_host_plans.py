@@ -189,3 +189,21 @@ def test_small_packed_calls_share_no_memory(shape):
     # the caller's explicit single launch is such a call at any size
     big = hb.hg_debug_fused_plan([(1, 9001, 3)], 3, 1, 4, 1, 128, 70, options={hb.HG_OPT_FUSED_KERNEL: 2})
     assert big["way"] == "single" and big["splits"] == 1
+
+
+@pytest.mark.parametrize("page,fp8", [(16, False), (0, True), (32, True), (0, False)], ids=["paged", "fp8", "paged_fp8", "packed"])
+def test_workspace_decides_whether_a_call_is_accepted(page, fp8):
+    """One partial result per shared level and one for the suffix (more where the vector-ALU kernel reads many pages): a call
+    that does not find that room is refused however it would run.  (Small packed calls and an explicit single launch need none.)"""
+    def plan(levels, B, Hq, Hkv, D, max_len, parts, **kw):
+        return hb.hg_debug_fused_plan(levels, B, 1, Hq, Hkv, D, max_len, page, fp8, hb.hg_workspace_bytes(B, Hq, D, parts), **kw)
+
+    shape = ([(1, 9001, 3)], 3, 4, 1, 128, 70) if not (page or fp8) else ([(1, 206, 72)], 72, 32, 8, 128, 40)
+    for parts in (0, 1):
+        assert plan(*shape, parts) == hb.HG_ERR_WORKSPACE
+    assert isinstance(plan(*shape, 2), dict) and plan(*shape, 32)["way"] == "single"
+    assert plan(*shape, 0, options={hb.HG_OPT_FUSED_KERNEL: 2})["way"] == "single"
+    if page:
+        long = ([(1, 60, 2)], 2, 2, 2, 64, 100 * page)      # four items of at most 32 pages each
+        assert plan(*long, 4) == hb.HG_ERR_WORKSPACE
+        assert plan(*long, 5)["way"] in ("single", "one_stream", "two_streams")

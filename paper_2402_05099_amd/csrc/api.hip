@@ -25,7 +25,7 @@ struct hg_ctx {
     int opt_suffix_ipw;    // matrix-core suffix kernel: work items per wavefront (0 automatic)
     int opt_suffix_tile;   // matrix-core suffix kernel: query rows per tile (0 automatic, 16, 32)
     int opt_fused_kernel;  // fused call: 0 automatic, 1 separate kernels, 2 single launch whenever it applies
-    unsigned* arrivals;    // kArrivalCounters device counters, zero between calls (null: none left, calls are not split)
+    unsigned* arrivals;    // kContextCounters device counters, zero between calls (null: none left, calls are not split)
     int arrivals_slot;
     hipStream_t aux;       // second stream for the overlap option
     hipEvent_t ev_fork, ev_join;
@@ -49,7 +49,7 @@ static std::mutex g_scratch_mu;
 // context's last kernel may still be running, so its slot is used again only once all fresh ones are gone and after
 // the device has been waited for; a context that finds no slot works without.
 constexpr int kArrivalSlots = 1024;
-static __device__ unsigned arrival_counters[kArrivalSlots * hg::kArrivalCounters];
+static __device__ unsigned arrival_counters[kArrivalSlots * hg::kContextCounters];
 struct ArrivalPool {
     unsigned* base = nullptr;
     int fresh = 0;                   // slots never handed out start here
@@ -310,8 +310,9 @@ int run_decode(const void* Q, int n_levels, const LevelDev* lv, const void* Ks, 
     return hip_rc(launch_decode(a, D, gt, s));
 }
 
-int run_merge(int n, const Parts& parts, int first, int D, void* O_out, int o_dtype, float* LSE_out, hipStream_t s) {
+int run_merge(int n, const Parts& parts, int first, int D, void* O_out, int o_dtype, float* LSE_out, hipStream_t s, unsigned* clear = nullptr) {
     MergeArgs m{};
+    m.clear = clear;
     m.n = n;
     for (int i = 0; i < n; ++i) {
         m.O[i] = parts.o(first + i);
@@ -418,7 +419,7 @@ unsigned* take_arrivals(int device, int* slot) {
         if (pool->n_ready == 0) return nullptr;
         *slot = pool->ready[--pool->n_ready];
     }
-    return pool->base + (size_t)*slot * kArrivalCounters;
+    return pool->base + (size_t)*slot * kContextCounters;
 }
 
 void give_arrivals(int device, int slot) {
@@ -845,9 +846,9 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             own_memory = c->opt_fused_kernel == 2 || (one <= 130.0 && one <= (one <= 40.0 ? 1.0 : 0.9) * other);
         }
         int& splits = p.splits;
-        if (!own_memory && f.counters && cols * 2 <= 256 && cols <= kArrivalCounters) {
+        if (!own_memory && f.counters && cols * 2 <= kSplitWorkgroups) {
             // (more workgroups than one stage per wavefront asks for only meet later)
-            const int most = (int)std::min<long long>({256 / cols, kSmallMaxSplits, (long long)ceil(stages / 8.0)});
+            const int most = (int)std::min<long long>({kSplitWorkgroups / cols, kSmallMaxSplits, (long long)ceil(stages / 8.0)});
             for (int S = 2; S <= most; ++S)
                 if (chain_at(S) < 0.95 * chain_at(splits) && small_part_floats((int)cols, S, D) * sizeof(float) <= f.ws_bytes) splits = S;
         }
@@ -1044,7 +1045,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         sa.cols = sa.tiles * Hkv;
         sa.splits = p.splits;
         sa.part = reinterpret_cast<float*>(ws.p);
-        sa.arrivals = c->arrivals;
+        sa.arrivals = p.splits > 1 ? c->arrivals + meeting_counter(p.splits) : nullptr;
         sa.scale = scale;
         sa.O = O_out; sa.LSE = LSE_out; sa.bf16 = (o_dtype == HG_BF16);
         return hip_rc(launch_fused_small(sa, D, c->stream));
@@ -1087,7 +1088,11 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         if (sp.mfma) rc = hip_rc(D == 128 ? launch_combined_tiles(ca, s) : launch_combined_tiles_d64(ca, s));
         else rc = hip_rc(D == 128 ? launch_combined_vector(ca, s) : launch_combined_vector_d64(ca, s));
         if (rc) return rc;
-        return run_merge(np, parts, 0, D, O_out, o_dtype, LSE_out, s);
+        // The merge sets the work counter back.  (Set back by the launch itself it could be lost when two calls of a context are
+        // in flight: wrong results for those two, which share the workspace, but also for every later call.)
+        rc = run_merge(np, parts, 0, D, O_out, o_dtype, LSE_out, s, ca.tickets);
+        if (rc) c->arrivals = nullptr;      // nobody will: no further use of the counters
+        return rc;
     }
 
     // one part, no timing events to place: straight to the outputs

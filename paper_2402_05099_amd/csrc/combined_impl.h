@@ -34,8 +34,8 @@ namespace {
 
 typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
 
-// The workgroup's other LDS, behind the ring: the queue, two counters, and the order of the sequences.
-constexpr int kQueueOffset = LDS_RING_BYTES, kDoneOffset = kQueueOffset + 16, kCountsOffset = kQueueOffset + 64;
+// The workgroup's other LDS, behind the ring: the queue, the sequences per length class, and the order of the sequences.
+constexpr int kQueueOffset = LDS_RING_BYTES, kCountsOffset = kQueueOffset + 64;
 constexpr int kOrderOffset = kQueueOffset + 512, kMaxOrdered = (LDS_BYTES - kOrderOffset) / 2 / 1024 * 1024;
 constexpr int kLengthClasses = 8;
 static_assert(offsetof(CombinedArgs, p) == 0 && sizeof(CombinedArgs) <= 4096, "the kernarg segment");
@@ -582,7 +582,6 @@ __global__ __launch_bounds__(64 * NW, 1) void combined_kernel(CombinedArgs c) {
         }
     }
     queue_word* const queue = reinterpret_cast<queue_word*>(smem + kQueueOffset);
-    unsigned* const done = reinterpret_cast<unsigned*>(smem + kDoneOffset);     // wavefronts of this workgroup that are done
     if (threadIdx.x == 0) {
         queue_word first = kQueueEmpty;
         unsigned given;
@@ -593,23 +592,10 @@ __global__ __launch_bounds__(64 * NW, 1) void combined_kernel(CombinedArgs c) {
             first = ((queue_word)stop << 32) | base;
         }
         *queue = first;
-        *done = 0;
     }
     if (c.d.B <= kMaxOrdered) order_by_length(c.d, smem);
     __syncthreads();
     Role::run(c, smem);
-    // no wavefront of this workgroup draws any more once all eight are here: the last workgroup of the launch sets the
-    // counters back to zero for the next call
-    if ((threadIdx.x & 63) == 0) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        if (__hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == NW - 1) {
-            unsigned* const wgs = c.tickets + 32;
-            if (__hip_atomic_fetch_add(wgs, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
-                __hip_atomic_store(c.tickets, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(wgs, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-    }
 }
 
 template <class Role>

@@ -13,8 +13,8 @@
 //
 // A column is worked on by `splits` workgroups (as many as leave the chip full: a small call has few columns, and one
 // workgroup per column would leave most CUs idle).  With more than one, each writes its combined result to the
-// workspace and counts itself in at the column's arrival counter; the last to arrive combines the column's results and
-// sets the counter back to zero for the next call.  No workgroup ever waits for another.
+// workspace and counts itself in at the column's arrival counter; the last to arrive combines the column's
+// results, and the counter wraps to zero for the next call.  No workgroup ever waits for another.
 //
 // A wavefront streams its stages through one K slot and one V slot of 8 KiB of its own (HBM -> LDS copies issued from
 // inline asm, counted s_waitcnt): the next stage's K rows are requested as soon as this stage's scores are done, its V
@@ -645,9 +645,9 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
         wait_vm<0>();                               // this wavefront's results are where every XCD sees them
         __syncthreads();
         if (tid == 0) {
-            const unsigned before = __hip_atomic_fetch_add(a.arrivals + col, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // (the counter wraps to zero by itself and is used with this S only: whatever happens, S arrivals per launch leave it at zero)
+            const unsigned before = atomicInc(a.arrivals + col, (unsigned)(S - 1));
             const int last = before == (unsigned)(S - 1);
-            if (last) __hip_atomic_store(a.arrivals + col, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
             *last_flag = last;
         }
         __syncthreads();

@@ -114,7 +114,7 @@ struct CombinedArgs {
     DecodeArgs d;
     int n_more;                     // further levels, one after another on the same workgroups
     MoreLevel more[kMoreLevels];
-    unsigned* tickets;    // [0]: work counter, [32]: workgroups that are done; both zero between calls
+    unsigned* tickets;    // work counter, zero at the start (the merge that follows sets it back)
     int long_runs;        // tickets that stand for kLongRun work items; the rest stand for tail_run
     int tail_run;
     int n_tickets;
@@ -125,8 +125,17 @@ struct CombinedArgs {
 constexpr int kLongRun = 8, kTailItems = 1024;
 
 // The single-launch fused kernel (fused_small.hip): every level, the suffix and the merge for 32-row tiles of query rows.
-constexpr int kArrivalCounters = 256;         // arrival counters a context owns (one per column of a call that is split)
 constexpr int kSmallMaxSplits = 32;           // workgroups per column at most
+constexpr int kSplitWorkgroups = 256;         // workgroups of a call whose columns are split, at most
+// Device counters of a context: the combined launch's work counter, from kMeetingCounters on those of split columns: one for
+// every number of workgroups per column (S) and column, so that a counter always counts to the same S.
+constexpr int kContextCounters = 1024, kMeetingCounters = 32;
+constexpr int meeting_counter(int S) {        // the first counter for S workgroups per column
+    int at = kMeetingCounters;
+    for (int s = 2; s < S; ++s) at += kSplitWorkgroups / s;
+    return at;
+}
+static_assert(meeting_counter(kSmallMaxSplits + 1) <= kContextCounters, "");
 struct SmallArgs {
     const uint16_t* Q;
     int n_levels;
@@ -146,7 +155,7 @@ struct SmallArgs {
     int cols;                 // tiles * Hkv columns
     int splits;               // workgroups per column
     float* part;              // splits > 1: partial results (small_part_floats)
-    unsigned* arrivals;       // splits > 1: [cols] arrival counters, zero between calls
+    unsigned* arrivals;       // splits > 1: [cols] counters that only ever count to `splits`, zero between calls
     float scale;
     void* O;                  // final results: [B, nq, Hq, D] bf16 or fp32, LSE [B, nq, Hq] (may be null)
     float* LSE;
@@ -160,6 +169,7 @@ struct MergeArgs {
     int64_t rows;
     void* O_out;
     float* L_out;     // may be null
+    unsigned* clear;  // a counter to set to zero, or null
 };
 
 // KV-cache update of a decode step: nq new rows per sequence appended to the suffix cache, lengths advanced.

@@ -14,6 +14,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
     constexpr int LPR = D / 4;
     constexpr int RPB = 256 / LPR;
     constexpr int U = 4;
+    if (a.clear && blockIdx.x == 0 && threadIdx.x == 0) *a.clear = 0u;
     const int64_t row = (int64_t)blockIdx.x * RPB + threadIdx.x / LPR;
     if (row >= a.rows) return;
     const int c = threadIdx.x % LPR;

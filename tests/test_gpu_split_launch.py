@@ -77,3 +77,56 @@ def test_split_launch_long_block(D, cache):
     """One column, a block long enough for the largest number of workgroups per column."""
     print(f"split launch: long block D={D} {cache}", file=sys.stderr, flush=True)
     calls(wl.make_workload("long", 41, 3, 4, 1, D, [(1, 9001, 3)], 1, 70), cache, f"long block D={D} {cache}")
+
+
+def test_one_context_alternates_between_ways_and_splits():
+    """Split single launches with different numbers of workgroups per column, and combined launches, take turns on one context
+    and its counters, some of them captured: every call leaves the counters as the next one needs them."""
+    small = [wl.make_workload("s1", 42, 5, 8, 1, 128, [(1, 6000, 5)], 1, 30), wl.make_workload("s2", 43, 60, 8, 2, 128, [(1, 900, 60)], 1, 30),
+             wl.make_workload("s3", 44, 20, 8, 4, 128, [(1, 400, 20)], 1, 90)]
+    big = wl.make_workload("big", 45, 300, 8, 1, 128, [(1, 200, 300)], 1, 40)
+    work = []
+    splits = set()
+    for w in small + [big]:
+        kv = dev.paged_to_device(wl.make_paged(w, 16))
+        dw = dev.to_device(w)
+        option = 1 if w is big else 2
+        rps = w.nq * w.Hq // w.Hkv
+        plan = hb.hg_debug_fused_plan([(l.Gn, l.max_rows, w.B) for l in w.levels], w.B, 1, w.Hq, w.Hkv, w.D, dw.max_len, 16,
+                                      options={hb.HG_OPT_FUSED_KERNEL: option})
+        assert plan["way"] == ("combined" if w is big else "single"), plan
+        splits.add(plan["splits"])
+        work.append((dw, kv, option, *oracle.attention(w)))
+    assert len(splits) == 4, splits
+    ctx = hb.Context(0, hb.hg_workspace_bytes(300, 8, 128, 32))
+
+    def call(dw, kv, option):
+        O = torch.full(dw.lead + (dw.D,), float("nan"), dtype=torch.float32, device="cuda:0")
+        L = torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0")
+        ctx.set_option(hb.HG_OPT_FUSED_KERNEL, option)
+        hb.hg_hydragen_attn_paged(ctx, dw.Q, dw.levels, kv, dw.lengths, dw.max_len, O, L, dw.scale)
+        return O, L
+
+    first = []
+    for dw, kv, option, Oref, Lref in work:
+        print(f"ways in turn: B={dw.B} option {option}", file=sys.stderr, flush=True)
+        O, L = call(dw, kv, option)
+        torch.cuda.synchronize()
+        check(to_np(O), to_np(L), Oref, Lref, f"B={dw.B}")
+        first.append((O, L))
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        ctx.set_stream(side)
+        captured = [call(dw, kv, option) for dw, kv, option, _, _ in work]
+    ctx.set_stream(None)
+    for turn in range(12):
+        i = (turn * 5 + turn // 3) % 4
+        O, L = call(*work[i][:3])
+        torch.cuda.synchronize()
+        assert torch.equal(O, first[i][0]) and torch.equal(L, first[i][1]), f"turn {turn}"
+        if turn % 4 == 1:
+            graph.replay()
+            torch.cuda.synchronize()
+            for (o, l), (fo, fl) in zip(captured, first):
+                assert torch.equal(o, fo) and torch.equal(l, fl), f"replay at turn {turn}"
+    ctx.close()

@@ -25,8 +25,10 @@ struct hg_ctx {
     int opt_suffix_ipw;    // matrix-core suffix kernel: work items per wavefront (0 automatic)
     int opt_suffix_tile;   // matrix-core suffix kernel: query rows per tile (0 automatic, 16, 32)
     int opt_fused_kernel;  // fused call: 0 automatic, 1 separate kernels, 2 single launch whenever it applies
-    unsigned* arrivals;    // kContextCounters device counters, zero between calls (null: none left, calls are not split)
-    int arrivals_slot;
+    unsigned* counters;    // kContextCounters device counters, zero between calls (null: none left)
+    int counter_slot;      // (-1: none, or not to be given back)
+    bool counters_used, counters_in_graph;
+    hipStream_t counter_stream;      // the stream that used them last
     hipStream_t aux;       // second stream for the overlap option
     hipEvent_t ev_fork, ev_join;
     // stage timing ring: slot = call % HG_TIMING_RING, 2 events (begin, end) per stage
@@ -44,19 +46,21 @@ static __device__ __align__(256) unsigned char scratch[HG_STATIC_SCRATCH_BYTES];
 static unsigned char* g_scratch_ptr[64];   // per device, set by hg_create on that device
 static std::mutex g_scratch_mu;
 
-// Arrival counters of the kernels whose workgroups meet (fused_small.hip): a fixed array in the device image (zero when
-// the library is loaded, and every kernel leaves its counters at zero), handed out to contexts in slots.  A destroyed
-// context's last kernel may still be running, so its slot is used again only once all fresh ones are gone and after
-// the device has been waited for; a context that finds no slot works without.
-constexpr int kArrivalSlots = 1024;
-static __device__ unsigned arrival_counters[kArrivalSlots * hg::kContextCounters];
-struct ArrivalPool {
+// The contexts' device counters (work counter of combined_impl.h, meeting counters of fused_small.hip): a fixed array in the
+// device image (zero when the library is loaded, and every call leaves its counters at zero), handed out to contexts
+// in slots.  A slot is given back with the context, behind an event on the stream that used it last, and is handed
+// out again once that event has happened: nothing ever waits for it.  Slots whose calls were captured stay out, for the
+// graph may be replayed at any time, and so do those whose last use cannot be marked.  A context that finds no slot works
+// without: separate kernels, one workgroup per column.
+constexpr int kCounterSlots = 1024;
+static __device__ unsigned context_counters[kCounterSlots * hg::kContextCounters];
+struct CounterPool {
     unsigned* base = nullptr;
     int fresh = 0;                   // slots never handed out start here
-    int n_ready = 0, n_retired = 0;
-    int ready[kArrivalSlots], retired[kArrivalSlots];
+    int n_back = 0;                  // slots given back, oldest first
+    struct { int slot; hipEvent_t done; } back[kCounterSlots];      // done: null if the slot was never used
 };
-static ArrivalPool* g_arrivals[64];   // per device, guarded by g_scratch_mu
+static CounterPool* g_counters[64];   // per device, guarded by g_scratch_mu
 
 namespace {
 
@@ -396,37 +400,73 @@ int pick_combined_slots(double flops, double bytes, double pieces, int D, bool t
     return 16;
 }
 
-// A context's arrival counters on `device` (current), or null.
-unsigned* take_arrivals(int device, int* slot) {
-    *slot = -1;
-    if (device < 0 || device >= 64) return nullptr;
+// Gives context c its counters on its device (current), if there are any left.
+void take_counters(hg_ctx* c) {
+    c->counters = nullptr;
+    c->counter_slot = -1;
+    if (c->device < 0 || c->device >= 64) return;
     std::lock_guard<std::mutex> lock(g_scratch_mu);
-    ArrivalPool*& pool = g_arrivals[device];
+    CounterPool*& pool = g_counters[c->device];
     if (!pool) {
         void* p = nullptr;
-        if (hipGetSymbolAddress(&p, HIP_SYMBOL(arrival_counters)) != hipSuccess || !p) return nullptr;
-        pool = new (std::nothrow) ArrivalPool();
-        if (!pool) return nullptr;
+        if (hipGetSymbolAddress(&p, HIP_SYMBOL(context_counters)) != hipSuccess || !p) return;
+        pool = new (std::nothrow) CounterPool();
+        if (!pool) return;
         pool->base = static_cast<unsigned*>(p);
     }
-    if (pool->fresh < kArrivalSlots) {
-        *slot = pool->fresh++;
+    if (pool->fresh < kCounterSlots) {
+        c->counter_slot = pool->fresh++;
     } else {
-        if (pool->n_ready == 0 && pool->n_retired > 0 && hipDeviceSynchronize() == hipSuccess) {
-            for (int i = 0; i < pool->n_retired; ++i) pool->ready[pool->n_ready++] = pool->retired[i];
-            pool->n_retired = 0;
+        // (an event query is allowed while some stream of the process is being captured, but not in the strictest mode)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        for (int i = 0; i < pool->n_back && c->counter_slot < 0; ++i) {
+            const hipEvent_t done = pool->back[i].done;
+            if (done) {
+                if (hipEventQuery(done) != hipSuccess) {
+                    (void)hipGetLastError();      // not ready: not an error of anybody's
+                    continue;
+                }
+                (void)hipEventDestroy(done);
+            }
+            c->counter_slot = pool->back[i].slot;
+            --pool->n_back;
+            for (int k = i; k < pool->n_back; ++k) pool->back[k] = pool->back[k + 1];
         }
-        if (pool->n_ready == 0) return nullptr;
-        *slot = pool->ready[--pool->n_ready];
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
-    return pool->base + (size_t)*slot * kContextCounters;
+    if (c->counter_slot >= 0) c->counters = pool->base + (size_t)c->counter_slot * kContextCounters;
 }
 
-void give_arrivals(int device, int slot) {
-    if (slot < 0) return;
+bool is_capturing(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// To be called for every call that uses the counters, before its launch.
+void use_counters(hg_ctx* c) {
+    c->counters_used = true;
+    c->counter_stream = c->stream;
+    if (!c->counters_in_graph && is_capturing(c->stream)) c->counters_in_graph = true;
+}
+
+void give_back_counters(hg_ctx* c) {
+    if (c->counter_slot < 0 || c->counters_in_graph) return;
+    hipEvent_t done = nullptr;
+    if (c->counters_used) {
+        if (!c->ev_fork || is_capturing(c->counter_stream) || hipEventRecord(c->ev_fork, c->counter_stream) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        done = c->ev_fork;
+        c->ev_fork = nullptr;
+    }
     std::lock_guard<std::mutex> lock(g_scratch_mu);
-    ArrivalPool* const pool = g_arrivals[device];
-    pool->retired[pool->n_retired++] = slot;
+    CounterPool* const pool = g_counters[c->device];
+    pool->back[pool->n_back].slot = c->counter_slot;
+    pool->back[pool->n_back++].done = done;
 }
 
 int fill_empty(void* O, int o_dtype, float* LSE, int64_t rows, int D, hipStream_t s) {
@@ -458,7 +498,7 @@ int hg_create(hg_ctx** out, int device, void* hip_stream, void* workspace, size_
     }
     hg_ctx* c = new (std::nothrow) hg_ctx();
     if (!c) return HG_ERR_HIP;
-    c->arrivals_slot = -1;
+    c->counter_slot = -1;
     c->device = device;
     c->stream = static_cast<hipStream_t>(hip_stream);
     c->ws = static_cast<unsigned char*>(workspace);
@@ -481,14 +521,14 @@ int hg_create(hg_ctx** out, int device, void* hip_stream, void* workspace, size_
         hg_destroy(c);
         return HG_ERR_HIP;
     }
-    c->arrivals = take_arrivals(device, &c->arrivals_slot);
+    take_counters(c);
     *out = c;
     return HG_OK;
 }
 
 void hg_destroy(hg_ctx* c) {
     if (!c) return;
-    give_arrivals(c->device, c->arrivals_slot);
+    give_back_counters(c);
     if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
     if (c->ev_join) (void)hipEventDestroy(c->ev_join);
     if (c->aux) (void)hipStreamDestroy(c->aux);
@@ -1018,10 +1058,11 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
 
     FusedPlan p;
     rc = plan_fused(c, FusedShape{n_levels, levels, has_suffix, max_len, pg.table ? pg.shift : -1, fmt.fp8 != 0, fmt.v_scale, LSE_out != nullptr, B, Hq, Hkv, D,
-                                  ws.p ? ws.bytes : 0, c->arrivals != nullptr}, &p);
+                                  ws.p ? ws.bytes : 0, c->counters != nullptr}, &p);
     if (rc) return rc;
     hipStream_t s = c->stream;
     if (p.way == kWayFill) return fill_empty(O_out, o_dtype, LSE_out, rows, D, s);
+    if (p.way == kWayCombined || (p.way == kWaySingle && p.splits > 1)) use_counters(c);
     if (p.way == kWaySingle) {
         SmallArgs sa{};
         sa.Q = static_cast<const uint16_t*>(Q);
@@ -1045,7 +1086,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         sa.cols = sa.tiles * Hkv;
         sa.splits = p.splits;
         sa.part = reinterpret_cast<float*>(ws.p);
-        sa.arrivals = p.splits > 1 ? c->arrivals + meeting_counter(p.splits) : nullptr;
+        sa.arrivals = p.splits > 1 ? c->counters + meeting_counter(p.splits) : nullptr;
         sa.scale = scale;
         sa.O = O_out; sa.LSE = LSE_out; sa.bf16 = (o_dtype == HG_BF16);
         return hip_rc(launch_fused_small(sa, D, c->stream));
@@ -1076,7 +1117,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
             part += ns[i];
         }
         ca.d = suffix_args(Q, Ks, Vs, offsets, lengths, max_len, B, nq, Hq, Hkv, scale, sp.chunk, sp.nchunks, 1, parts_out(parts, part), pg, fmt);
-        ca.tickets = c->arrivals;
+        ca.tickets = c->counters;
         if (sp.mfma) {
             ca.d.tile_rows = (nq * G <= 16 && c->opt_suffix_tile != 32) ? 16 : 32;
             ca.d.units = (int64_t)B * sp.nchunks * ceil_div(nq * G, ca.d.tile_rows) * Hkv;
@@ -1091,7 +1132,10 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         // The merge sets the work counter back.  (Set back by the launch itself it could be lost when two calls of a context are
         // in flight: wrong results for those two, which share the workspace, but also for every later call.)
         rc = run_merge(np, parts, 0, D, O_out, o_dtype, LSE_out, s, ca.tickets);
-        if (rc) c->arrivals = nullptr;      // nobody will: no further use of the counters
+        if (rc) {      // nobody will: no further use of these counters, by whomever
+            c->counters = nullptr;
+            c->counter_slot = -1;
+        }
         return rc;
     }
 

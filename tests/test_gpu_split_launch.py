@@ -2,6 +2,7 @@
 and over every suffix cache: packed, paged, 8-bit, paged 8-bit.  Seeded random trees against the fp64 oracle; every
 call runs twice in a row (the first must leave its arrival counters at zero) with the same bits, with and without room
 for partial results."""
+import ctypes
 import sys
 
 import pytest
@@ -130,3 +131,56 @@ def test_one_context_alternates_between_ways_and_splits():
             for (o, l), (fo, fl) in zip(captured, first):
                 assert torch.equal(o, fo) and torch.equal(l, fl), f"replay at turn {turn}"
     ctx.close()
+
+
+def test_contexts_beyond_the_counter_slots_while_a_stream_is_captured():
+    """Counter slots come back from closed contexts without anybody waiting: more contexts than there are slots are created, used
+    and closed while their calls are in flight, the last ones while a stream is being captured.  Every call has the bits of
+    the first (a context without counters would not split its columns), and so has the graph replayed at the end, long after its
+    context is gone."""
+    print("split launch: 1100 contexts", file=sys.stderr, flush=True)
+    w = wl.make_workload("slots", 46, 5, 8, 1, 128, [(1, 6000, 5)], 1, 30)
+    kv = dev.paged_to_device(wl.make_paged(w, 16))
+    dw = dev.to_device(w)
+    ws = torch.empty(hb.hg_workspace_bytes(5, 8, 128, 32), dtype=torch.uint8, device="cuda:0")
+
+    def call(stream=None):
+        ctx = hb.Context(0, 0, stream=stream)      # (a context per call on one workspace: the calls are ordered on one stream)
+        ctx.close()
+        h = ctypes.c_void_p()
+        hb._check(hb.lib().hg_create(ctypes.byref(h), 0, ctypes.c_void_p(ctx._stream_handle(stream)), hb._p(ws), ws.numel()), "hg_create")
+        ctx.h = h
+        ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 2)
+        O = torch.empty(dw.lead + (dw.D,), dtype=torch.float32, device="cuda:0")
+        L = torch.empty(dw.lead, dtype=torch.float32, device="cuda:0")
+        hb.hg_hydragen_attn_paged(ctx, dw.Q, dw.levels, kv, dw.lengths, dw.max_len, O, L, dw.scale)
+        ctx.close()
+        return O, L
+
+    first = call()
+    torch.cuda.synchronize()
+    check(to_np(first[0]), to_np(first[1]), *oracle.attention(w), "first context")
+    for i in range(1100):
+        O, L = call()
+        if i % 100 == 0:
+            torch.cuda.synchronize()
+            assert torch.equal(O, first[0]) and torch.equal(L, first[1]), f"context {i}"
+    torch.cuda.synchronize()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        for _ in range(1100):
+            hb.Context(0, 0, stream=side).close()
+        captured = [call(side) for _ in range(3)]
+    for i in range(20):
+        O, L = call()
+        torch.cuda.synchronize()
+        assert torch.equal(O, first[0]) and torch.equal(L, first[1]), f"context {i} after the capture"
+        if i % 5 == 0:
+            for o, l in captured:
+                o.fill_(float("nan"))
+                l.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for o, l in captured:
+                assert torch.equal(o, first[0]) and torch.equal(l, first[1]), f"replay {i}"

@@ -785,6 +785,7 @@ struct FusedPlan {
     int main_level, joint;          // the level with the most work (caller's list); combined launch: the level it is launched for
     SuffixPlan sp;
     int np;                         // partial results altogether
+    bool tiny;                      // so little work that the event edges between two streams cost more than overlap can gain
 };
 // What a fused call is asked to do, as far as the host knows it.
 struct FusedShape {
@@ -801,6 +802,106 @@ struct FusedShape {
     bool counters;                  // the context has its device counters
 };
 
+// Parts per level and for the suffix, shrunk to fit the workspace: for the combined launch, or for separate kernels.
+static int plan_parts(const hg_ctx* c, const FusedShape& f, bool combine, FusedPlan& p) {
+    const int n_levels = f.n_levels, max_len = f.max_len, B = f.B, Hq = f.Hq, Hkv = f.Hkv, D = f.D, nq = c->opt_nq, G = Hq / Hkv;
+    const hg_level* const levels = f.levels;
+    const bool has_suffix = f.has_suffix, paged = f.page_shift >= 0, sfx_mfma = p.sfx_mfma;
+    const int cap = parts_cap(f.ws_bytes, (int64_t)B * nq * Hq, D);
+    LevelDev* const lv = p.lv;
+    LevelPlan* const plan = p.plan;
+    int *const ns = p.ns, *const index = p.index;
+    int &nlev = p.nlev, &main_level = p.main_level;
+    nlev = 0;
+    main_level = -1;
+    for (int i = 0; i < n_levels; ++i) {
+        const double seqs = levels[i].kv_off ? levels[i].max_seqs : B;
+        if (main_level < 0 || (double)levels[i].max_rows * levels[i].n_blocks * seqs >
+                                  (double)levels[main_level].max_rows * levels[main_level].n_blocks * (levels[main_level].kv_off ? levels[main_level].max_seqs : B))
+            main_level = i;
+    }
+    // In the combined launch levels of more than 64 query rows run on the persistent kernel as well: it costs no launch of its
+    // own there.  Only the level with the most work may use the plan with a table.
+    const int wide_above = combine ? 64 : kPrefixRowsNarrow;
+    int wide_slots = 32;
+    bool& tiny = p.tiny;
+    tiny = false;
+    if (has_suffix && c->opt_overlap != 1) {
+        double flops = 0.0;
+        int T = 1;
+        double pieces = 0.0, padded = 0.0;     // 256-row tiles of all levels, blocks and KV heads; flops with whole tiles
+        for (int i = 0; i < n_levels; ++i) {
+            const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B;
+            flops += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * seqs * nq * Hq * D;
+            const long long tiles = (seqs * nq * G + kPrefixRowsWide - 1) / kPrefixRowsWide;
+            if (seqs * nq * G > kPrefixRowsNarrow && tiles <= 32 && tiles > T) T = (int)tiles;
+            if (levels[i].max_rows > 0 && seqs * nq * G > wide_above) {
+                pieces += (double)tiles * levels[i].n_blocks * Hkv;
+                padded += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * tiles * kPrefixRowsWide * Hkv * D;
+            }
+        }
+        // K and V, bf16 (or 8-bit codes; on the matrix cores their expansion costs about a third of the saving); the
+        // vector-ALU kernel reads them once per query; mean length taken as 0.75 max_len
+        const double per_elem = f.fp8 ? (sfx_mfma ? 2.6 : 2.0) : 4.0;
+        const double bytes = per_elem * B * (sfx_mfma ? 1 : nq) * (0.75 * max_len) * Hkv * D;
+        wide_slots = pick_wide_slots(flops, bytes, T);
+        tiny = c->opt_overlap == 0 && flops / 1.14e15 + bytes / 6.0e12 < 60e-6;
+        if (tiny) wide_slots = 32;
+        if (combine) wide_slots = pick_combined_slots(padded, 0.8 * bytes, pieces, D, sfx_mfma);     // (here the mean is taken as 0.6 max_len)
+    }
+    for (int i = 0; i < n_levels; ++i) {
+        LevelDev d = to_dev(levels[i], B);
+        if (d.max_rows == 0 || d.max_seqs == 0) continue;  // empty level contributes nothing
+        lv[nlev] = d;
+        index[nlev] = i;
+        plan[nlev] = plan_level(c, d, Hkv, nq * G, D, cap, wide_slots, wide_above, !combine || i == main_level);
+        ns[nlev] = plan[nlev].ns;
+        ++nlev;
+    }
+    const int max_chunk = paged ? 32 << f.page_shift : 1 << 30;
+    SuffixPlan& sp = p.sp;
+    sp = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, max_chunk, f.fp8);
+    // (the combined launch has 2048 wavefronts: items for all of them, equal shares of the longest suffix)
+    if (combine && sp.mfma && c->opt_suffix_chunk == 0) {
+        const long long whole = (long long)B * Hkv * ceil_div(nq * G, 32);
+        const int n = (int)std::min<long long>({(2047 + whole) / whole, 4, std::max(1, max_len / 128)});
+        if (n > sp.nchunks) {
+            sp.chunk = round_up(ceil_div(max_len, n), 32);
+            sp.nchunks = ceil_div(max_len, sp.chunk);
+        }
+    }
+    if (!has_suffix) sp.nchunks = 0;
+    auto total_parts = [&]() { int t = sp.nchunks; for (int i = 0; i < nlev; ++i) t += ns[i]; return t; };
+    if (nlev + (has_suffix ? 1 : 0) > cap) return HG_ERR_WORKSPACE;
+    while (total_parts() > cap) {  // shrink the largest split count first
+        int big = -1, bigv = 1;
+        for (int i = 0; i < nlev; ++i) if (ns[i] > bigv) { bigv = ns[i]; big = i; }
+        if (sp.nchunks > bigv) {
+            sp.nchunks -= 1;
+            sp.chunk = round_up(ceil_div(max_len, sp.nchunks), 32);
+            sp.nchunks = ceil_div(max_len, sp.chunk);
+        } else if (big >= 0) {
+            plan[big] = plan_level(c, lv[big], Hkv, nq * G, D, ns[big] - 1, wide_slots, wide_above, !combine || index[big] == main_level);
+            ns[big] = plan[big].ns;
+        } else {
+            return HG_ERR_WORKSPACE;
+        }
+    }
+    if (has_suffix && !sp.mfma && sp.chunk > max_chunk) return HG_ERR_WORKSPACE;
+    // every size limit of the launches below is checked here, before anything is enqueued
+    for (int i = 0; i < nlev; ++i) {
+        if (plan[i].wide) continue;
+        const int64_t tiles = (int64_t)lv[i].n_blocks * ns[i] * Hkv * ceil_div(lv[i].max_seqs * nq * G, kPrefixRowsNarrow);
+        if (tiles >= (1LL << 28)) return HG_ERR_UNSUPPORTED;
+    }
+    if (has_suffix && sp.mfma) {
+        const int tile_rows = (nq * G <= 16 && c->opt_suffix_tile != 32) ? 16 : 32;
+        if ((int64_t)B * sp.nchunks * ceil_div(nq * G, tile_rows) * Hkv >= (1LL << 31)) return HG_ERR_UNSUPPORTED;
+    }
+    p.np = total_parts();
+    return HG_OK;
+}
+
 static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     FusedPlan& p = *out;
     p.way = kWaySingle;
@@ -810,7 +911,6 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     const int n_levels = f.n_levels, max_len = f.max_len, B = f.B, Hq = f.Hq, Hkv = f.Hkv, D = f.D, nq = c->opt_nq, G = Hq / Hkv;
     const hg_level* const levels = f.levels;
     const bool has_suffix = f.has_suffix, paged = f.page_shift >= 0;
-    const int cap = parts_cap(f.ws_bytes, (int64_t)B * nq * Hq, D);
 
     const bool sfx_mfma = p.sfx_mfma = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8).mfma;
 
@@ -920,121 +1020,36 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         }
     }
 
-    // plan: parts per level and for the suffix, shrunk to fit the workspace
-    LevelDev* const lv = p.lv;
-    LevelPlan* const plan = p.plan;
-    int *const ns = p.ns, *const index = p.index;
-    int &nlev = p.nlev, &main_level = p.main_level;
-    // In the combined launch levels of more than 64 query rows run on the persistent kernel as well, provided that one has more
-    // than 128: it costs no launch of its own there.  Only the level with the most work may use the plan with a table.
-    bool combine = false;
-    for (int i = 0; i < n_levels; ++i) {
-        const double seqs = levels[i].kv_off ? levels[i].max_seqs : B;
-        if (may_combine && levels[i].max_rows > 0 && seqs * nq * G > kPrefixRowsNarrow) combine = true;
-        if (main_level < 0 || (double)levels[i].max_rows * levels[i].n_blocks * seqs >
-                                  (double)levels[main_level].max_rows * levels[main_level].n_blocks * (levels[main_level].kv_off ? levels[main_level].max_seqs : B))
-            main_level = i;
-    }
-    const int combined_above = combine ? 64 : kPrefixRowsNarrow;
-    int wide_slots = 32;
-    bool tiny = false;   // so little work that the event edges between two streams cost more than overlap can gain
-    if (has_suffix && c->opt_overlap != 1) {
-        double flops = 0.0;
-        int T = 1;
-        double pieces = 0.0, padded = 0.0;     // 256-row tiles of all levels, blocks and KV heads; flops with whole tiles
-        for (int i = 0; i < n_levels; ++i) {
-            const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B;
-            flops += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * seqs * nq * Hq * D;
-            const long long tiles = (seqs * nq * G + kPrefixRowsWide - 1) / kPrefixRowsWide;
-            if (seqs * nq * G > kPrefixRowsNarrow && tiles <= 32 && tiles > T) T = (int)tiles;
-            if (levels[i].max_rows > 0 && seqs * nq * G > combined_above) {
-                pieces += (double)tiles * levels[i].n_blocks * Hkv;
-                padded += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * tiles * kPrefixRowsWide * Hkv * D;
+    // The levels on the persistent kernel share the suffix's launch, provided that one has more than 128 query rows; the
+    // others, and more than a few, go before it.
+    if (may_combine && !take_single && c->opt_prefix_kernel != 1) {
+        bool large = false;
+        for (int i = 0; i < n_levels; ++i)
+            large = large || (levels[i].max_rows > 0 && (double)(levels[i].kv_off ? levels[i].max_seqs : B) * nq * G > kPrefixRowsNarrow);
+        if (large && plan_parts(c, f, true, p) == HG_OK && (int64_t)B * nq * G * p.sp.nchunks * Hkv < (1LL << 30)) {
+            for (int i = 0; i < p.nlev; ++i)
+                if (p.plan[i].wide && (p.joint < 0 || p.index[i] == p.main_level)) p.joint = i;
+            if (p.joint >= 0) {
+                p.way = kWayCombined;
+                return HG_OK;
             }
         }
-        // K and V, bf16 (or 8-bit codes; on the matrix cores their expansion costs about a third of the saving); the
-        // vector-ALU kernel reads them once per query; mean length taken as 0.75 max_len
-        const double per_elem = f.fp8 ? (sfx_mfma ? 2.6 : 2.0) : 4.0;
-        const double bytes = per_elem * B * (sfx_mfma ? 1 : nq) * (0.75 * max_len) * Hkv * D;
-        wide_slots = pick_wide_slots(flops, bytes, T);
-        tiny = c->opt_overlap == 0 && flops / 1.14e15 + bytes / 6.0e12 < 60e-6;
-        if (tiny) wide_slots = 32;
-        if (may_combine) wide_slots = pick_combined_slots(padded, 0.8 * bytes, pieces, D, sfx_mfma);     // (here the mean is taken as 0.6 max_len)
     }
-    for (int i = 0; i < n_levels; ++i) {
-        LevelDev d = to_dev(levels[i], B);
-        if (d.max_rows == 0 || d.max_seqs == 0) continue;  // empty level contributes nothing
-        lv[nlev] = d;
-        index[nlev] = i;
-        plan[nlev] = plan_level(c, d, Hkv, nq * G, D, cap, wide_slots, combined_above, i == main_level);
-        ns[nlev] = plan[nlev].ns;
-        ++nlev;
-    }
-    const int max_chunk = paged ? 32 << f.page_shift : 1 << 30;
-    SuffixPlan& sp = p.sp;
-    sp = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, max_chunk, f.fp8);
-    // (the combined launch has 2048 wavefronts: items for all of them, equal shares of the longest suffix)
-    if (may_combine && sp.mfma && c->opt_suffix_chunk == 0) {
-        const long long whole = (long long)B * Hkv * ceil_div(nq * G, 32);
-        const int n = (int)std::min<long long>({(2047 + whole) / whole, 4, std::max(1, max_len / 128)});
-        if (n > sp.nchunks) {
-            sp.chunk = round_up(ceil_div(max_len, n), 32);
-            sp.nchunks = ceil_div(max_len, sp.chunk);
-        }
-    }
-    if (!has_suffix) sp.nchunks = 0;
-    auto total_parts = [&]() { int t = sp.nchunks; for (int i = 0; i < nlev; ++i) t += ns[i]; return t; };
-    if (nlev + (has_suffix ? 1 : 0) > cap) return HG_ERR_WORKSPACE;
-    while (total_parts() > cap) {  // shrink the largest split count first
-        int big = -1, bigv = 1;
-        for (int i = 0; i < nlev; ++i) if (ns[i] > bigv) { bigv = ns[i]; big = i; }
-        if (sp.nchunks > bigv) {
-            sp.nchunks -= 1;
-            sp.chunk = round_up(ceil_div(max_len, sp.nchunks), 32);
-            sp.nchunks = ceil_div(max_len, sp.chunk);
-        } else if (big >= 0) {
-            plan[big] = plan_level(c, lv[big], Hkv, nq * G, D, ns[big] - 1, wide_slots, combined_above, index[big] == main_level);
-            ns[big] = plan[big].ns;
-        } else {
-            return HG_ERR_WORKSPACE;
-        }
-    }
-    if (has_suffix && !sp.mfma && sp.chunk > max_chunk) return HG_ERR_WORKSPACE;
-    // every size limit of the launches below is checked here, before anything is enqueued
-    for (int i = 0; i < nlev; ++i) {
-        if (plan[i].wide) continue;
-        const int64_t tiles = (int64_t)lv[i].n_blocks * ns[i] * Hkv * ceil_div(lv[i].max_seqs * nq * G, kPrefixRowsNarrow);
-        if (tiles >= (1LL << 28)) return HG_ERR_UNSUPPORTED;
-    }
-    if (has_suffix && sp.mfma) {
-        const int tile_rows = (nq * G <= 16 && c->opt_suffix_tile != 32) ? 16 : 32;
-        if ((int64_t)B * sp.nchunks * ceil_div(nq * G, tile_rows) * Hkv >= (1LL << 31)) return HG_ERR_UNSUPPORTED;
-    }
-    // (up to here also for the single launch: a call is refused for its shape and workspace, not for what the estimates say)
+    const int rc = plan_parts(c, f, false, p);
+    if (rc) return rc;
+    // (planned for the single launch too: a call is refused for its shape and workspace, not for what the estimates say)
     if (take_single) return HG_OK;
-    p.np = total_parts();
     if (p.np == 0) {
         p.way = kWayFill;
-        return HG_OK;
-    }
-
-    // The levels on the persistent kernel share the suffix's launch; the others, and more than a few, go before it.
-    int& joint = p.joint;
-    if (combine && (int64_t)B * nq * G * sp.nchunks * Hkv < (1LL << 30)) {
-        for (int i = 0; i < nlev; ++i)
-            if (plan[i].wide && (joint < 0 || index[i] == main_level)) joint = i;
-    }
-    if (joint >= 0) {
-        p.way = kWayCombined;
         return HG_OK;
     }
 
     // Two streams unless asked for one.  In automatic mode a call whose levels all run in the persistent kernel on
     // the whole chip stays on one stream (there is no CU left for the suffix kernel to run beside it), and so does a
     // call with less than about 60 us of work (forking and joining streams costs more than it can gain).
-    bool all_wide_full = nlev > 0;
-    for (int i = 0; i < nlev; ++i) all_wide_full = all_wide_full && plan[i].wide && plan[i].wp.slots == 32;
-    const bool two = c->opt_overlap != 1 && has_suffix && nlev > 0 && !(c->opt_overlap == 0 && (all_wide_full || tiny));
+    bool all_wide_full = p.nlev > 0;
+    for (int i = 0; i < p.nlev; ++i) all_wide_full = all_wide_full && p.plan[i].wide && p.plan[i].wp.slots == 32;
+    const bool two = c->opt_overlap != 1 && has_suffix && p.nlev > 0 && !(c->opt_overlap == 0 && (all_wide_full || p.tiny));
     p.way = two ? kWayTwoStreams : kWayOneStream;
     return HG_OK;
 }

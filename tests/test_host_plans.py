@@ -207,3 +207,22 @@ def test_workspace_decides_whether_a_call_is_accepted(page, fp8):
         long = ([(1, 60, 2)], 2, 2, 2, 64, 100 * page)      # four items of at most 32 pages each
         assert plan(*long, 4) == hb.HG_ERR_WORKSPACE
         assert plan(*long, 5)["way"] in ("single", "one_stream", "two_streams")
+
+
+@pytest.mark.parametrize("options", [{}, {hb.HG_OPT_PREFIX_KERNEL: 1}, {hb.HG_OPT_OVERLAP: 1}, {hb.HG_OPT_OVERLAP: 2}], ids=str)
+@pytest.mark.parametrize("levels", [[], [(1, 4000, 64)], [(1, 900, 64), (16, 30, 4)]], ids=str)
+def test_separate_kernels_are_planned_for_themselves(levels, options):
+    """Work items and CUs chosen for the combined launch apply to it only: a call that runs separate kernels (no level of more than
+    128 query rows, or an option that rules the combined launch out) cuts its suffix as the suffix call does, and one whose
+    options only rule out overlap keeps the whole chip for its shared blocks."""
+    options = {hb.HG_OPT_FUSED_KERNEL: 1, **options}
+    for B, nq, Hq, Hkv, D, max_len in [(64, 1, 16, 8, 128, 512), (64, 2, 8, 8, 128, 1000), (64, 1, 8, 8, 64, 700)]:
+        plan = hb.hg_debug_fused_plan(levels, B, nq, Hq, Hkv, D, max_len, options=options)
+        if hb.HG_OPT_PREFIX_KERNEL in options:
+            assert plan["way"] != "combined" and plan["slots"] == 0
+        elif not levels or (B * nq * Hq // Hkv <= 128):
+            assert plan["way"] in ("one_stream", "two_streams")
+        if plan["way"] == "combined":
+            continue
+        alone = hb.hg_debug_suffix_plan(B, nq, Hq, Hkv, D, max_len)
+        assert (plan["chunk"], plan["nchunks"]) == (alone["chunk"], alone["nchunks"]), (plan, alone)

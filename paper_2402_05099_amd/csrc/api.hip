@@ -914,12 +914,20 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
 
     const bool sfx_mfma = p.sfx_mfma = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8).mfma;
 
+    // One row per KV head on the vector ALU: an item that short is over before the eight wavefronts of a CU have covered its
+    // fixed price (its query, its result, the next item's look-up), where the suffix kernel has twenty.  Combined / separate, us:
+    // 576 x 40 heads, 5766 keys, up to 34 rows 132 / 128; 179 x 40, 11K keys, 23 rows 106 / 98; 286 x 40, 6168 keys, 46 rows
+    // 103 / 125; 8-bit: 832 x 40, D = 64, 71 rows 86 / 72; 1802 x 40, 2268 keys, 36 rows 240 / 216; 130 x 40, 4307 keys, 104
+    // rows 67 / 72.  (46 calls of this kind: 1.062 times as fast as separate kernels if all combine, 1.074 with these bounds.)
+    // A caller that sets the CUs of the shared block has asked for the two side by side.
+    constexpr int kCombineRows = 40, kCombineCodes = 80;
+
     // Shared block and suffix in one launch (combined_impl.h): calls with a level on the persistent kernel and a suffix on the
     // matrix cores or with one query row per KV head.  The stage timings need separate kernels.
     // (8-bit codes in 32-row tiles stay on separate kernels: half the bytes in flight per wavefront do not cover the longer
     // stage; 215 sequences, 64/8 heads, 4 queries: 83 against 76 us.)
     const bool may_combine = c->opt_overlap == 0 && !c->opt_timing && has_suffix && f.counters && !(f.fp8 && (nq * G > 16 || c->opt_suffix_tile == 32)) &&
-                             ((nq == 1 && G == 1) || sfx_mfma);
+                             (sfx_mfma || (nq == 1 && G == 1 && (c->opt_wide_slots > 0 || max_len >= (f.fp8 ? kCombineCodes : kCombineRows))));
 
     // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
     // column of 32 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two

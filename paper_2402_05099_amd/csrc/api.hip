@@ -934,23 +934,27 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // event edges and a round trip of the partial results through HBM for the separate kernels.  Both durations are
     // estimated, in microseconds, from fits to 82 shapes (B = 4 .. 2048, 0 .. 16K shared keys, every cache and head layout):
     //   single launch: 4 + rounds x (4 + c x stages per wavefront), c = 1.6 us per 32-key stage while a quarter of the CUs
-    //                  are busy (the latency of one stage's K and V rows), 2.3 with all of them; 4.5 + 0.3 x splits more when
+    //                  are busy (the latency of one stage's K and V rows), 2.3 with all of them, 1.6 times that for codes with fp32 weights and 32 sequences to a column; 4.5 + 0.3 x splits more when
     //                  a column's workgroups have to meet; never faster than the suffix rows stream in (5 TB/s, 4 on blocks of few rows, 3.3 through a page table)
     //                  and the shared rows, which every column reads for itself, at 8 TB/s once they do not fit the L2;
     //   separate:      10.5 and 0.7 of the suffix time without a shared block; else 18, 6 and 10 more with one and two shared levels, 8 more once a block is long enough to be split,
+    //                  6 less with one row per KV head,
     //                  suffix rows at 5 TB/s, shared blocks at 1.1 PFLOP/s or 5 TB/s; with many suffix rows and one launch for
     //                  both (below) 25, and 0.8 of the suffix time.
     // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single launch is
-    // taken below the other estimate; from 60 us on (45 where the other way is two launches side by side) only when it is 25 %
-    // below (the model of the separate kernels is pessimistic where suffixes and shared blocks overlap).  Measured single /
+    // taken below the other estimate; from 60 us on (45 where the other way is two launches side by side, 35 with
+    // one row per KV head) only when it is 25 % below (the model of the separate kernels is pessimistic where suffixes and shared blocks overlap).  Measured single /
     // other way: 12.4 / 25 us (72 sequences, 206 rows), 17.3 / 26 (2.5K shared keys, 16 sequences), 15.9 / 24 (256
     // sequences, 1K keys), 59 / 46 (128 x 32/8 heads, 2K keys, paged, with the cache update: not taken), 74 / 59 (53 x 32/8
-    // heads, 12K + 12 x 276 keys, 8-bit: not taken), 222 / 131 (256 x 40 heads, 2K keys: not taken).
+    // heads, 12K + 12 x 276 keys, 8-bit: not taken), 222 / 131 (256 x 40 heads, 2K keys: not taken); one row per KV head:
+    // 22 / 18 (37 x 40 heads, 219 keys, 23 codes: not taken), 25 / 19 (30 x 4, 299 keys, 200 codes, paged: not taken), 11 / 20
+    // (5 x 40, 269 keys, 37 codes).
     // (the single launch divides sums by the V scale and multiplies them again: not with scales near the ends of fp32)
     const bool odd_scale = f.fp8 && has_suffix && !(f.v_scale >= 0x1p-60f && f.v_scale <= 0x1p60f);
     bool take_single = false;
     if (c->opt_fused_kernel != 1 && !c->opt_timing && !odd_scale) {
         const int rps = nq * G;
+        const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma, one_row = rps == 1;
         long long shared_keys = 0;
         double flops = 0.0, shared_bytes = 0.0, shared_stages = 0.0;
         bool any = has_suffix, joins = false;      // joins: shared block and suffix would share a launch otherwise
@@ -977,7 +981,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const double per_round = D == 128 ? 256.0 : 512.0;       // workgroups that run at a time (LDS)
         auto chain_at = [&](int S) {
             const double wgs = (double)cols * S;
-            const double per_stage = 1.6 + 0.7 * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0));
+            const double per_stage = (one_row && fp32_weights ? 1.6 : 1.0) * (1.6 + 0.7 * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
             return 4.0 + ceil(wgs / per_round) * (4.0 + per_stage * ceil(stages / (8.0 * S))) + (S > 1 ? 4.5 + 0.3 * S : 0.0);
         };
         // Small calls on packed rows touch nothing but their inputs and outputs: one workgroup per column, no workspace, no
@@ -1009,9 +1013,10 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const double est_single = std::max({chain_at(splits), (paged ? 1.5 : joins ? 1.0 : 1.2) * suffix_us + shared_us + 7.0, restream_us});
         double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
                                     suffix_us + std::max(flops / 1.1e9, shared_us);
+        if (one_row && nonempty > 0) est_separate -= 6.0;
         if (nonempty == 0) est_separate = 10.5 + 0.7 * suffix_us;      // the suffix kernel alone: no event edges, hardly a merge
         if (suffix_us >= 30.0 && joins && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
-        const bool small = est_single <= (est_single <= (joins ? 60.0 : 45.0) ? 1.0 : 0.75) * est_separate;
+        const bool small = est_single <= (est_single <= (one_row ? 35.0 : joins ? 60.0 : 45.0) ? 1.0 : 0.75) * est_separate;
         if (own_memory) {
             // (a suffix alone, in one work item per row, goes from its kernel straight to the outputs: 782 x 4 heads, 21 rows
             // 14 us against 18 for the single launch)

@@ -822,7 +822,8 @@ static int plan_parts(const hg_ctx* c, const FusedShape& f, bool combine, FusedP
     }
     // In the combined launch levels of more than 64 query rows run on the persistent kernel as well: it costs no launch of its
     // own there.  Only the level with the most work may use the plan with a table.
-    const int wide_above = combine ? 64 : kPrefixRowsNarrow;
+    // (A number of splits is asked of the 128-row kernel.)
+    const int wide_above = combine && c->opt_prefix_splits == 0 ? 64 : kPrefixRowsNarrow;
     int wide_slots = 32;
     bool& tiny = p.tiny;
     tiny = false;
@@ -923,10 +924,10 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     constexpr int kCombineRows = 40, kCombineCodes = 80;
 
     // Shared block and suffix in one launch (combined_impl.h): calls with a level on the persistent kernel and a suffix on the
-    // matrix cores or with one query row per KV head.  The stage timings need separate kernels.
+    // matrix cores or with one query row per KV head.  The stage timings need separate kernels, items per wavefront the suffix kernel.
     // (8-bit codes in 32-row tiles stay on separate kernels: half the bytes in flight per wavefront do not cover the longer
     // stage; 215 sequences, 64/8 heads, 4 queries: 83 against 76 us.)
-    const bool may_combine = c->opt_overlap == 0 && !c->opt_timing && has_suffix && f.counters && !(f.fp8 && (nq * G > 16 || c->opt_suffix_tile == 32)) &&
+    const bool may_combine = c->opt_overlap == 0 && c->opt_suffix_ipw == 0 && !c->opt_timing && has_suffix && f.counters && !(f.fp8 && (nq * G > 16 || c->opt_suffix_tile == 32)) &&
                              (sfx_mfma || (nq == 1 && G == 1 && (c->opt_wide_slots > 0 || max_len >= (f.fp8 ? kCombineCodes : kCombineRows))));
 
     // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
@@ -1029,7 +1030,9 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         }
         if (any && cols * splits < (1LL << 31)) {
             if (c->opt_fused_kernel == 2) return HG_OK;
-            take_single = small;
+            // (an option of the separate kernels asks for them)
+            take_single = small && !c->opt_prefix_splits && !c->opt_prefix_kernel && !c->opt_wide_slots && !c->opt_overlap && !c->opt_suffix_kernel &&
+                          !c->opt_suffix_chunk && !c->opt_suffix_ipw && !c->opt_suffix_tile;
         }
     }
 

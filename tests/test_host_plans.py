@@ -244,3 +244,19 @@ def test_small_calls_on_separate_kernels_where_those_are_faster(shape):
     levels, B, H, max_len, page = shape
     assert hb.hg_debug_fused_plan(levels, B, 1, H, H, 128, max_len, page, True)["way"] == "one_stream"
     assert hb.hg_debug_fused_plan([(1, 269, 5)], 5, 1, 40, 40, 128, 37, page, True)["way"] == "single"
+
+
+def test_options_of_the_separate_kernels_ask_for_them():
+    """An option names the kernel it tunes: small calls on paged or 8-bit rows then run that kernel instead of the single launch, items
+    per wavefront and splits of the 128-row kernel are not dropped in the combined launch."""
+    small = lambda **kw: hb.hg_debug_fused_plan([(1, 206, 72)], 72, 1, 32, 8, 128, 40, 16, **kw)
+    assert small()["way"] == "single"
+    for option, value in [(hb.HG_OPT_PREFIX_SPLITS, 2), (hb.HG_OPT_SUFFIX_CHUNK, 32), (hb.HG_OPT_OVERLAP, 1), (hb.HG_OPT_PREFIX_KERNEL, 1),
+                          (hb.HG_OPT_WIDE_SLOTS, 8), (hb.HG_OPT_SUFFIX_KERNEL, 1), (hb.HG_OPT_SUFFIX_ITEMS_PER_WAVE, 3), (hb.HG_OPT_SUFFIX_TILE_ROWS, 32)]:
+        assert small(options={option: value})["way"] != "single", option
+    tree = lambda **kw: hb.hg_debug_fused_plan([(1, 1024, 2048), (16, 512, 128)], 2048, 1, 40, 40, 128, 64, **kw)
+    assert tree()["way"] == "combined" and tree()["wide_levels"] == 3
+    assert tree(options={hb.HG_OPT_PREFIX_SPLITS: 3})["wide_levels"] == 1
+    gqa = lambda **kw: hb.hg_debug_fused_plan([(1, 4096, 512)], 512, 1, 64, 8, 128, 512, **kw)
+    assert gqa()["way"] == "combined"
+    assert gqa(options={hb.HG_OPT_SUFFIX_ITEMS_PER_WAVE: 3})["way"] in ("one_stream", "two_streams")

@@ -1,5 +1,5 @@
 """Shared block and suffix in one launch (combined_impl.h): the calls that take it (a level with more than 128 query rows
-on the persistent kernel) over every suffix cache, at the edges of its batches, chunks, pages and runs of
+on the persistent kernel; the planner's view says which cells those are) over every suffix cache, at the edges of its batches, chunks, pages and runs of
 work items, against the fp64 oracle.  Every call runs twice in a row: the first must leave its work counter at zero."""
 import sys
 
@@ -26,6 +26,7 @@ SHAPES = {
     "four_levels": (300, 1, 128, [(1, 40, 300), (2, 65, 150), (3, 33, 100), (1, 64, 280)], 0, 20),
     "several_blocks": (600, 2, 64, [(3, 90, 200)], 0, 50),
     "many_items": (1300, 10, 128, [(1, 40, 1300)], 1, 24),
+    "many_sequences": (15400, 1, 64, [(1, 33, 15400)], 0, 6),        # more sequences than the table of their order holds
 }
 
 
@@ -41,11 +42,24 @@ TILE_SHAPES = {
     "one_row": (400, 1, 1, 128, 1, [(1, 70, 400)], 0, 390),         # long suffixes with one row per KV head
     "tile_chunks": (70, 8, 2, 128, 1, [(2, 60, 35)], 0, 1100),
     "tile_levels": (200, 8, 2, 128, 1, [(1, 200, 200), (8, 33, 25)], 0, 20),
-    "tile_items": (1100, 8, 4, 128, 1, [(1, 40, 1100)], 1, 24),
+    "tile_items": (1100, 8, 4, 128, 1, [(1, 40, 1100)], 1, 24),     # two rows per KV head and short suffixes: separate kernels
+    "tile_items_g4": (1100, 16, 4, 128, 1, [(1, 40, 1100)], 1, 24),
 }
 
 
-@pytest.mark.parametrize("cache", ["packed", "paged", "fp8", "paged_fp8"])
+def takes_combined_launch(shape, cache, slots):
+    """What the automatic choice makes of a cell: 8-bit rows in 32-row tiles or on the vector ALU with several rows per KV head
+    keep separate kernels, and so do short suffixes of one row per KV head unless the CUs of the shared block are set."""
+    codes = cache in ("fp8", "paged_fp8", "paged_fp8_16")
+    if shape in SHAPES:
+        return slots > 0 or SHAPES[shape][5] >= (80 if codes else 40)
+    B, H, Hkv, D, nq = TILE_SHAPES[shape][:5]
+    if shape == "tile_items":
+        return False
+    return not codes or (D == 128 and nq * H // Hkv <= 16)
+
+
+@pytest.mark.parametrize("cache", ["packed", "paged", "fp8", "paged_fp8", "paged_fp8_16"])
 @pytest.mark.parametrize("shape", [*SHAPES, *TILE_SHAPES])
 def test_combined(shape, cache):
     if shape in SHAPES:
@@ -63,6 +77,10 @@ def test_combined(shape, cache):
     ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 1)       # (not the single launch of small calls)
     for slots in (0, 4, 32):                        # workgroups per XCD that take the shared block first
         ctx.set_option(hb.HG_OPT_WIDE_SLOTS, slots)
+        page = {"paged": 16, "paged_fp8": 32, "paged_fp8_16": 16}.get(cache, 0)
+        plan = hb.hg_debug_fused_plan(levels, B, nq, H, Hkv, D, dw.max_len, page, "fp8" in cache,
+                                      hb.hg_workspace_bytes(B * nq, H, D, 32), {hb.HG_OPT_FUSED_KERNEL: 1, hb.HG_OPT_WIDE_SLOTS: slots})
+        assert (plan["way"] == "combined") == takes_combined_launch(shape, cache, slots), plan
         got = []
         for _ in range(2):
             O = torch.full(dw.lead + (dw.D,), float("nan"), dtype=torch.float32, device="cuda:0")
@@ -75,7 +93,7 @@ def test_combined(shape, cache):
     ctx.close()
 
 
-@pytest.mark.parametrize("shape", ["many_items", "tile_items"])
+@pytest.mark.parametrize("shape", ["many_items", "tile_items", "tile_items_g4"])
 def test_combined_capture(shape):
     """Captured once, replayed with eager calls and other inputs in between: every replay leaves its counters at zero."""
     if shape in SHAPES:
@@ -87,6 +105,9 @@ def test_combined_capture(shape):
     dw = dev.to_device(wl.make_workload(shape, 78, B, H, Hkv, D, levels, lo, hi, nq=nq))
     ctx = dev.make_context(dw, parts=32)
     ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 1)
+    ctx.set_option(hb.HG_OPT_WIDE_SLOTS, 12)
+    way = hb.hg_debug_fused_plan(levels, B, nq, H, Hkv, D, dw.max_len, options={hb.HG_OPT_FUSED_KERNEL: 1, hb.HG_OPT_WIDE_SLOTS: 12})["way"]
+    assert (way == "combined") == takes_combined_launch(shape, "packed", 12)
     O = torch.empty(dw.lead + (dw.D,), dtype=torch.float32, device="cuda:0")
     L = torch.empty(dw.lead, dtype=torch.float32, device="cuda:0")
 

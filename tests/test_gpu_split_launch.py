@@ -1,7 +1,8 @@
-"""The single launch with several workgroups per 32-row column (they meet through arrival counters and the workspace)
-and over every suffix cache: packed, paged, 8-bit, paged 8-bit.  Seeded random trees against the fp64 oracle; every
-call runs twice in a row (the first must leave its arrival counters at zero) with the same bits, with and without room
-for partial results."""
+"""The single launch with several workgroups per 32-row column (they meet through counters and the workspace) and over every
+suffix cache: packed, paged, 8-bit, paged 8-bit.  Seeded random trees against the fp64 oracle; every call runs twice in
+a row (the first must leave its counters at zero) with the same bits, with and without room for partial results.  (Asked
+for by option, packed rows are not split: those cells run one workgroup per column; test_split_launch_of_packed_rows has
+the ones that the automatic choice splits.)"""
 import ctypes
 import sys
 
@@ -37,7 +38,7 @@ def reference(w, cache):
         Ks8, Vs8, off = (torch.from_numpy(x).cuda() for x in (f8.Ks8, f8.Vs8, f8.offsets))
         return O, L, lambda c, dw, o, l: hb.hg_hydragen_attn_fp8(c, dw.Q, dw.levels, Ks8, Vs8, f8.k_scale, f8.v_scale, off, dw.lengths,
                                                                 dw.max_len, o, l, dw.scale)
-    pg, ks, vs = wl.make_paged_fp8(w, 32)
+    pg, ks, vs = wl.make_paged_fp8(w, 16 if cache == "paged_fp8_16" else 32)
     kv = hb.PagedKV(K=torch.from_numpy(pg.K).cuda(), V=torch.from_numpy(pg.V).cuda(), page_table=torch.from_numpy(pg.table).cuda(),
                     page_size=pg.page_size, kv_format=hb.HG_KV_E4M3, k_scale=ks, v_scale=vs)
     return O, L, lambda c, dw, o, l: hb.hg_hydragen_attn_paged(c, dw.Q, dw.levels, kv, dw.lengths, dw.max_len, o, l, dw.scale)
@@ -70,6 +71,30 @@ def test_split_launch_random_trees(seed, cache):
     print(f"split launch: random shape {seed} {cache}: B={w.B} Hq={w.Hq} Hkv={w.Hkv} D={w.D} nq={w.nq} "
           f"levels={[(l.Gn, l.max_rows) for l in w.levels]} max_len={w.max_len}", file=sys.stderr, flush=True)
     calls(w, cache, f"random {seed} {cache}")
+
+
+@pytest.mark.parametrize("shape", [(3, 4, 1, 128, 9001, 70), (3, 4, 1, 64, 9001, 70), (7, 16, 2, 128, 5000, 33), (40, 16, 2, 64, 4100, 1)], ids=str)
+def test_split_launch_of_packed_rows(shape):
+    """Packed rows and a long block: several workgroups per column by the automatic choice."""
+    B, Hq, Hkv, D, P, hi = shape
+    print(f"split launch: packed rows {shape}", file=sys.stderr, flush=True)
+    w = wl.make_workload("packed split", 47, B, Hq, Hkv, D, [(1, P, B)], 1, hi)
+    dw = dev.to_device(w)
+    Oref, Lref, call = reference(w, "packed")
+    plan = hb.hg_debug_fused_plan([(1, P, B)], B, 1, Hq, Hkv, D, dw.max_len, workspace_bytes=hb.hg_workspace_bytes(B, Hq, D, 32))
+    assert plan["way"] == "single" and plan["splits"] > 1, plan
+    ctx = dev.make_context(dw, parts=32)
+    ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 0)
+    got = []
+    for _ in range(2):
+        O = torch.full(dw.lead + (D,), float("nan"), dtype=torch.float32, device="cuda:0")
+        L = torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0")
+        call(ctx, dw, O, L)
+        got.append((O, L))
+    torch.cuda.synchronize()
+    check(to_np(got[0][0]), to_np(got[0][1]), Oref, Lref, f"packed split {shape}")
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    ctx.close()
 
 
 @pytest.mark.parametrize("cache", ["packed", "paged_fp8"])

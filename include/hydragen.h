@@ -53,6 +53,12 @@
  *     library's second stream has been joined back to the context's stream.
  *     No C++ exception crosses this boundary.
  *   - Calls on one context must not overlap in time from several host threads.
+ *   - The calls of a context share its workspace.  Two of them that keep partial results in it must not be in flight
+ *     at the same time, be they enqueued on two streams, replayed from a graph or on two branches of one: such calls
+ *     spoil each other's results (but no later call's).  hg_set_stream does not order anything by itself.  A call whose
+ *     result comes out in one piece uses no workspace and may run beside any other: hg_merge, hg_kv_append*, and
+ *     hg_hydragen_attn on packed bf16 rows with little work (see HG_OPT_FUSED_KERNEL), which also needs none.
+ *   - Calls in flight, and graphs that hold calls, may outlive their context (not the workspace they were given).
  */
 #ifndef HYDRAGEN_H
 #define HYDRAGEN_H
@@ -79,13 +85,14 @@ enum {
     HG_OPT_OVERLAP = 3,       /* fused call: 0 shared blocks and suffix side by side (in one launch where it applies, else on two streams), 1 one kernel after another on one stream, 2 two streams with the shared-block kernels enqueued first */
     HG_OPT_NAIVE_CHUNK = 4,   /* keys per work item of the non-decomposed comparison kernel */
     HG_OPT_STAGE_TIMING = 5,  /* 1: hg_hydragen_attn brackets each of its kernels with timing events */
-    HG_OPT_PREFIX_KERNEL = 6, /* shared-block kernel: 0 automatic (persistent 256-row kernel for blocks with more than 128 query rows, else the 128-row kernel), 1 always 128-row, 2 always 256-row */
-    HG_OPT_WIDE_SLOTS = 7,    /* CUs per XCD (1..32) that the persistent 256-row kernel occupies; 0 = automatic */
+    HG_OPT_PREFIX_KERNEL = 6, /* shared-block kernel: 0 automatic (persistent 256-row kernel for blocks with more than 128 query rows, and for those with more than 64 that share a launch with one; else the 128-row kernel), 1 always 128-row, 2 always 256-row */
+    HG_OPT_WIDE_SLOTS = 7,    /* CUs per XCD (1..32) that the persistent 256-row kernel occupies, with the suffix beside it; 0 = automatic */
     HG_OPT_NUM_QUERIES = 8,   /* queries per sequence, 1..64 (default 1 = decode); see "Several queries per sequence" below */
-    HG_OPT_SUFFIX_ITEMS_PER_WAVE = 10, /* matrix-core suffix kernel: consecutive work items one wavefront takes (1..1024; 0 = automatic) */
+    HG_OPT_SUFFIX_ITEMS_PER_WAVE = 10, /* matrix-core suffix kernel: consecutive work items one wavefront takes (1..1024; 0 = automatic); a fused call then runs that kernel, not a launch shared with the shared blocks */
     HG_OPT_SUFFIX_TILE_ROWS = 11, /* matrix-core suffix kernel: query rows per tile: 0 automatic (16 when a KV head serves at most 16 rows of a sequence, else 32), 16 (honoured under the same condition), 32 */
-    HG_OPT_FUSED_KERNEL = 12, /* hg_hydragen_attn on a packed bf16 suffix cache: 0 automatic (one launch for the whole call when it holds so little work that launches and partial results would dominate, else one kernel per part and a merge), 1 always the separate kernels, 2 the single launch whenever it applies */
-    HG_OPT_SUFFIX_KERNEL = 9  /* suffix kernel: 0 automatic (matrix-core kernel when a KV head serves several query rows of a sequence: two or more queries, three or more query heads, or two heads with max_len >= 256; or when D = 128 and max_len >= 384 whatever the rows; else the vector-ALU kernel), 1 always vector-ALU, 2 always matrix-core; an 8-bit cache with D = 64 is always read by the vector-ALU kernel */
+    HG_OPT_FUSED_KERNEL = 12, /* fused calls: 0 automatic: one launch for the whole call when it holds so little work that launches and partial results would dominate, else shared blocks and suffix in one launch or one kernel per part, and a merge (on paged or 8-bit rows another option set to tune the separate kernels asks for those); 1 never the single launch; 2 the single launch at any size (not with an 8-bit V scale outside [2^-60, 2^60]), without need of a workspace.
+                               * On packed bf16 rows the single launch of a small call, and of any call with 2, touches nothing but the call's inputs and outputs; other small calls use the workspace, which is checked as for the separate kernels, to spread their work */
+    HG_OPT_SUFFIX_KERNEL = 9  /* suffix kernel: 0 automatic (matrix-core kernel when a KV head serves several query rows of a sequence: two or more queries, three or more query heads, or two heads with max_len >= 256; or when D = 128 and max_len >= 384 whatever the rows; else the vector-ALU kernel), 1 always vector-ALU, 2 always matrix-core; an 8-bit cache with D = 64 is read by the vector-ALU kernel (in a small call by the single launch, at the same precision) */
 };
 enum { HG_TIMING_RING = 128, HG_MAX_STAGES = HG_MAX_LEVELS + 2 };
 
@@ -186,8 +193,9 @@ int hg_hydragen_attn(hg_ctx* ctx, const void* Q, int n_levels, const hg_level* l
  * else HG_ERR_STATIC_LIMIT and nothing is enqueued; with room to spare, long key ranges are split as in
  * hg_hydragen_attn.  Devices numbered 64 and above: HG_ERR_UNSUPPORTED.
  * All calls on one GPU share the array, whatever their context or stream: two such calls that overlap in time on one
- * GPU race on it (calls ordered on one stream do not).  Nothing in it needs to start at zero and nothing is kept
- * from call to call: every part a merge reads is written, or marked empty, by that call's own kernels.
+ * GPU race on it (calls ordered on one stream do not; small calls on packed rows do not use it).  Nothing in it needs to
+ * start at zero and nothing is kept from call to call: every part a merge reads is written, or marked empty, by that
+ * call's own kernels.  (The counters by which workgroups meet belong to the context and are zero between calls.)
  */
 int hg_hydragen_attn_static(hg_ctx* ctx, const void* Q, int n_levels, const hg_level* levels,
                             const void* Ks, const void* Vs, const int32_t* offsets, const int32_t* lengths, int max_len,
@@ -257,7 +265,9 @@ int hg_kv_append_paged(hg_ctx* ctx, const void* Knew, const void* Vnew, const hg
  * code * k_scale and a value code * v_scale, with one finite positive fp32 scale per tensor.  Rows are addressed as
  * in hg_suffix_attn (offsets / lengths: DEVICE int32[B]).  Shared levels, Q and the results keep their formats.
  *   hg_suffix_attn_fp8 / hg_hydragen_attn_fp8: hg_suffix_attn / hg_hydragen_attn over such a cache: the attention
- *     of the decoded values (the codes are expanded exactly; all arithmetic is fp32).  Rows that no sequence owns
+ *     of the decoded values.  The codes are expanded exactly, the scales multiply fp32 sums; the softmax weights stay
+ *     fp32 where the vector-ALU kernel is the choice for these rows (in the single launch too) and are rounded to bf16
+ *     where the matrix-core kernel is, as for a bf16 cache.  Rows that no sequence owns
  *     may hold any code.  The suffix kernel is chosen as for a bf16 cache (HG_OPT_SUFFIX_KERNEL).
  *   hg_kv_append_fp8: hg_kv_append with the new bf16 rows quantised on the way in:
  *     code = nearest E4M3 value to (x / scale) (fp32 quotient), ties to the even code, magnitudes above 448 -> 448.

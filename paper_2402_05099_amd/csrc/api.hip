@@ -939,12 +939,12 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     //                  a column's workgroups have to meet; never faster than the suffix rows stream in (5 TB/s, 4 on blocks of few rows, 3.3 through a page table)
     //                  and the shared rows, which every column reads for itself, at 8 TB/s once they do not fit the L2;
     //   separate:      10.5 and 0.7 of the suffix time without a shared block; else 18, 6 and 10 more with one and two shared levels, 8 more once a block is long enough to be split,
-    //                  6 less with one row per KV head,
+    //                  6 less with one row per KV head on the vector ALU,
     //                  suffix rows at 5 TB/s, shared blocks at 1.1 PFLOP/s or 5 TB/s; with many suffix rows and one launch for
     //                  both (below) 25, and 0.8 of the suffix time.
     // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single launch is
     // taken below the other estimate; from 60 us on (45 where the other way is two launches side by side, 35 with
-    // one row per KV head) only when it is 25 % below (the model of the separate kernels is pessimistic where suffixes and shared blocks overlap).  Measured single /
+    // one row per KV head on the vector ALU) only when it is 25 % below (the model of the separate kernels is pessimistic where suffixes and shared blocks overlap).  Measured single /
     // other way: 12.4 / 25 us (72 sequences, 206 rows), 17.3 / 26 (2.5K shared keys, 16 sequences), 15.9 / 24 (256
     // sequences, 1K keys), 59 / 46 (128 x 32/8 heads, 2K keys, paged, with the cache update: not taken), 74 / 59 (53 x 32/8
     // heads, 12K + 12 x 276 keys, 8-bit: not taken), 222 / 131 (256 x 40 heads, 2K keys: not taken); one row per KV head:
@@ -955,7 +955,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     bool take_single = false;
     if (c->opt_fused_kernel != 1 && !c->opt_timing && !odd_scale) {
         const int rps = nq * G;
-        const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma, one_row = rps == 1;
+        const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma, one_row = rps == 1 && !sfx_mfma;
         long long shared_keys = 0;
         double flops = 0.0, shared_bytes = 0.0, shared_stages = 0.0;
         bool any = has_suffix, joins = false;      // joins: shared block and suffix would share a launch otherwise

@@ -244,6 +244,7 @@ def test_small_calls_on_separate_kernels_where_those_are_faster(shape):
     levels, B, H, max_len, page = shape
     assert hb.hg_debug_fused_plan(levels, B, 1, H, H, 128, max_len, page, True)["way"] == "one_stream"
     assert hb.hg_debug_fused_plan([(1, 269, 5)], 5, 1, 40, 40, 128, 37, page, True)["way"] == "single"
+    assert hb.hg_debug_fused_plan([(1, 95, 14)], 14, 1, 4, 4, 128, 539)["way"] == "single"      # (long rows: matrix cores; 23 against 29 us)
 
 
 def test_options_of_the_separate_kernels_ask_for_them():

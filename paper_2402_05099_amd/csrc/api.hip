@@ -933,7 +933,8 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
     // column of 32 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two
     // event edges and a round trip of the partial results through HBM for the separate kernels.  Both durations are
-    // estimated, in microseconds, from fits to 82 shapes (B = 4 .. 2048, 0 .. 16K shared keys, every cache and head layout):
+    // estimated, in microseconds, from fits to some eighty shapes (B = 4 .. 2048, 0 .. 16K shared keys, every cache and head
+    // layout); profiles/fused_ways_sweep.txt has the choice and both sides for 250 calls drawn from those ranges:
     //   single launch: 4 + rounds x (4 + c x stages per wavefront), c = 1.6 us per 32-key stage while a quarter of the CUs
     //                  are busy (the latency of one stage's K and V rows), 2.3 with all of them, 1.6 times that for codes with fp32 weights and 32 sequences to a column; 4.5 + 0.3 x splits more when
     //                  a column's workgroups have to meet; never faster than the suffix rows stream in (5 TB/s, 4 on blocks of few rows, 3.3 through a page table)

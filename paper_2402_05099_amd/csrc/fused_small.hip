@@ -12,7 +12,7 @@
 // results of a workgroup meet in LDS and are combined with the weights exp(LSE_i - max LSE).
 //
 // A column is worked on by `splits` workgroups (as many as leave the chip full: a small call has few columns, and one
-// workgroup per column would leave most CUs idle).  With more than one, each writes its combined result to the
+// workgroup per column would leave most CUs idle; calls that must not share the workspace keep one, see plan_fused).  With more than one, each writes its combined result to the
 // workspace and counts itself in at the column's arrival counter; the last to arrive combines the column's
 // results, and the counter wraps to zero for the next call.  No workgroup ever waits for another.
 //
@@ -22,9 +22,10 @@
 // flight as four wavefronts with two slots for each, and the second wavefront fills the first one's waits.
 // Products, XOR swizzles and lazy rescaling are those of the other kernels (prefix_wide.hip, decode_mfma.hip).
 //
-// What bounds it: latency.  A call of one stage per wavefront takes about 10 us (launch 2, lengths, Q and the key list
-// 3, first rows 2, one stage 1.5, combination and output 1.5), every further stage 1.6 us (2.3 with all CUs busy), the
-// meeting of a column's workgroups 5.  Measured, four wavefronts and one workgroup per column before, this form after:
+// What bounds it: latency.  With one stage per wavefront the kernel takes 6 us (lengths, Q and the key list, the first
+// rows, one stage, combination and output; 4 sequences x 4 heads, 128 keys, by a kernel trace; such a call through Python
+// takes 10 us, all of it on the host), every further stage 1.6 us (2.3 with all CUs busy), the
+// meeting of a column's workgroups 5.  Measured, four wavefronts and one workgroup per column before, eight wavefronts after:
 // 256 sequences x 8 heads on one KV head, 1024 shared keys, 128 suffix rows 23.4 -> 15.9 us; 45 x 16 heads on two KV
 // heads, 515 keys, ragged up to 150 rows 19.2 -> 13.6; paged and 8-bit caches, which took the separate kernels:
 // 25-50 -> 15-25 us on calls of that size.

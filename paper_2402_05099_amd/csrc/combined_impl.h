@@ -538,8 +538,8 @@ struct SuffixTiles {
                 else dm::wait_vm<0>();
                 asm volatile("" ::: "memory");
                 // rows that are nobody's keys may hold anything
-                if (PAGED && key0 + KEYS > it.ke) tile.clear_v_rows(vslot, 0, it.ke - key0);
-                if (k0c != key0) tile.clear_v_rows(vslot, key0 - k0c, KEYS);
+                if (PAGED && key0 + KEYS > it.ke) tile.clear_v_from(vslot, it.ke - key0);
+                if (k0c != key0) tile.clear_v_below(vslot, key0 - k0c);
                 tile.values(vslot, pb);
                 if (!last) issue_v(it, t + 1);
             }

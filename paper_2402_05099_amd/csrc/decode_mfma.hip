@@ -354,8 +354,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
             const int k0c = min(key0, cit.kwin);
             // paged: the rows past the range are a page's unwritten tail (or another page altogether); else the stage rows before
             // its first key were re-read from below the range (another sequence's slot, possibly never written)
-            if (PAGED && key0 + KT > cit.ke) tile.clear_v_rows(vstage, 0, cit.ke - key0);
-            if (k0c != key0) tile.clear_v_rows(vstage, key0 - k0c, KT);
+            if (PAGED && key0 + KT > cit.ke) tile.clear_v_from(vstage, cit.ke - key0);
+            if (k0c != key0) tile.clear_v_below(vstage, key0 - k0c);
             typename Tile::Scores S;
             uintx4 pb[2];
             tile.scores(sb, S);

@@ -336,14 +336,18 @@ struct MfmaTile {
         asm volatile("" ::: "memory");
     }
 
-    // V rows of the stage at vs that are outside [lo, hi) -> 0 (they may hold anything; their weights are zero, but
-    // 0 * NaN is NaN).  Lane l of copy instruction i holds cache row RPIG i + l / CPRG.
-    __device__ __forceinline__ void clear_v_rows(unsigned char* vs, int lo, int hi) const {
+    // V rows below lo / from hi on of the stage at vs -> 0 (they may hold anything; their weights are zero, but 0 * NaN is
+    // NaN).  Lane l of copy instruction i holds cache row RPIG i + l / CPRG.  (Two functions: as one with both bounds it cost
+    // the paged and comparison forms of decode_mfma.hip 11 to 13 spilled scalar registers, and the paged one 2 %.)
+    __device__ __forceinline__ void clear_v_below(unsigned char* vs, int lo) const {
 #pragma unroll
-        for (int i = 0; i < CPSG; ++i) {
-            const int r = i * RPIG + l / CPRG;
-            if (r < lo || r >= hi) *reinterpret_cast<uintx4*>(vs + i * 1024 + l * 16) = uintx4{0u, 0u, 0u, 0u};
-        }
+        for (int i = 0; i < CPSG; ++i)
+            if (i * RPIG + l / CPRG < lo) *reinterpret_cast<uintx4*>(vs + i * 1024 + l * 16) = uintx4{0u, 0u, 0u, 0u};
+    }
+    __device__ __forceinline__ void clear_v_from(unsigned char* vs, int hi) const {
+#pragma unroll
+        for (int i = 0; i < CPSG; ++i)
+            if (i * RPIG + l / CPRG >= hi) *reinterpret_cast<uintx4*>(vs + i * 1024 + l * 16) = uintx4{0u, 0u, 0u, 0u};
     }
 
     // (O, LSE) of this lane's row to part `c`; rv: the row exists; vscale: scale of the values (1 for bf16 rows)

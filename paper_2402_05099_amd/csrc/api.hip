@@ -919,16 +919,17 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // fixed price (its query, its result, the next item's look-up), where the suffix kernel has twenty.  Combined / separate, us:
     // 576 x 40 heads, 5766 keys, up to 34 rows 132 / 128; 179 x 40, 11K keys, 23 rows 106 / 98; 286 x 40, 6168 keys, 46 rows
     // 103 / 125; 8-bit: 832 x 40, D = 64, 71 rows 86 / 72; 1802 x 40, 2268 keys, 36 rows 240 / 216; 130 x 40, 4307 keys, 104
-    // rows 67 / 72.  (46 calls of this kind: 1.062 times as fast as separate kernels if all combine, 1.074 with these bounds.)
-    // A caller that sets the CUs of the shared block has asked for the two side by side.
-    constexpr int kCombineRows = 40, kCombineCodes = 80;
+    // rows 67 / 72.  A caller that sets the CUs of the shared block has asked for the two side by side.
+    const int combine_rows = !f.fp8 ? 24 : D == 128 ? 48 : 80;
 
     // Shared block and suffix in one launch (combined_impl.h): calls with a level on the persistent kernel and a suffix on the
     // matrix cores or with one query row per KV head.  The stage timings need separate kernels, items per wavefront the suffix kernel.
     // (8-bit codes in 32-row tiles stay on separate kernels: half the bytes in flight per wavefront do not cover the longer
     // stage; 215 sequences, 64/8 heads, 4 queries: 83 against 76 us.)
-    const bool may_combine = c->opt_overlap == 0 && c->opt_suffix_ipw == 0 && !c->opt_timing && has_suffix && f.counters && !(f.fp8 && (nq * G > 16 || c->opt_suffix_tile == 32)) &&
-                             (sfx_mfma || (nq == 1 && G == 1 && (c->opt_wide_slots > 0 || max_len >= (f.fp8 ? kCombineCodes : kCombineRows))));
+    const bool long_enough = sfx_mfma || c->opt_wide_slots > 0 || max_len >= combine_rows;
+    const bool may_join = c->opt_overlap == 0 && c->opt_suffix_ipw == 0 && !c->opt_timing && has_suffix && f.counters && !(f.fp8 && (nq * G > 16 || c->opt_suffix_tile == 32)) &&
+                          (sfx_mfma || (nq == 1 && G == 1));
+    const bool may_combine = may_join && long_enough;
 
     // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
     // column of 32 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two
@@ -936,21 +937,22 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // estimated, in microseconds, from fits to some eighty shapes (B = 4 .. 2048, 0 .. 16K shared keys, every cache and head
     // layout); profiles/fused_ways_sweep.txt has the choice and both sides for 250 calls drawn from those ranges:
     //   single launch: 4 + rounds x (4 + c x stages per wavefront), c = 1.6 us per 32-key stage while a quarter of the CUs
-    //                  are busy (the latency of one stage's K and V rows), 2.3 with all of them, 1.6 times that for codes with fp32 weights and 32 sequences to a column; 4.5 + 0.3 x splits more when
+    //                  are busy (the latency of one stage's K and V rows), 2.3 with all of them, 1.6 times that for 8-bit rows of D = 128 with fp32 weights and 24 or more sequences to a column; 4.5 + 0.3 x splits more when
     //                  a column's workgroups have to meet; never faster than the suffix rows stream in (5 TB/s, 4 on blocks of few rows, 3.3 through a page table)
     //                  and the shared rows, which every column reads for itself, at 8 TB/s once they do not fit the L2;
     //   separate:      10.5 and 0.7 of the suffix time without a shared block; else 18, 6 and 10 more with one and two shared levels, 8 more once a block is long enough to be split,
-    //                  6 less with one row per KV head on the vector ALU,
+    //                  6 less for those 8-bit rows where no block has rows for the persistent kernel,
     //                  suffix rows at 5 TB/s, shared blocks at 1.1 PFLOP/s or 5 TB/s; with many suffix rows and one launch for
     //                  both (below) 25, and 0.8 of the suffix time.
     // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single launch is
-    // taken below the other estimate; from 60 us on (45 where the other way is two launches side by side, 35 with
-    // one row per KV head on the vector ALU) only when it is 25 % below (the model of the separate kernels is pessimistic where suffixes and shared blocks overlap).  Measured single /
+    // taken below the other estimate; from 60 us on (45 where the other way is two launches side by side, unless the suffix is one
+    // row per KV head on the vector ALU; 35 for those 8-bit rows) only when it is 25 % below (the model of the separate kernels is
+    // pessimistic where suffixes and shared blocks overlap).  Measured single /
     // other way: 12.4 / 25 us (72 sequences, 206 rows), 17.3 / 26 (2.5K shared keys, 16 sequences), 15.9 / 24 (256
     // sequences, 1K keys), 59 / 46 (128 x 32/8 heads, 2K keys, paged, with the cache update: not taken), 74 / 59 (53 x 32/8
     // heads, 12K + 12 x 276 keys, 8-bit: not taken), 222 / 131 (256 x 40 heads, 2K keys: not taken); one row per KV head:
     // 22 / 18 (37 x 40 heads, 219 keys, 23 codes: not taken), 25 / 19 (30 x 4, 299 keys, 200 codes, paged: not taken), 11 / 20
-    // (5 x 40, 269 keys, 37 codes).
+    // (5 x 40, 269 keys, 37 codes), 17 / 25 (9 x 4, 583 keys, 350 codes, paged), 21 / 31 (171 x 40, D = 64, 660 keys, 32 codes).
     // (the single launch divides sums by the V scale and multiplies them again: not with scales near the ends of fp32)
     const bool odd_scale = f.fp8 && has_suffix && !(f.v_scale >= 0x1p-60f && f.v_scale <= 0x1p60f);
     bool take_single = false;
@@ -959,7 +961,8 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma, one_row = rps == 1 && !sfx_mfma;
         long long shared_keys = 0;
         double flops = 0.0, shared_bytes = 0.0, shared_stages = 0.0;
-        bool any = has_suffix, joins = false;      // joins: shared block and suffix would share a launch otherwise
+        // wide: a level runs on the persistent kernel otherwise; joins: and shares its launch with the suffix, or could if that were longer
+        bool any = has_suffix, wide = false;
         int nonempty = 0;
         for (int i = 0; i < n_levels; ++i) {
             const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B;
@@ -971,19 +974,22 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
                 flops += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * seqs * nq * Hq * D;
                 shared_bytes += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * Hkv * D;
                 any = true;
-                joins = joins || (may_combine && seqs * rps > kPrefixRowsNarrow);
+                wide = wide || seqs * rps > kPrefixRowsNarrow;
                 ++nonempty;
             }
         }
+        const bool joins = may_join && wide;
         const int seqs_per_tile = rps >= 32 ? 1 : (32 + rps - 1) / rps + (32 % rps ? 1 : 0);
         const long long seqs_here = seqs_per_tile < B ? seqs_per_tile : B;
+        // the separate kernels at their lightest, the single launch at its slowest: full columns of codes with fp32 weights
+        const bool light = one_row && fp32_weights && D == 128 && !wide && seqs_here >= 24;
         const double stages = shared_stages + (has_suffix ? seqs_here * ((0.75 * max_len + 16.0) / 32.0) : 0.0);
         const long long tiles = ((long long)B * rps + 31) / 32;
         const long long cols = tiles * Hkv;
         const double per_round = D == 128 ? 256.0 : 512.0;       // workgroups that run at a time (LDS)
         auto chain_at = [&](int S) {
             const double wgs = (double)cols * S;
-            const double per_stage = (one_row && fp32_weights ? 1.6 : 1.0) * (1.6 + 0.7 * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
+            const double per_stage = (light ? 1.6 : 1.0) * (1.6 + 0.7 * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
             return 4.0 + ceil(wgs / per_round) * (4.0 + per_stage * ceil(stages / (8.0 * S))) + (S > 1 ? 4.5 + 0.3 * S : 0.0);
         };
         // Small calls on packed rows touch nothing but their inputs and outputs: one workgroup per column, no workspace, no
@@ -1015,10 +1021,10 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const double est_single = std::max({chain_at(splits), (paged ? 1.5 : joins ? 1.0 : 1.2) * suffix_us + shared_us + 7.0, restream_us});
         double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
                                     suffix_us + std::max(flops / 1.1e9, shared_us);
-        if (one_row && nonempty > 0) est_separate -= 6.0;
+        if (light && nonempty > 0) est_separate -= 6.0;
         if (nonempty == 0) est_separate = 10.5 + 0.7 * suffix_us;      // the suffix kernel alone: no event edges, hardly a merge
         if (suffix_us >= 30.0 && joins && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
-        const bool small = est_single <= (est_single <= (one_row ? 35.0 : joins ? 60.0 : 45.0) ? 1.0 : 0.75) * est_separate;
+        const bool small = est_single <= (est_single <= (light ? 35.0 : joins || (one_row && has_suffix) ? 60.0 : 45.0) ? 1.0 : 0.75) * est_separate;
         if (own_memory) {
             // (a suffix alone, in one work item per row, goes from its kernel straight to the outputs: 782 x 4 heads, 21 rows
             // 14 us against 18 for the single launch)

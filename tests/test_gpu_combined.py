@@ -52,7 +52,7 @@ def takes_combined_launch(shape, cache, slots):
     keep separate kernels, and so do short suffixes of one row per KV head unless the CUs of the shared block are set."""
     codes = cache in ("fp8", "paged_fp8", "paged_fp8_16")
     if shape in SHAPES:
-        return slots > 0 or SHAPES[shape][5] >= (80 if codes else 40)
+        return slots > 0 or SHAPES[shape][5] >= (24 if not codes else 48 if SHAPES[shape][3] == 128 else 80)
     B, H, Hkv, D, nq = TILE_SHAPES[shape][:5]
     if shape == "tile_items":
         return False

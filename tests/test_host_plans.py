@@ -228,7 +228,7 @@ def test_separate_kernels_are_planned_for_themselves(levels, options):
         assert (plan["chunk"], plan["nchunks"]) == (alone["chunk"], alone["nchunks"]), (plan, alone)
 
 
-@pytest.mark.parametrize("shape", [([(1, 5766, 576)], 576, 128, 34, False), ([(1, 3028, 867)], 867, 64, 16, False), ([(1, 11315, 179), (15, 91, 12)], 179, 128, 23, False),
+@pytest.mark.parametrize("shape", [([(1, 5766, 576)], 576, 128, 23, False), ([(1, 3028, 867)], 867, 64, 16, False), ([(1, 11315, 179), (15, 91, 12)], 179, 128, 23, False),
                                    ([(1, 190, 965)], 965, 64, 29, True), ([(1, 79, 832)], 832, 64, 71, True), ([(1, 2268, 1802)], 1802, 128, 36, True)], ids=str)
 def test_short_suffixes_of_one_row_do_not_join_the_shared_block(shape):
     """One query row per KV head and few rows: separate kernels (the combined launch took 3 to 24 % longer on these)."""
@@ -245,6 +245,14 @@ def test_small_calls_on_separate_kernels_where_those_are_faster(shape):
     assert hb.hg_debug_fused_plan(levels, B, 1, H, H, 128, max_len, page, True)["way"] == "one_stream"
     assert hb.hg_debug_fused_plan([(1, 269, 5)], 5, 1, 40, 40, 128, 37, page, True)["way"] == "single"
     assert hb.hg_debug_fused_plan([(1, 95, 14)], 14, 1, 4, 4, 128, 539)["way"] == "single"      # (long rows: matrix cores; 23 against 29 us)
+
+
+@pytest.mark.parametrize("shape", [([(1, 76, 1880)], 1880, 4, 128, 29, 16), ([(1, 156, 155)], 155, 40, 128, 41, 0), ([(1, 6705, 323)], 323, 4, 64, 45, 16),
+                                   ([(1, 660, 171)], 171, 40, 64, 32, 0), ([(1, 1697, 733)], 733, 4, 64, 73, 0), ([(1, 9424, 330)], 330, 4, 64, 93, 0), ([(1, 583, 9)], 9, 4, 128, 350, 16)], ids=str)
+def test_small_calls_in_one_launch_where_that_is_faster(shape):
+    """8-bit rows, one query row per KV head, a shared block for the persistent kernel, D = 64 or few sequences: 20 to 60 % faster in the single launch."""
+    levels, B, H, D, max_len, page = shape
+    assert hb.hg_debug_fused_plan(levels, B, 1, H, H, D, max_len, page, True)["way"] == "single"
 
 
 def test_options_of_the_separate_kernels_ask_for_them():

@@ -917,9 +917,11 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
 
     // One row per KV head on the vector ALU: an item that short is over before the eight wavefronts of a CU have covered its
     // fixed price (its query, its result, the next item's look-up), where the suffix kernel has twenty.  Combined / separate, us:
-    // 576 x 40 heads, 5766 keys, up to 34 rows 132 / 128; 179 x 40, 11K keys, 23 rows 106 / 98; 286 x 40, 6168 keys, 46 rows
-    // 103 / 125; 8-bit: 832 x 40, D = 64, 71 rows 86 / 72; 1802 x 40, 2268 keys, 36 rows 240 / 216; 130 x 40, 4307 keys, 104
-    // rows 67 / 72.  A caller that sets the CUs of the shared block has asked for the two side by side.
+    // 179 x 40 heads, 11K keys, 23 rows 106 / 98; 1554 x 40, D = 64, 4521 keys, 29 rows 188 / 210; 286 x 40, 6168 keys, 46 rows
+    // 103 / 125; 8-bit: 832 x 40, D = 64, 71 rows 86 / 72; 1802 x 40, 2268 keys, 36 rows 240 / 216; 130 x 40, 4307 keys, 104 rows
+    // 67 / 72.  Over some 120 drawn calls, separate / combined in the mean: packed bf16 0.94 (D = 64) and 1.02 at 16 to 23 rows, 1.04 and
+    // 1.07 from 24 on; codes 0.80 below 24 rows, 0.93 at 40 to 47, level from 48 on; at D = 64 0.85 to 0.97 up to 79.
+    // A caller that sets the CUs of the shared block has asked for the two side by side.
     const int combine_rows = !f.fp8 ? 24 : D == 128 ? 48 : 80;
 
     // Shared block and suffix in one launch (combined_impl.h): calls with a level on the persistent kernel and a suffix on the

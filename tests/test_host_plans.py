@@ -231,7 +231,7 @@ def test_separate_kernels_are_planned_for_themselves(levels, options):
 @pytest.mark.parametrize("shape", [([(1, 5766, 576)], 576, 128, 23, False), ([(1, 3028, 867)], 867, 64, 16, False), ([(1, 11315, 179), (15, 91, 12)], 179, 128, 23, False),
                                    ([(1, 190, 965)], 965, 64, 29, True), ([(1, 79, 832)], 832, 64, 71, True), ([(1, 2268, 1802)], 1802, 128, 36, True)], ids=str)
 def test_short_suffixes_of_one_row_do_not_join_the_shared_block(shape):
-    """One query row per KV head and few rows: separate kernels (the combined launch took 3 to 24 % longer on these)."""
+    """One query row per KV head and few rows: separate kernels (the combined launch took up to 24 % longer on calls like these)."""
     levels, B, D, max_len, fp8 = shape
     assert hb.hg_debug_fused_plan(levels, B, 1, 40, 40, D, max_len, 0, fp8)["way"] in ("one_stream", "two_streams")
     assert hb.hg_debug_fused_plan(levels, B, 1, 40, 40, D, 300, 0, fp8)["way"] == "combined"

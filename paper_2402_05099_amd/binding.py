@@ -1,4 +1,6 @@
-"""Thin ctypes binding of libhydragen.so: same names as include/hydragen.h, argument marshalling only.
+"""Thin ctypes binding of libhydragen.so: same names as include/hydragen.h, argument marshalling only.  The calls of a decode step
+(fused attention, cache update) are marshalled by a native extension (csrc/marshal.cpp); what it does not take comes
+back here, to the same checks in Python.
 
 PyTorch is used for device memory and streams; every step of the attention path runs in the HIP kernels of
 the shared library.  There is no fallback: if the library is missing or fails to load, importing the symbols
@@ -7,6 +9,7 @@ works but the first call raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from dataclasses import dataclass
 from typing import List, Optional, Sequence
@@ -134,6 +137,28 @@ def lib() -> ctypes.CDLL:
         L.hg_strerror.restype = ctypes.c_char_p
         _lib = L
     return _lib
+
+
+# The native marshalling of the decode-step calls: what each returns is the library's code, or None for arguments that it
+# leaves to the checks below.
+_native = None
+
+
+def native():
+    """Load _marshal.so (built with the library) and hand it the library's functions; raises if it is not there."""
+    global _native
+    if _native is None:
+        path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal.so")
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is missing: build it with `python -m paper_2402_05099_amd.build`")
+        L = lib()
+        spec = importlib.util.spec_from_file_location("_marshal", path)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        fns = (L.hg_hydragen_attn, L.hg_hydragen_attn_fp8, L.hg_hydragen_attn_paged, L.hg_kv_append, L.hg_kv_append_fp8, L.hg_kv_append_paged)
+        m.setup([ctypes.cast(f, ctypes.c_void_p).value for f in fns], Level, PagedKV)
+        _native = m
+    return _native
 
 
 def strerror(code: int) -> str:
@@ -342,6 +367,11 @@ def _fused(fn, name, ctx, Q, levels: List[Level], Ks, Vs, offsets, lengths, max_
 
 def hg_hydragen_attn(ctx: Context, Q, levels: List[Level], Ks, Vs, offsets, lengths, max_len: int, O_out, LSE_out=None,
                      scale: float = 0.0) -> None:
+    rc = (_native or native()).attn(ctx, Q, levels, Ks, Vs, offsets, lengths, max_len, O_out, LSE_out, scale)
+    if rc is not None:
+        if rc:
+            _check(rc, "hg_hydragen_attn")
+        return
     _fused(lib().hg_hydragen_attn, "hg_hydragen_attn", ctx, Q, levels, Ks, Vs, offsets, lengths, max_len, O_out, LSE_out, scale)
 
 
@@ -377,6 +407,11 @@ def hg_suffix_attn_paged(ctx: Context, Q, kv: PagedKV, lengths, max_len: int, O,
 
 def hg_hydragen_attn_paged(ctx: Context, Q, levels: List[Level], kv: PagedKV, lengths, max_len: int, O_out, LSE_out=None,
                            scale: float = 0.0) -> None:
+    rc = (_native or native()).attn_paged(ctx, Q, levels, kv, lengths, max_len, O_out, LSE_out, scale)
+    if rc is not None:
+        if rc:
+            _check(rc, "hg_hydragen_attn_paged")
+        return
     B, Hq, D, lead = _qshape(ctx, Q)
     Hkv = _want_paged(kv, B, D)
     _want(Q, torch.bfloat16, name="Q"); _want(lengths, torch.int32, (B,), "lengths")
@@ -400,6 +435,11 @@ def _new_rows(ctx: Context, Knew, Vnew):
 
 
 def hg_kv_append(ctx: Context, Knew, Vnew, Ks, Vs, offsets, lengths, capacity: int) -> None:
+    rc = (_native or native()).append(ctx, Knew, Vnew, Ks, Vs, offsets, lengths, capacity)
+    if rc is not None:
+        if rc:
+            _check(rc, "hg_kv_append")
+        return
     B, Hkv, D = _new_rows(ctx, Knew, Vnew)
     _want(Ks, torch.bfloat16, name="Ks"); _want(Vs, torch.bfloat16, Ks.shape, "Vs")
     if tuple(Ks.shape[1:]) != (Hkv, D):
@@ -429,6 +469,11 @@ def hg_suffix_attn_fp8(ctx: Context, Q, Ks8, Vs8, k_scale: float, v_scale: float
 
 def hg_hydragen_attn_fp8(ctx: Context, Q, levels: List[Level], Ks8, Vs8, k_scale: float, v_scale: float, offsets, lengths,
                          max_len: int, O_out, LSE_out=None, scale: float = 0.0) -> None:
+    rc = (_native or native()).attn_fp8(ctx, Q, levels, Ks8, Vs8, k_scale, v_scale, offsets, lengths, max_len, O_out, LSE_out, scale)
+    if rc is not None:
+        if rc:
+            _check(rc, "hg_hydragen_attn_fp8")
+        return
     B, Hq, D, lead = _qshape(ctx, Q)
     _want(Q, torch.bfloat16, name="Q")
     _want_fp8(Ks8, Vs8)
@@ -447,6 +492,11 @@ def hg_hydragen_attn_fp8(ctx: Context, Q, levels: List[Level], Ks8, Vs8, k_scale
 
 
 def hg_kv_append_fp8(ctx: Context, Knew, Vnew, Ks8, Vs8, k_scale: float, v_scale: float, offsets, lengths, capacity: int) -> None:
+    rc = (_native or native()).append_fp8(ctx, Knew, Vnew, Ks8, Vs8, k_scale, v_scale, offsets, lengths, capacity)
+    if rc is not None:
+        if rc:
+            _check(rc, "hg_kv_append_fp8")
+        return
     B, Hkv, D = _new_rows(ctx, Knew, Vnew)
     _want_fp8(Ks8, Vs8, Hkv, D)
     _want(offsets, torch.int32, (B,), "offsets"); _want(lengths, torch.int32, (B,), "lengths")
@@ -455,6 +505,11 @@ def hg_kv_append_fp8(ctx: Context, Knew, Vnew, Ks8, Vs8, k_scale: float, v_scale
 
 
 def hg_kv_append_paged(ctx: Context, Knew, Vnew, kv: PagedKV, lengths, capacity: int) -> None:
+    rc = (_native or native()).append_paged(ctx, Knew, Vnew, kv, lengths, capacity)
+    if rc is not None:
+        if rc:
+            _check(rc, "hg_kv_append_paged")
+        return
     B, Hkv, D = _new_rows(ctx, Knew, Vnew)
     if _want_paged(kv, B, D) != Hkv:
         raise ValueError("paged K must be [n_pages * page_size, Hkv, D]")

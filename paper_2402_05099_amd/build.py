@@ -1,4 +1,5 @@
-"""Builds libhydragen.so (HIP, gfx950 only) in-tree with hipcc.  `python -m paper_2402_05099_amd.build`."""
+"""Builds libhydragen.so (HIP, gfx950 only) in-tree with hipcc, and the extension that marshals arguments for it (_marshal.so,
+host code) with g++.  `python -m paper_2402_05099_amd.build`."""
 from __future__ import annotations
 
 import os
@@ -9,6 +10,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libhydragen.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 SOURCES = ["api.hip", "prefix.hip", "prefix_wide.hip", "prefix_wide_d64.hip", "combined_tiles.hip", "combined.hip", "combined_d64.hip", "combined_tiles_d64.hip", "decode.hip", "merge.hip", "kvcache.hip", "decode_mfma.hip", "fused_small.hip", "ceilings.hip"]
 
 # packed fp32 VALU forms are switched off for every device compile of this library
@@ -29,6 +31,21 @@ def hipcc() -> str:
 PER_SOURCE_FLAGS = {}   # source file name -> extra hipcc flags
 
 
+def marshal_command(out: str):
+    """The compiler's command line for the marshalling extension (it uses PyTorch's tensor class, so its headers and ABI)."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for d in [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", d]
+    cmd += ["-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "marshal.cpp"), "-o", out]
+    for d in cpp_extension.library_paths():
+        cmd += ["-L", d]
+    return cmd + ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def build(verbose: bool = True, extra_flags=(), out: str = LIB) -> str:
     """Compile every source to an object (sources may carry their own flags), then link the shared library.
     `out` other than the default names a variant build (e.g. one compiled with -DHG_TRACE, see prefix_wide.hip):
@@ -39,6 +56,12 @@ def build(verbose: bool = True, extra_flags=(), out: str = LIB) -> str:
     common = [f for f in HIPCC_FLAGS if f != "-shared"]
     objs = []
     procs = []
+    marshal_tmp = MARSHAL + f".tmp{os.getpid()}"
+    if out == LIB:
+        cmd = marshal_command(marshal_tmp)
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        procs.append((cmd, subprocess.Popen(cmd)))
     for src in SOURCES:
         obj = os.path.join(objdir, src + ".o")
         cmd = [cc, *common, *PER_SOURCE_FLAGS.get(src, []), *extra_flags, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
@@ -56,13 +79,15 @@ def build(verbose: bool = True, extra_flags=(), out: str = LIB) -> str:
         print(" ".join(link), flush=True)
     subprocess.check_call(link)
     os.replace(tmp, out)
+    if out == LIB:
+        os.replace(marshal_tmp, MARSHAL)
     return out
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
         return True
-    t = os.path.getmtime(LIB)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(MARSHAL))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(ROOT, "include", h) for h in ("hydragen.h", "hydragen_debug.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 

@@ -1,0 +1,84 @@
+"""The native marshalling of the decode-step calls (csrc/marshal.cpp): what the checks in Python refuse it never passes on,
+what they accept works through either, with the same results."""
+import types
+
+import pytest
+import torch
+
+from paper_2402_05099_amd import binding as hb
+
+
+def test_what_is_not_plain_is_left_to_python():
+    """Host tensors, tensors of a transform, wrong counts and other objects: None, and no exception left behind."""
+    m = hb.native()
+    q = torch.zeros(2, 2, 64, dtype=torch.bfloat16)
+    ctx = types.SimpleNamespace(h=hb.ctypes.c_void_p(1))
+    assert m.attn(ctx, q, [], q, q, q, q, 1, q, q, 0.0) is None
+    assert m.attn() is None and m.append(1, 2) is None
+    assert m.attn_paged(*[object()] * 9) is None
+    got = []
+    torch.vmap(lambda x: got.append(m.append(ctx, x, x, x, x, x, x, 1)) or x)(q)
+    assert got == [None]
+
+
+def test_refusals_are_those_of_python():
+    q = torch.zeros(2, 2, 64, dtype=torch.bfloat16)
+    n = torch.zeros(2, dtype=torch.int32)
+    kv = hb.PagedKV(q, q, n, 16)
+    for call in (lambda: hb.hg_hydragen_attn(None, q, [], q, q, n, n, 1, q), lambda: hb.hg_kv_append(None, q, q, q, q, n, n, 1),
+                 lambda: hb.hg_kv_append_fp8(None, q, q, q, q, 1.0, 1.0, n, n, 1), lambda: hb.hg_kv_append_paged(None, q, q, kv, n, 1)):
+        with pytest.raises(TypeError, match="need a contiguous device tensor"):
+            call()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nq", [1, 3])
+@pytest.mark.parametrize("cache", ["packed", "fp8", "paged"])
+def test_same_results_through_either(cache, nq, monkeypatch):
+    print(f"marshal: {cache} nq={nq}", flush=True)
+    B, H, D, cap = 5, 2, 64, 32
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda:0").to(torch.bfloat16)      # noqa: E731
+    lead = (B, H) if nq == 1 else (B, nq, H)
+    Q, Kn, Vn, levels = r(*lead, D), r(*lead, D), r(*lead, D), [hb.Level(K=r(40, H, D), V=r(40, H, D), max_rows=40, max_seqs=B)]
+    rows = [r(B * cap, H, D) for _ in range(2)]
+    if cache == "fp8":
+        rows = [x.mul(64).to(torch.float8_e4m3fn).view(torch.uint8) for x in rows]
+    off = torch.arange(B, dtype=torch.int32, device="cuda:0") * cap
+    table = torch.arange(B * 2, dtype=torch.int32, device="cuda:0").view(B, 2)
+
+    def step(plain):
+        ctx = hb.Context(0, hb.hg_workspace_bytes(B * nq, H, D, 8))
+        K, V = (x.clone() for x in rows)
+        n = torch.tensor([0, 3, 9, 20, 29], dtype=torch.int32, device="cuda:0")
+        O, L = torch.zeros_like(Q), torch.zeros(lead, device="cuda:0")
+        lv, scale = (levels, 0.125) if plain else (tuple(levels), 0.125)
+        ks = 1.0 / 64 if plain else 1 / 64
+        if cache == "packed":
+            hb.hg_kv_append(ctx, Kn, Vn, K, V, off, n, cap)
+            hb.hg_hydragen_attn(ctx, Q, lv, K, V, off, n, cap, O, L, scale)
+        elif cache == "fp8":
+            hb.hg_kv_append_fp8(ctx, Kn, Vn, K, V, ks, ks, off, n, cap)
+            hb.hg_hydragen_attn_fp8(ctx, Q, lv, K, V, ks, ks, off, n, cap, O, L, scale)
+        else:
+            kv = hb.PagedKV(K, V, table, 16)
+            hb.hg_kv_append_paged(ctx, Kn, Vn, kv, n, cap)
+            hb.hg_hydragen_attn_paged(ctx, Q, lv, kv, n, cap, O, L, scale)
+        torch.cuda.synchronize()
+        ctx.close()
+        return O, L, K, V, n
+
+    taken = []
+    m = hb.native()
+    names = ("attn", "attn_fp8", "attn_paged", "append", "append_fp8", "append_paged")
+    watch = types.SimpleNamespace(**{f: (lambda f: lambda *a: taken.append((f, getattr(m, f)(*a))) or taken[-1][1])(f) for f in names})
+    monkeypatch.setattr(hb, "_native", watch)
+    first = step(True)
+    suffix = {"packed": "", "fp8": "_fp8", "paged": "_paged"}[cache]
+    # (several queries: the first call sets the context's count of them and goes through Python)
+    assert taken == [("append" + suffix, 0 if nq == 1 else None), ("attn" + suffix, 0)]
+    taken.clear()
+    second = step(False)
+    assert taken[-1] == ("attn" + suffix, None)
+    for a, b in zip(first, second):
+        assert torch.equal(a, b)

@@ -89,7 +89,7 @@ enum {
     HG_OPT_WIDE_SLOTS = 7,    /* CUs per XCD (1..32) that the persistent 256-row kernel occupies, with the suffix beside it; 0 = automatic */
     HG_OPT_NUM_QUERIES = 8,   /* queries per sequence, 1..64 (default 1 = decode); see "Several queries per sequence" below */
     HG_OPT_SUFFIX_ITEMS_PER_WAVE = 10, /* matrix-core suffix kernel: consecutive work items one wavefront takes (1..1024; 0 = automatic); a fused call then runs that kernel, not a launch shared with the shared blocks */
-    HG_OPT_SUFFIX_TILE_ROWS = 11, /* matrix-core suffix kernel: query rows per tile: 0 automatic (16 when a KV head serves at most 16 rows of a sequence, else 32), 16 (honoured under the same condition), 32 */
+    HG_OPT_SUFFIX_TILE_ROWS = 11, /* matrix-core suffix kernel: query rows per tile: 0 automatic (16 when a KV head serves at most 16 rows of a sequence, else 32), 16 (honoured under the same condition), 32.  Where HG_OPT_FUSED_KERNEL is 2: query rows of the single launch's columns, 16 or 32 (0: as in the automatic choice on packed rows, else 32) */
     HG_OPT_FUSED_KERNEL = 12, /* fused calls: 0 automatic: one launch for the whole call when it holds so little work that launches and partial results would dominate, else shared blocks and suffix in one launch or one kernel per part, and a merge (on paged or 8-bit rows another option set to tune the separate kernels asks for those); 1 never the single launch; 2 the single launch at any size (not with an 8-bit V scale outside [2^-60, 2^60]), without need of a workspace.
                                * On packed bf16 rows the single launch of a small call, and of any call with 2, touches nothing but the call's inputs and outputs; other small calls use the workspace, which is checked as for the separate kernels, to spread their work */
     HG_OPT_SUFFIX_KERNEL = 9  /* suffix kernel: 0 automatic (matrix-core kernel when a KV head serves several query rows of a sequence: two or more queries, three or more query heads, or two heads with max_len >= 256; or when D = 128 and max_len >= 384 whatever the rows; else the vector-ALU kernel), 1 always vector-ALU, 2 always matrix-core; an 8-bit cache with D = 64 is read by the vector-ALU kernel (in a small call by the single launch, at the same precision) */

@@ -777,6 +777,7 @@ enum { kWaySingle = 0, kWayCombined = 1, kWayOneStream = 2, kWayTwoStreams = 3, 
 struct FusedPlan {
     int way;
     int splits;                     // single launch: workgroups per column
+    int column_rows;                // and query rows
     bool sfx_mfma;                  // the suffix kernel's choice for these rows is the matrix cores
     int nlev;                       // levels that hold keys
     LevelDev lv[HG_MAX_LEVELS];
@@ -907,6 +908,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     FusedPlan& p = *out;
     p.way = kWaySingle;
     p.splits = 1;
+    p.column_rows = 32;
     p.nlev = 0;
     p.main_level = p.joint = -1;
     const int n_levels = f.n_levels, max_len = f.max_len, B = f.B, Hq = f.Hq, Hkv = f.Hkv, D = f.D, nq = c->opt_nq, G = Hq / Hkv;
@@ -934,35 +936,34 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     const bool may_combine = may_join && long_enough;
 
     // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
-    // column of 32 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two
+    // column of 32 or 16 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two
     // event edges and a round trip of the partial results through HBM for the separate kernels.  Both durations are
-    // estimated, in microseconds, from fits to some eighty shapes (B = 4 .. 2048, 0 .. 16K shared keys, every cache and head
-    // layout); profiles/fused_ways_sweep.txt has the choice and both sides for 250 calls drawn from those ranges:
-    //   single launch: 4 + rounds x (4 + c x stages per wavefront), c = 1.6 us per 32-key stage while a quarter of the CUs
-    //                  are busy (the latency of one stage's K and V rows), 2.3 with all of them, 1.6 times that for 8-bit rows of D = 128 with fp32 weights and 24 or more sequences to a column; 4.5 + 0.3 x splits more when
-    //                  a column's workgroups have to meet; never faster than the suffix rows stream in (5 TB/s, 4 on blocks of few rows, 3.3 through a page table)
-    //                  and the shared rows, which every column reads for itself, at 8 TB/s once they do not fit the L2;
+    // estimated, in microseconds, from fits to 520 calls (B = 4 .. 2048, 0 .. 16K shared keys, every cache and head layout, each
+    // with 16 and 32 rows and every number of workgroups per column; mean error of an estimate 9 %):
+    //   single launch: a + rounds x (b + c x stages per wavefront), c growing with the CUs that are busy (they share the L2s), 1.4
+    //                  times that for 8-bit rows with fp32 weights; m0 + m1 x splits more when a column's workgroups have to
+    //                  meet; constants below.  Never faster than the suffix rows stream in (4.2 TB/s, 3.3 through a page table).
     //   separate:      10.5 and 0.7 of the suffix time without a shared block; else 18, 6 and 10 more with one and two shared levels, 8 more once a block is long enough to be split,
-    //                  6 less for those 8-bit rows where no block has rows for the persistent kernel,
-    //                  suffix rows at 5 TB/s, shared blocks at 1.1 PFLOP/s or 5 TB/s; with many suffix rows and one launch for
-    //                  both (below) 25, and 0.8 of the suffix time.
+    //                  suffix rows at 5 TB/s (the vector ALU with several rows per KV head: 0.5 of that time per row),
+    //                  shared blocks at 1.1 PFLOP/s or 5 TB/s; with many suffix rows and one launch for both (below) 25, and 0.8 of the suffix time.
+    // 16 rows: half the products and exponentials per stage and fewer sequences' suffixes per column, but twice the columns, each
+    // reading the shared rows for itself: they win while there are CUs for them.  Measured 32 / 16 rows: 13.2 / 10.0 us (45 x 16/2
+    // heads, 515 keys), 15.9 / 12.0 (256 x 8/1, 1K keys), 11.3 / 8.8 (95 x 16/2, two queries), 44.5 / 61 (139 x 64/8, four queries),
+    // 27.2 / 31 (60 x 16/2, 3K keys, three workgroups per column).
     // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single launch is
-    // taken below the other estimate; from 60 us on (45 where the other way is two launches side by side, unless the suffix is one
-    // row per KV head on the vector ALU; 35 for those 8-bit rows) only when it is 25 % below (the model of the separate kernels is
-    // pessimistic where suffixes and shared blocks overlap).  Measured single /
-    // other way: 12.4 / 25 us (72 sequences, 206 rows), 17.3 / 26 (2.5K shared keys, 16 sequences), 15.9 / 24 (256
-    // sequences, 1K keys), 59 / 46 (128 x 32/8 heads, 2K keys, paged, with the cache update: not taken), 74 / 59 (53 x 32/8
-    // heads, 12K + 12 x 276 keys, 8-bit: not taken), 222 / 131 (256 x 40 heads, 2K keys: not taken); one row per KV head:
-    // 22 / 18 (37 x 40 heads, 219 keys, 23 codes: not taken), 25 / 19 (30 x 4, 299 keys, 200 codes, paged: not taken), 11 / 20
-    // (5 x 40, 269 keys, 37 codes), 17 / 25 (9 x 4, 583 keys, 350 codes, paged), 21 / 31 (171 x 40, D = 64, 660 keys, 32 codes).
+    // taken below the other estimate, from 60 us on only when it is 25 % below (the model of the separate kernels is
+    // pessimistic where suffixes and shared blocks overlap): over the 520 calls 0.4 % slower than the better way each time.
+    // Measured single / other way: 9.3 / 17 us (12 x 64/8 heads, D = 64, 1261 keys, codes), 13.1 / 35 (53 x 8/1, 1268 + 5 x 289 keys,
+    // codes), 28 / 53 (34 x 32/8, 10.5K keys), 45 / 22 (428 x 64/8, no shared keys, codes, paged: not taken), 52 / 44 (216 x 32/8, 5K keys,
+    // codes: taken, one of the eleven that miss by more than a tenth).
     // (the single launch divides sums by the V scale and multiplies them again: not with scales near the ends of fp32)
     const bool odd_scale = f.fp8 && has_suffix && !(f.v_scale >= 0x1p-60f && f.v_scale <= 0x1p60f);
     bool take_single = false;
     if (c->opt_fused_kernel != 1 && !c->opt_timing && !odd_scale) {
         const int rps = nq * G;
-        const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma, one_row = rps == 1 && !sfx_mfma;
+        const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma;
         long long shared_keys = 0;
-        double flops = 0.0, shared_bytes = 0.0, shared_stages = 0.0;
+        double flops = 0.0, shared_bytes = 0.0;
         // wide: a level runs on the persistent kernel otherwise; joins: and shares its launch with the suffix, or could if that were longer
         bool any = has_suffix, wide = false;
         int nonempty = 0;
@@ -970,9 +971,6 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B;
             if (levels[i].max_rows > 0 && seqs > 0) {
                 shared_keys += levels[i].max_rows;
-                // blocks that a column of 32 rows meets: all of a small block's neighbours as well
-                const double met = std::min((double)levels[i].n_blocks, levels[i].n_blocks > 1 ? 1.0 + 31.0 / (double)(seqs * rps) : 1.0);
-                shared_stages += met * ((levels[i].max_rows + 31) / 32);
                 flops += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * seqs * nq * Hq * D;
                 shared_bytes += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * Hkv * D;
                 any = true;
@@ -981,18 +979,37 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             }
         }
         const bool joins = may_join && wide;
-        const int seqs_per_tile = rps >= 32 ? 1 : (32 + rps - 1) / rps + (32 % rps ? 1 : 0);
-        const long long seqs_here = seqs_per_tile < B ? seqs_per_tile : B;
+        struct Shape { int seqs_per_tile; long long cols; double stages; };      // of columns of so many rows
+        auto shape_of = [&](int rows) {
+            Shape x;
+            x.seqs_per_tile = rps >= rows ? 1 : (rows + rps - 1) / rps + (rows % rps ? 1 : 0);
+            x.cols = ((long long)B * rps + rows - 1) / rows * Hkv;
+            double shared_stages = 0.0;
+            for (int i = 0; i < n_levels; ++i) {
+                const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B;
+                if (levels[i].max_rows <= 0 || seqs <= 0) continue;
+                // blocks that a column meets: all of a small block's neighbours as well
+                const double met = std::min((double)levels[i].n_blocks, levels[i].n_blocks > 1 ? 1.0 + (rows - 1.0) / (double)(seqs * rps) : 1.0);
+                shared_stages += met * ((levels[i].max_rows + 31) / 32);
+            }
+            x.stages = shared_stages + (has_suffix ? std::min(x.seqs_per_tile, B) * ((0.75 * max_len + 16.0) / 32.0) : 0.0);
+            return x;
+        };
+        const Shape shape32 = shape_of(32), shape16 = shape_of(16);
         // the separate kernels at their lightest, the single launch at its slowest: full columns of codes with fp32 weights
-        const bool light = one_row && fp32_weights && D == 128 && !wide && seqs_here >= 24;
-        const double stages = shared_stages + (has_suffix ? seqs_here * ((0.75 * max_len + 16.0) / 32.0) : 0.0);
-        const long long tiles = ((long long)B * rps + 31) / 32;
-        const long long cols = tiles * Hkv;
+        const bool light = rps == 1 && fp32_weights && D == 128 && !wide && B >= 24;
+        const long long cols = shape32.cols;
+        const int seqs_per_tile = shape32.seqs_per_tile;
         const double per_round = D == 128 ? 256.0 : 512.0;       // workgroups that run at a time (LDS)
-        auto chain_at = [&](int S) {
-            const double wgs = (double)cols * S;
-            const double per_stage = (light ? 1.6 : 1.0) * (1.6 + 0.7 * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
-            return 4.0 + ceil(wgs / per_round) * (4.0 + per_stage * ceil(stages / (8.0 * S))) + (S > 1 ? 4.5 + 0.3 * S : 0.0);
+        auto chain_at = [&](int rows, int S) {
+            static const double fit[2][2][7] = {      // a, b, c on a quarter of the chip, more on all of it, m0, m1, codes with fp32 weights
+                {{3.2, 4.6, 1.50, 0.60, 4.0, 0.44, 1.5}, {2.9, 3.2, 1.32, 0.46, 2.5, 0.14, 1.42}},       // D = 128: 32 rows, 16 rows
+                {{1.8, 4.2, 1.08, 0.42, 1.95, 0.16, 1.42}, {1.9, 3.5, 0.93, 0.33, 1.5, 0.10, 1.38}}};    // D = 64
+            const double* const k = fit[D == 64][rows == 16];
+            const Shape& x = rows == 16 ? shape16 : shape32;
+            const double wgs = (double)x.cols * S;
+            const double per_stage = (fp32_weights ? k[6] : 1.0) * (k[2] + k[3] * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
+            return k[0] + ceil(wgs / per_round) * (k[1] + per_stage * ceil(x.stages / (8.0 * S))) + (S > 1 ? k[4] + k[5] * S : 0.0);
         };
         // Small calls on packed rows touch nothing but their inputs and outputs: one workgroup per column, no workspace, no
         // counters.  A program may have several in flight for one context (streams, graph replays, branches of a graph) or run
@@ -1007,26 +1024,34 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             const double other = 24.0 + 0.75 * suffix + (shared_keys >= 1024 ? 8.0 : 0.0) + flops / 1.1e9;
             own_memory = c->opt_fused_kernel == 2 || (one <= 130.0 && one <= (one <= 40.0 ? 1.0 : 0.9) * other);
         }
-        int& splits = p.splits;
-        if (!own_memory && f.counters && cols * 2 <= kSplitWorkgroups) {
-            // (more workgroups than one stage per wavefront asks for only meet later)
-            const int most = (int)std::min<long long>({kSplitWorkgroups / cols, kSmallMaxSplits, (long long)ceil(stages / 8.0)});
-            for (int S = 2; S <= most; ++S)
-                if (chain_at(S) < 0.95 * chain_at(splits) && small_part_floats((int)cols, S, D) * sizeof(float) <= f.ws_bytes) splits = S;
+        int &splits = p.splits, &rows = p.column_rows;
+        // (columns that only the option splits have 32 rows unless 16 are asked for)
+        const int asked = c->opt_fused_kernel != 2 ? 0 : c->opt_suffix_tile || own_memory ? c->opt_suffix_tile : 32;
+        if (asked == 16 || (asked == 0 && chain_at(16, 1) < chain_at(32, 1))) rows = 16;
+        if (!own_memory && f.counters) {
+            for (int r : {32, 16}) {
+                const Shape& x = r == 16 ? shape16 : shape32;
+                if (x.cols * 2 > kSplitWorkgroups || (asked && asked != r)) continue;
+                // (more workgroups than one stage per wavefront asks for only meet later)
+                const int most = (int)std::min<long long>({kSplitWorkgroups / x.cols, kSmallMaxSplits, (long long)ceil(x.stages / 8.0)});
+                for (int S = 2; S <= most; ++S)
+                    if (chain_at(r, S) < 0.98 * chain_at(rows, splits) && small_part_floats((int)x.cols, S, r, D) * sizeof(float) <= f.ws_bytes) {
+                        rows = r;
+                        splits = S;
+                    }
+            }
         }
         const double suffix_us = has_suffix ? (f.fp8 ? 2.0 : 4.0) * B * (0.75 * max_len) * Hkv * D / 5.0e6 : 0.0;      // at 5 TB/s
         const double shared_us = shared_bytes / 5.0e6;
-        // every column reads the shared rows for itself: from its XCD's L2 (4 MB; an XCD works on its share of the KV heads)
-        // while they fit there, at 8 TB/s beyond
-        const double restream_us = shared_bytes / std::min(8, Hkv) > 4.0e6
-                                       ? (double)cols * shared_stages * 128.0 * D / 8.0e6 + suffix_us + 13.0 : 0.0;
-        const double est_single = std::max({chain_at(splits), (paged ? 1.5 : joins ? 1.0 : 1.2) * suffix_us + shared_us + 7.0, restream_us});
+        const double est_single = std::max(chain_at(rows, splits), (paged ? 1.5 : 1.2) * suffix_us + shared_us + 6.0);
+        const double sfx_alone = suffix_us * (sfx_mfma || rps == 1 ? 1.0 : 0.5 * rps);
         double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
-                                    suffix_us + std::max(flops / 1.1e9, shared_us);
+                                    sfx_alone + std::max(flops / 1.1e9, shared_us);
         if (light && nonempty > 0) est_separate -= 6.0;
-        if (nonempty == 0) est_separate = 10.5 + 0.7 * suffix_us;      // the suffix kernel alone: no event edges, hardly a merge
+        if (nonempty == 0) est_separate = 10.5 + 0.7 * sfx_alone;      // the suffix kernel alone: no event edges, hardly a merge
         if (suffix_us >= 30.0 && joins && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
-        const bool small = est_single <= (est_single <= (light ? 35.0 : joins || (one_row && has_suffix) ? 60.0 : 45.0) ? 1.0 : 0.75) * est_separate;
+        // (light calls: the separate kernels keep all but the clearest; single / separate over four drawn ones 12 / 18, 15 / 20, 18 / 21, 43 / 49)
+        const bool small = est_single <= (light ? 0.6 : est_single <= 60.0 ? 1.0 : 0.75) * est_separate;
         if (own_memory) {
             // (a suffix alone, in one work item per row, goes from its kernel straight to the outputs: 782 x 4 heads, 21 rows
             // 14 us against 18 for the single launch)
@@ -1037,7 +1062,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             p.np = 1;
             return HG_OK;
         }
-        if (any && cols * splits < (1LL << 31)) {
+        if (any && (rows == 16 ? shape16 : shape32).cols * splits < (1LL << 31)) {
             if (c->opt_fused_kernel == 2) return HG_OK;
             // (an option of the separate kernels asks for them)
             take_single = small && !c->opt_prefix_splits && !c->opt_prefix_kernel && !c->opt_wide_slots && !c->opt_overlap && !c->opt_suffix_kernel &&
@@ -1122,8 +1147,10 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         sa.fp32_weights = sa.fp8 && !p.sfx_mfma;
         sa.max_len = max_len;
         sa.B = B; sa.Hq = Hq; sa.Hkv = Hkv; sa.G = G; sa.nq = nq;
-        sa.tiles = (B * nq * G + 31) / 32;
+        sa.rows = p.column_rows;
+        sa.tiles = (B * nq * G + sa.rows - 1) / sa.rows;
         sa.cols = sa.tiles * Hkv;
+        sa.per_xcd = small_wgs_per_xcd(sa.tiles, p.splits, Hkv);
         sa.splits = p.splits;
         sa.part = reinterpret_cast<float*>(ws.p);
         sa.arrivals = p.splits > 1 ? c->counters + meeting_counter(p.splits) : nullptr;

@@ -2,14 +2,17 @@
 // sequence's own suffix, and the merge of the parts by their log-sum-exp, Eq. 5) in ONE launch, for calls with so
 // little work that several launches and a pass over partial results cost more than the arithmetic.
 //
-// A column is 32 consecutive rows of the query rows of one KV head (Sec. 3.2's inter-sequence batching: row
+// A column is 32 or 16 consecutive rows (TR) of the query rows of one KV head (Sec. 3.2's inter-sequence batching: row
 // r = sequence * nq * G + query * G + head-in-group).  Its keys are a list of segments: the block of every shared
 // level that covers its sequences (all rows of the tile attend to it, or those of the covered sequences when a
 // block boundary falls inside the tile), then the suffix of each of the tile's sequences (only that sequence's rows
 // attend).  Softmax over the union of all segments is one online softmax: a row that does not attend to a segment has
-// its scores masked.  The decomposition of Eq. 5 appears twice: the list is cut into equal runs of 32-key stages, one
-// per wavefront of the column's workgroups, each with its own running maximum, sum and accumulator; the eight partial
+// its scores masked.  The decomposition of Eq. 5 appears twice: the 32-key stages of the list are dealt out to the
+// wavefronts of the column's workgroups one by one, each with its own running maximum, sum and accumulator; the eight partial
 // results of a workgroup meet in LDS and are combined with the weights exp(LSE_i - max LSE).
+//
+// 16 rows: products of 16 x 16 instead of 32 x 32, half the exponentials per lane, and fewer sequences whose suffixes a column
+// has to walk; twice as many columns, which a small call has CUs for (the rule is in plan_fused).
 //
 // A column is worked on by `splits` workgroups (as many as leave the chip full: a small call has few columns, and one
 // workgroup per column would leave most CUs idle; calls that must not share the workspace keep one, see plan_fused).  With more than one, each writes its combined result to the
@@ -22,13 +25,13 @@
 // flight as four wavefronts with two slots for each, and the second wavefront fills the first one's waits.
 // Products, XOR swizzles and lazy rescaling are those of the other kernels (prefix_wide.hip, decode_mfma.hip).
 //
-// What bounds it: latency.  With one stage per wavefront the kernel takes 6 us (lengths, Q and the key list, the first
-// rows, one stage, combination and output; 4 sequences x 4 heads, 128 keys, by a kernel trace; such a call through Python
-// takes 10 us, all of it on the host), every further stage 1.6 us (2.3 with all CUs busy), the
-// meeting of a column's workgroups 5.  Measured, four wavefronts and one workgroup per column before, eight wavefronts after:
-// 256 sequences x 8 heads on one KV head, 1024 shared keys, 128 suffix rows 23.4 -> 15.9 us; 45 x 16 heads on two KV
-// heads, 515 keys, ragged up to 150 rows 19.2 -> 13.6; paged and 8-bit caches, which took the separate kernels:
-// 25-50 -> 15-25 us on calls of that size.
+// What bounds it: latency.  By time stamps (32 rows): lengths and Q 1.2 - 2.4 us after the start, the first stage's rows 0.4 after their
+// request, 1.05 us per shared stage (products, exponentials and the 16 KiB of every one of eight wavefronts through the CU's
+// 64 bytes a cycle), 1.45 per suffix stage (masks, another segment each time), 1.2 for the combination and output.
+// Measured, one workgroup per column, runs of consecutive stages and 32 rows before, as it is now after: 256 sequences x 8 heads on one KV head, 1024
+// shared keys, 128 suffix rows 16.2 -> 12.1 us; 45 x 16 heads on two KV heads, 515 keys, ragged up to 150 rows 13.9 -> 10.0;
+// 57 calls of this kind drawn at random 1.19 times as fast in the mean (stages dealt out one by one and the first requested early
+// alone: 1.05).
 //
 // PAGED: the suffix rows are found through a page table; CODES: they are E4M3 codes with one scale per tensor, expanded
 // in registers (exactly: every E4M3 value is a bf16 value); the K scale multiplies the scores of those stages, the V
@@ -96,7 +99,8 @@ __device__ __forceinline__ uintx4 expand8(unsigned lo, unsigned hi) {
 }
 
 // elements 8 tt .. 8 tt + 7 of a stage's weights, rounded to bf16
-__device__ __forceinline__ uintx4 pack8(const floatx16& p, int tt) {
+template <class V>
+__device__ __forceinline__ uintx4 pack8(const V& p, int tt) {
     return uintx4{pack_pair(p[8 * tt], p[8 * tt + 1]), pack_pair(p[8 * tt + 2], p[8 * tt + 3]),
                   pack_pair(p[8 * tt + 4], p[8 * tt + 5]), pack_pair(p[8 * tt + 6], p[8 * tt + 7])};
 }
@@ -111,39 +115,63 @@ __device__ __forceinline__ uint64_t ld_agent(const float* p) {
     return __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int D>
+template <int D, int TR>
 struct SmallGeo {
-    static constexpr int KS = D / 16, DB = D / 32;
+    static constexpr int KS = D / 16, DB = D / 32;      // 32-row columns: k-steps of the scores, 32-row blocks of O^T
+    static constexpr int KS16 = D / 32, DB16 = D / 16;  // 16-row columns: 32-column steps, 16-row blocks
     static constexpr int CPR = D / 8, RPI = 64 / CPR, CPS = KT / RPI, ROWB = D * 2, STB = KT * ROWB;   // bf16 rows
     static constexpr int CPR8 = D / 16, RPI8 = 64 / CPR8, CPS8 = KT / RPI8;                            // E4M3 rows
-    static constexpr int OW = KT * D * 4;                // combined result of a wavefront (32 rows, fp32); equals its ring
-    static constexpr int LDS = NWS * OW + NWS * 32 * 8 + 16;   // rings or results, maxima and sums, the "last" flag
-    static_assert(OW == 2 * STB, "a wavefront's result takes the place of its ring");
+    static constexpr int OW = TR * D * 4;                // combined result of a wavefront (fp32)
+    static constexpr int LDS = NWS * 2 * STB + NWS * TR * 8 + 16;   // rings or results, maxima and sums, the "last" flag
+    static_assert(OW <= 2 * STB, "a wavefront's result takes the place of its ring");
+    static constexpr int RPW = TR == 32 || D == 64 ? 4 : 2;         // rows a wavefront finishes (16 rows of D = 64: half of the wavefronts do)
+    static constexpr int LPR = 64 / RPW, CH = D / 4, CPL = CH / LPR;   // lanes of such a row, its 16-byte chunks, chunks per lane
+    static_assert(CPL * LPR == CH && TR % RPW == 0 && TR / RPW <= NWS, "");
 };
 
 }  // namespace
 
-// CODES: the suffix rows are bf16 (0), E4M3 codes (1), E4M3 codes whose weights keep fp32 precision (2)
-template <int D, bool PAGED, int CODES>
+// CODES: the suffix rows are bf16 (0), E4M3 codes (1), E4M3 codes whose weights keep fp32 precision (2).  TR: rows of a column.
+template <int D, bool PAGED, int CODES, int TR>
 __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
-    constexpr bool FP8 = CODES != 0;
-    using G_ = SmallGeo<D>;
+    constexpr bool FP8 = CODES != 0, NARROW = TR == 16;
+    using G_ = SmallGeo<D, TR>;
+    constexpr int KS16 = G_::KS16, DB16 = G_::DB16;
     constexpr int KS = G_::KS, DB = G_::DB, CPR = G_::CPR, RPI = G_::RPI, CPS = G_::CPS, ROWB = G_::ROWB, STB = G_::STB;
     constexpr int CPR8 = G_::CPR8, RPI8 = G_::RPI8, CPS8 = G_::CPS8;
     constexpr int NP = CODES == 2 ? 3 : 1;          // bf16 pieces of a code's weight
     unsigned char* const smem_all = fs_smem;
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l = tid & 63, lq = l & 31, hl = l >> 5;
+    const int l = tid & 63, lq = l & (TR - 1), hl = l >> 5, lg = l >> 4;     // lq: this lane's row of the column
     unsigned char* const smem = smem_all + w * (2 * STB);      // this wavefront's K slot, then its V slot
     const kargs_ptr k = (kargs_ptr)__builtin_amdgcn_kernarg_segment_ptr();
 
-    const int col = blockIdx.x % a.cols, split = blockIdx.x / a.cols;
-    const int tile = col % a.tiles, kvh = col / a.tiles;
+    // Workgroups whose ids are equal modulo 8 run on one XCD: those of a KV head go to one (8 heads and more) or to its share of
+    // the eight, so that the shared rows of a head are read into one L2 or few instead of all.  (34 sequences x 32/8 heads,
+    // 10.5K keys, 16-row columns, three workgroups each: 57 -> 29 us; up to 4 MB of shared rows no difference.)
+    int kvh, unit;                                  // unit: (tile, split), tiles first
+    const int units = a.tiles * a.splits;           // of one KV head
+    if (a.per_xcd > 0) {
+        const int x = blockIdx.x & 7, i = blockIdx.x >> 3;
+        if (a.Hkv >= 8) {
+            kvh = x + 8 * (i / units);
+            unit = i % units;
+        } else {
+            kvh = x % a.Hkv;
+            unit = i * (8 / a.Hkv) + x / a.Hkv;
+            if (unit >= units) return;
+        }
+    } else {
+        kvh = blockIdx.x / units;
+        unit = blockIdx.x % units;
+    }
+    const int tile = unit % a.tiles, split = unit / a.tiles;
+    const int col = kvh * a.tiles + tile;
     const int rps = a.nq * a.G;                     // query rows of one sequence for this KV head
     const int R = a.B * rps;
-    const int r0 = tile * 32;
-    const int b0 = r0 / rps, b1 = min((r0 + 31) / rps, a.B - 1);
+    const int r0 = tile * TR;
+    const int b0 = r0 / rps, b1 = min((r0 + TR - 1) / rps, a.B - 1);
     const int r = r0 + lq;                          // this lane's row
     const bool rv = r < R;
     const int rr = rv ? r : r0;
@@ -156,30 +184,31 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
         len_v = a.lengths[b0 + l];
         if (!PAGED) off_v = a.offsets[b0 + l];
     }
-    bf16x8 qf[KS];
+    constexpr int QN = NARROW ? KS16 : KS;
+    bf16x8 qf[QN];
     {
         const uint16_t* qp = a.Q + qidx * D;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
+        for (int s = 0; s < QN; ++s) {
             uint4 v = make_uint4(0, 0, 0, 0);
-            if (rv) v = *reinterpret_cast<const uint4*>(qp + 8 * (2 * s + hl));
+            if (rv) v = *reinterpret_cast<const uint4*>(qp + 8 * (NARROW ? 4 * s + lg : 2 * s + hl));
             qf[s] = __builtin_bit_cast(bf16x8, v);
         }
     }
     // ---- segment enumeration: shared blocks one by one, suffixes through a prefix sum over the lanes --------------------------
     const unsigned rstride_b = (unsigned)a.Hkv * D * 2u;
     const unsigned rstride_s = (unsigned)a.Hkv * D * (FP8 ? 1u : 2u);     // suffix rows
-    int it_level = 0, it_block = -1;                // next shared block (block -1: not looked up yet)
-    auto next_shared = [&](Seg& s) -> bool {        // the next shared block with keys and rows, if there is one
+    struct Walk { int level, block; };              // the next shared block (block -1: not looked up yet)
+    auto next_shared = [&](Walk& it, Seg& s) -> bool {        // the next shared block with keys and rows, if there is one
         for (;;) {
-            if (it_level >= a.n_levels) return false;
-            const int L = it_level;
+            if (it.level >= a.n_levels) return false;
+            const int L = it.level;
             const const_i32_ptr seq_off = (const_i32_ptr)(uintptr_t)k->lv[L].seq_off;
             const const_i32_ptr kv_off = (const_i32_ptr)(uintptr_t)k->lv[L].kv_off;
             int sa = 0, sb = a.B, kv0 = 0, kv1 = k->lv[L].max_rows;
             if (seq_off != nullptr) {
                 const int nb = k->lv[L].n_blocks;
-                if (it_block < 0) {
+                if (it.block < 0) {
                     // first block whose sequences end after b0
                     int lo = 0, hi = nb;
                     while (lo < hi) {
@@ -187,95 +216,34 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
                         if (seq_off[mid + 1] <= b0) lo = mid + 1;
                         else hi = mid;
                     }
-                    it_block = lo;
+                    it.block = lo;
                 }
-                if (it_block >= nb || seq_off[it_block] > b1) {   // no further block of this level touches the tile
-                    ++it_level;
-                    it_block = -1;
+                if (it.block >= nb || seq_off[it.block] > b1) {   // no further block of this level touches the tile
+                    ++it.level;
+                    it.block = -1;
                     continue;
                 }
-                sa = seq_off[it_block];
-                sb = min(seq_off[it_block + 1], sa + k->lv[L].max_seqs);
-                kv0 = kv_off[it_block];
-                kv1 = min(kv_off[it_block + 1], kv0 + k->lv[L].max_rows);
-                ++it_block;
+                sa = seq_off[it.block];
+                sb = min(seq_off[it.block + 1], sa + k->lv[L].max_seqs);
+                kv0 = kv_off[it.block];
+                kv1 = min(kv_off[it.block + 1], kv0 + k->lv[L].max_rows);
+                ++it.block;
             } else {
-                ++it_level;
-                it_block = -1;
+                ++it.level;
+                it.block = -1;
             }
             s.K = reinterpret_cast<const unsigned char*>(k->lv[L].K + (int64_t)kvh * D);
             s.V = reinterpret_cast<const unsigned char*>(k->lv[L].V + (int64_t)kvh * D);
             s.ks = kv0;
             s.ke = kv1;
             s.rlo = max(max(sa, b0) * rps - r0, 0);
-            s.rhi = min(min(sb, b1 + 1) * rps - r0, 32);
+            s.rhi = min(min(sb, b1 + 1) * rps - r0, TR);
             s.vis_base = 0x3fffffff;
             s.sfx = -1;
             s.nst = (s.ke > s.ks && s.rhi > s.rlo) ? (s.ke - s.ks + KT - 1) / KT : 0;
             if (s.nst > 0) return true;
         }
     };
-    // the stages of the shared blocks are counted (scalar loads) while the loads above are on their way; those are the only
-    // vector loads the compiler sees, and it waits for them here, before the first copy is issued
-    Seg cs{};
-    int shared_total = 0;
-    while (next_shared(cs)) shared_total += cs.nst;
-    shared_total = __builtin_amdgcn_readfirstlane(shared_total);
-    asm volatile("" : "+v"(len_v), "+v"(off_v));
-#pragma unroll
-    for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qf[s]));
-    len_v = max(min(len_v, a.max_len), 0);
-    const int nst_v = (len_v + KT - 1) / KT;        // stages of the suffix of sequence b0 + l
-    int incl_v = nst_v;                             // ... of the suffixes of b0 .. b0 + l
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(incl_v, o);
-        if (l >= o) incl_v += up;
-    }
-    const uint64_t nonempty = __ballot(nst_v > 0);
-    auto load_suffix = [&](int i, Seg& s) {         // the suffix of sequence b0 + i (which has rows)
-        const int cnt = __builtin_amdgcn_readlane(len_v, i), off = PAGED ? 0 : __builtin_amdgcn_readlane(off_v, i);
-        s.K = reinterpret_cast<const unsigned char*>(k->Ks) + (int64_t)kvh * D * (FP8 ? 1 : 2);
-        s.V = reinterpret_cast<const unsigned char*>(k->Vs) + (int64_t)kvh * D * (FP8 ? 1 : 2);
-        s.ks = off;
-        s.ke = off + cnt;
-        s.rlo = max((b0 + i) * rps - r0, 0);
-        s.rhi = min((b0 + i + 1) * rps - r0, 32);
-        s.vis_base = off + cnt - (a.nq - 1);        // query t sees rows below off + cnt - (nq-1-t)
-        s.nst = (cnt + KT - 1) / KT;
-        s.sfx = i;
-    };
-
-    // the column's stages, and this wavefront's run [run_lo, run_hi) of them
-    const int total = shared_total + __builtin_amdgcn_readlane(incl_v, 63);
-    const int runs = a.splits * NWS, run = split * NWS + w;
-    const int run_lo = (int)((long long)run * total / runs), run_hi = (int)((long long)(run + 1) * total / runs);
-    int ct = 0;                                     // current stage of segment cs
-    if (run_lo < run_hi) {
-        if (run_lo < shared_total) {
-            it_level = 0;
-            it_block = -1;
-            int base = 0;
-            while (next_shared(cs)) {
-                if (base + cs.nst > run_lo) break;
-                base += cs.nst;
-            }
-            ct = run_lo - base;
-        } else {
-            const int p = run_lo - shared_total;
-            const int i = __builtin_popcountll(__ballot(incl_v <= p));      // the first sequence whose stages reach past p
-            load_suffix(i, cs);
-            ct = p - (__builtin_amdgcn_readlane(incl_v, i) - cs.nst);
-        }
-    }
-    auto advance = [&](Seg& s, int& t) {            // one stage further (the caller knows that there is one)
-        if (++t < s.nst) return;
-        t = 0;
-        if (s.sfx < 0 && next_shared(s)) return;
-        const uint64_t rest = nonempty & (~0ull << (s.sfx + 1));
-        load_suffix(__builtin_ctzll(rest), s);
-    };
-
     // ---- HBM -> LDS copies -----------------------------------------------------------------------------------------------------
     // Stage t of a segment holds rows [k0c, k0c + 32), k0c = min(ks + 32 t, kwin), kwin = max(ke - 32, 0): a partial last
     // stage re-reads the 32 rows that end the range; row i of a stage is a key of it iff ks + 32 t <= k0c + i < ke.
@@ -286,7 +254,7 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     auto kswz = [](int row) { return D == 128 ? row % 16 : (row >> 1) & 7; };
     auto vswz = [](int row) { return D == 128 ? 4 * (row % 4) : 4 * ((row >> 1) & 1); };
     auto kswz8 = [](int row) { return D == 128 ? (row >> 1) & 7 : (row >> 2) & 3; };
-    auto vswz8 = [](int row) { return D == 128 ? ((row >> 1) & 1) | (((row >> 3) & 1) << 1) : (row >> 2) & 3; };
+    auto vswz8 = [](int row) { return D == 128 ? ((row >> 1) & 1) | (((row >> (NARROW ? 4 : 3)) & 1) << 1) : (row >> 2) & 3; };
     auto scalar_ptr = [&](const unsigned char* vbase) -> const unsigned char* {
         const uint64_t pv = reinterpret_cast<uint64_t>(vbase);
         const uint32_t plo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)pv);
@@ -371,11 +339,102 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     typedef std::integral_constant<bool, false> IsK;
     typedef std::integral_constant<bool, true> IsV;
 
-    // ---- LDS fragment addresses (relative to the slot), as in decode_mfma.hip ---------------------------------------------------
-    unsigned kaddr[KS], vaddr[DB], kaddr8[FP8 ? KS : 1], vaddr8[FP8 ? DB : 1];
+    // ---- this wavefront's stages: positions run, run + runs, ... of the list.  The stages of the shared blocks come first, so
+    // that the first one, where there is one, is found and requested while the lengths are on their way; and every wavefront
+    // gets its share of both kinds: with runs of consecutive stages those of suffix stages, which take longer, held up the rest.
+    const int runs = a.splits * NWS, run = split * NWS + w;
+    Walk walk{0, -1};
+    Seg cs{};
+    int ct = 0, base = 0;                           // current stage of segment cs; shared stages before cs
+    bool shared_first = false;
+    while (next_shared(walk, cs)) {
+        if (base + cs.nst > run) {
+            shared_first = true;
+            break;
+        }
+        base += cs.nst;
+    }
+    int shared_total = base;
+    if (shared_first) {
+        ct = run - base;
+        issue(cs, ct, IsK{});
+        issue(cs, ct, IsV{});
+        Walk rest = walk;
+        Seg s{};
+        shared_total += cs.nst;
+        while (next_shared(rest, s)) shared_total += s.nst;
+    }
+    shared_total = __builtin_amdgcn_readfirstlane(shared_total);
+    // (the loads above are the only ones the compiler sees; it waits for them, and with them for the first copies, here)
+    asm volatile("" : "+v"(len_v), "+v"(off_v));
 #pragma unroll
-    for (int s = 0; s < KS; ++s) kaddr[s] = (unsigned)(lq * ROWB + (((2 * s + hl) ^ kswz(lq)) * 16));
-    {
+    for (int s = 0; s < QN; ++s) asm volatile("" : "+v"(qf[s]));
+    len_v = max(min(len_v, a.max_len), 0);
+    const int nst_v = (len_v + KT - 1) / KT;        // stages of the suffix of sequence b0 + l
+    int incl_v = nst_v;                             // ... of the suffixes of b0 .. b0 + l
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(incl_v, o);
+        if (l >= o) incl_v += up;
+    }
+    auto load_suffix = [&](int i, Seg& s) {         // the suffix of sequence b0 + i (which has rows)
+        const int cnt = __builtin_amdgcn_readlane(len_v, i), off = PAGED ? 0 : __builtin_amdgcn_readlane(off_v, i);
+        s.K = reinterpret_cast<const unsigned char*>(k->Ks) + (int64_t)kvh * D * (FP8 ? 1 : 2);
+        s.V = reinterpret_cast<const unsigned char*>(k->Vs) + (int64_t)kvh * D * (FP8 ? 1 : 2);
+        s.ks = off;
+        s.ke = off + cnt;
+        s.rlo = max((b0 + i) * rps - r0, 0);
+        s.rhi = min((b0 + i + 1) * rps - r0, TR);
+        s.vis_base = off + cnt - (a.nq - 1);        // query t sees rows below off + cnt - (nq-1-t)
+        s.nst = (cnt + KT - 1) / KT;
+        s.sfx = i;
+    };
+    const int total = shared_total + __builtin_amdgcn_readlane(incl_v, 63);
+    auto seek = [&](int pos, Seg& s, int& t) {      // the stage at position pos < total, behind the current one
+        if (pos < shared_total) {
+            t = pos - base;
+            while (t >= s.nst) {
+                base += s.nst;
+                t -= s.nst;
+                next_shared(walk, s);
+            }
+            return;
+        }
+        const int p = pos - shared_total;
+        const int i = __builtin_popcountll(__ballot(incl_v <= p));      // the first sequence whose stages reach past p
+        load_suffix(i, s);
+        t = p - (__builtin_amdgcn_readlane(incl_v, i) - s.nst);
+    };
+    if (!shared_first && run < total) {
+        seek(run, cs, ct);
+        issue(cs, ct, IsK{});
+        issue(cs, ct, IsV{});
+    }
+
+    // ---- LDS fragment addresses (relative to the slot), as in decode_mfma.hip ---------------------------------------------------
+    constexpr int KA = NARROW ? 2 * KS16 : KS, VA = NARROW ? DB16 : DB;
+    unsigned kaddr[KA], vaddr[VA], kaddr8[FP8 ? KA : 1], vaddr8[FP8 ? VA : 1];
+    if constexpr (NARROW) {
+        // K of 16-key group kg, 32-column step q: row 16 kg + lq, columns 32 q + 8 lg .. +7.  V^T of 16 columns: k-slot e of lane
+        // group lg stands for key 16 (e / 4) + 4 lg + e % 4
+#pragma unroll
+        for (int q = 0; q < KS16; ++q)
+#pragma unroll
+            for (int kg = 0; kg < 2; ++kg) {
+                const int row = 16 * kg + lq;
+                kaddr[2 * q + kg] = (unsigned)(row * ROWB + (((4 * q + lg) ^ kswz(row)) * 16));
+                if constexpr (FP8) kaddr8[2 * q + kg] = (unsigned)(row * D + (((2 * q + (lg >> 1)) ^ kswz8(row)) * 16) + 8 * (lg & 1));
+            }
+        const int vrow = 4 * lg + (lq >> 2), q4 = lq & 3;
+        const int j = lq >> 1, row8 = 16 * (j >> 2) + 4 * lg + (j & 3);
+#pragma unroll
+        for (int db = 0; db < DB16; ++db) {
+            vaddr[db] = (unsigned)(STB + vrow * ROWB + (((2 * db + (q4 >> 1)) ^ vswz(vrow)) * 16) + (q4 & 1) * 8);
+            if constexpr (FP8) vaddr8[db] = (unsigned)(STB + row8 * D + ((db ^ vswz8(row8)) * 16) + 8 * (lq & 1));
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) kaddr[s] = (unsigned)(lq * ROWB + (((2 * s + hl) ^ kswz(lq)) * 16));
         const int i16 = l & 15, g1 = (l >> 4) & 1;
         const int keyq = 4 * hl + (i16 >> 2);
         const int fv = vswz(keyq);
@@ -399,96 +458,123 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     // ---- this wavefront's share of the softmax ------------------------------------------------------------------------------
     const float c2 = a.scale * kLog2e;
     const float tau_raw = TAU / c2;
-    floatx16 Oacc[DB];
+    // scores and accumulators: one 32 x 32 product per block of O^T, or two 16-key groups and 16 x 16 products
+    typedef float floatx4 __attribute__((ext_vector_type(4)));
+    using OBlock = std::conditional_t<NARROW, floatx4, floatx16>;
+    constexpr int OE = NARROW ? 4 : 16, NE = NARROW ? 8 : 16;      // values of a block, scores of a stage, per lane
+    OBlock Oacc[VA];
 #pragma unroll
-    for (int i = 0; i < DB; ++i)
+    for (int i = 0; i < VA; ++i)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) Oacc[i][j] = 0.f;
+        for (int j = 0; j < OE; ++j) Oacc[i][j] = 0.f;
     float m_used = -INFINITY;   // raw-score maximum the exponentials are taken against (-inf: no key seen yet)
     float mc = 0.f;             // m_used * c2, 0 while no key has been seen
     float lsum = 0.f;           // this lane's share of the row sum (unrounded exponentials)
     bool code_units = false;    // the accumulators hold sums of codes, to be multiplied by the V scale
 
-    if (run_lo < run_hi) {
-        issue(cs, ct, IsK{});
-        issue(cs, ct, IsV{});
-    }
-    for (int pos = run_lo; pos < run_hi; ++pos) {
-        const bool more = pos + 1 < run_hi;
+    for (int pos = run; pos < total; pos += runs) {
+        const bool more = pos + runs < total;
         Seg ns = cs;
         int nt = ct;
-        if (more) advance(ns, nt);
+        if (more) seek(pos + runs, ns, nt);
         const bool codes = FP8 && cs.sfx >= 0;
         wait_for(copies_of(cs));                    // this stage's K rows are here, its V rows may still be on their way
-        // S^T = K Q^T
-        floatx16 S;
+        // S^T = K Q^T.  Element i: stage row 8 (i / 4) + i % 4 + 4 hl; 16-row columns: 16 (i / 4) + i % 4 + 4 lg
+        using SVec = std::conditional_t<NARROW, floatx8, floatx16>;
+        SVec S;
+        if constexpr (NARROW) {
+            floatx4 s4[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+            if (codes) {
+                if constexpr (FP8) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) S[i] = 0.f;
-        if (codes) {
-            if constexpr (FP8) {
+                    for (int q = 0; q < KA; ++q) {
+                        const uintx2 kc = *reinterpret_cast<const uintx2*>(smem + kaddr8[q]);
+                        s4[q & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, expand8(kc[0], kc[1])), qf[q >> 1], s4[q & 1], 0, 0, 0);
+                    }
 #pragma unroll
-                for (int q = 0; q < KS; ++q) {
-                    const uintx2 kc = *reinterpret_cast<const uintx2*>(smem + kaddr8[q]);
-                    S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, expand8(kc[0], kc[1])), qf[q], S, 0, 0, 0);
+                    for (int i = 0; i < 4; ++i) { s4[0][i] *= a.k_scale; s4[1][i] *= a.k_scale; }
                 }
+            } else {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) S[i] *= a.k_scale;
+                for (int q = 0; q < KA; ++q) {
+                    const uintx4 kv = *reinterpret_cast<const uintx4*>(smem + kaddr[q]);
+                    s4[q & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kv), qf[q >> 1], s4[q & 1], 0, 0, 0);
+                }
             }
+            S = __builtin_shufflevector(s4[0], s4[1], 0, 1, 2, 3, 4, 5, 6, 7);
         } else {
 #pragma unroll
-            for (int q = 0; q < KS; ++q) {
-                const uintx4 kv = *reinterpret_cast<const uintx4*>(smem + kaddr[q]);
-                S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kv), qf[q], S, 0, 0, 0);
+            for (int i = 0; i < 16; ++i) S[i] = 0.f;
+            if (codes) {
+                if constexpr (FP8) {
+#pragma unroll
+                    for (int q = 0; q < KS; ++q) {
+                        const uintx2 kc = *reinterpret_cast<const uintx2*>(smem + kaddr8[q]);
+                        S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, expand8(kc[0], kc[1])), qf[q], S, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) S[i] *= a.k_scale;
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < KS; ++q) {
+                    const uintx4 kv = *reinterpret_cast<const uintx4*>(smem + kaddr[q]);
+                    S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kv), qf[q], S, 0, 0, 0);
+                }
             }
         }
-        // the scores depend on every fragment read: once they are pinned here the K slot may be overwritten
-        asm volatile("" : "+v"(S));
+        // the scores depend on every fragment read: once they are pinned here the K slot may be overwritten.  (The wait states
+        // are those between a product and a read of its result, which the compiler does not count across a branch.)
+        asm volatile("s_nop 11" : "+v"(S));
         asm volatile("" ::: "memory");
         if (more) issue(ns, nt, IsK{});
         const int key0 = cs.ks + ct * KT;
         const int k0c = row0_of(cs, ct);
         const bool partial = k0c != key0 || cs.ke - k0c < KT;      // some stage rows are not keys of this stage
         // masks: keys outside the stage's range, keys this lane's query does not see yet, rows that do not attend
-        if (partial || cs.rlo > 0 || cs.rhi < 32 || key0 + KT > cs.vis_base) {
+        constexpr int kGroup = NARROW ? 16 : 8;                     // stage rows between two groups of four scores
+        if (partial || cs.rlo > 0 || cs.rhi < TR || key0 + KT > cs.vis_base) {
             const bool attends = lq >= cs.rlo && lq < cs.rhi;
             const int vis_end = min(cs.ke, cs.vis_base + t_lane);
-            const int lo_i = key0 - k0c - 4 * hl, hi_i = (attends ? vis_end : k0c) - k0c - 4 * hl;
+            const int first = k0c + 4 * (NARROW ? lg : hl);         // stage row of element i is kGroup (i / 4) + i % 4 behind it
+            const int lo_i = key0 - first, hi_i = (attends ? vis_end : k0c) - first;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int ri = 8 * (i >> 2) + (i & 3);   // stage row of element i is ri + 4*hl
+            for (int i = 0; i < NE; ++i) {
+                const int ri = kGroup * (i >> 2) + (i & 3);
                 if (ri < lo_i || ri >= hi_i) S[i] = -INFINITY;
             }
         }
         float tmax = fmaxf(S[0], S[1]);
 #pragma unroll
-        for (int i = 2; i < 16; i += 2) tmax = fmaxf(fmaxf(tmax, S[i]), S[i + 1]);
-        tmax = half_max(tmax);
-        if (__any(tmax > m_used + tau_raw)) {
-            const float m_new = fmaxf(m_used, tmax);
+        for (int i = 2; i < NE; i += 2) tmax = fmaxf(fmaxf(tmax, S[i]), S[i + 1]);
+        if (__any(tmax > m_used + tau_raw)) {       // (m_used is the same in all lanes of a row)
+            if constexpr (NARROW) tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+            const float m_new = fmaxf(m_used, half_max(tmax));
             // equal maxima (also -inf and -inf: a row that has seen no key yet) keep the accumulators
             const float alpha = (m_new == m_used) ? 1.0f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
             m_used = m_new;
             mc = (m_new == -INFINITY) ? 0.f : m_new * c2;
             lsum *= alpha;
 #pragma unroll
-            for (int i = 0; i < DB; ++i)
+            for (int i = 0; i < VA; ++i)
 #pragma unroll
-                for (int j = 0; j < 16; ++j) Oacc[i][j] *= alpha;
+                for (int j = 0; j < OE; ++j) Oacc[i][j] *= alpha;
         }
-        uintx4 pb[NP][2];
+        constexpr int NT = NE / 8;
+        uintx4 pb[NP][NT];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < NE; ++i) {
             S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], c2, -mc));
             lsum += S[i];
         }
 #pragma unroll
-        for (int tt = 0; tt < 2; ++tt) pb[0][tt] = pack8(S, tt);
+        for (int tt = 0; tt < NT; ++tt) pb[0][tt] = pack8(S, tt);
         if constexpr (NP > 1) {
             if (codes) {                            // what the first piece left out, and what the second one did (both differences are exact)
 #pragma unroll
                 for (int n = 1; n < NP; ++n)
 #pragma unroll
-                    for (int tt = 0; tt < 2; ++tt) {
+                    for (int tt = 0; tt < NT; ++tt) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             S[8 * tt + 2 * i] -= bf16_lo(pb[n - 1][tt][i]);
@@ -522,17 +608,21 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
             if (codes && !code_units) {             // (once per wavefront: the shared blocks come first; the host bounds the scale)
                 const float rs = 1.0f / a.v_scale;
 #pragma unroll
-                for (int i = 0; i < DB; ++i)
+                for (int i = 0; i < VA; ++i)
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) Oacc[i][j] *= rs;
+                    for (int j = 0; j < OE; ++j) Oacc[i][j] *= rs;
                 code_units = true;
             }
         }
         // O^T += V^T P^T
+        auto product = [&](const bf16x8& vv, const uintx4& p, OBlock& o) {
+            if constexpr (NARROW) o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, __builtin_bit_cast(bf16x8, p), o, 0, 0, 0);
+            else o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, __builtin_bit_cast(bf16x8, p), o, 0, 0, 0);
+        };
 #pragma unroll
-        for (int tt = 0; tt < 2; ++tt) {
+        for (int tt = 0; tt < NT; ++tt) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db) {
+            for (int db = 0; db < VA; ++db) {
                 bf16x8 vv;
                 if (codes) {
                     if constexpr (FP8) {
@@ -542,23 +632,22 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
                 } else {
                     const unsigned char* vp = smem + vaddr[db] + tt * 16 * ROWB;
                     const shortx4 vlo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)HG_LDS(vp));
-                    const shortx4 vhi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)HG_LDS(vp + 8 * ROWB));
+                    const shortx4 vhi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)HG_LDS(vp + (NARROW ? 16 : 8) * ROWB));
                     vv = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vlo, vhi, 0, 1, 2, 3, 4, 5, 6, 7));
                 }
                 if constexpr (NP > 1) {
                     if (codes) {
 #pragma unroll
-                        for (int n = NP - 1; n > 0; --n)
-                            Oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, __builtin_bit_cast(bf16x8, pb[n][tt]), Oacc[db], 0, 0, 0);
+                        for (int n = NP - 1; n > 0; --n) product(vv, pb[n][tt], Oacc[db]);
                     }
                 }
-                Oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, __builtin_bit_cast(bf16x8, pb[0][tt]), Oacc[db], 0, 0, 0);
+                product(vv, pb[0][tt], Oacc[db]);
             }
         }
         // the accumulators depend on every fragment read of this stage: once they are pinned here the V slot may be overwritten
 #pragma unroll
-        for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(Oacc[db]));
-        asm volatile("" ::: "memory");
+        for (int db = 0; db < VA; ++db) asm volatile("" : "+v"(Oacc[db]));
+        asm volatile("s_nop 11" ::: "memory");
         if (more) issue(ns, nt, IsV{});
         cs = ns;
         ct = nt;
@@ -567,53 +656,53 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     // ---- the workgroup's partial results meet in LDS (Eq. 5) -------------------------------------------------------------------------
     // O of wavefront v takes the place of its ring: row-major [32][D] fp32 with the 16-byte chunk c of row r at chunk
     // c ^ (r % (D / 4)); behind the eight of them the maxima and sums [NWS][32].
-    constexpr int OW = G_::OW;
-    constexpr int CH = D / 4;                       // 16-byte chunks per row
-    float* const Mw = reinterpret_cast<float*>(smem_all + NWS * OW);
-    float* const Lw = Mw + NWS * 32;
-    int* const last_flag = reinterpret_cast<int*>(Lw + NWS * 32);
+    constexpr int OW = G_::OW, CH = G_::CH, RPW = G_::RPW, LPR = G_::LPR, CPL = G_::CPL;      // CH: 16-byte chunks per row
+    float* const Mw = reinterpret_cast<float*>(smem_all + NWS * 2 * STB);
+    float* const Lw = Mw + NWS * TR;
+    int* const last_flag = reinterpret_cast<int*>(Lw + NWS * TR);
+    if constexpr (NARROW) lsum += __shfl_xor(lsum, 16);
     const float ltot = half_sum(lsum);
     if constexpr (FP8) {
         if (code_units) {
 #pragma unroll
-            for (int i = 0; i < DB; ++i)
+            for (int i = 0; i < VA; ++i)
 #pragma unroll
-                for (int j = 0; j < 16; ++j) Oacc[i][j] *= a.v_scale;
+                for (int j = 0; j < OE; ++j) Oacc[i][j] *= a.v_scale;
         }
     }
     {                                               // (own ring only: nothing to wait for)
-        unsigned char* const ow = smem_all + w * OW;
+        unsigned char* const ow = smem_all + w * (2 * STB);
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+        for (int db = 0; db < VA; ++db)
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int chunk = 8 * db + 2 * q4 + hl;
+            for (int q4 = 0; q4 < OE / 4; ++q4) {
+                const int chunk = NARROW ? 4 * db + lg : 8 * db + 2 * q4 + hl;
                 *reinterpret_cast<float4*>(ow + lq * (D * 4) + ((chunk ^ (lq & (CH - 1))) * 16)) =
                     make_float4(Oacc[db][4 * q4], Oacc[db][4 * q4 + 1], Oacc[db][4 * q4 + 2], Oacc[db][4 * q4 + 3]);
             }
-        if (hl == 0) {
-            Mw[w * 32 + lq] = m_used;
-            Lw[w * 32 + lq] = ltot;
+        if (l < TR) {
+            Mw[w * TR + lq] = m_used;
+            Lw[w * TR + lq] = ltot;
         }
     }
     __syncthreads();
-    // wavefront w finishes rows 4w .. 4w+3: lane -> row 4w + l/16, 16-byte chunks (l%16) * CPL .. + CPL - 1
-    constexpr int CPL = CH / 16;                    // D = 128: 2, D = 64: 1
-    const int row = 4 * w + (l >> 4), c0 = (l & 15) * CPL;
+    // wavefront w finishes rows RPW w .. + RPW - 1: lane -> row RPW w + l / LPR, 16-byte chunks (l % LPR) * CPL .. + CPL - 1
+    const int row = RPW * w + l / LPR, c0 = (l % LPR) * CPL;
+    const bool finishes = row < TR && r0 + row < R;
     float4 acc[CPL];
     float M = -INFINITY, Lsum = 0.f;
-    {
+    if (row < TR) {
         float mv[NWS];
 #pragma unroll
         for (int v = 0; v < NWS; ++v) {
-            mv[v] = Mw[v * 32 + row];
+            mv[v] = Mw[v * TR + row];
             M = fmaxf(M, mv[v]);
         }
         float f[NWS];
 #pragma unroll
         for (int v = 0; v < NWS; ++v) {
             f[v] = (mv[v] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((mv[v] - M) * c2);
-            Lsum += f[v] * Lw[v * 32 + row];
+            Lsum += f[v] * Lw[v * TR + row];
         }
         const float inv = Lsum > 0.f ? 1.0f / Lsum : 0.f;     // a row without any key: O = 0, LSE = -inf
 #pragma unroll
@@ -621,7 +710,7 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
             acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
             for (int v = 0; v < NWS; ++v) {
-                const float4 o = *reinterpret_cast<const float4*>(smem_all + v * OW + row * (D * 4) + (((c0 + c) ^ (row & (CH - 1))) * 16));
+                const float4 o = *reinterpret_cast<const float4*>(smem_all + v * (2 * STB) + row * (D * 4) + (((c0 + c) ^ (row & (CH - 1))) * 16));
                 acc[c].x += f[v] * o.x; acc[c].y += f[v] * o.y; acc[c].z += f[v] * o.z; acc[c].w += f[v] * o.w;
             }
             acc[c].x *= inv; acc[c].y *= inv; acc[c].z *= inv; acc[c].w *= inv;
@@ -632,16 +721,16 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     if (a.splits > 1) {
         // ---- the column's results meet in the workspace ----------------------------------------------------------------------------------
         const int S = a.splits;
-        float* const cO = a.part + (int64_t)col * S * (32 * D);                       // [S][32][D], then [S][32] behind all columns
-        float* const cL = a.part + (int64_t)a.cols * S * (32 * D) + (int64_t)col * S * 32 * 2;   // (LSE, unused) pairs
-        float* const mine = cO + (int64_t)split * (32 * D) + row * D + 4 * c0;
-        if (r0 + row < R) {
+        float* const cO = a.part + (int64_t)col * S * (TR * D);                       // [S][TR][D], then [S][TR] behind all columns
+        float* const cL = a.part + (int64_t)a.cols * S * (TR * D) + (int64_t)col * S * TR * 2;   // (LSE, unused) pairs
+        float* const mine = cO + (int64_t)split * (TR * D) + row * D + 4 * c0;
+        if (finishes) {
 #pragma unroll
             for (int c = 0; c < CPL; ++c) {
                 st_agent(mine + 4 * c, acc[c].x, acc[c].y);
                 st_agent(mine + 4 * c + 2, acc[c].z, acc[c].w);
             }
-            if ((l & 15) == 0) st_agent(cL + (split * 32 + row) * 2, lse, 0.f);
+            if (l % LPR == 0) st_agent(cL + (split * TR + row) * 2, lse, 0.f);
         }
         wait_vm<0>();                               // this wavefront's results are where every XCD sees them
         __syncthreads();
@@ -652,7 +741,7 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
             *last_flag = last;
         }
         __syncthreads();
-        if (!*last_flag || r0 + row >= R) return;
+        if (!*last_flag || !finishes) return;
         M = -INFINITY;
         Lsum = 0.f;
 #pragma unroll
@@ -663,9 +752,9 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int i = min(i0 + u, S - 1);
-                lw[u] = ld_agent(cL + (i * 32 + row) * 2);
+                lw[u] = ld_agent(cL + (i * TR + row) * 2);
 #pragma unroll
-                for (int c = 0; c < 2 * CPL; ++c) ow[u][c] = ld_agent(cO + (int64_t)i * (32 * D) + row * D + 4 * c0 + 2 * c);
+                for (int c = 0; c < 2 * CPL; ++c) ow[u][c] = ld_agent(cO + (int64_t)i * (TR * D) + row * D + 4 * c0 + 2 * c);
             }
             float li[U], gm = M;
 #pragma unroll
@@ -699,7 +788,7 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     }
 
     const int rg = r0 + row;                        // the row this lane finishes
-    if (rg < R) {
+    if (finishes) {
         const int64_t oidx = ((int64_t)(rg / rps) * a.nq + (rg % rps) / a.G) * a.Hq + kvh * a.G + rg % a.G;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
@@ -707,43 +796,54 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
             if (a.bf16) *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.O) + oidx * D + d) = make_uint2(pack_bf16(acc[c].x, acc[c].y), pack_bf16(acc[c].z, acc[c].w));
             else *reinterpret_cast<float4*>(static_cast<float*>(a.O) + oidx * D + d) = acc[c];
         }
-        if ((l & 15) == 0 && a.LSE != nullptr) a.LSE[oidx] = lse;
+        if (l % LPR == 0 && a.LSE != nullptr) a.LSE[oidx] = lse;
     }
 }
 
-template <int D, bool PAGED, int CODES>
+template <int D, bool PAGED, int CODES, int TR>
 static hipError_t launch_small_t(const SmallArgs& a, hipStream_t s) {
-    constexpr int lds = SmallGeo<D>::LDS;
+    constexpr int lds = SmallGeo<D, TR>::LDS;
     static bool attr_set[64] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64 && !attr_set[dev]) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_small_kernel<D, PAGED, CODES>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_small_kernel<D, PAGED, CODES, TR>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         attr_set[dev] = true;
     }
-    fused_small_kernel<D, PAGED, CODES><<<(unsigned)(a.cols * a.splits), 64 * NWS, lds, s>>>(a);
+    const unsigned grid = a.per_xcd > 0 ? 8u * (unsigned)a.per_xcd : (unsigned)(a.cols * a.splits);
+    fused_small_kernel<D, PAGED, CODES, TR><<<grid, 64 * NWS, lds, s>>>(a);
     return hipGetLastError();
 }
 
-template <int D>
+template <int D, int TR>
 static hipError_t launch_small_d(const SmallArgs& a, hipStream_t s) {
     if constexpr (D == 128)      // (at D = 64 the vector-ALU kernel reads all 8-bit rows)
-        if (a.fp8 && !a.fp32_weights) return a.pg.table ? launch_small_t<D, true, 1>(a, s) : launch_small_t<D, false, 1>(a, s);
-    if (a.fp8) return a.pg.table ? launch_small_t<D, true, 2>(a, s) : launch_small_t<D, false, 2>(a, s);
-    return a.pg.table ? launch_small_t<D, true, 0>(a, s) : launch_small_t<D, false, 0>(a, s);
+        if (a.fp8 && !a.fp32_weights) return a.pg.table ? launch_small_t<D, true, 1, TR>(a, s) : launch_small_t<D, false, 1, TR>(a, s);
+    if (a.fp8) return a.pg.table ? launch_small_t<D, true, 2, TR>(a, s) : launch_small_t<D, false, 2, TR>(a, s);
+    return a.pg.table ? launch_small_t<D, true, 0, TR>(a, s) : launch_small_t<D, false, 0, TR>(a, s);
 }
 
-// Workspace floats the splits of a call need: [cols][splits][32][D] results, [cols][splits][32] pairs of (LSE, unused)
-size_t small_part_floats(int cols, int splits, int D) { return (size_t)cols * splits * 32 * (D + 2); }
+// Workspace floats the splits of a call need: [cols][splits][rows][D] results, [cols][splits][rows] pairs of (LSE, unused)
+size_t small_part_floats(int cols, int splits, int rows, int D) { return (size_t)cols * splits * rows * (D + 2); }
+
+// Workgroups of each XCD where KV heads can be dealt out to XCDs evenly (else 0): every eighth head, or 8 / Hkv XCDs per head
+int small_wgs_per_xcd(int tiles, int splits, int Hkv) {
+    if (Hkv % 8 == 0) return Hkv / 8 * tiles * splits;
+    if (8 % Hkv == 0) return (tiles * splits + 8 / Hkv - 1) / (8 / Hkv);
+    return 0;
+}
 
 hipError_t launch_fused_small(const SmallArgs& a, int D, hipStream_t s) {
     if (a.tiles < 1 || a.Hkv < 1 || a.splits < 1 || (D != 64 && D != 128)) return hipErrorInvalidValue;
+    if (a.per_xcd != small_wgs_per_xcd(a.tiles, a.splits, a.Hkv)) return hipErrorInvalidValue;
     if ((long long)a.tiles * a.Hkv != a.cols || (long long)a.cols * a.splits >= (1LL << 31)) return hipErrorInvalidValue;
     if (a.splits > 1 && (!a.part || !a.arrivals)) return hipErrorInvalidValue;
     if (a.pg.table && (a.pg.shift < 4 || a.pg.stride < 1 || a.pg.n_pages < 1)) return hipErrorInvalidValue;
-    return D == 128 ? launch_small_d<128>(a, s) : launch_small_d<64>(a, s);
+    if (a.rows != 16 && a.rows != 32) return hipErrorInvalidValue;
+    if (a.rows == 16) return D == 128 ? launch_small_d<128, 16>(a, s) : launch_small_d<64, 16>(a, s);
+    return D == 128 ? launch_small_d<128, 32>(a, s) : launch_small_d<64, 32>(a, s);
 }
 
 }  // namespace hg

@@ -151,8 +151,10 @@ struct SmallArgs {
     int max_len;
     int B, Hq, Hkv, G;
     int nq;
-    int tiles;                // 32-row tiles of the B * nq * G query rows of one KV head
+    int rows;                 // query rows of a column: 32 or 16
+    int tiles;                // that many rows at a time of the B * nq * G query rows of one KV head
     int cols;                 // tiles * Hkv columns
+    int per_xcd;              // workgroups per XCD (small_wgs_per_xcd; 0: in the order of their numbers)
     int splits;               // workgroups per column
     float* part;              // splits > 1: partial results (small_part_floats)
     unsigned* arrivals;       // splits > 1: [cols] counters that only ever count to `splits`, zero between calls
@@ -206,7 +208,8 @@ hipError_t launch_decode(const DecodeArgs& a, int D, int GT, hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeArgs& a, int D, hipStream_t s);   // matrix-core per-sequence kernel (8-bit rows: D = 128 only)
 hipError_t launch_merge(const MergeArgs& a, int D, bool in_bf16, bool out_bf16, hipStream_t s);
 hipError_t launch_fused_small(const SmallArgs& a, int D, hipStream_t s);
-size_t small_part_floats(int cols, int splits, int D);   // workspace floats of a split single launch
+int small_wgs_per_xcd(int tiles, int splits, int Hkv);
+size_t small_part_floats(int cols, int splits, int rows, int D);   // workspace floats of a split single launch
 hipError_t launch_mfma_loop(int iters, int random_operands, unsigned long long* clocks, float* sink, hipStream_t s);
 hipError_t launch_stream_read(const void* src, size_t bytes, float* sink, hipStream_t s);
 hipError_t launch_xcd_probe(int n_workgroups, int* out, hipStream_t s);

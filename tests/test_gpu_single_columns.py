@@ -1,0 +1,55 @@
+"""The single launch with columns of 16 and of 32 query rows, asked for by option, over every suffix cache: rows around the ends
+of a column, KV heads that are dealt out to the XCDs evenly and that are not, block boundaries inside a column, runs of
+stages that end in the shared rows and in the suffixes.  Against the fp64 oracle; without a workspace and with one (columns
+of paged and 8-bit calls are then split over workgroups); twice in a row with the same bits."""
+import sys
+
+import pytest
+import torch
+
+from paper_2402_05099_amd import binding as hb
+from paper_2402_05099_amd import device as dev
+from paper_2402_05099_amd import workloads as wl
+from parity import check, to_np
+from test_gpu_split_launch import reference
+
+pytestmark = pytest.mark.gpu
+
+# name: (B, query heads, KV heads, D, queries per sequence, levels (blocks, rows, sequences per block), suffix lengths)
+SHAPES = {
+    "one_row": (1, 1, 1, 128, 1, [(1, 1, 1)], 1, 1),
+    "rows_15": (15, 3, 3, 128, 1, [(1, 33, 15)], 1, 40),             # three KV heads: columns in the order of their numbers
+    "rows_17": (17, 2, 2, 64, 1, [(1, 300, 17)], 0, 33),
+    "rows_33": (11, 24, 8, 128, 1, [(1, 31, 11)], 1, 65),            # a sequence's rows cross the end of a column; one KV head per XCD
+    "group_of_5": (7, 10, 2, 128, 1, [(1, 97, 7)], 0, 90),
+    "group_of_32": (3, 64, 2, 128, 1, [(1, 40, 3)], 5, 64),
+    "queries": (9, 8, 8, 64, 5, [(1, 64, 9)], 2, 70),                # causal among the new tokens
+    "block_edges": (50, 4, 4, 128, 1, [(1, 20, 50), (7, 35, 7)], 0, 20),      # boundaries inside columns, a sequence no block covers
+    "no_shared": (40, 16, 16, 128, 1, [], 0, 50),                    # two KV heads per XCD
+    "shared_only_first": (20, 4, 1, 128, 1, [(1, 700, 20)], 0, 1),   # more shared stages than wavefronts, hardly a suffix
+}
+
+
+@pytest.mark.parametrize("cache", ["packed", "paged", "fp8", "paged_fp8_16"])
+@pytest.mark.parametrize("rows", [16, 32])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_columns(shape, rows, cache):
+    B, H, Hkv, D, nq, levels, lo, hi = SHAPES[shape]
+    print(f"columns: {shape} rows={rows} {cache}", file=sys.stderr, flush=True)
+    w = wl.make_workload(shape, 91, B, H, Hkv, D, levels, lo, hi, nq=nq)
+    dw = dev.to_device(w)
+    Oref, Lref, call = reference(w, cache)
+    for parts in (32, 0):
+        ctx = dev.make_context(dw, parts=parts) if parts else hb.Context(0, 0)
+        ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 2)
+        ctx.set_option(hb.HG_OPT_SUFFIX_TILE_ROWS, rows)
+        got = []
+        for _ in range(2):
+            O = torch.full(dw.lead + (dw.D,), float("nan"), dtype=torch.float32, device="cuda:0")
+            L = torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0")
+            call(ctx, dw, O, L)
+            got.append((O, L))
+        torch.cuda.synchronize()
+        check(to_np(got[0][0]), to_np(got[0][1]), Oref, Lref, f"{shape} rows={rows} {cache} parts={parts}")
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+        ctx.close()

@@ -216,12 +216,16 @@ struct MfmaTile {
 #pragma unroll
                 for (int kg = 0; kg < 2; ++kg)
                     r.S4[kg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k_fragment(sb + kaddr16[kg][s])), qf16[s], r.S4[kg], 0, 0, 0);
+            // (the wait states between a product and a read of its result: the compiler leaves them out where a branch lies
+            // between, as the one around the mask does)
+            asm volatile("s_nop 7" : "+v"(r.S4[0]), "+v"(r.S4[1]));
         } else {
 #pragma unroll
             for (int i = 0; i < 16; ++i) r.S[i] = 0.f;
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 r.S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k_fragment(sb + kaddr[s])), qf[s], r.S, 0, 0, 0);
+            asm volatile("s_nop 11" : "+v"(r.S));
         }
     }
 

@@ -183,10 +183,19 @@ struct SuffixStream {
     const unsigned char* kb;  // the next batch's first row
     const unsigned char* vb;
     const unsigned char* qp;  // the item's query row
+    // results that are kept (see below)
+    unsigned char *ring_rows, *more_rows;
+    int n_kept, kept_max;
 
     __device__ __forceinline__ SuffixStream(const CombinedArgs& c, unsigned char* sm, int l)
         : ca(c), a(c.d), lane(l), sub(l / LPR), rstride_b((unsigned)c.d.Hkv * D * ES), colb((unsigned)(l % LPR) * EPL * ES),
           subrow((unsigned)(l / LPR) * ((unsigned)c.d.Hkv * D * ES) + (unsigned)(l % LPR) * EPL * ES), smem(sm), queue(reinterpret_cast<queue_word*>(sm + kQueueOffset)) {
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int used = (kOrderOffset + (a.B <= kMaxOrdered ? 2 * a.B : 0) + 15) & ~15, more = (LDS_BYTES - used) / (NW * kRowBytes);
+        ring_rows = smem + w * (LDS_RING_BYTES / NW);
+        more_rows = smem + used + w * more * kRowBytes;
+        kept_max = kInRing + more;
+        n_kept = 0;
         no_more = 0;
         left = 0;
         first = 0;
@@ -335,12 +344,54 @@ struct SuffixStream {
                     consume_batch<D, 1, U, FP8, EPL>(st, cb.kv, sub, cb.left);
                     if (cb.left <= STEP) {
                         const int u = cb.unit & 0x7fffffff;
-                        decode_finish<D, 1, FP8, EPL>(st, a, 0, u / a.nchunks, u % a.nchunks, lane);
+                        if (n_kept < kept_max) keep(st, u);
+                        else decode_finish<D, 1, FP8, EPL>(st, a, 0, u / a.nchunks, u % a.nchunks, lane);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         } while (bt[NB - 1].left > 0);
+        write_kept();
+    }
+
+    // ---- results ------------------------------------------------------------------------------------------------------------
+    // Written one by one while the rows stream in, results cost the HBM far more time than their bytes: 8-bit suffixes of 32..128
+    // rows, 1024 x 40 heads, hardly a shared block: the last rows are read at 171 us, and at 147 without the writes, which
+    // are 2.5 % of the bytes.  So a wavefront keeps its results in LDS (the ring's, which this role does not need, and what is
+    // left behind the order of the sequences) and writes them when it has no more rows to read; one that finds no room is written at once.
+    // (Merging them right there with the parts of the shared levels, and passing over such rows in the merge kernel, was no
+    // faster: those parts have to come past the XCD's caches, in a phase as long as the merge kernel.)
+    // Measured, us: 1024 x 40 heads, 16K keys 494 -> 484; D = 64, 4K keys 187.8 -> 184.6; 2048 x 40, two levels 562 -> 549; 256 x 40, 2K keys 128.6 ->
+    // 127.3; 8-bit rows, 4K keys, where the shared block ends last, 233.4 -> 233.1 (hardly a shared block: 183 -> 170).
+    static constexpr int kRowBytes = D * 4 + 16;                          // O, LSE, index in the results
+    static constexpr int kInRing = LDS_RING_BYTES / NW / kRowBytes;       // results of a wavefront in the ring's memory
+    __device__ __forceinline__ unsigned char* kept_row(int i) const {
+        return i < kInRing ? ring_rows + i * kRowBytes : more_rows + (i - kInRing) * kRowBytes;
+    }
+
+    __device__ __forceinline__ void keep(const DecodeState<D, 1, EPL>& st, int unit) {
+        float M, l, o[EPL];
+        decode_combine<D, 1, EPL>(st, 0, M, l, o);
+        if (lane < LPR) {
+            unsigned char* const p = kept_row(n_kept);
+            const float inv = l > 0.f ? (FP8 ? a.v_scale / l : 1.0f / l) : 0.f;
+#pragma unroll
+            for (int j = 0; j < EPL; j += 4) *reinterpret_cast<float4*>(p + (lane * EPL + j) * 4) = make_float4(o[j] * inv, o[j + 1] * inv, o[j + 2] * inv, o[j + 3] * inv);
+            if (lane == 0) *reinterpret_cast<float2*>(p + D * 4) = make_float2(l > 0.f ? (M + __log2f(l)) * kLn2 : -INFINITY, __builtin_bit_cast(float, unit));
+        }
+        n_kept = __builtin_amdgcn_readfirstlane(n_kept + 1);
+    }
+
+    __device__ __forceinline__ void write_kept() const {
+        constexpr int LR = D / 4;                     // lanes per row
+        const int col = 4 * (lane % LR);
+        for (int i = lane / LR; i < n_kept; i += 64 / LR) {
+            const unsigned char* const p = kept_row(i);
+            const float2 info = *reinterpret_cast<const float2*>(p + D * 4);
+            const int unit = __builtin_bit_cast(int, info.y), row = unit / a.nchunks, c = unit % a.nchunks;
+            *reinterpret_cast<float4*>(static_cast<float*>(a.out.O) + (int64_t)c * a.out.part_stride_O + (int64_t)row * D + col) = *reinterpret_cast<const float4*>(p + col * 4);
+            if (col == 0) a.out.LSE[(int64_t)c * a.out.part_stride_L + row] = info.x;
+        }
     }
 };
 

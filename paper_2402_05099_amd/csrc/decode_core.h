@@ -326,27 +326,34 @@ __device__ __forceinline__ void block_of(const LevelDev& lv, int b, int B, int& 
     }
 }
 
-// Combines the 64/LPR key sub-streams of the wavefront and writes (O, LSE) of chunk c.
+// Combines the 64/LPR key sub-streams of the wavefront for query head g: maximum (0 if there is none), sum, and value sums.
+template <int D, int GT, int EPL>
+__device__ __forceinline__ void decode_combine(const DecodeState<D, GT, EPL>& st, int g, float& Ms, float& l, float (&o)[EPL]) {
+    constexpr int LPR = D / EPL;
+    float M = st.m[g];
+#pragma unroll
+    for (int off = LPR; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
+    Ms = (M == -INFINITY) ? 0.f : M;
+    const float f = __builtin_amdgcn_exp2f(st.m[g] - Ms);
+    l = st.l[g] * f;
+#pragma unroll
+    for (int off = LPR; off < 64; off <<= 1) l += __shfl_xor(l, off);
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) {
+        o[j] = st.acc[g][j] * f;
+#pragma unroll
+        for (int off = LPR; off < 64; off <<= 1) o[j] += __shfl_xor(o[j], off);
+    }
+}
+
+// Combines the sub-streams and writes (O, LSE) of chunk c.
 template <int D, int GT, bool FP8, int EPL>
 __device__ __forceinline__ void decode_finish(const DecodeState<D, GT, EPL>& st, const DecodeArgs& a, int bq, int h0, int c, int lane) {
     constexpr int LPR = D / EPL;
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
-        float M = st.m[g];
-#pragma unroll
-        for (int off = LPR; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
-        const float Ms = (M == -INFINITY) ? 0.f : M;
-        const float f = __builtin_amdgcn_exp2f(st.m[g] - Ms);
-        float l = st.l[g] * f;
-#pragma unroll
-        for (int off = LPR; off < 64; off <<= 1) l += __shfl_xor(l, off);
-        float o[EPL];
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) {
-            o[j] = st.acc[g][j] * f;
-#pragma unroll
-            for (int off = LPR; off < 64; off <<= 1) o[j] += __shfl_xor(o[j], off);
-        }
+        float Ms, l, o[EPL];
+        decode_combine<D, GT, EPL>(st, g, Ms, l, o);
         if (lane < LPR) {
             const float inv = l > 0.f ? (FP8 ? a.v_scale / l : 1.0f / l) : 0.f;
             const int64_t idx = (int64_t)bq * a.Hq + h0 + g;

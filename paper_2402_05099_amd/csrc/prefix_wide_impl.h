@@ -24,6 +24,7 @@
 //     from LDS four MFMAs before their use; the vector-ALU work is spread over the gaps between the MFMAs.  At D = 64 a
 //     stage has two 32-key score tiles: the same 16 MFMAs per step with twice the softmax work between them.
 #include <algorithm>
+#include <numeric>
 #include <type_traits>
 
 #include "hg_internal.h"
@@ -794,18 +795,37 @@ bool plan_prefix_wide(const LevelDev& lv, int Hkv, int G, int D, int max_parts, 
     // groups can fill them at the price of reading the block once more per group.  Both in units of the products' time on
     // all of the slots (a K/V row of 4 D bytes costs as much as multiplying it with 190 query rows: 4 D / 6 TB/s against
     // 4 D / 1.14 PFLOP/s per row): 4096 query rows on 24 CUs per XCD run as two teams of 8 tiles on 24 of them, not 16 on 16.
+    // That leaves out what a group costs where blocks are short or teams many: the column ends that fall inside a team's
+    // range, and the partial results, which every piece writes for its rows and the merge reads again (0.08 stages per piece
+    // and tile).  Where the price in stages with these finds a choice better by a twentieth, it is taken: 563 x 16/2
+    // heads, 395 keys, 4 queries 56.2 -> 41.9 us (18 tiles on 28 CUs instead of 9 three times), 614 x 64/8, 1892 keys 86.1 -> 73.4,
+    // 1024 x 8/1, 16K keys 86.5 -> 83.0 (8 columns of 4 tiles, cut evenly, instead of 5 of 7).  22 of 1500 drawn calls change, by
+    // 1.09 in the mean, none slower by more than 2 %; without the margin 58, some of them 7 % slower.  On fewer than 16 CUs per XCD the suffix
+    // decides, and these terms only disturb (267 x 64/8, 253 keys, 8-bit rows: 50.9 -> 53.7).
     {
         const int r0 = (mtiles + p.slots - 1) / p.slots;
-        double best = 0.0;
-        for (int r = r0; r <= mtiles && (r == r0 || (mtiles >= 8 && r <= 8 * r0)); ++r) {      // (few tiles: nothing to gain)
-            const int T = (mtiles + r - 1) / r;
-            const double cost = (double)r * T / mtiles * p.slots / (p.slots / T * T) + 190.0 * r / ((double)mtiles * kPrefixRowsWide);
-            if (r == r0 || cost < 0.97 * best) {
-                best = cost;
-                p.rowgroups = r;
-                p.T = T;
-            }
+        const int r_end = mtiles >= 8 ? std::min(mtiles, 8 * r0) : r0;      // (few tiles: nothing to gain)
+        const auto tiles_of = [&](int r) { return (mtiles + r - 1) / r; };
+        const auto busy = [&](int r, double read) {
+            const int T = tiles_of(r);
+            return (double)r * T / mtiles * p.slots / (p.slots / T * T) + read * r / ((double)mtiles * kPrefixRowsWide);
+        };
+        const auto stages = [&](int r) {
+            const int T = tiles_of(r);
+            const long long teams = 8 * (p.slots / T), cols = (long long)lv.n_blocks * Hkv * r;
+            const double even = (double)lv.n_blocks * Hkv * mtiles * ((lv.max_rows + KT - 1) / KT) / (8.0 * p.slots);
+            const double cuts = (double)(cols - std::gcd(cols, teams));
+            return busy(r, 100.0) * even + kWideBoundaryCost * cuts / teams +
+                   (D == 128 ? 0.08 : 0.02) * T * (std::max(teams, cols) + std::min(cuts, (double)teams));
+        };
+        int r1 = r0, r2 = r0;
+        for (int r = r0 + 1; r <= r_end; ++r) {
+            if ((r - 1) * tiles_of(r) >= mtiles) continue;      // the last group would be empty
+            if (busy(r, 190.0) < 0.97 * busy(r1, 190.0)) r1 = r;
+            if (stages(r) < 0.97 * stages(r2)) r2 = r;
         }
+        p.rowgroups = p.slots >= 16 && stages(r2) < 0.95 * stages(r1) ? r2 : r1;
+        p.T = tiles_of(p.rowgroups);
     }
     p.tpx = p.slots / p.T;
     p.n_c = (lv.max_rows + KT - 1) / KT;

@@ -113,6 +113,18 @@ def test_wide_plan_gives_ranges_of_equal_cost():
     assert hb.hg_debug_wide_plan(1, 4096, 512, 8, 8, 24, 32)["mode"] == 0
 
 
+@pytest.mark.parametrize("max_rows,max_seqs,Hkv,rps,slots,groups,tiles", [
+    (395, 563, 2, 32, 28, 4, 18), (389, 168, 8, 32, 28, 1, 21), (16384, 1024, 1, 8, 28, 8, 4),      # short blocks; ends inside ranges
+    (4096, 512, 8, 8, 16, 1, 16), (253, 267, 8, 8, 4, 5, 2), (16384, 1024, 40, 1, 20, 1, 4),         # as the products alone decide
+])
+def test_wide_plan_counts_pieces_when_it_groups_rows(max_rows, max_seqs, Hkv, rps, slots, groups, tiles):
+    plan = hb.hg_debug_wide_plan(1, max_rows, max_seqs, Hkv, rps, 24, slots)
+    assert (plan["rowgroups"], plan["T"]) == (groups, tiles)
+    assert (plan["rowgroups"] - 1) * plan["T"] < -(-max_seqs * rps // 256)
+    for ps in walk(plan).values():
+        assert sum(p[1] for p in ps) == plan["n_c"] and sorted(p[2] for p in ps) == list(range(len(ps)))
+
+
 def test_wide_plan_rejects_what_it_cannot_run():
     assert hb.hg_debug_wide_plan(1, 0, 100, 1, 1, 4, 32) is None      # no keys
     assert hb.hg_debug_wide_plan(1, 100, 100, 1, 1, 0, 32) is None     # no room for a result

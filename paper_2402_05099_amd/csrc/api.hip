@@ -386,14 +386,17 @@ int pick_wide_slots(double flops, double bytes, int T) {
 // tenth: it is the slower to catch up.  Measured calls at 4 / 8 / 12 / 16 / 20 / 24 CUs: 1024 x 40 heads, 16K keys:
 // - / 819 / 599 / 516 / 484 / 510; 4K keys, 8-bit cache: 433 / 245 / 219 / 223 / 229 / 246; 256 x 40 heads, 2K keys:
 // 132 / 138 / 139 / 141 / 147 / 150; 512 x 64/8 heads, 4K keys: 349 / 186 / 153 / 134 / 157 / 166; 128 x 32/8 heads, 2K keys, paged:
-// 46 / 52 / 55 / 60 / 64 / 69.
+// 46 / 52 / 55 / 60 / 64 / 69.  Where 4 would do, 5 are taken: the shared blocks end a fifth
+// earlier for the start-up of eight more workgroups, and 40 teams hold the columns of 40 KV heads whole.  4 / 5 CUs, us: 256 x 40 heads, 2K keys
+// 128.3 / 124.3; 267 x 64/8, 253 keys, 8-bit 51.4 / 41.9; 191 x 40, 699 keys, 8-bit 85.0 / 81.5; 1050 x 40, 78 keys, 8-bit paged 382.5 / 378.6; 32/8 heads, 515 keys 51.7 / 51.4; over 41 drawn calls
+// that had 4: 1.015 in the mean, the worst 0.8 % slower.
 int pick_combined_slots(double flops, double bytes, double pieces, int D, bool tiles) {
     static const double rate[] = {0.18, 0.36, 0.543, 0.693, 0.823, 0.895, 0.964, 1.0};      // on 4, 8, .., 32 CUs per XCD
     const double tp = flops / (D == 128 ? 1.14e15 : 0.63e15) * 1e6, ts = bytes / 6.0e12 * 1e6;
     const double end = ts + 0.65 * (tp + 13.0);
     auto shared_us = [&](int s) { return 1.2 * tp / rate[s / 4 - 1] + 13.0 + 7.0 * std::max(0.0, pieces / (8.0 * s) - 1.0); };
     for (int s = 4; s < 32; s += 4)
-        if (shared_us(s) <= (tiles ? 0.9 * end + 5.0 : end)) return s;
+        if (shared_us(s) <= (tiles ? 0.9 * end + 5.0 : end)) return std::max(s, 5);
     // the shared block decides: the most CUs that leave enough for the suffix meanwhile
     for (int s = 28; s > 16; s -= 4)
         if (ts <= 1.3 * (32 - s) / 32.0 * shared_us(s)) return s;

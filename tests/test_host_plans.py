@@ -281,3 +281,15 @@ def test_options_of_the_separate_kernels_ask_for_them():
     gqa = lambda **kw: hb.hg_debug_fused_plan([(1, 4096, 512)], 512, 1, 64, 8, 128, 512, **kw)
     assert gqa()["way"] == "combined"
     assert gqa(options={hb.HG_OPT_SUFFIX_ITEMS_PER_WAVE: 3})["way"] in ("one_stream", "two_streams")
+
+
+@pytest.mark.parametrize("shape", [([(1, 2048, 256)], 256, 40, 40, 256, 0, False), ([(1, 253, 267)], 267, 64, 8, 397, 0, True), ([(1, 515, 130)], 130, 32, 8, 665, 16, False)], ids=str)
+def test_combined_calls_bound_by_their_suffix_give_the_shared_levels_five_cus(shape):
+    """And never fewer, also where the workspace only just holds the parts."""
+    levels, B, Hq, Hkv, max_len, page, fp8 = shape
+    plan = hb.hg_debug_fused_plan(levels, B, 1, Hq, Hkv, 128, max_len, page, fp8)
+    assert (plan["way"], plan["slots"]) == ("combined", 5)
+    room = hb.hg_workspace_bytes(B, Hq, 128, plan["parts"])
+    assert hb.hg_debug_fused_plan(levels, B, 1, Hq, Hkv, 128, max_len, page, fp8, workspace_bytes=room) == plan
+    less = hb.hg_debug_fused_plan(levels, B, 1, Hq, Hkv, 128, max_len, page, fp8, workspace_bytes=hb.hg_workspace_bytes(B, Hq, 128, plan["parts"] - 1))
+    assert isinstance(less, int) or less["parts"] < plan["parts"]

@@ -48,6 +48,10 @@ extern "C" {
  * stream, 3 on two streams, 4 no keys at all; workgroups per column (way 0, else 0); partial results per row (0 for way 0); keys
  * per work item of the suffix kernel; work items per row; 1 if the suffix runs on the matrix cores; levels on the persistent
  * kernel (bit i: levels[i]); CUs per XCD of the persistent kernel, 0 if it does not run }.
+ *
+ * hg_debug_single_work: what a workgroup of a single launch works on, `tiles` columns per KV head with `splits` workgroups each:
+ * fills out[3] = { KV head, column of that head, split } and returns 1, or returns 0 if that workgroup has nothing to do or does
+ * not exist (there are tiles * splits * Hkv of them, rounded up to a multiple of 8).  Ids equal modulo 8 share an XCD.
  */
 int hg_debug_wide_plan(int n_blocks, int max_rows, int max_seqs, int Hkv, int rows_per_seq, int max_parts,
                        int slots_per_xcd, int D, int out[9]);
@@ -56,6 +60,7 @@ int hg_debug_wide_ranges(int n_blocks, int max_rows, int max_seqs, int Hkv, int 
 int hg_debug_suffix_plan(int B, int nq, int Hq, int Hkv, int D, int max_len, int page_size, int out[4]);
 int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const hg_level* levels, int B, int nq, int Hq, int Hkv, int D,
                         int max_len, int page_size, int fp8, size_t workspace_bytes, int out[8]);
+int hg_debug_single_work(int workgroup, int tiles, int splits, int Hkv, int out[3]);
 
 /*
  * What the chip sustains on the two resources the attention kernels are priced against (Sec. 4.2 and App. D.2 time

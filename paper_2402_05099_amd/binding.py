@@ -38,7 +38,7 @@ EXPORTS = (
     "hg_create", "hg_destroy", "hg_set_stream", "hg_set_option", "hg_workspace_bytes", "hg_prefix_attn",
     "hg_prefix_attn_grouped", "hg_suffix_attn", "hg_merge", "hg_hydragen_attn", "hg_naive_attn", "hg_read_stage_timings",
     "hg_strerror", "hg_suffix_attn_paged", "hg_hydragen_attn_paged", "hg_kv_append", "hg_kv_append_paged",
-    "hg_debug_wide_plan", "hg_debug_wide_ranges", "hg_debug_suffix_plan", "hg_debug_fused_plan", "hg_suffix_attn_fp8", "hg_hydragen_attn_fp8", "hg_kv_append_fp8",
+    "hg_debug_wide_plan", "hg_debug_wide_ranges", "hg_debug_suffix_plan", "hg_debug_fused_plan", "hg_debug_single_work", "hg_suffix_attn_fp8", "hg_hydragen_attn_fp8", "hg_kv_append_fp8",
     "hg_hydragen_attn_static", "hg_debug_mfma_loop", "hg_debug_stream_read", "hg_debug_xcd_of_workgroups",
 )
 
@@ -125,6 +125,8 @@ def lib() -> ctypes.CDLL:
         L.hg_debug_suffix_plan.restype = ci
         L.hg_debug_fused_plan.argtypes = [ctypes.POINTER(ci), ci, ci, ctypes.POINTER(hg_level)] + [ci] * 8 + [cs, ctypes.POINTER(ci)]
         L.hg_debug_fused_plan.restype = ci
+        L.hg_debug_single_work.argtypes = [ci] * 4 + [ctypes.POINTER(ci)]
+        L.hg_debug_single_work.restype = ci
         L.hg_debug_mfma_loop.argtypes = [vp, ci, ci, vp, vp]
         L.hg_debug_mfma_loop.restype = ci
         L.hg_debug_stream_read.argtypes = [vp, vp, cs, vp]
@@ -577,3 +579,9 @@ def hg_debug_xcd_of_workgroups(ctx: Context, out: torch.Tensor) -> None:
     """Enqueue out.numel() workgroups shaped like the persistent kernel's; workgroup i writes its XCD to out[i] (int32)."""
     _want(out, torch.int32, (out.numel(),), "out")
     _check(lib().hg_debug_xcd_of_workgroups(ctx.h, out.numel(), _p(out)), "hg_debug_xcd_of_workgroups")
+
+
+def hg_debug_single_work(workgroup: int, tiles: int, splits: int, Hkv: int):
+    """(KV head, column of that head, split) that a workgroup of a single launch works on, or None (host only)."""
+    out = (ctypes.c_int * 3)()
+    return tuple(out) if lib().hg_debug_single_work(workgroup, tiles, splits, Hkv, out) else None

@@ -1153,7 +1153,6 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         sa.rows = p.column_rows;
         sa.tiles = (B * nq * G + sa.rows - 1) / sa.rows;
         sa.cols = sa.tiles * Hkv;
-        sa.per_xcd = small_wgs_per_xcd(sa.tiles, p.splits, Hkv);
         sa.splits = p.splits;
         sa.part = reinterpret_cast<float*>(ws.p);
         sa.arrivals = p.splits > 1 ? c->counters + meeting_counter(p.splits) : nullptr;
@@ -1559,6 +1558,12 @@ int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const h
         if (p.index[i] == p.main_level || !out[7]) out[7] = p.plan[i].wp.slots;
     }
     return HG_OK;
+}
+
+int hg_debug_single_work(int workgroup, int tiles, int splits, int Hkv, int out[3]) {
+    if (workgroup < 0 || tiles < 1 || splits < 1 || Hkv < 1 || !out || (long long)tiles * splits * Hkv >= (1LL << 31) - 8) return 0;
+    if ((unsigned)workgroup >= hg::small_grid(tiles * splits * Hkv)) return 0;
+    return hg::small_work((unsigned)workgroup, tiles, splits, Hkv, out[0], out[1], out[2]) ? 1 : 0;
 }
 
 int hg_debug_mfma_loop(hg_ctx* c, int random_operands, int iters, unsigned long long* clocks, float* sink) {

@@ -147,26 +147,14 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     unsigned char* const smem = smem_all + w * (2 * STB);      // this wavefront's K slot, then its V slot
     const kargs_ptr k = (kargs_ptr)__builtin_amdgcn_kernarg_segment_ptr();
 
-    // Workgroups whose ids are equal modulo 8 run on one XCD: those of a KV head go to one (8 heads and more) or to its share of
-    // the eight, so that the shared rows of a head are read into one L2 or few instead of all.  (34 sequences x 32/8 heads,
-    // 10.5K keys, 16-row columns, three workgroups each: 57 -> 29 us; up to 4 MB of shared rows no difference.)
-    int kvh, unit;                                  // unit: (tile, split), tiles first
-    const int units = a.tiles * a.splits;           // of one KV head
-    if (a.per_xcd > 0) {
-        const int x = blockIdx.x & 7, i = blockIdx.x >> 3;
-        if (a.Hkv >= 8) {
-            kvh = x + 8 * (i / units);
-            unit = i % units;
-        } else {
-            kvh = x % a.Hkv;
-            unit = i * (8 / a.Hkv) + x / a.Hkv;
-            if (unit >= units) return;
-        }
-    } else {
-        kvh = blockIdx.x / units;
-        unit = blockIdx.x % units;
-    }
-    const int tile = unit % a.tiles, split = unit / a.tiles;
+    // Workgroups whose ids are equal modulo 8 run on one XCD: each XCD takes an eighth of the list (KV head, split, tile), so that
+    // the shared rows of a head are read into one L2 or few instead of all, whatever the number of heads.  Numbers of KV heads
+    // that neither divide 8 nor are a multiple of it, dealt out over all XCDs before: 64 sequences x 40/10 heads, 8K keys, paged
+    // 59.8 -> 33.6 us; 34 x 40/10, 10.5K keys, paged 50.3 -> 28.4; 56 x 24/12, 8574 keys, codes 45.9 -> 30.1.  The others, which had
+    // an order of their own to the same end: 1.005 in the mean over 117 calls.
+    int kvh, tile, split;
+    asm volatile("" ::"s"(a.nq), "s"(a.G), "s"(a.B), "s"(a.Q), "s"(a.lengths), "s"(a.offsets));      // (loaded with the rest, not behind the way out)
+    if (!small_work(blockIdx.x, a.tiles, a.splits, a.Hkv, kvh, tile, split)) return;
     const int col = kvh * a.tiles + tile;
     const int rps = a.nq * a.G;                     // query rows of one sequence for this KV head
     const int R = a.B * rps;
@@ -812,7 +800,7 @@ static hipError_t launch_small_t(const SmallArgs& a, hipStream_t s) {
         if (e != hipSuccess) return e;
         attr_set[dev] = true;
     }
-    const unsigned grid = a.per_xcd > 0 ? 8u * (unsigned)a.per_xcd : (unsigned)(a.cols * a.splits);
+    const unsigned grid = small_grid(a.cols * a.splits);
     fused_small_kernel<D, PAGED, CODES, TR><<<grid, 64 * NWS, lds, s>>>(a);
     return hipGetLastError();
 }
@@ -828,16 +816,8 @@ static hipError_t launch_small_d(const SmallArgs& a, hipStream_t s) {
 // Workspace floats the splits of a call need: [cols][splits][rows][D] results, [cols][splits][rows] pairs of (LSE, unused)
 size_t small_part_floats(int cols, int splits, int rows, int D) { return (size_t)cols * splits * rows * (D + 2); }
 
-// Workgroups of each XCD where KV heads can be dealt out to XCDs evenly (else 0): every eighth head, or 8 / Hkv XCDs per head
-int small_wgs_per_xcd(int tiles, int splits, int Hkv) {
-    if (Hkv % 8 == 0) return Hkv / 8 * tiles * splits;
-    if (8 % Hkv == 0) return (tiles * splits + 8 / Hkv - 1) / (8 / Hkv);
-    return 0;
-}
-
 hipError_t launch_fused_small(const SmallArgs& a, int D, hipStream_t s) {
     if (a.tiles < 1 || a.Hkv < 1 || a.splits < 1 || (D != 64 && D != 128)) return hipErrorInvalidValue;
-    if (a.per_xcd != small_wgs_per_xcd(a.tiles, a.splits, a.Hkv)) return hipErrorInvalidValue;
     if ((long long)a.tiles * a.Hkv != a.cols || (long long)a.cols * a.splits >= (1LL << 31)) return hipErrorInvalidValue;
     if (a.splits > 1 && (!a.part || !a.arrivals)) return hipErrorInvalidValue;
     if (a.pg.table && (a.pg.shift < 4 || a.pg.stride < 1 || a.pg.n_pages < 1)) return hipErrorInvalidValue;

@@ -136,6 +136,21 @@ constexpr int meeting_counter(int S) {        // the first counter for S workgro
     return at;
 }
 static_assert(meeting_counter(kSmallMaxSplits + 1) <= kContextCounters, "");
+// Workgroups of a single launch: XCD x (ids equal to x modulo 8) takes the x-th eighth of the list (KV head, split, tile), tiles
+// fastest.  false: nothing for this one.
+__host__ __device__ inline unsigned small_grid(int n) { return 8u * (((unsigned)n + 7u) / 8u); }      // n: entries of the list
+__host__ __device__ inline bool small_work(unsigned id, int tiles, int splits, int Hkv, int& kvh, int& tile, int& split) {
+    const unsigned of_head = (unsigned)(tiles * splits), n = of_head * (unsigned)Hkv, x = id & 7u;
+    const unsigned eighth = n >> 3, rest = n & 7u;       // x n / 8 without its 64 bits
+    const unsigned first = x * eighth + (x * rest >> 3), count = eighth + (((x + 1) * rest >> 3) - (x * rest >> 3));
+    if (id >> 3 >= count) return false;
+    const unsigned at = first + (id >> 3);
+    kvh = (int)(at / of_head);
+    const unsigned in_head = at - (unsigned)kvh * of_head;
+    split = (int)(in_head / (unsigned)tiles);
+    tile = (int)(in_head - (unsigned)split * (unsigned)tiles);
+    return true;
+}
 struct SmallArgs {
     const uint16_t* Q;
     int n_levels;
@@ -154,7 +169,6 @@ struct SmallArgs {
     int rows;                 // query rows of a column: 32 or 16
     int tiles;                // that many rows at a time of the B * nq * G query rows of one KV head
     int cols;                 // tiles * Hkv columns
-    int per_xcd;              // workgroups per XCD (small_wgs_per_xcd; 0: in the order of their numbers)
     int splits;               // workgroups per column
     float* part;              // splits > 1: partial results (small_part_floats)
     unsigned* arrivals;       // splits > 1: [cols] counters that only ever count to `splits`, zero between calls
@@ -208,7 +222,6 @@ hipError_t launch_decode(const DecodeArgs& a, int D, int GT, hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeArgs& a, int D, hipStream_t s);   // matrix-core per-sequence kernel (8-bit rows: D = 128 only)
 hipError_t launch_merge(const MergeArgs& a, int D, bool in_bf16, bool out_bf16, hipStream_t s);
 hipError_t launch_fused_small(const SmallArgs& a, int D, hipStream_t s);
-int small_wgs_per_xcd(int tiles, int splits, int Hkv);
 size_t small_part_floats(int cols, int splits, int rows, int D);   // workspace floats of a split single launch
 hipError_t launch_mfma_loop(int iters, int random_operands, unsigned long long* clocks, float* sink, hipStream_t s);
 hipError_t launch_stream_read(const void* src, size_t bytes, float* sink, hipStream_t s);

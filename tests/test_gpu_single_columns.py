@@ -1,5 +1,5 @@
 """The single launch with columns of 16 and of 32 query rows, asked for by option, over every suffix cache: rows around the ends
-of a column, KV heads that are dealt out to the XCDs evenly and that are not, block boundaries inside a column, runs of
+of a column, numbers of KV heads that divide the XCDs evenly and that do not, block boundaries inside a column, runs of
 stages that end in the shared rows and in the suffixes.  Against the fp64 oracle; without a workspace and with one (columns
 of paged and 8-bit calls are then split over workgroups); twice in a row with the same bits."""
 import sys
@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 # name: (B, query heads, KV heads, D, queries per sequence, levels (blocks, rows, sequences per block), suffix lengths)
 SHAPES = {
     "one_row": (1, 1, 1, 128, 1, [(1, 1, 1)], 1, 1),
-    "rows_15": (15, 3, 3, 128, 1, [(1, 33, 15)], 1, 40),             # three KV heads: columns in the order of their numbers
+    "rows_15": (15, 3, 3, 128, 1, [(1, 33, 15)], 1, 40),             # three KV heads: eighths that end inside a head
     "rows_17": (17, 2, 2, 64, 1, [(1, 300, 17)], 0, 33),
     "rows_33": (11, 24, 8, 128, 1, [(1, 31, 11)], 1, 65),            # a sequence's rows cross the end of a column; one KV head per XCD
     "group_of_5": (7, 10, 2, 128, 1, [(1, 97, 7)], 0, 90),

@@ -293,3 +293,18 @@ def test_combined_calls_bound_by_their_suffix_give_the_shared_levels_five_cus(sh
     assert hb.hg_debug_fused_plan(levels, B, 1, Hq, Hkv, 128, max_len, page, fp8, workspace_bytes=room) == plan
     less = hb.hg_debug_fused_plan(levels, B, 1, Hq, Hkv, 128, max_len, page, fp8, workspace_bytes=hb.hg_workspace_bytes(B, Hq, 128, plan["parts"] - 1))
     assert isinstance(less, int) or less["parts"] < plan["parts"]
+
+
+@pytest.mark.parametrize("tiles,splits,Hkv", [(1, 1, 1), (7, 1, 1), (3, 5, 1), (2, 3, 10), (5, 1, 3), (4, 5, 10), (4, 5, 12), (9, 1, 36), (13, 2, 8), (6, 1, 40), (1, 32, 5)])
+def test_single_launch_deals_heads_out_to_the_xcds(tiles, splits, Hkv):
+    """Every column and split once, the same number for every XCD, and the workgroups of a KV head side by side: on its share of the
+    XCDs (and the two that it may have in common with its neighbours) for any number of heads."""
+    grid = -(-tiles * splits * Hkv // 8) * 8
+    work = {i: hb.hg_debug_single_work(i, tiles, splits, Hkv) for i in range(grid)}
+    got = {w: i % 8 for i, w in work.items() if w}
+    assert sorted(got) == [(h, t, s) for h in range(Hkv) for t in range(tiles) for s in range(splits)] and len(got) == sum(w is not None for w in work.values())
+    assert hb.hg_debug_single_work(grid, tiles, splits, Hkv) is None
+    counts = [sum(x == y for y in got.values()) for x in range(8)]
+    assert max(counts) - min(counts) <= 1
+    for h in range(Hkv):
+        assert len({x for w, x in got.items() if w[0] == h}) <= -(-8 // Hkv) + 1

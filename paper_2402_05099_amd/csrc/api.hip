@@ -957,16 +957,16 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // taken below the other estimate, from 60 us on only when it is 25 % below (the model of the separate kernels is
     // pessimistic where suffixes and shared blocks overlap): over the 520 calls 0.4 % slower than the better way each time.
     // Measured single / other way: 9.3 / 17 us (12 x 64/8 heads, D = 64, 1261 keys, codes), 13.1 / 35 (53 x 8/1, 1268 + 5 x 289 keys,
-    // codes), 28 / 53 (34 x 32/8, 10.5K keys), 45 / 22 (428 x 64/8, no shared keys, codes, paged: not taken), 52 / 44 (216 x 32/8, 5K keys,
-    // codes: taken, one of the eleven that miss by more than a tenth).
+    // codes), 28 / 53 (34 x 32/8, 10.5K keys), 45 / 22 (428 x 64/8, no shared keys, codes, paged: not taken), 73 / 45 (268 x 16/16, 4648 keys,
+    // 35 rows, paged: taken, one of the eleven that miss by more than a tenth).
     // (the single launch divides sums by the V scale and multiplies them again: not with scales near the ends of fp32)
     const bool odd_scale = f.fp8 && has_suffix && !(f.v_scale >= 0x1p-60f && f.v_scale <= 0x1p60f);
-    bool take_single = false;
+    bool take_single = false, combined_wins = false;      // (over the single launch, if there is room for it)
     if (c->opt_fused_kernel != 1 && !c->opt_timing && !odd_scale) {
         const int rps = nq * G;
         const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma;
         long long shared_keys = 0;
-        double flops = 0.0, shared_bytes = 0.0;
+        double flops = 0.0, padded = 0.0, shared_bytes = 0.0;      // padded: flops with whole 256-row tiles
         // wide: a level runs on the persistent kernel otherwise; joins: and shares its launch with the suffix, or could if that were longer
         bool any = has_suffix, wide = false;
         int nonempty = 0;
@@ -975,6 +975,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             if (levels[i].max_rows > 0 && seqs > 0) {
                 shared_keys += levels[i].max_rows;
                 flops += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * seqs * nq * Hq * D;
+                padded += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * ((seqs * rps + kPrefixRowsWide - 1) / kPrefixRowsWide * kPrefixRowsWide) * Hkv * D;
                 shared_bytes += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * Hkv * D;
                 any = true;
                 wide = wide || seqs * rps > kPrefixRowsNarrow;
@@ -1045,7 +1046,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             }
         }
         const double suffix_us = has_suffix ? (f.fp8 ? 2.0 : 4.0) * B * (0.75 * max_len) * Hkv * D / 5.0e6 : 0.0;      // at 5 TB/s
-        const double shared_us = shared_bytes / 5.0e6;
+        const double shared_us = shared_bytes / 5.0e6, part_us = 4.0 * B * nq * Hq * (double)D / 5.0e6;      // (one partial result of every row)
         const double est_single = std::max(chain_at(rows, splits), (paged ? 1.5 : 1.2) * suffix_us + shared_us + 6.0);
         const double sfx_alone = suffix_us * (sfx_mfma || rps == 1 ? 1.0 : 0.5 * rps);
         double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
@@ -1053,6 +1054,14 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         if (light && nonempty > 0) est_separate -= 6.0;
         if (nonempty == 0) est_separate = 10.5 + 0.7 * sfx_alone;      // the suffix kernel alone: no event edges, hardly a merge
         if (suffix_us >= 30.0 && joins && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
+        // The combined launch by a price of its own, where many columns walk one long shared block with a workgroup each and the two
+        // estimates above are within their error: codes, and few rows per KV head with a suffix of some length.  Single / combined, us:
+        // 216 x 32/8 heads, 5K keys, up to 128 codes 47.7 / 40.3; 150 x 32/8, 4.5K keys, 100 codes 44.9 / 34.9; 104 x 64/8, 5319 keys,
+        // 154 codes 48.2 / 40.6; 106 x 32/8, 3189 keys, 475 rows, paged 45.3 / 39.6.  The 114 of 50000 drawn calls that it moves: 0.84 in the mean,
+        // eight more than 3 % slower.  (Over calls of every kind this price would send as many to the slower way as to the faster.)
+        const double tiles_us = padded / 1.1e9, combined_us = 24.0 + 0.5 * suffix_us + (D == 128 ? 0.9 : 1.2) * tiles_us + 4.0 * part_us;
+        combined_wins = may_combine && wide && nonempty == 1 && splits == 1 && tiles_us >= 5.0 && shared_keys >= 1600 &&
+                                   (f.fp8 ? est_single > 1.05 * combined_us : rps <= 4 && suffix_us >= 10.0 && est_single > 1.1 * combined_us);
         // (light calls: the separate kernels keep all but the clearest; single / separate over four drawn ones 12 / 18, 15 / 20, 18 / 21, 43 / 49)
         const bool small = est_single <= (light ? 0.6 : est_single <= 60.0 ? 1.0 : 0.75) * est_separate;
         if (own_memory) {
@@ -1075,7 +1084,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
 
     // The levels on the persistent kernel share the suffix's launch, provided that one has more than 128 query rows; the
     // others, and more than a few, go before it.
-    if (may_combine && !take_single && c->opt_prefix_kernel != 1) {
+    if (may_combine && (!take_single || combined_wins) && c->opt_prefix_kernel != 1) {
         bool large = false;
         for (int i = 0; i < n_levels; ++i)
             large = large || (levels[i].max_rows > 0 && (double)(levels[i].kv_off ? levels[i].max_seqs : B) * nq * G > kPrefixRowsNarrow);

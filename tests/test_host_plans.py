@@ -308,3 +308,19 @@ def test_single_launch_deals_heads_out_to_the_xcds(tiles, splits, Hkv):
     assert max(counts) - min(counts) <= 1
     for h in range(Hkv):
         assert len({x for w, x in got.items() if w[0] == h}) <= -(-8 // Hkv) + 1
+
+
+@pytest.mark.parametrize("shape,way", [
+    (([(1, 5000, 216)], 216, 32, 8, 64, 0, True), "combined"), (([(1, 5000, 216)], 216, 32, 8, 128, 0, True), "combined"), (([(1, 5000, 216)], 216, 32, 8, 200, 0, True), "combined"),
+    (([(1, 4500, 150)], 150, 32, 8, 100, 0, True), "combined"), (([(1, 5000, 180)], 180, 32, 8, 150, 0, True), "combined"),
+    (([(1, 3189, 106)], 106, 32, 8, 475, 16, False), "combined"),
+    (([(1, 8192, 64)], 64, 40, 10, 100, 16, False), "single"), (([(1, 10500, 34)], 34, 32, 8, 100, 16, False), "single"), (([(1, 1026, 341)], 341, 32, 8, 20, 0, True), "single"),
+], ids=str)
+def test_combined_launch_is_priced_beside_the_single_one(shape, way):
+    """Many columns that walk one long shared block with a workgroup each (48 against 40 us and the like); fewer, whose blocks several
+    workgroups share, stay in the single launch.  Only the workspace may refuse a call, whichever way it would take."""
+    levels, B, Hq, Hkv, max_len, page, fp8 = shape
+    call = lambda **kw: hb.hg_debug_fused_plan(levels, B, 1, Hq, Hkv, 128, max_len, page, fp8, **kw)      # noqa: E731
+    assert call()["way"] == way
+    assert call(workspace_bytes=hb.hg_workspace_bytes(B, Hq, 128, 2))["way"] in ("single", "combined")
+    assert call(workspace_bytes=hb.hg_workspace_bytes(B, Hq, 128, 1)) == hb.HG_ERR_WORKSPACE

@@ -3,7 +3,7 @@
 back here, to the same checks in Python.
 
 PyTorch is used for device memory and streams; every step of the attention path runs in the HIP kernels of
-the shared library.  There is no fallback: if the library is missing or fails to load, importing the symbols
+the shared library.  There is no fallback for it: if the library is missing or fails to load, importing the symbols
 works but the first call raises.
 """
 from __future__ import annotations
@@ -11,6 +11,7 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import os
+import warnings
 from dataclasses import dataclass
 from typing import List, Optional, Sequence
 
@@ -143,22 +144,38 @@ def lib() -> ctypes.CDLL:
 
 # The native marshalling of the decode-step calls: what each returns is the library's code, or None for arguments that it
 # leaves to the checks below.
+MARSHAL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal.so")
 _native = None
 
 
+class _PythonOnly:
+    """Leaves every call to the checks below."""
+
+    @staticmethod
+    def _none(*args):
+        return None
+
+    attn = attn_fp8 = attn_paged = append = append_fp8 = append_paged = _none
+
+
 def native():
-    """Load _marshal.so (built with the library) and hand it the library's functions; raises if it is not there."""
+    """_marshal.so (built with the library) with the library's functions; where it cannot be loaded (not built, another PyTorch) a warning, once,
+    and the calls go through the checks in Python, which take a few microseconds longer."""
     global _native
     if _native is None:
-        path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal.so")
-        if not os.path.exists(path):
-            raise RuntimeError(f"{path} is missing: build it with `python -m paper_2402_05099_amd.build`")
         L = lib()
-        spec = importlib.util.spec_from_file_location("_marshal", path)
-        m = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(m)
-        fns = (L.hg_hydragen_attn, L.hg_hydragen_attn_fp8, L.hg_hydragen_attn_paged, L.hg_kv_append, L.hg_kv_append_fp8, L.hg_kv_append_paged)
-        m.setup([ctypes.cast(f, ctypes.c_void_p).value for f in fns], Level, PagedKV)
+        try:
+            spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
+            m = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(m)
+            if torch.__version__.split("+")[0] != m.torch_version:
+                raise ImportError(f"{MARSHAL_PATH} was built with PyTorch {m.torch_version}")
+        except ImportError as e:
+            warnings.warn(f"decode-step calls are marshalled in Python: {e} (build it with `python -m paper_2402_05099_amd.build`)", RuntimeWarning)
+            m = _PythonOnly
+        else:
+            fns = (L.hg_hydragen_attn, L.hg_hydragen_attn_fp8, L.hg_hydragen_attn_paged, L.hg_kv_append, L.hg_kv_append_fp8, L.hg_kv_append_paged)
+            m.setup([ctypes.cast(f, ctypes.c_void_p).value for f in fns], Level, PagedKV)
         _native = m
     return _native
 

@@ -2,14 +2,15 @@
 // binding.py on the tensors, their device pointers, and the call into libhydragen.so, whose functions it is handed as addresses.
 //
 // Why native: such a call is one to three kernel launches of a few microseconds each, and checking a dozen tensors
-// attribute by attribute in Python took longer than the kernels.  4 sequences x 4 heads, 128 shared keys: 10.2 us a call through
-// Python, 6.0 through this (the kernel's own time); the same with a cache update before it 21 -> 10.
+// attribute by attribute in Python took longer than the kernels.  4 sequences x 4 heads, 128 shared keys: 10.0 us a call through
+// Python, 5.4 through this (the kernel's own time); a decode step of the same size (copy of the lengths, cache update, attention) 20.2 -> 10.3.
 //
 // Every function returns the library's return code, or None where anything about the arguments is not plainly as the call
 // wants it (another type, a wrong shape, a tensor that is not an ordinary one): binding.py then goes through its own
 // checks, which say what is wrong or accept it.  Nothing is kept from one call for the next.
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <climits>
 
@@ -356,5 +357,11 @@ PyMODINIT_FUNC PyInit__marshal(void) {
         {&s_k_scale, "k_scale"}, {&s_v_scale, "v_scale"}};
     for (auto& n : names)
         if (!(*n.s = PyUnicode_InternFromString(n.text))) return nullptr;
-    return PyModule_Create(&module);
+    PyObject* const m = PyModule_Create(&module);
+    // (binding.py compares it: another version's tensors may be laid out in another way)
+    if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }

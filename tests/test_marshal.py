@@ -1,6 +1,7 @@
 """The native marshalling of the decode-step calls (csrc/marshal.cpp): what the checks in Python refuse it never passes on,
 what they accept works through either, with the same results."""
 import types
+import warnings
 
 import pytest
 import torch
@@ -29,6 +30,23 @@ def test_refusals_are_those_of_python():
                  lambda: hb.hg_kv_append_fp8(None, q, q, q, q, 1.0, 1.0, n, n, 1), lambda: hb.hg_kv_append_paged(None, q, q, kv, n, 1)):
         with pytest.raises(TypeError, match="need a contiguous device tensor"):
             call()
+
+
+@pytest.mark.parametrize("missing", [True, False])
+def test_without_the_extension_calls_go_through_python(missing, monkeypatch, tmp_path):
+    """Not built, or built with another PyTorch: a warning, once, and the checks in Python."""
+    if missing:
+        monkeypatch.setattr(hb, "MARSHAL_PATH", str(tmp_path / "_marshal.so"))
+    else:
+        monkeypatch.setattr(torch, "__version__", "1.0.0")
+    monkeypatch.setattr(hb, "_native", None)
+    q = torch.zeros(2, 2, 64, dtype=torch.bfloat16)
+    n = torch.zeros(2, dtype=torch.int32)
+    with pytest.warns(RuntimeWarning, match="_marshal.so"), pytest.raises(TypeError, match="need a contiguous device tensor"):
+        hb.hg_hydragen_attn(None, q, [], q, q, n, n, 1, q)
+    with warnings.catch_warnings(), pytest.raises(TypeError, match="need a contiguous device tensor"):
+        warnings.simplefilter("error")
+        hb.hg_kv_append(None, q, q, q, q, n, n, 1)
 
 
 @pytest.mark.gpu

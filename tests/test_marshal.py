@@ -65,23 +65,25 @@ def test_same_results_through_either(cache, nq, monkeypatch):
     off = torch.arange(B, dtype=torch.int32, device="cuda:0") * cap
     table = torch.arange(B * 2, dtype=torch.int32, device="cuda:0").view(B, 2)
 
-    def step(plain):
+    def step(levels, count_known):
         ctx = hb.Context(0, hb.hg_workspace_bytes(B * nq, H, D, 8))
+        if count_known:      # (else the first call sets the context's count of queries, in Python)
+            ctx.set_option(hb.HG_OPT_NUM_QUERIES, nq)
+            ctx._nq = nq
         K, V = (x.clone() for x in rows)
         n = torch.tensor([0, 3, 9, 20, 29], dtype=torch.int32, device="cuda:0")
         O, L = torch.zeros_like(Q), torch.zeros(lead, device="cuda:0")
-        lv, scale = (levels, 0.125) if plain else (tuple(levels), 0.125)
-        ks = 1.0 / 64 if plain else 1 / 64
+        ks, scale = 1.0 / 64, 0.125
         if cache == "packed":
             hb.hg_kv_append(ctx, Kn, Vn, K, V, off, n, cap)
-            hb.hg_hydragen_attn(ctx, Q, lv, K, V, off, n, cap, O, L, scale)
+            hb.hg_hydragen_attn(ctx, Q, levels, K, V, off, n, cap, O, L, scale)
         elif cache == "fp8":
             hb.hg_kv_append_fp8(ctx, Kn, Vn, K, V, ks, ks, off, n, cap)
-            hb.hg_hydragen_attn_fp8(ctx, Q, lv, K, V, ks, ks, off, n, cap, O, L, scale)
+            hb.hg_hydragen_attn_fp8(ctx, Q, levels, K, V, ks, ks, off, n, cap, O, L, scale)
         else:
             kv = hb.PagedKV(K, V, table, 16)
             hb.hg_kv_append_paged(ctx, Kn, Vn, kv, n, cap)
-            hb.hg_hydragen_attn_paged(ctx, Q, lv, kv, n, cap, O, L, scale)
+            hb.hg_hydragen_attn_paged(ctx, Q, levels, kv, n, cap, O, L, scale)
         torch.cuda.synchronize()
         ctx.close()
         return O, L, K, V, n
@@ -91,12 +93,15 @@ def test_same_results_through_either(cache, nq, monkeypatch):
     names = ("attn", "attn_fp8", "attn_paged", "append", "append_fp8", "append_paged")
     watch = types.SimpleNamespace(**{f: (lambda f: lambda *a: taken.append((f, getattr(m, f)(*a))) or taken[-1][1])(f) for f in names})
     monkeypatch.setattr(hb, "_native", watch)
-    first = step(True)
+    first = step(levels, True)
     suffix = {"packed": "", "fp8": "_fp8", "paged": "_paged"}[cache]
-    # (several queries: the first call sets the context's count of them and goes through Python)
-    assert taken == [("append" + suffix, 0 if nq == 1 else None), ("attn" + suffix, 0)]
+    assert taken == [("append" + suffix, 0), ("attn" + suffix, 0)]
+    monkeypatch.setattr(hb, "_native", hb._PythonOnly)
+    second = step(levels, True)
+    monkeypatch.setattr(hb, "_native", watch)
     taken.clear()
-    second = step(False)
-    assert taken[-1] == ("attn" + suffix, None)
-    for a, b in zip(first, second):
-        assert torch.equal(a, b)
+    third = step(tuple(levels), False)      # (levels in a tuple are left to Python too)
+    assert taken == [("append" + suffix, 0 if nq == 1 else None), ("attn" + suffix, None)]
+    for other in (second, third):
+        for a, b in zip(first, other):
+            assert torch.equal(a, b)

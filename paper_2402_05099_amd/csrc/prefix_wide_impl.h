@@ -806,25 +806,30 @@ bool plan_prefix_wide(const LevelDev& lv, int Hkv, int G, int D, int max_parts, 
         const int r0 = (mtiles + p.slots - 1) / p.slots;
         const int r_end = mtiles >= 8 ? std::min(mtiles, 8 * r0) : r0;      // (few tiles: nothing to gain)
         const auto tiles_of = [&](int r) { return (mtiles + r - 1) / r; };
-        const auto busy = [&](int r, double read) {
-            const int T = tiles_of(r);
-            return (double)r * T / mtiles * p.slots / (p.slots / T * T) + read * r / ((double)mtiles * kPrefixRowsWide);
-        };
-        const auto stages = [&](int r) {
-            const int T = tiles_of(r);
+        const double row = (double)mtiles * kPrefixRowsWide, even = (double)lv.n_blocks * Hkv * mtiles * ((lv.max_rows + KT - 1) / KT) / (8.0 * p.slots);
+        // the price of r groups in stages; `idle`: their products' time.  (The divisors last: they decide only where the rest is not too much.)
+        const auto stages = [&](int r, int T, double idle, double limit) {
             const long long teams = 8 * (p.slots / T), cols = (long long)lv.n_blocks * Hkv * r;
-            const double even = (double)lv.n_blocks * Hkv * mtiles * ((lv.max_rows + KT - 1) / KT) / (8.0 * p.slots);
-            const double cuts = (double)(cols - std::gcd(cols, teams));
-            return busy(r, 100.0) * even + kWideBoundaryCost * cuts / teams +
-                   (D == 128 ? 0.08 : 0.02) * T * (std::max(teams, cols) + std::min(cuts, (double)teams));
+            const double piece = (D == 128 ? 0.08 : 0.02) * T, most = (double)std::max(teams, cols), read = (idle + 100.0 * r / row) * even;
+            if (read + piece * most >= limit) return limit;
+            const double cuts = (double)(cols - std::gcd((int)(cols % teams), (int)teams));
+            return read + kWideBoundaryCost * cuts / teams + piece * (most + std::min(cuts, (double)teams));
         };
+        const bool priced = p.slots >= 16;
         int r1 = r0, r2 = r0;
-        for (int r = r0 + 1; r <= r_end; ++r) {
-            if ((r - 1) * tiles_of(r) >= mtiles) continue;      // the last group would be empty
-            if (busy(r, 190.0) < 0.97 * busy(r1, 190.0)) r1 = r;
-            if (stages(r) < 0.97 * stages(r2)) r2 = r;
+        double best1 = 1e300, best2 = 1e300, price1 = 1e300;      // (price1: of r1, by stages)
+        for (int r = r0; r <= r_end; ++r) {
+            const int T = tiles_of(r);
+            if ((r - 1) * T >= mtiles) continue;      // the last group would be empty
+            const double idle = (double)r * T / mtiles * p.slots / (p.slots / T * T), cost = idle + 190.0 * r / row;
+            const bool better = cost < 0.97 * best1;
+            if (better) { r1 = r; best1 = cost; }
+            if (!priced || r_end == r0) continue;
+            const double price = stages(r, T, idle, better ? 1e300 : 0.97 * best2);
+            if (better) price1 = price;
+            if (price < 0.97 * best2) { r2 = r; best2 = price; }
         }
-        p.rowgroups = p.slots >= 16 && stages(r2) < 0.95 * stages(r1) ? r2 : r1;
+        p.rowgroups = best2 < 0.95 * price1 ? r2 : r1;
         p.T = tiles_of(p.rowgroups);
     }
     p.tpx = p.slots / p.T;

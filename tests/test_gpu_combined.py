@@ -93,6 +93,35 @@ def test_combined(shape, cache):
     ctx.close()
 
 
+@pytest.mark.parametrize("cache", ["packed", "paged", "fp8", "paged_fp8"])
+@pytest.mark.parametrize("B,H,D", [(200, 480, 128), (2400, 40, 128), (15000, 7, 128), (200, 880, 64), (4200, 40, 64), (15360, 9, 64)])
+def test_combined_more_results_than_a_wavefront_keeps(B, H, D, cache):
+    """More work items per wavefront than results fit its LDS: in the 16 KiB of the ring's memory, then behind the order of the sequences (7, 6 and
+    no rows at D = 128, 14, 10 and none at D = 64), then each written at once."""
+    row = 4 * D + 16
+    kept = 16384 // row + max(0, 32768 - 512 - 2 * B) // (8 * row)
+    assert B * H > 1.1 * 2048 * kept
+    print(f"combined, results: {cache} B={B} H={H} D={D} {kept} kept", file=sys.stderr, flush=True)
+    w = wl.make_workload("kept", 79, B, H, H, D, [(1, 33, B)], 1, 3)
+    dw = dev.to_device(w)
+    Oref, Lref, call = reference(w, cache)
+    ctx = dev.make_context(dw, parts=8)
+    ctx.set_option(hb.HG_OPT_WIDE_SLOTS, 4)
+    plan = hb.hg_debug_fused_plan([(1, 33, B)], B, 1, H, H, D, dw.max_len, {"paged": 16, "paged_fp8": 32}.get(cache, 0), "fp8" in cache,
+                                  hb.hg_workspace_bytes(B, H, D, 8), {hb.HG_OPT_FUSED_KERNEL: 1, hb.HG_OPT_WIDE_SLOTS: 4})
+    assert plan["way"] == "combined" and plan["nchunks"] == 1, plan
+    got = []
+    for _ in range(2):
+        O = torch.full(dw.lead + (dw.D,), float("nan"), dtype=torch.float32, device="cuda:0")
+        L = torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0")
+        call(ctx, dw, O, L)
+        got.append((O, L))
+    torch.cuda.synchronize()
+    check(to_np(got[0][0]), to_np(got[0][1]), Oref, Lref, f"kept results {cache} B={B} H={H} D={D}")
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    ctx.close()
+
+
 @pytest.mark.parametrize("shape", ["many_items", "tile_items", "tile_items_g4"])
 def test_combined_capture(shape):
     """Captured once, replayed with eager calls and other inputs in between: every replay leaves its counters at zero."""

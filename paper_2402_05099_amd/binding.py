@@ -575,6 +575,8 @@ def hg_debug_fused_plan(levels, B: int, nq: int, Hq: int, Hkv: int, D: int, max_
         return rc
     plan = dict(zip(("way", "splits", "parts", "chunk", "nchunks", "mfma", "wide_levels", "slots"), list(out)))
     plan["way"] = ("single", "combined", "one_stream", "two_streams", "fill")[plan["way"]]
+    if plan["way"] == "single":
+        plan["column_rows"], plan["chunk"] = plan["chunk"], 0
     return plan
 
 

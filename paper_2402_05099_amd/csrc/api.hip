@@ -1557,7 +1557,7 @@ int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const h
     out[0] = p.way;
     out[1] = single ? p.splits : 0;
     out[2] = single ? 0 : p.np;
-    out[3] = single ? 0 : p.sp.chunk;
+    out[3] = single ? p.column_rows : p.sp.chunk;
     out[4] = single ? 0 : p.sp.nchunks;
     out[5] = !single && p.sp.nchunks > 0 && p.sp.mfma ? 1 : 0;
     out[6] = out[7] = 0;

@@ -324,3 +324,24 @@ def test_combined_launch_is_priced_beside_the_single_one(shape, way):
     assert call()["way"] == way
     assert call(workspace_bytes=hb.hg_workspace_bytes(B, Hq, 128, 2))["way"] in ("single", "combined")
     assert call(workspace_bytes=hb.hg_workspace_bytes(B, Hq, 128, 1)) == hb.HG_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("shape,rows,splits", [
+    (([(1, 128, 4)], 4, 1, 4, 4, 64, 16), 16, 1), (([(1, 515, 45)], 45, 1, 16, 2, 128, 150), 16, 1), (([(1, 515, 95)], 95, 2, 16, 2, 128, 60), 16, 1),
+    (([(1, 300, 139)], 139, 4, 64, 8, 128, 64), 32, 1),                                             # twice the columns would take two rounds
+    (([(1, 3000, 60)], 60, 1, 16, 2, 128, 100, 16), 16, 4), (([(1, 4000, 100)], 100, 1, 32, 8, 128, 60, 16), 32, 2), (([(1, 9000, 20)], 20, 1, 16, 2, 128, 60, 0, True), 16, 12),
+], ids=str)
+def test_rows_and_workgroups_of_the_single_launch(shape, rows, splits):
+    """What the library chooses by itself; a workspace that just holds the results of that many workgroups per column keeps the choice, a byte less does not."""
+    levels, B, nq, Hq, Hkv, D = shape[:6]
+    plan = hb.hg_debug_fused_plan(*shape)
+    assert (plan["way"], plan["column_rows"], plan["splits"]) == ("single", rows, splits)
+    if splits > 1:
+        cols = -(-B * nq * Hq // Hkv // rows) * Hkv
+        room = cols * splits * rows * (D + 2) * 4
+        assert hb.hg_debug_fused_plan(*shape, workspace_bytes=room) == plan
+        assert hb.hg_debug_fused_plan(*shape, workspace_bytes=room - 1) != plan
+    # asked for by option
+    for asked in (16, 32):
+        forced = hb.hg_debug_fused_plan(*shape, options={hb.HG_OPT_FUSED_KERNEL: 2, hb.HG_OPT_SUFFIX_TILE_ROWS: asked})
+        assert (forced["way"], forced["column_rows"]) == ("single", asked)

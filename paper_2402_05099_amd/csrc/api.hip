@@ -941,8 +941,9 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
     // column of 32 or 16 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two
     // event edges and a round trip of the partial results through HBM for the separate kernels.  Both durations are
-    // estimated, in microseconds, from fits to 520 calls (B = 4 .. 2048, 0 .. 16K shared keys, every cache and head layout, each
-    // with 16 and 32 rows and every number of workgroups per column; mean error of an estimate 9 %):
+    // estimated, in microseconds, from fits to 520 calls (B = 4 .. 2048, 0 .. 16K shared keys, every cache, KV heads that divide 8
+    // or are a multiple of it, each with 16 and 32 rows and every number of workgroups per column; mean error of an estimate 9 %; over
+    // 87 calls with other numbers of heads the choice is 0.88 of the other way's time in the mean, over 117 of the former 0.84):
     //   single launch: a + rounds x (b + c x stages per wavefront), c growing with the CUs that are busy (they share the L2s), 1.4
     //                  times that for 8-bit rows with fp32 weights; m0 + m1 x splits more when a column's workgroups have to
     //                  meet; constants below.  Never faster than the suffix rows stream in (4.2 TB/s, 3.3 through a page table).

@@ -642,9 +642,9 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     }
 
     // ---- the workgroup's partial results meet in LDS (Eq. 5) -------------------------------------------------------------------------
-    // O of wavefront v takes the place of its ring: row-major [32][D] fp32 with the 16-byte chunk c of row r at chunk
-    // c ^ (r % (D / 4)); behind the eight of them the maxima and sums [NWS][32].
-    constexpr int OW = G_::OW, CH = G_::CH, RPW = G_::RPW, LPR = G_::LPR, CPL = G_::CPL;      // CH: 16-byte chunks per row
+    // O of wavefront v takes the place of its ring: row-major [TR][D] fp32 with the 16-byte chunk c of row r at chunk
+    // c ^ (r % (D / 4)); behind the eight of them the maxima and sums [NWS][TR].
+    constexpr int CH = G_::CH, RPW = G_::RPW, LPR = G_::LPR, CPL = G_::CPL;      // CH: 16-byte chunks per row
     float* const Mw = reinterpret_cast<float*>(smem_all + NWS * 2 * STB);
     float* const Lw = Mw + NWS * TR;
     int* const last_flag = reinterpret_cast<int*>(Lw + NWS * TR);

@@ -124,7 +124,7 @@ struct CombinedArgs {
 // 8 / 2 135, 4 138.)
 constexpr int kLongRun = 8, kTailItems = 1024;
 
-// The single-launch fused kernel (fused_small.hip): every level, the suffix and the merge for 32-row tiles of query rows.
+// The single-launch fused kernel (fused_small.hip): every level, the suffix and the merge for columns of 32 or 16 query rows.
 constexpr int kSmallMaxSplits = 32;           // workgroups per column at most
 constexpr int kSplitWorkgroups = 256;         // workgroups of a call whose columns are split, at most
 // Device counters of a context: the combined launch's work counter, from kMeetingCounters on those of split columns: one for

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     unsigned char* const smem = smem_all + w * (2 * STB);      // this wavefront's K slot, then its V slot
     const kargs_ptr k = (kargs_ptr)__builtin_amdgcn_kernarg_segment_ptr();
 
-    // Workgroups whose ids are equal modulo 8 run on one XCD: each XCD takes an eighth of the list (KV head, split, tile), so that
+    // Workgroups whose ids are equal modulo 8 run on one XCD: each XCD takes an eighth of the list (KV head, tile, split), so that
     // the shared rows of a head are read into one L2 or few instead of all, whatever the number of heads.  Numbers of KV heads
     // that neither divide 8 nor are a multiple of it, dealt out over all XCDs before: 64 sequences x 40/10 heads, 8K keys, paged
     // 59.8 -> 33.6 us; 34 x 40/10, 10.5K keys, paged 50.3 -> 28.4; 56 x 24/12, 8574 keys, codes 45.9 -> 30.1.  The others, which had

@@ -46,7 +46,8 @@ extern "C" {
  * codes; workspace_bytes: room for partial results.  Returns what the call would return before it enqueues anything, and on
  * HG_OK fills out[8] = { way: 0 single launch, 1 shared blocks and suffix in one launch, 2 one kernel after another on one
  * stream, 3 on two streams, 4 no keys at all; workgroups per column (way 0, else 0); partial results per row (0 for way 0); keys
- * per work item of the suffix kernel (way 0: query rows per column); work items per row; 1 if the suffix runs on the matrix cores; levels on the persistent
+ * per work item of the suffix kernel (way 0: query rows per column); work items per row (way 0: 1 if the
+ * stages of a column go to its wavefronts one by one, 0 if in runs); 1 if the suffix runs on the matrix cores; levels on the persistent
  * kernel (bit i: levels[i]); CUs per XCD of the persistent kernel, 0 if it does not run }.
  *
  * hg_debug_single_work: what a workgroup of a single launch works on, `tiles` columns per KV head with `splits` workgroups each:

@@ -781,6 +781,7 @@ struct FusedPlan {
     int way;
     int splits;                     // single launch: workgroups per column
     int column_rows;                // and query rows
+    bool dealt;                     // its stages go to the wavefronts one by one
     bool sfx_mfma;                  // the suffix kernel's choice for these rows is the matrix cores
     int nlev;                       // levels that hold keys
     LevelDev lv[HG_MAX_LEVELS];
@@ -912,6 +913,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     p.way = kWaySingle;
     p.splits = 1;
     p.column_rows = 32;
+    p.dealt = true;
     p.nlev = 0;
     p.main_level = p.joint = -1;
     const int n_levels = f.n_levels, max_len = f.max_len, B = f.B, Hq = f.Hq, Hkv = f.Hkv, D = f.D, nq = c->opt_nq, G = Hq / Hkv;
@@ -1049,6 +1051,12 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const double suffix_us = has_suffix ? (f.fp8 ? 2.0 : 4.0) * B * (0.75 * max_len) * Hkv * D / 5.0e6 : 0.0;      // at 5 TB/s
         const double shared_us = shared_bytes / 5.0e6, part_us = 4.0 * B * nq * Hq * (double)D / 5.0e6;      // (one partial result of every row)
         const double est_single = std::max(chain_at(rows, splits), (paged ? 1.5 : 1.2) * suffix_us + shared_us + 6.0);
+        // Stages in runs where a round or two of workgroups fill the chip and the suffix rows are two fifths of the call: dealt out one by
+        // one, all wavefronts multiply shared rows first and wait for the HBM together afterwards.  Dealt / runs, us: 1024 x 8/1 heads, 1K keys, 128 rows
+        // 21.5 / 18.6; 512 rows 57.9 / 51.6; 2048 x 8/1, 1K keys, 512 rows 118 / 103; 456 x 16/2, 532 keys, up to 184 rows 17.8 / 16.4; 482 x 16/2, two
+        // queries, 1359 keys, up to 996 rows 73.7 / 76.9 (the worst of 39, 0.955 in the mean).  Elsewhere dealing is the better by 6 %: fewer or more
+        // columns (1.00 / 1.01 at this share), 16 rows (the phases are shorter), D = 64 (two workgroups per CU overlap), codes, several KV heads.
+        p.dealt = f.fp8 || D == 64 || rows == 16 || splits > 1 || Hkv > 2 || cols < 200 || cols > 512 || suffix_us < 0.4 * est_single;
         const double sfx_alone = suffix_us * (sfx_mfma || rps == 1 ? 1.0 : 0.5 * rps);
         double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
                                     sfx_alone + std::max(flops / 1.1e9, shared_us);
@@ -1164,6 +1172,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         sa.tiles = (B * nq * G + sa.rows - 1) / sa.rows;
         sa.cols = sa.tiles * Hkv;
         sa.splits = p.splits;
+        sa.dealt = p.dealt;
         sa.part = reinterpret_cast<float*>(ws.p);
         sa.arrivals = p.splits > 1 ? c->counters + meeting_counter(p.splits) : nullptr;
         sa.scale = scale;
@@ -1559,7 +1568,7 @@ int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const h
     out[1] = single ? p.splits : 0;
     out[2] = single ? 0 : p.np;
     out[3] = single ? p.column_rows : p.sp.chunk;
-    out[4] = single ? 0 : p.sp.nchunks;
+    out[4] = single ? p.dealt : p.sp.nchunks;
     out[5] = !single && p.sp.nchunks > 0 && p.sp.mfma ? 1 : 0;
     out[6] = out[7] = 0;
     for (int i = 0; !single && i < p.nlev; ++i) {

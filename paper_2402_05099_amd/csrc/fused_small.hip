@@ -8,7 +8,7 @@
 // block boundary falls inside the tile), then the suffix of each of the tile's sequences (only that sequence's rows
 // attend).  Softmax over the union of all segments is one online softmax: a row that does not attend to a segment has
 // its scores masked.  The decomposition of Eq. 5 appears twice: the 32-key stages of the list are dealt out to the
-// wavefronts of the column's workgroups one by one, each with its own running maximum, sum and accumulator; the eight partial
+// wavefronts of the column's workgroups one by one (or in runs, see below), each with its own running maximum, sum and accumulator; the eight partial
 // results of a workgroup meet in LDS and are combined with the weights exp(LSE_i - max LSE).
 //
 // 16 rows: products of 16 x 16 instead of 32 x 32, half the exponentials per lane, and fewer sequences whose suffixes a column
@@ -327,23 +327,25 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     typedef std::integral_constant<bool, false> IsK;
     typedef std::integral_constant<bool, true> IsV;
 
-    // ---- this wavefront's stages: positions run, run + runs, ... of the list.  The stages of the shared blocks come first, so
-    // that the first one, where there is one, is found and requested while the lengths are on their way; and every wavefront
-    // gets its share of both kinds: with runs of consecutive stages those of suffix stages, which take longer, held up the rest.
+    // ---- this wavefront's stages.  Dealt out one by one (positions run, run + runs, ... of the list): the stages of the shared blocks
+    // come first, so that the first one, where there is one, is found and requested while the lengths are on their way, and every
+    // wavefront gets its share of both kinds: with runs of consecutive stages those of suffix stages, which take longer, hold up the rest.
+    // In runs where the suffix rows keep the HBM busy (see the rule in plan_fused): some wavefronts then stream them from the start, while
+    // others multiply shared rows.
     const int runs = a.splits * NWS, run = split * NWS + w;
     Walk walk{0, -1};
     Seg cs{};
     int ct = 0, base = 0;                           // current stage of segment cs; shared stages before cs
-    bool shared_first = false;
+    bool requested = false;
     while (next_shared(walk, cs)) {
-        if (base + cs.nst > run) {
-            shared_first = true;
+        if (a.dealt && base + cs.nst > run) {
+            requested = true;
             break;
         }
         base += cs.nst;
     }
     int shared_total = base;
-    if (shared_first) {
+    if (requested) {
         ct = run - base;
         issue(cs, ct, IsK{});
         issue(cs, ct, IsV{});
@@ -393,8 +395,15 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
         load_suffix(i, s);
         t = p - (__builtin_amdgcn_readlane(incl_v, i) - s.nst);
     };
-    if (!shared_first && run < total) {
-        seek(run, cs, ct);
+    const int step = a.dealt ? runs : 1;
+    const int first = a.dealt ? run : (int)((long long)run * total / runs), end = a.dealt ? total : (int)((long long)(run + 1) * total / runs);
+    if (!requested && first < end) {
+        if (!a.dealt && first < shared_total) {     // (the walk has counted the shared stages: once more from the beginning)
+            walk = Walk{0, -1};
+            base = 0;
+            next_shared(walk, cs);
+        }
+        seek(first, cs, ct);
         issue(cs, ct, IsK{});
         issue(cs, ct, IsV{});
     }
@@ -460,11 +469,14 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     float lsum = 0.f;           // this lane's share of the row sum (unrounded exponentials)
     bool code_units = false;    // the accumulators hold sums of codes, to be multiplied by the V scale
 
-    for (int pos = run; pos < total; pos += runs) {
-        const bool more = pos + runs < total;
+    for (int pos = first; pos < end; pos += step) {
+        const bool more = pos + step < end;
         Seg ns = cs;
         int nt = ct;
-        if (more) seek(pos + runs, ns, nt);
+        if (more) {
+            if (ct + step < cs.nst) nt = ct + step;
+            else seek(pos + step, ns, nt);
+        }
         const bool codes = FP8 && cs.sfx >= 0;
         wait_for(copies_of(cs));                    // this stage's K rows are here, its V rows may still be on their way
         // S^T = K Q^T.  Element i: stage row 8 (i / 4) + i % 4 + 4 hl; 16-row columns: 16 (i / 4) + i % 4 + 4 lg

@@ -171,6 +171,7 @@ struct SmallArgs {
     int tiles;                // that many rows at a time of the B * nq * G query rows of one KV head
     int cols;                 // tiles * Hkv columns
     int splits;               // workgroups per column
+    int dealt;                // stages go to the wavefronts one by one (else in runs)
     float* part;              // splits > 1: partial results (small_part_floats)
     unsigned* arrivals;       // splits > 1: [cols] counters that only ever count to `splits`, zero between calls
     float scale;

@@ -53,3 +53,38 @@ def test_columns(shape, rows, cache):
         check(to_np(got[0][0]), to_np(got[0][1]), Oref, Lref, f"{shape} rows={rows} {cache} parts={parts}")
         assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
         ctx.close()
+
+
+# suffixes that keep the HBM busy while the chip holds one round of columns: a wavefront's stages are then consecutive
+RUN_SHAPES = {
+    "runs": (820, 8, 1, 128, 1, [(1, 70, 820)], 0, 260),
+    "runs_blocks": (500, 16, 2, 128, 1, [(1, 40, 500), (7, 35, 71)], 0, 300),      # boundaries inside columns, sequences no block covers
+    "runs_queries": (210, 8, 1, 128, 4, [(1, 64, 210)], 4, 700),
+    "runs_no_shared": (800, 8, 1, 128, 1, [], 1, 300),
+}
+
+
+@pytest.mark.parametrize("cache", ["packed", "paged"])
+@pytest.mark.parametrize("shape", RUN_SHAPES)
+def test_stages_in_runs(shape, cache):
+    B, H, Hkv, D, nq, levels, lo, hi = RUN_SHAPES[shape]
+    print(f"stages in runs: {shape} {cache}", file=sys.stderr, flush=True)
+    w = wl.make_workload(shape, 92, B, H, Hkv, D, levels, lo, hi, nq=nq)
+    dw = dev.to_device(w)
+    Oref, Lref, call = reference(w, cache)
+    options = {hb.HG_OPT_FUSED_KERNEL: 2, hb.HG_OPT_SUFFIX_TILE_ROWS: 32}
+    plan = hb.hg_debug_fused_plan(levels, B, nq, H, Hkv, D, dw.max_len, 16 if cache == "paged" else 0, options=options)
+    assert (plan["way"], plan["dealt"]) == ("single", False)
+    ctx = dev.make_context(dw, parts=32)
+    for option, value in options.items():
+        ctx.set_option(option, value)
+    got = []
+    for _ in range(2):
+        O = torch.full(dw.lead + (dw.D,), float("nan"), dtype=torch.float32, device="cuda:0")
+        L = torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0")
+        call(ctx, dw, O, L)
+        got.append((O, L))
+    torch.cuda.synchronize()
+    check(to_np(got[0][0]), to_np(got[0][1]), Oref, Lref, f"{shape} {cache}")
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    ctx.close()

@@ -345,3 +345,14 @@ def test_rows_and_workgroups_of_the_single_launch(shape, rows, splits):
     for asked in (16, 32):
         forced = hb.hg_debug_fused_plan(*shape, options={hb.HG_OPT_FUSED_KERNEL: 2, hb.HG_OPT_SUFFIX_TILE_ROWS: asked})
         assert (forced["way"], forced["column_rows"]) == ("single", asked)
+
+
+@pytest.mark.parametrize("shape,dealt", [
+    (([(1, 1024, 1024)], 1024, 1, 8, 1, 128, 128), False), (([(1, 1024, 2048)], 2048, 1, 8, 1, 128, 512), False), (([(1, 532, 456)], 456, 1, 16, 2, 128, 184), False),
+    (([(1, 4096, 1024)], 1024, 1, 8, 1, 128, 128), True),       # the shared rows are most of the call
+    (([(1, 1024, 256)], 256, 1, 8, 1, 128, 512), True),         # 16 rows
+    (([(1, 100, 90)], 90, 1, 32, 8, 128, 200), True), (([(1, 300, 1000)], 1000, 1, 8, 1, 64, 300), True),
+], ids=str)
+def test_stages_of_the_single_launch_in_runs_where_the_suffix_decides(shape, dealt):
+    plan = hb.hg_debug_fused_plan(*shape)
+    assert (plan["way"], plan["dealt"]) == ("single", dealt)

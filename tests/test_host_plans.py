@@ -356,3 +356,14 @@ def test_rows_and_workgroups_of_the_single_launch(shape, rows, splits):
 def test_stages_of_the_single_launch_in_runs_where_the_suffix_decides(shape, dealt):
     plan = hb.hg_debug_fused_plan(*shape)
     assert (plan["way"], plan["dealt"]) == ("single", dealt)
+
+
+@pytest.mark.parametrize("shape,way,rows", [
+    (([(1, 7171, 109)], 109, 1, 40, 40, 64, 69, 32), "single", 32), (([(1, 8192, 112)], 112, 1, 40, 40, 64, 8), "one_stream", None),
+    (([(1, 4171, 264)], 264, 1, 32, 8, 64, 207, 64, True), "one_stream", None), (([(1, 2048, 112)], 112, 1, 40, 40, 64, 8), "single", 32),
+], ids=str)
+def test_two_workgroups_share_a_cu_at_head_dimension_64(shape, way, rows):
+    """More than 256 columns take longer than 256 though they all run at a time: 280 columns of 16 rows 37, 66 and 108 us where 160 of 32 rows or
+    separate kernels take 30, 41 and 60."""
+    plan = hb.hg_debug_fused_plan(*shape)
+    assert (plan["way"], plan.get("column_rows")) == (way, rows)

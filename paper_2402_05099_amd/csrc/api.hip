@@ -986,7 +986,11 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             }
         }
         const bool joins = may_join && wide;
-        struct Shape { int seqs_per_tile; long long cols; double stages; };      // of columns of so many rows
+        // Shared rows that neither their XCD's L2 (4 MB) nor, with the suffix rows and another layer's, the 256 MB behind all of them hold: a stage takes
+        // half as long again (from five workgroups per column on the waits overlap).  109 x 40/40 heads, D = 64, 7168 keys, 160 columns: 32 suffix rows 45.8 us, 68 rows 76 (separate kernels 48); 64 keys only 11.7
+        // and 22; 32 x 40/40, 4K / 8K keys 1.9 / 3.0 us a stage.
+        const bool far = shared_bytes / std::min(8, Hkv) > 4.0e6 && shared_bytes + (has_suffix ? (f.fp8 ? 2.0 : 4.0) * B * (0.75 * max_len) * Hkv * D : 0.0) > 1.25e8;
+        struct Shape { int seqs_per_tile; long long cols; double stages, shared; };      // of columns of so many rows
         auto shape_of = [&](int rows) {
             Shape x;
             x.seqs_per_tile = rps >= rows ? 1 : (rows + rps - 1) / rps + (rows % rps ? 1 : 0);
@@ -999,6 +1003,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
                 const double met = std::min((double)levels[i].n_blocks, levels[i].n_blocks > 1 ? 1.0 + (rows - 1.0) / (double)(seqs * rps) : 1.0);
                 shared_stages += met * ((levels[i].max_rows + 31) / 32);
             }
+            x.shared = shared_stages;
             x.stages = shared_stages + (has_suffix ? std::min(x.seqs_per_tile, B) * ((0.75 * max_len + 16.0) / 32.0) : 0.0);
             return x;
         };
@@ -1023,7 +1028,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             const Shape& x = rows == 16 ? shape16 : shape32;
             const double wgs = (double)x.cols * S;
             const double per_stage = (fp32_weights ? k[6] : 1.0) * (k[2] + k[3] * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
-            return k[0] + rounds_of(rows, wgs) * (k[1] + per_stage * ceil(x.stages / (8.0 * S))) + (S > 1 ? k[4] + k[5] * S : 0.0);
+            return k[0] + rounds_of(rows, wgs) * (k[1] + per_stage * ceil((x.stages + (far && S <= 4 ? 0.5 * x.shared : 0.0)) / (8.0 * S))) + (S > 1 ? k[4] + k[5] * S : 0.0);
         };
         // Small calls on packed rows touch nothing but their inputs and outputs: one workgroup per column, no workspace, no
         // counters.  A program may have several in flight for one context (streams, graph replays, branches of a graph) or run

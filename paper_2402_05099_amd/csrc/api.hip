@@ -1012,13 +1012,12 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const bool light = rps == 1 && fp32_weights && D == 128 && !wide && B >= 24;
         const long long cols = shape32.cols;
         const int seqs_per_tile = shape32.seqs_per_tile;
-        // Rounds of workgroups that run at a time.  At D = 64 two fit a CU's LDS, and share it: 112 x 40/40 heads, 8K keys take 48 us with 160 columns of 32
-        // rows and 66 with 280 of 16 rows (45 with 160 of them).  Of 32 rows with fp32 weights the registers hold one per CU: 264 x 32/8, 4171 keys,
-        // 264 columns 70 us against 51 on separate kernels.  Counted as one round before: over 700 drawn calls 0.97 of the time.
-        auto rounds_of = [&](int rows, double wgs) {
-            if (D == 128) return ceil(wgs / 256.0);
-            const double n = ceil(wgs / 512.0);
-            return n > 1.0 || wgs <= 256.0 ? n : !fp32_weights ? 1.3 : rows == 32 ? 1.5 : 1.0;
+        // Workgroups that run at a time: one per CU, at D = 64 two (LDS).  Those share it, and a stage takes longer: 112 x 40/40 heads, 8K keys: 48 us with 160
+        // columns of 32 rows, 66 with 280 of 16 rows (45 with 160 of them).  Of 32 rows with fp32 weights the registers hold one per CU: 264 x 32/8, 4171
+        // keys, 264 columns 70 us against 51 on separate kernels.  With both counted, over 700 drawn calls 0.97 of the time.
+        auto rounds_of = [&](double wgs) { return ceil(wgs / (D == 128 ? 256.0 : 512.0)); };
+        auto shared_cu = [&](int rows, double wgs) {
+            return D == 128 || wgs <= 256.0 || wgs > 512.0 ? 1.0 : !fp32_weights ? 1.3 : rows == 32 ? 1.5 : 1.0;
         };
         auto chain_at = [&](int rows, int S) {
             static const double fit[2][2][7] = {      // a, b, c on a quarter of the chip, more on all of it, m0, m1, codes with fp32 weights
@@ -1027,8 +1026,8 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             const double* const k = fit[D == 64][rows == 16];
             const Shape& x = rows == 16 ? shape16 : shape32;
             const double wgs = (double)x.cols * S;
-            const double per_stage = (fp32_weights ? k[6] : 1.0) * (k[2] + k[3] * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
-            return k[0] + rounds_of(rows, wgs) * (k[1] + per_stage * ceil((x.stages + (far && S <= 4 ? 0.5 * x.shared : 0.0)) / (8.0 * S))) + (S > 1 ? k[4] + k[5] * S : 0.0);
+            const double per_stage = shared_cu(rows, wgs) * (fp32_weights ? k[6] : 1.0) * (k[2] + k[3] * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
+            return k[0] + rounds_of(wgs) * (k[1] + per_stage * ceil((x.stages + (far && S <= 4 ? 0.5 * x.shared : 0.0)) / (8.0 * S))) + (S > 1 ? k[4] + k[5] * S : 0.0);
         };
         // Small calls on packed rows touch nothing but their inputs and outputs: one workgroup per column, no workspace, no
         // counters.  A program may have several in flight for one context (streams, graph replays, branches of a graph) or run

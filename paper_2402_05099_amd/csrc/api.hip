@@ -1183,6 +1183,10 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         sa.tiles = (B * nq * G + sa.rows - 1) / sa.rows;
         sa.cols = sa.tiles * Hkv;
         sa.splits = p.splits;
+        sa.by_head = divider((unsigned)(sa.tiles * sa.splits));
+        sa.by_split = divider((unsigned)sa.splits);
+        sa.by_seq = divider((unsigned)(nq * G));
+        sa.by_group = divider((unsigned)G);
         sa.dealt = p.dealt;
         sa.part = reinterpret_cast<float*>(ws.p);
         sa.arrivals = p.splits > 1 ? c->counters + meeting_counter(p.splits) : nullptr;
@@ -1593,7 +1597,7 @@ int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const h
 int hg_debug_single_work(int workgroup, int tiles, int splits, int Hkv, int out[3]) {
     if (workgroup < 0 || tiles < 1 || splits < 1 || Hkv < 1 || !out || (long long)tiles * splits * Hkv >= (1LL << 31) - 8) return 0;
     if ((unsigned)workgroup >= hg::small_grid(tiles * splits * Hkv)) return 0;
-    return hg::small_work((unsigned)workgroup, tiles, splits, Hkv, out[0], out[1], out[2]) ? 1 : 0;
+    return hg::small_work((unsigned)workgroup, tiles, splits, Hkv, hg::divider((unsigned)(tiles * splits)), hg::divider((unsigned)splits), out[0], out[1], out[2]) ? 1 : 0;
 }
 
 int hg_debug_mfma_loop(hg_ctx* c, int random_operands, int iters, unsigned long long* clocks, float* sink) {

@@ -25,9 +25,13 @@
 // flight as four wavefronts with two slots for each, and the second wavefront fills the first one's waits.
 // Products, XOR swizzles and lazy rescaling are those of the other kernels (prefix_wide.hip, decode_mfma.hip).
 //
-// What bounds it: latency.  By time stamps (32 rows): lengths and Q 1.2 - 2.4 us after the start, the first stage's rows 0.4 after their
-// request, 1.05 us per shared stage (products, exponentials and the 16 KiB of every one of eight wavefronts through the CU's
-// 64 bytes a cycle), 1.45 per suffix stage (masks, another segment each time), 1.2 for the combination and output.
+// What bounds it: latency.  By time stamps (16 rows, D = 128): arguments 0.4 us after the start, lengths, Q and the first stages' rows 1.7 later (128 KiB
+// through the CU's 64 bytes a cycle), the first product 0.4 after them, 1.05 us per shared stage (products, exponentials and the
+// 16 KiB of every one of eight wavefronts), 1.45 per suffix stage (masks, another segment each time), 1.2 for the combination
+// and output.  What needs no loaded value (LDS addresses, index arithmetic) is therefore done while the first loads are on their way, the
+// divisions are multiplications by numbers from the host, the prefix sum of the lengths stays in the vector ALU, and copies whose
+// rows need no clamp run without a branch: before, lengths to first product 0.95 us, arguments to first request 0.1 longer;
+// 45 x 16/2 heads, 515 keys, ragged up to 150 rows 9.86 -> 8.56 us, 256 x 8/1, 1K keys, 128 rows 12.2 -> 11.4, 40 drawn calls 1.046 in the mean.
 // Measured, one workgroup per column, runs of consecutive stages and 32 rows before, as it is now after: 256 sequences x 8 heads on one KV head, 1024
 // shared keys, 128 suffix rows 16.2 -> 12.1 us; 45 x 16 heads on two KV heads, 515 keys, ragged up to 150 rows 13.9 -> 10.0;
 // 57 calls of this kind drawn at random 1.19 times as fast in the mean (stages dealt out one by one and the first requested early
@@ -153,17 +157,19 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     // 59.8 -> 33.6 us; 34 x 40/10, 10.5K keys, paged 50.3 -> 28.4; 56 x 24/12, 8574 keys, codes 45.9 -> 30.1.  The others, which had
     // an order of their own to the same end: 1.005 in the mean over 117 calls.
     int kvh, tile, split;
-    asm volatile("" ::"s"(a.nq), "s"(a.G), "s"(a.B), "s"(a.Q), "s"(a.lengths), "s"(a.offsets));      // (loaded with the rest, not behind the way out)
-    if (!small_work(blockIdx.x, a.tiles, a.splits, a.Hkv, kvh, tile, split)) return;
+    // (loaded at once with the rest, not behind the way out or where they are first used)
+    asm volatile("" ::"s"(a.nq), "s"(a.G), "s"(a.B), "s"(a.Q), "s"(a.lengths), "s"(a.offsets), "s"(a.by_seq.mul), "s"(a.by_group.mul), "s"(a.n_levels));
+    asm volatile("" ::"s"(a.lv[0].K), "s"(a.lv[0].V), "s"(a.lv[0].seq_off), "s"(a.lv[0].max_rows));
+    if (!small_work(blockIdx.x, a.tiles, a.splits, a.Hkv, a.by_head, a.by_split, kvh, tile, split)) return;
     const int col = kvh * a.tiles + tile;
     const int rps = a.nq * a.G;                     // query rows of one sequence for this KV head
     const int R = a.B * rps;
     const int r0 = tile * TR;
-    const int b0 = r0 / rps, b1 = min((r0 + TR - 1) / rps, a.B - 1);
+    const int b0 = (int)a.by_seq.of((unsigned)r0), b1 = min((int)a.by_seq.of((unsigned)(r0 + TR - 1)), a.B - 1);
     const int r = r0 + lq;                          // this lane's row
     const bool rv = r < R;
     const int rr = rv ? r : r0;
-    const int b_lane = rr / rps, t_lane = (rr % rps) / a.G, g_lane = rr % a.G;
+    const int b_lane = (int)a.by_seq.of((unsigned)rr), in_seq = rr - b_lane * rps, t_lane = (int)a.by_group.of((unsigned)in_seq), g_lane = in_seq - t_lane * a.G;
     const int64_t qidx = ((int64_t)b_lane * a.nq + t_lane) * a.Hq + kvh * a.G + g_lane;   // (b*nq + t)*Hq + h
 
     // ---- Q operand (registers) and the tile's suffix lengths / offsets (lane i: sequence b0 + i), loaded before any copy ----
@@ -295,26 +301,26 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
         }
         if (codes) {
             if constexpr (FP8) {
+                if (__builtin_expect(rowclamp < KT - 1, 0)) {
 #pragma unroll
-                for (int i = 0; i < CPS8; ++i) {
-                    unsigned vo = V ? voffV8[i] : voffK8[i];
-                    if (rowclamp < KT - 1) {
+                    for (int i = 0; i < CPS8; ++i) {
                         const int srow = i * RPI8 + lrow8;
-                        vo -= (unsigned)(srow - min(srow, rowclamp)) * rs;
+                        copy16(base0, (V ? voffV8[i] : voffK8[i]) - (unsigned)(srow - min(srow, rowclamp)) * rs, dst + i * 1024);
                     }
-                    copy16(i < CPS8 / 2 ? base0 : base1, vo, dst + i * 1024);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < CPS8; ++i) copy16(i < CPS8 / 2 ? base0 : base1, V ? voffV8[i] : voffK8[i], dst + i * 1024);
                 }
+            }
+        } else if (__builtin_expect(rowclamp < KT - 1, 0)) {
+#pragma unroll
+            for (int i = 0; i < CPS; ++i) {
+                const int srow = i * RPI + lrow;
+                copy16(base0, (V ? voffV[i] : voffK[i]) - (unsigned)(srow - min(srow, rowclamp)) * rs, dst + i * 1024);
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < CPS; ++i) {
-                unsigned vo = V ? voffV[i] : voffK[i];
-                if (rowclamp < KT - 1) {
-                    const int srow = i * RPI + lrow;
-                    vo -= (unsigned)(srow - min(srow, rowclamp)) * rs;
-                }
-                copy16(i < CPS / 2 ? base0 : base1, vo, dst + i * 1024);
-            }
+            for (int i = 0; i < CPS; ++i) copy16(i < CPS / 2 ? base0 : base1, V ? voffV[i] : voffK[i], dst + i * 1024);
         }
     };
     // wait until at most `younger` copy instructions are outstanding (those of one tensor of one stage, or none)
@@ -355,59 +361,6 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
         while (next_shared(rest, s)) shared_total += s.nst;
     }
     shared_total = __builtin_amdgcn_readfirstlane(shared_total);
-    // (the loads above are the only ones the compiler sees; it waits for them, and with them for the first copies, here)
-    asm volatile("" : "+v"(len_v), "+v"(off_v));
-#pragma unroll
-    for (int s = 0; s < QN; ++s) asm volatile("" : "+v"(qf[s]));
-    len_v = max(min(len_v, a.max_len), 0);
-    const int nst_v = (len_v + KT - 1) / KT;        // stages of the suffix of sequence b0 + l
-    int incl_v = nst_v;                             // ... of the suffixes of b0 .. b0 + l
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(incl_v, o);
-        if (l >= o) incl_v += up;
-    }
-    auto load_suffix = [&](int i, Seg& s) {         // the suffix of sequence b0 + i (which has rows)
-        const int cnt = __builtin_amdgcn_readlane(len_v, i), off = PAGED ? 0 : __builtin_amdgcn_readlane(off_v, i);
-        s.K = reinterpret_cast<const unsigned char*>(k->Ks) + (int64_t)kvh * D * (FP8 ? 1 : 2);
-        s.V = reinterpret_cast<const unsigned char*>(k->Vs) + (int64_t)kvh * D * (FP8 ? 1 : 2);
-        s.ks = off;
-        s.ke = off + cnt;
-        s.rlo = max((b0 + i) * rps - r0, 0);
-        s.rhi = min((b0 + i + 1) * rps - r0, TR);
-        s.vis_base = off + cnt - (a.nq - 1);        // query t sees rows below off + cnt - (nq-1-t)
-        s.nst = (cnt + KT - 1) / KT;
-        s.sfx = i;
-    };
-    const int total = shared_total + __builtin_amdgcn_readlane(incl_v, 63);
-    auto seek = [&](int pos, Seg& s, int& t) {      // the stage at position pos < total, behind the current one
-        if (pos < shared_total) {
-            t = pos - base;
-            while (t >= s.nst) {
-                base += s.nst;
-                t -= s.nst;
-                next_shared(walk, s);
-            }
-            return;
-        }
-        const int p = pos - shared_total;
-        const int i = __builtin_popcountll(__ballot(incl_v <= p));      // the first sequence whose stages reach past p
-        load_suffix(i, s);
-        t = p - (__builtin_amdgcn_readlane(incl_v, i) - s.nst);
-    };
-    const int step = a.dealt ? runs : 1;
-    const int first = a.dealt ? run : (int)((long long)run * total / runs), end = a.dealt ? total : (int)((long long)(run + 1) * total / runs);
-    if (!requested && first < end) {
-        if (!a.dealt && first < shared_total) {     // (the walk has counted the shared stages: once more from the beginning)
-            walk = Walk{0, -1};
-            base = 0;
-            next_shared(walk, cs);
-        }
-        seek(first, cs, ct);
-        issue(cs, ct, IsK{});
-        issue(cs, ct, IsV{});
-    }
-
     // ---- LDS fragment addresses (relative to the slot), as in decode_mfma.hip ---------------------------------------------------
     constexpr int KA = NARROW ? 2 * KS16 : KS, VA = NARROW ? DB16 : DB;
     unsigned kaddr[KA], vaddr[VA], kaddr8[FP8 ? KA : 1], vaddr8[FP8 ? VA : 1];
@@ -451,10 +404,71 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
             for (int db = 0; db < DB; ++db) vaddr8[db] = (unsigned)(STB + row * D + (((2 * db + g1) ^ vswz8(row)) * 16) + 8 * pp);
         }
     }
+    // (computed while lengths, queries and first rows are on their way)
+#pragma unroll
+    for (int i = 0; i < KA; ++i) asm volatile("" : "+v"(kaddr[i]));
+#pragma unroll
+    for (int i = 0; i < VA; ++i) asm volatile("" : "+v"(vaddr[i]));
+
+    // (the loads above are the only ones the compiler sees; it waits for them, and with them for the first copies, here)
+    asm volatile("" : "+v"(len_v), "+v"(off_v));
+#pragma unroll
+    for (int s = 0; s < QN; ++s) asm volatile("" : "+v"(qf[s]));
+    len_v = max(min(len_v, a.max_len), 0);
+    const int nst_v = (len_v + KT - 1) / KT;        // stages of the suffix of sequence b0 + l
+    // ... of the suffixes of b0 .. b0 + l: a prefix sum over the TR lanes that can hold a sequence (within rows of 16 lanes, then the first row's total
+    // into the second)
+    int incl_v = nst_v;
+    incl_v += __builtin_amdgcn_update_dpp(0, incl_v, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8
+    incl_v += __builtin_amdgcn_update_dpp(0, incl_v, 0x112, 0xf, 0xf, false);
+    incl_v += __builtin_amdgcn_update_dpp(0, incl_v, 0x114, 0xf, 0xf, false);
+    incl_v += __builtin_amdgcn_update_dpp(0, incl_v, 0x118, 0xf, 0xf, false);
+    if constexpr (TR == 32) incl_v += __builtin_amdgcn_update_dpp(0, incl_v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+    constexpr uint64_t kSeqLanes = TR == 32 ? 0xffffffffull : 0xffffull;
+    auto load_suffix = [&](int i, Seg& s) {         // the suffix of sequence b0 + i (which has rows)
+        const int cnt = __builtin_amdgcn_readlane(len_v, i), off = PAGED ? 0 : __builtin_amdgcn_readlane(off_v, i);
+        s.K = reinterpret_cast<const unsigned char*>(k->Ks) + (int64_t)kvh * D * (FP8 ? 1 : 2);
+        s.V = reinterpret_cast<const unsigned char*>(k->Vs) + (int64_t)kvh * D * (FP8 ? 1 : 2);
+        s.ks = off;
+        s.ke = off + cnt;
+        s.rlo = max((b0 + i) * rps - r0, 0);
+        s.rhi = min((b0 + i + 1) * rps - r0, TR);
+        s.vis_base = off + cnt - (a.nq - 1);        // query t sees rows below off + cnt - (nq-1-t)
+        s.nst = (cnt + KT - 1) / KT;
+        s.sfx = i;
+    };
+    const int total = shared_total + __builtin_amdgcn_readlane(incl_v, TR - 1);
+    auto seek = [&](int pos, Seg& s, int& t) {      // the stage at position pos < total, behind the current one
+        if (pos < shared_total) {
+            t = pos - base;
+            while (t >= s.nst) {
+                base += s.nst;
+                t -= s.nst;
+                next_shared(walk, s);
+            }
+            return;
+        }
+        const int p = pos - shared_total;
+        const int i = __builtin_popcountll(__ballot(incl_v <= p) & kSeqLanes);      // the first sequence whose stages reach past p
+        load_suffix(i, s);
+        t = p - (__builtin_amdgcn_readlane(incl_v, i) - s.nst);
+    };
+    const int step = a.dealt ? runs : 1;
+    // (runs: the host gives a column one workgroup then; 9 total stays below 2^31, a block's rows being fewer than 2^24)
+    const int first = a.dealt ? run : (int)((unsigned)(run * total) / NWS), end = a.dealt ? total : (int)((unsigned)((run + 1) * total) / NWS);
+    if (!requested && first < end) {
+        if (!a.dealt && first < shared_total) {     // (the walk has counted the shared stages: once more from the beginning)
+            walk = Walk{0, -1};
+            base = 0;
+            next_shared(walk, cs);
+        }
+        seek(first, cs, ct);
+        issue(cs, ct, IsK{});
+        issue(cs, ct, IsV{});
+    }
 
     // ---- this wavefront's share of the softmax ------------------------------------------------------------------------------
-    const float c2 = a.scale * kLog2e;
-    const float tau_raw = TAU / c2;
+    const float c2 = a.c2, tau_raw = a.tau_raw;
     // scores and accumulators: one 32 x 32 product per block of O^T, or two 16-key groups and 16 x 16 products
     typedef float floatx4 __attribute__((ext_vector_type(4)));
     using OBlock = std::conditional_t<NARROW, floatx4, floatx16>;
@@ -789,7 +803,8 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
 
     const int rg = r0 + row;                        // the row this lane finishes
     if (finishes) {
-        const int64_t oidx = ((int64_t)(rg / rps) * a.nq + (rg % rps) / a.G) * a.Hq + kvh * a.G + rg % a.G;
+        const int ob = (int)a.by_seq.of((unsigned)rg), of_seq = rg - ob * rps, ot = (int)a.by_group.of((unsigned)of_seq);
+        const int64_t oidx = ((int64_t)ob * a.nq + ot) * a.Hq + kvh * a.G + (of_seq - ot * a.G);
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
             const int d = 4 * (c0 + c);
@@ -828,7 +843,11 @@ static hipError_t launch_small_d(const SmallArgs& a, hipStream_t s) {
 // Workspace floats the splits of a call need: [cols][splits][rows][D] results, [cols][splits][rows] pairs of (LSE, unused)
 size_t small_part_floats(int cols, int splits, int rows, int D) { return (size_t)cols * splits * rows * (D + 2); }
 
-hipError_t launch_fused_small(const SmallArgs& a, int D, hipStream_t s) {
+hipError_t launch_fused_small(const SmallArgs& args, int D, hipStream_t s) {
+    SmallArgs a = args;
+    a.c2 = a.scale * kLog2e;
+    a.tau_raw = TAU / a.c2;
+    if (!a.dealt && a.splits != 1) return hipErrorInvalidValue;
     if (a.tiles < 1 || a.Hkv < 1 || a.splits < 1 || (D != 64 && D != 128)) return hipErrorInvalidValue;
     if ((long long)a.tiles * a.Hkv != a.cols || (long long)a.cols * a.splits >= (1LL << 31)) return hipErrorInvalidValue;
     if (a.splits > 1 && (!a.part || !a.arrivals)) return hipErrorInvalidValue;

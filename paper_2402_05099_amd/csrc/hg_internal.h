@@ -124,6 +124,18 @@ struct CombinedArgs {
 // 8 / 2 135, 4 138.)
 constexpr int kLongRun = 8, kTailItems = 1024;
 
+// Division by a number that the host knows, without one: q = n / d for n < 2^31 (Granlund and Montgomery, "Division by invariant
+// integers using multiplication": with s = ceil(log2 d) and mul = ceil(2^(31 + s) / d) < 2^32, q = floor(n mul / 2^(31 + s))).
+struct Divider {
+    unsigned mul, shift;
+    __host__ __device__ unsigned of(unsigned n) const { return (unsigned)(((uint64_t)(2u * n) * mul) >> 32) >> shift; }
+};
+inline Divider divider(unsigned d) {      // 1 <= d < 2^31
+    unsigned s = 0;
+    while ((1u << s) < d) ++s;
+    return Divider{(unsigned)(((1ull << (31 + s)) + d - 1) / d), s};
+}
+
 // The single-launch fused kernel (fused_small.hip): every level, the suffix and the merge for columns of 32 or 16 query rows.
 constexpr int kSmallMaxSplits = 32;           // workgroups per column at most
 constexpr int kSplitWorkgroups = 256;         // workgroups of a call whose columns are split, at most
@@ -140,41 +152,45 @@ static_assert(meeting_counter(kSmallMaxSplits + 1) <= kContextCounters, "");
 // fastest (those of a column share its suffix rows and meet: 64 sequences x 8/1 heads, 4K keys, 512 rows, seven workgroups per column 14.8 us
 // with the tiles fastest, 13.9 so).  false: nothing for this one.
 __host__ __device__ inline unsigned small_grid(int n) { return 8u * (((unsigned)n + 7u) / 8u); }      // n: entries of the list
-__host__ __device__ inline bool small_work(unsigned id, int tiles, int splits, int Hkv, int& kvh, int& tile, int& split) {
+// by_head, by_split: division by tiles * splits and by splits
+__host__ __device__ inline bool small_work(unsigned id, int tiles, int splits, int Hkv, Divider by_head, Divider by_split, int& kvh, int& tile, int& split) {
     const unsigned of_head = (unsigned)(tiles * splits), n = of_head * (unsigned)Hkv, x = id & 7u;
     const unsigned eighth = n >> 3, rest = n & 7u;       // x n / 8 without its 64 bits
     const unsigned first = x * eighth + (x * rest >> 3), count = eighth + (((x + 1) * rest >> 3) - (x * rest >> 3));
     if (id >> 3 >= count) return false;
     const unsigned at = first + (id >> 3);
-    kvh = (int)(at / of_head);
+    kvh = (int)by_head.of(at);
     const unsigned in_head = at - (unsigned)kvh * of_head;
-    tile = (int)(in_head / (unsigned)splits);
+    tile = (int)by_split.of(in_head);
     split = (int)(in_head - (unsigned)tile * (unsigned)splits);
     return true;
 }
 struct SmallArgs {
+    // what a wavefront needs before its first request, side by side: the kernel starts by reading it
     const uint16_t* Q;
+    const int32_t* lengths;   // null: no suffix
+    const int32_t* offsets;
+    Divider by_head, by_split, by_seq, by_group;      // division by tiles * splits, splits, nq * G, G
+    int B, Hq, Hkv, G;
+    int nq;
+    int tiles;                // `rows` at a time of the B * nq * G query rows of one KV head
+    int splits;               // workgroups per column
+    int dealt;                // stages go to the wavefronts one by one (else in runs)
     int n_levels;
+    int max_len;
     LevelDev lv[HG_MAX_LEVELS];
     const uint16_t* Ks;
     const uint16_t* Vs;
-    const int32_t* offsets;
-    const int32_t* lengths;   // null: no suffix
     PagedDev pg;              // suffix read through a page table when pg.table != null
     int fp8;                  // suffix rows are E4M3 codes: value = code * scale
     float k_scale, v_scale;
     int fp32_weights;         // the weights of codes are not rounded to bf16
-    int max_len;
-    int B, Hq, Hkv, G;
-    int nq;
     int rows;                 // query rows of a column: 32 or 16
-    int tiles;                // that many rows at a time of the B * nq * G query rows of one KV head
     int cols;                 // tiles * Hkv columns
-    int splits;               // workgroups per column
-    int dealt;                // stages go to the wavefronts one by one (else in runs)
     float* part;              // splits > 1: partial results (small_part_floats)
     unsigned* arrivals;       // splits > 1: [cols] counters that only ever count to `splits`, zero between calls
     float scale;
+    float c2, tau_raw;        // scale * log2(e); by how much a raw score may pass the maximum before sums are rescaled (small_scales)
     void* O;                  // final results: [B, nq, Hq, D] bf16 or fp32, LSE [B, nq, Hq] (may be null)
     float* LSE;
     int bf16;

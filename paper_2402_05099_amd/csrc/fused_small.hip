@@ -18,6 +18,10 @@
 // workgroup per column would leave most CUs idle; calls that must not share the workspace keep one, see plan_fused).  With more than one, each writes its combined result to the
 // workspace and counts itself in at the column's arrival counter; the last to arrive combines the column's
 // results, and the counter wraps to zero for the next call.  No workgroup ever waits for another.
+// That meeting is a chain too: results stored and acknowledged 0.4 - 0.9 us, the counter 0.5, the results read 1.1 and up.  The reading
+// lane asks for all results of its row at once, 16 bytes at a time (before: 8 at a time, repeated when there were fewer, 8 bytes each: 2.8
+// and 3.3 us instead of 1.4 and 1.5 with nine workgroups of 16 rows and four of 32).  76 sequences x 4 heads, 1496 keys (nine
+// workgroups per column) 10.9 -> 8.9 us, 32 x 64/8, 4752 keys (four, 32 rows) 21.4 -> 17.5; 26 drawn calls with split columns 1.076.
 //
 // A wavefront streams its stages through one K slot and one V slot of 8 KiB of its own (HBM -> LDS copies issued from
 // inline asm, counted s_waitcnt): the next stage's K rows are requested as soon as this stage's scores are done, its V
@@ -109,15 +113,26 @@ __device__ __forceinline__ uintx4 pack8(const V& p, int tt) {
                   pack_pair(p[8 * tt + 4], p[8 * tt + 5]), pack_pair(p[8 * tt + 6], p[8 * tt + 7])};
 }
 
-// Results that another workgroup of the same launch will read: relaxed stores and loads at agent scope go past the
-// caches that the XCDs do not share, so that nothing has to be flushed before the arrival is counted.
-__device__ __forceinline__ void st_agent(float* p, float a, float b) {
-    const uint64_t v = (uint64_t)__builtin_bit_cast(unsigned, a) | ((uint64_t)__builtin_bit_cast(unsigned, b) << 32);
-    __hip_atomic_store(reinterpret_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t ld_agent(const float* p) {
-    return __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// Results that another workgroup of the same launch will read: stores and loads at agent scope (the cache policy's bit SC1) go past
+// the caches that the XCDs do not share, so that nothing has to be flushed before the arrival is counted.  Buffer
+// instructions take 16 bytes at that scope, where an atomic access takes 8.
+constexpr int kAgentScope = 16;
+struct AgentBuffer {                        // `bytes` (less than 4 GiB) from p on
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ AgentBuffer(float* p, unsigned bytes) : rsrc(__builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00020000)) {}
+    __device__ __forceinline__ void store4(unsigned off, const float4& v) const {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, v), rsrc, (int)off, 0, kAgentScope);
+    }
+    __device__ __forceinline__ void store1(unsigned off, float v) const {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rsrc, (int)off, 0, kAgentScope);
+    }
+    __device__ __forceinline__ float4 load4(unsigned off) const {
+        return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, kAgentScope));
+    }
+    __device__ __forceinline__ float load1(unsigned off) const {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off, 0, kAgentScope));
+    }
+};
 
 template <int D, int TR>
 struct SmallGeo {
@@ -734,17 +749,15 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
 
     if (a.splits > 1) {
         // ---- the column's results meet in the workspace ----------------------------------------------------------------------------------
+        // (a column's [S][TR][D] results and, behind them, [S][TR] LSEs; every access below is at a row < TR of a split < S)
         const int S = a.splits;
-        float* const cO = a.part + (int64_t)col * S * (TR * D);                       // [S][TR][D], then [S][TR] behind all columns
-        float* const cL = a.part + (int64_t)a.cols * S * (TR * D) + (int64_t)col * S * TR * 2;   // (LSE, unused) pairs
-        float* const mine = cO + (int64_t)split * (TR * D) + row * D + 4 * c0;
+        constexpr unsigned OB = TR * D * 4, LB = TR * 4;      // bytes of one split's
+        const AgentBuffer part(a.part + (int64_t)col * S * (TR * (D + 1)), (unsigned)S * (OB + LB));
+        const unsigned at = (unsigned)(row * D + 4 * c0) * 4u, lse_at = (unsigned)S * OB + (unsigned)row * 4u;
         if (finishes) {
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                st_agent(mine + 4 * c, acc[c].x, acc[c].y);
-                st_agent(mine + 4 * c + 2, acc[c].z, acc[c].w);
-            }
-            if (l % LPR == 0) st_agent(cL + (split * TR + row) * 2, lse, 0.f);
+            for (int c = 0; c < CPL; ++c) part.store4((unsigned)split * OB + at + 16 * c, acc[c]);
+            if (l % LPR == 0) part.store1((unsigned)split * LB + lse_at, lse);
         }
         wait_vm<0>();                               // this wavefront's results are where every XCD sees them
         __syncthreads();
@@ -760,22 +773,23 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
         Lsum = 0.f;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-        constexpr int U = 8;                        // results in flight per lane
+        constexpr int U = 16 / CPL;                 // results in flight per lane: all of them, mostly
         for (int i0 = 0; i0 < S; i0 += U) {
-            uint64_t lw[U], ow[U][2 * CPL];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = min(i0 + u, S - 1);
-                lw[u] = ld_agent(cL + (i * TR + row) * 2);
-#pragma unroll
-                for (int c = 0; c < 2 * CPL; ++c) ow[u][c] = ld_agent(cO + (int64_t)i * (TR * D) + row * D + 4 * c0 + 2 * c);
-            }
             float li[U], gm = M;
+            float4 ow[U][CPL];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                li[u] = i0 + u < S ? __builtin_bit_cast(float, (unsigned)lw[u]) : -INFINITY;
-                gm = fmaxf(gm, li[u]);
+                li[u] = -INFINITY;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) ow[u][c] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (i0 + u < S) {
+                    li[u] = part.load1((unsigned)(i0 + u) * LB + lse_at);
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) ow[u][c] = part.load4((unsigned)(i0 + u) * OB + at + 16 * c);
+                }
             }
+#pragma unroll
+            for (int u = 0; u < U; ++u) gm = fmaxf(gm, li[u]);
             const float gs = gm == -INFINITY ? 0.f : gm;        // nothing but empty results so far: every weight is 0
             const float re = __builtin_amdgcn_exp2f((M - gs) * kLog2e);
             M = gm;
@@ -788,10 +802,10 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
                 Lsum += f;
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
-                    acc[c].x = fmaf(f, __builtin_bit_cast(float, (unsigned)ow[u][2 * c]), acc[c].x);
-                    acc[c].y = fmaf(f, __builtin_bit_cast(float, (unsigned)(ow[u][2 * c] >> 32)), acc[c].y);
-                    acc[c].z = fmaf(f, __builtin_bit_cast(float, (unsigned)ow[u][2 * c + 1]), acc[c].z);
-                    acc[c].w = fmaf(f, __builtin_bit_cast(float, (unsigned)(ow[u][2 * c + 1] >> 32)), acc[c].w);
+                    acc[c].x = fmaf(f, ow[u][c].x, acc[c].x);
+                    acc[c].y = fmaf(f, ow[u][c].y, acc[c].y);
+                    acc[c].z = fmaf(f, ow[u][c].z, acc[c].z);
+                    acc[c].w = fmaf(f, ow[u][c].w, acc[c].w);
                 }
             }
         }
@@ -840,7 +854,8 @@ static hipError_t launch_small_d(const SmallArgs& a, hipStream_t s) {
     return a.pg.table ? launch_small_t<D, true, 0, TR>(a, s) : launch_small_t<D, false, 0, TR>(a, s);
 }
 
-// Workspace floats the splits of a call need: [cols][splits][rows][D] results, [cols][splits][rows] pairs of (LSE, unused)
+// Workspace floats the splits of a call need: per column [splits][rows][D] results and [splits][rows] LSEs (and as many left over, which
+// earlier layouts used: what fits a workspace does not change)
 size_t small_part_floats(int cols, int splits, int rows, int D) { return (size_t)cols * splits * rows * (D + 2); }
 
 hipError_t launch_fused_small(const SmallArgs& args, int D, hipStream_t s) {

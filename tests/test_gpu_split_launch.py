@@ -105,6 +105,29 @@ def test_split_launch_long_block(D, cache):
     calls(wl.make_workload("long", 41, 3, 4, 1, D, [(1, 9001, 3)], 1, 70), cache, f"long block D={D} {cache}")
 
 
+@pytest.mark.parametrize("P", [6000, 9001, 12000, 30000, 60000])
+@pytest.mark.parametrize("option", [0, 2])
+@pytest.mark.parametrize("D", [64, 128])
+def test_split_launch_many_partial_results(D, option, P):
+    """The last workgroup of a column reads up to 16 (columns of 16 rows, or D = 64) or 8 results at a time: fewer, as many, one more
+    and several times as many, over empty suffixes (sequence 1 has none)."""
+    w = wl.make_workload("many parts", 48, 3, 4, 1, D, [(1, P, 3)], 1, 70)
+    w.lengths[1] = 0
+    kv = dev.paged_to_device(wl.make_paged(w, 16))
+    dw = dev.to_device(w)
+    plan = hb.hg_debug_fused_plan([(1, P, 3)], 3, 1, 4, 1, D, dw.max_len, 16, options={hb.HG_OPT_FUSED_KERNEL: option})
+    assert plan["way"] == "single" and plan["splits"] > 4, plan
+    print(f"split launch: D={D} option {option}: {plan['splits']} results of {plan['column_rows']} rows", file=sys.stderr, flush=True)
+    ctx = dev.make_context(dw, parts=64)
+    ctx.set_option(hb.HG_OPT_FUSED_KERNEL, option)
+    O = torch.full(dw.lead + (D,), float("nan"), dtype=torch.float32, device="cuda:0")
+    L = torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0")
+    hb.hg_hydragen_attn_paged(ctx, dw.Q, dw.levels, kv, dw.lengths, dw.max_len, O, L, dw.scale)
+    torch.cuda.synchronize()
+    check(to_np(O), to_np(L), *oracle.attention(w), f"{plan['splits']} results")
+    ctx.close()
+
+
 def test_one_context_alternates_between_ways_and_splits():
     """Split single launches with different numbers of workgroups per column, and combined launches, take turns on one context
     and its counters, some of them captured: every call leaves the counters as the next one needs them."""

@@ -268,3 +268,40 @@ def test_paged_error_paths_launch_nothing():
     assert float(O.min()) == 7.0 and float(L.min()) == 7.0
     small.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("codes", [False, True], ids=["bf16", "e4m3"])
+@pytest.mark.parametrize("nq,Hkv,D", [(1, 1, 64), (1, 9, 128), (8, 8, 128), (2, 40, 128), (64, 40, 64)])
+def test_kv_append_pieces_per_workgroup(nq, Hkv, D, codes):
+    """Rows of fewer pieces than a wavefront, of a number that is no multiple of one, of exactly as many as a workgroup has threads (1024), of
+    more, and of many times more; sequences with room for all new rows, for some, for none, and one with a negative length."""
+    say(f"append pieces nq={nq} Hkv={Hkv} D={D} codes={codes}")
+    cap, scale = 70, 0.25
+    lengths = torch.tensor([0, 3, cap - 1, cap, cap + 5, -1, 5], dtype=torch.int32)
+    B = len(lengths)
+    g = torch.Generator().manual_seed(5)
+    Kn, Vn = (torch.randn((B, nq, Hkv, D) if nq > 1 else (B, Hkv, D), generator=g).to(torch.bfloat16) for _ in range(2))
+    kind = torch.uint8 if codes else torch.int16
+    K0, V0 = (torch.randint(0, 100, (B * cap, Hkv, D), generator=g).to(kind) for _ in range(2))
+    want = [K0.clone(), V0.clone()]
+    for b, L in enumerate(lengths.tolist()):
+        for t in range(nq):
+            if 0 <= L and L + t < cap:
+                for out, new in zip(want, (Kn, Vn)):
+                    row = new.view(B, nq, Hkv, D)[b, t]
+                    out[b * cap + L + t] = ((row.float() / scale).clamp(-448.0, 448.0).to(torch.float8_e4m3fn).view(torch.uint8) if codes
+                                            else row.view(torch.int16))
+    K, V = (x.cuda() if codes else x.cuda().view(torch.bfloat16) for x in (K0, V0))
+    off, ln = (torch.arange(B, dtype=torch.int32) * cap).cuda(), lengths.cuda()
+    ctx = hb.Context(0, 0)
+    if nq > 1:
+        ctx.set_option(hb.HG_OPT_NUM_QUERIES, nq)
+    if codes:
+        hb.hg_kv_append_fp8(ctx, Kn.cuda(), Vn.cuda(), K, V, scale, scale, off, ln, cap)
+    else:
+        hb.hg_kv_append(ctx, Kn.cuda(), Vn.cuda(), K, V, off, ln, cap)
+    torch.cuda.synchronize()
+    for got, w in zip((K, V), want):
+        assert torch.equal(got.cpu().view(kind), w)
+    assert ln.cpu().tolist() == [L if L < 0 or L >= cap else min(L + nq, cap) for L in lengths.tolist()]
+    ctx.close()

@@ -194,6 +194,9 @@ PrefixArgs level_args(const void* Q, const LevelDev& lv, const LevelPlan& plan, 
     a.lv = lv;
     a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.G = Hq / Hkv;
     a.nq = nq;
+    a.by_heads = divider((unsigned)Hkv);
+    a.by_seq = divider((unsigned)(nq * a.G));
+    a.by_group = divider((unsigned)a.G);
     a.scale = scale;
     a.out = out;
     if (plan.wide) a.wide = plan.wp;

@@ -42,8 +42,8 @@ static_assert(offsetof(CombinedArgs, p) == 0 && sizeof(CombinedArgs) <= 4096, "t
 static_assert(kLengthClasses * NW == 64, "one lane per class and wavefront");
 
 // order[0 .. B): the sequences in descending order of their length class (eighths of max_len), by number within a class, so
-// that the last items handed out are the short ones.  Every workgroup computes it for itself (3 us, 512 lengths per round)
-// and all come to the same order.  Longest first against order of the sequences: 512 x 64/8 heads with suffixes of 1..512
+// that the last items handed out are the short ones.  Every workgroup computes it for itself (512 lengths per round, read once if
+// that is all; the prefix sum stays in the vector ALU) and all come to the same order.  Longest first against order of the sequences: 512 x 64/8 heads with suffixes of 1..512
 // rows 148 -> 131 us, 256 x 40 heads, 1..256 rows 135 -> 127.
 __device__ __forceinline__ void order_by_length(const DecodeArgs& a, unsigned char* smem) {
     uint16_t* const order = reinterpret_cast<uint16_t*>(smem + kOrderOffset);
@@ -57,8 +57,9 @@ __device__ __forceinline__ void order_by_length(const DecodeArgs& a, unsigned ch
         return b < b1 ? kLengthClasses - 1 - min((int)((float)n * per), kLengthClasses - 1) : kLengthClasses;
     };
     int cnt[kLengthClasses] = {};
+    const int k0 = class_of(b0 + lane);         // (up to 512 sequences: all there is, and its length is read once)
     for (int b = b0; b < b1; b += 64) {
-        const int k = class_of(b + lane);
+        const int k = b == b0 ? k0 : class_of(b + lane);
 #pragma unroll
         for (int i = 0; i < kLengthClasses; ++i) cnt[i] += __popcll(__ballot(k == i));
     }
@@ -66,19 +67,21 @@ __device__ __forceinline__ void order_by_length(const DecodeArgs& a, unsigned ch
 #pragma unroll
         for (int i = 0; i < kLengthClasses; ++i) counts[i * NW + w] = cnt[i];
     __syncthreads();
-    unsigned at = counts[lane];
-    const unsigned own = at;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {          // exclusive prefix sum over (class, wavefront)
-        const unsigned below = __shfl_up(at, d);
-        if (lane >= d) at += below;
-    }
+    int at = (int)counts[lane];
+    const int own = at;
+    // exclusive prefix sum over (class, wavefront): within rows of 16 lanes, then the rows' totals
+    at += __builtin_amdgcn_update_dpp(0, at, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8
+    at += __builtin_amdgcn_update_dpp(0, at, 0x112, 0xf, 0xf, false);
+    at += __builtin_amdgcn_update_dpp(0, at, 0x114, 0xf, 0xf, false);
+    at += __builtin_amdgcn_update_dpp(0, at, 0x118, 0xf, 0xf, false);
+    at += __builtin_amdgcn_update_dpp(0, at, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+    at += __builtin_amdgcn_update_dpp(0, at, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
     at -= own;
     int base[kLengthClasses];
 #pragma unroll
-    for (int i = 0; i < kLengthClasses; ++i) base[i] = __builtin_amdgcn_readlane((int)at, i * NW + w);
+    for (int i = 0; i < kLengthClasses; ++i) base[i] = __builtin_amdgcn_readlane(at, i * NW + w);
     for (int b = b0; b < b1; b += 64) {
-        const int k = class_of(b + lane);
+        const int k = b == b0 ? k0 : class_of(b + lane);
 #pragma unroll
         for (int i = 0; i < kLengthClasses; ++i) {
             const unsigned long long m = __ballot(k == i);

@@ -11,6 +11,18 @@ namespace hg {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
+// Division by a number that the host knows, without one: q = n / d for n < 2^31 (Granlund and Montgomery, "Division by invariant
+// integers using multiplication": with s = ceil(log2 d) and mul = ceil(2^(31 + s) / d) < 2^32, q = floor(n mul / 2^(31 + s))).
+struct Divider {
+    unsigned mul, shift;
+    __host__ __device__ unsigned of(unsigned n) const { return (unsigned)(((uint64_t)(2u * n) * mul) >> 32) >> shift; }
+};
+inline Divider divider(unsigned d) {      // 1 <= d < 2^31
+    unsigned s = 0;
+    while ((1u << s) < d) ++s;
+    return Divider{(unsigned)(((1ull << (31 + s)) + d - 1) / d), s};
+}
+
 // ---- device-side descriptions --------------------------------------------------------------------
 
 struct LevelDev {
@@ -50,6 +62,9 @@ struct WidePlan {
                     // cut evenly among its own teams, or whole columns per team when there are more columns than teams);
                     // 2: ranges of equal cost from the table below (a column boundary inside a range counts as
                     // kWideBoundaryCost stages: the team's workgroups store a result and load a Q tile there)
+    Divider by_T, by_n_c, by_rowgroups;          // divisions that a workgroup makes on its way to a piece
+    Divider by_quota, by_cols, by_teams;         // (quota, ncols, 8 * tpx)
+    Divider by_cut[2];                           // mode 1: by the teams of a column, nteams / ncols and one more
     int starts[kWideMaxTeams + 1];      // mode 2: team t walks [starts[t], starts[t + 1])
     int first_part[kWideMaxTeams];      // mode 2: part index of team t's first piece (pieces of its column before it)
 };
@@ -59,6 +74,7 @@ struct PrefixArgs {
     LevelDev lv;
     int B, Hq, Hkv, G;
     int nq;           // queries per sequence: a sequence contributes nq*G rows per KV head, row = t*G + g
+    Divider by_heads, by_seq, by_group;      // division by Hkv, nq * G, G
     int mtiles;       // query-row tiles per (block, KV head)
     int nsplit;       // key-range splits per block
     int chunk;        // keys per split (multiple of the key tile)
@@ -123,18 +139,6 @@ struct CombinedArgs {
 // CU busy for 45 us.  (256 x 40 heads with suffixes of 1..256 rows: runs of 32 and 8 150 us, 32 / 8 / 2 150, 16 / 4 / 2 134,
 // 8 / 2 135, 4 138.)
 constexpr int kLongRun = 8, kTailItems = 1024;
-
-// Division by a number that the host knows, without one: q = n / d for n < 2^31 (Granlund and Montgomery, "Division by invariant
-// integers using multiplication": with s = ceil(log2 d) and mul = ceil(2^(31 + s) / d) < 2^32, q = floor(n mul / 2^(31 + s))).
-struct Divider {
-    unsigned mul, shift;
-    __host__ __device__ unsigned of(unsigned n) const { return (unsigned)(((uint64_t)(2u * n) * mul) >> 32) >> shift; }
-};
-inline Divider divider(unsigned d) {      // 1 <= d < 2^31
-    unsigned s = 0;
-    while ((1u << s) < d) ++s;
-    return Divider{(unsigned)(((1ull << (31 + s)) + d - 1) / d), s};
-}
 
 // The single-launch fused kernel (fused_small.hip): every level, the suffix and the merge for columns of 32 or 16 query rows.
 constexpr int kSmallMaxSplits = 32;           // workgroups per column at most

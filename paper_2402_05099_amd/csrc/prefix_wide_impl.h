@@ -153,6 +153,7 @@ struct WidePiece {
 // What one workgroup of the persistent kernel does with one level: the first 8 * wide.slots workgroups of the launch call
 // this.  `ka` points at the level's arguments in the kernarg segment (without the tables at its end unless they are used).
 typedef const __attribute__((address_space(4))) PrefixArgs* wide_args_ptr;
+__device__ __forceinline__ unsigned div_by(unsigned n, const __attribute__((address_space(4))) Divider& d) { return Divider{d.mul, d.shift}.of(n); }
 __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     HG_T(0);
 #ifdef HG_TRACE
@@ -172,35 +173,38 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     const auto& p = ka->wide;
     const int pid = blockIdx.x;
     const int xcd = pid & 7, cu_slot = pid >> 3;         // workgroups whose ids are equal modulo 8 run on one XCD (which one varies by launch)
-    const int team_local = cu_slot / p.T, member = cu_slot % p.T;
+    const int team_local = (int)div_by((unsigned)cu_slot, p.by_T), member = cu_slot - team_local * p.T;
     if (team_local >= p.tpx) return;
     const int team = xcd * p.tpx + team_local;
     const int nteams = 8 * p.tpx;
     const int total = p.ncols * p.n_c;      // the planner keeps this below 2^31 (and the columns below 2^20)
 
     // ---- this team's range [f0, f1) of the flattened (column, stage) space; sp0 = part index of its first piece ----
-    // (32-bit arithmetic: a 64-bit division costs a loop of its own on this chip)
+    // (Divisions, here, in the look-up of a piece and in the lanes' row numbers, are multiplications by numbers from the host: on this
+    // chip one by a run-time divisor takes some 30 instructions that wait for each other, one of 64 bits a loop.  With the order of the sequences
+    // in combined_impl.h: 256 x 64/8 heads, 4K keys, four queries 185.4 -> 184.5 us, 512 x 64/8, 4K keys 135.0 -> 134.2; eleven drawn combined calls 1.008 in the mean.)
     int f0, f1, sp0;
     if (p.mode == 0) {            // equal contiguous ranges
         const long long lo = (long long)team * p.quota;
         if (lo >= total) return;
         f0 = (int)lo;
         f1 = (int)(lo + p.quota < total ? lo + p.quota : total);
-        sp0 = team - (int)((unsigned)(f0 / p.n_c * p.n_c) / (unsigned)p.quota);
+        sp0 = team - (int)div_by(div_by((unsigned)f0, p.by_n_c) * (unsigned)p.n_c, p.by_quota);
     } else if (p.mode == 2) {     // ranges of equal cost, from the planner's table
         f0 = p.starts[team];
         f1 = p.starts[team + 1];
         sp0 = p.first_part[team];
     } else if (p.ncols <= nteams) {   // every column is cut evenly among its own teams
-        const int c = team * p.ncols / nteams;
-        const int tf = (c * nteams + p.ncols - 1) / p.ncols;
-        const int nt = ((c + 1) * nteams + p.ncols - 1) / p.ncols - tf;
+        const int c = (int)div_by((unsigned)(team * p.ncols), p.by_teams);
+        const int tf = (int)div_by((unsigned)(c * nteams + p.ncols - 1), p.by_cols);
+        const int nt = (int)div_by((unsigned)((c + 1) * nteams + p.ncols - 1), p.by_cols) - tf;
+        const int more = nt * p.ncols > nteams;      // nteams / ncols teams, or one more
         sp0 = team - tf;
-        f0 = c * p.n_c + (int)((unsigned)sp0 * (unsigned)p.n_c / (unsigned)nt);
-        f1 = c * p.n_c + (int)((unsigned)(sp0 + 1) * (unsigned)p.n_c / (unsigned)nt);
+        f0 = c * p.n_c + (int)div_by((unsigned)(sp0 * p.n_c), p.by_cut[more]);
+        f1 = c * p.n_c + (int)div_by((unsigned)((sp0 + 1) * p.n_c), p.by_cut[more]);
     } else {                      // whole columns per team
-        f0 = (int)((unsigned)team * (unsigned)p.ncols / (unsigned)nteams) * p.n_c;
-        f1 = (int)((unsigned)(team + 1) * (unsigned)p.ncols / (unsigned)nteams) * p.n_c;
+        f0 = (int)div_by((unsigned)(team * p.ncols), p.by_teams) * p.n_c;
+        f1 = (int)div_by((unsigned)((team + 1) * p.ncols), p.by_teams) * p.n_c;
         sp0 = 0;
     }
     if (f0 >= f1) return;
@@ -228,9 +232,8 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     auto load_piece = [&](kargs_ptr k, int f, int c, int k0, int sp, WidePiece& q) -> int {
         const int n_c = k->wide.n_c, rowgroups = k->wide.rowgroups, Hkv = k->Hkv;
         const int len = min(n_c - k0, f1 - f);
-        const int rg = c % rowgroups;
-        const int kvh = (c / rowgroups) % Hkv;
-        const int g = c / (rowgroups * Hkv);
+        const int head = (int)div_by((unsigned)c, k->wide.by_rowgroups), rg = c - head * rowgroups;
+        const int g = (int)div_by((unsigned)head, k->by_heads), kvh = head - g * Hkv;
         int seq0 = 0, seq1 = k->B, kv0 = 0, kv1 = k->lv.max_rows;
         const const_i32_ptr seq_off_c = (const_i32_ptr)(uintptr_t)k->lv.seq_off;
         if (seq_off_c) {
@@ -276,7 +279,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
         int valid;
     } cur{};
     int cf = f0;                     // position of the piece after the cursor's
-    int cc = f0 / p.n_c, ck0 = f0 - cc * p.n_c;
+    int cc = (int)div_by((unsigned)f0, p.by_n_c), ck0 = f0 - cc * p.n_c;
     auto cursor_set = [&](kargs_ptr k, const WidePiece& q) {      // points the cursor at the first stage of piece q (q.nst > 0)
         // (everything but the lane offsets is uniform; saying so keeps it in scalar registers, where the copy
         // instructions take their base address from)
@@ -363,8 +366,9 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     struct RowCtx { bool rv; int64_t qidx; };
     // a sequence contributes nq * G rows per KV head: (query t, head g) at t*G + g
     auto row_index = [&](kargs_ptr k, const WidePiece& q, int r) -> int64_t {     // (b*nq + t)*Hq + h of row r of the block
-        const int G = k->G, nq = k->nq, rps = nq * G;
-        return ((int64_t)(q.seq0 + r / rps) * nq + (r % rps) / G) * k->Hq + q.kvh * G + r % G;
+        const int G = k->G, nq = k->nq;
+        const int b = (int)div_by((unsigned)r, k->by_seq), in_seq = r - b * (nq * G), t = (int)div_by((unsigned)in_seq, k->by_group);
+        return ((int64_t)(q.seq0 + b) * nq + t) * k->Hq + q.kvh * G + (in_seq - t * G);
     };
     auto row_ctx = [&](kargs_ptr k, const WidePiece& q) -> RowCtx {
         const int r = q.row0 + w * 32 + lq;     // this lane's query row inside the block
@@ -959,6 +963,15 @@ bool plan_prefix_wide(const LevelDev& lv, int Hkv, int G, int D, int max_parts, 
             }
         }
     }
+    p.by_T = divider((unsigned)p.T);
+    p.by_n_c = divider((unsigned)p.n_c);
+    p.by_rowgroups = divider((unsigned)p.rowgroups);
+    p.by_quota = divider((unsigned)p.quota);
+    p.by_cols = divider((unsigned)p.ncols);
+    p.by_teams = divider((unsigned)nteams);
+    const int cut = std::max(1, nteams / p.ncols);
+    p.by_cut[0] = divider((unsigned)cut);
+    p.by_cut[1] = divider((unsigned)cut + 1);
     *out = p;
     return true;
 }

@@ -295,6 +295,20 @@ def test_combined_calls_bound_by_their_suffix_give_the_shared_levels_five_cus(sh
     assert isinstance(less, int) or less["parts"] < plan["parts"]
 
 
+@pytest.mark.parametrize("tiles,splits,Hkv", [(1, 1, 1), (3, 7, 40), (65537, 1, 5), (1000003, 1, 40), (46341, 31, 40), (2**20 + 1, 16, 64), (8388593, 32, 8 - 1), (2**31 // 8 - 3, 1, 8)])
+def test_divisions_by_numbers_from_the_host(tiles, splits, Hkv):
+    """The kernels divide by multiplying with a number from the host; exact for every numerator below 2^31.  Here through the work of
+    a workgroup of a single launch, over divisors and numerators up to the limits."""
+    n = tiles * splits * Hkv
+    rng = np.random.default_rng(3)
+    for x in range(8):
+        first, end = x * n // 8, (x + 1) * n // 8
+        near = [a + d for a in (first, (first + end) // 2, (first // (tiles * splits) + 1) * tiles * splits, end) for d in (-2, -1, 0, 1)]
+        for at in sorted({a for a in near + rng.integers(first, max(end, first + 1), 20).tolist() if first <= a < end}):
+            kvh, rest = divmod(at, tiles * splits)
+            assert hb.hg_debug_single_work(8 * (at - first) + x, tiles, splits, Hkv) == (kvh, *divmod(rest, splits)), at
+
+
 @pytest.mark.parametrize("tiles,splits,Hkv", [(1, 1, 1), (7, 1, 1), (3, 5, 1), (2, 3, 10), (5, 1, 3), (4, 5, 10), (4, 5, 12), (9, 1, 36), (13, 2, 8), (6, 1, 40), (1, 32, 5)])
 def test_single_launch_deals_heads_out_to_the_xcds(tiles, splits, Hkv):
     """Every column and split once, the same number for every XCD, and the workgroups of a KV head side by side: on its share of the

@@ -48,7 +48,7 @@ extern "C" {
  * stream, 3 on two streams, 4 no keys at all; workgroups per column (way 0, else 0); partial results per row (0 for way 0); keys
  * per work item of the suffix kernel (way 0: query rows per column); work items per row (way 0: 1 if the
  * stages of a column go to its wavefronts one by one, 0 if in runs); 1 if the suffix runs on the matrix cores; levels on the persistent
- * kernel (bit i: levels[i]); CUs per XCD of the persistent kernel, 0 if it does not run }.
+ * kernel (bit i: levels[i]); CUs per XCD of the persistent kernel, 0 if it does not run (way 0: wavefronts of a workgroup) }.
  *
  * hg_debug_single_work: what a workgroup of a single launch works on, `tiles` columns per KV head with `splits` workgroups each:
  * fills out[3] = { KV head, column of that head, split } and returns 1, or returns 0 if that workgroup has nothing to do or does

@@ -577,6 +577,7 @@ def hg_debug_fused_plan(levels, B: int, nq: int, Hq: int, Hkv: int, D: int, max_
     plan["way"] = ("single", "combined", "one_stream", "two_streams", "fill")[plan["way"]]
     if plan["way"] == "single":
         plan["column_rows"], plan["chunk"] = plan["chunk"], 0
+        plan["wavefronts"], plan["slots"] = plan["slots"], 0
         plan["dealt"], plan["nchunks"] = bool(plan["nchunks"]), 0
     return plan
 

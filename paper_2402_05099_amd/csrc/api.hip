@@ -784,6 +784,7 @@ struct FusedPlan {
     int way;
     int splits;                     // single launch: workgroups per column
     int column_rows;                // and query rows
+    int wavefronts;                 // of a workgroup
     bool dealt;                     // its stages go to the wavefronts one by one
     bool sfx_mfma;                  // the suffix kernel's choice for these rows is the matrix cores
     int nlev;                       // levels that hold keys
@@ -916,6 +917,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     p.way = kWaySingle;
     p.splits = 1;
     p.column_rows = 32;
+    p.wavefronts = 8;
     p.dealt = true;
     p.nlev = 0;
     p.main_level = p.joint = -1;
@@ -943,37 +945,39 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
                           (sfx_mfma || (nq == 1 && G == 1));
     const bool may_combine = may_join && long_enough;
 
-    // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts per
-    // column of 32 or 16 query rows walk every shared block and the column's suffixes and merge, against one launch per part, two
-    // event edges and a round trip of the partial results through HBM for the separate kernels.  Both durations are
-    // estimated, in microseconds, from fits to 520 calls (B = 4 .. 2048, 0 .. 16K shared keys, every cache, KV heads that divide 8
-    // or are a multiple of it, each with 16 and 32 rows and every number of workgroups per column; mean error of an estimate 9 %; over
-    // 87 calls with other numbers of heads the choice is 0.88 of the other way's time in the mean, over 117 of the former 0.84):
-    //   single launch: a + rounds x (b + c x stages per wavefront), c growing with the CUs that are busy (they share the L2s), 1.4
-    //                  times that for 8-bit rows with fp32 weights; m0 + m1 x splits more when a column's workgroups have to
-    //                  meet; constants below.  Never faster than the suffix rows stream in (4.2 TB/s, 3.3 through a page table).
-    //   separate:      10.5 and 0.7 of the suffix time without a shared block; else 18, 6 and 10 more with one and two shared levels, 8 more once a block is long enough to be split,
-    //                  suffix rows at 5 TB/s (the vector ALU with several rows per KV head: 0.5 of that time per row),
-    //                  shared blocks at 1.1 PFLOP/s or 5 TB/s; with many suffix rows and one launch for both (below) 25, and 0.8 of the suffix time.
+    // One launch for everything when that is the faster way (fused_small.hip): `splits` workgroups of eight wavefronts, or one of four, per
+    // column of 32 or 16 query rows walk every shared block and the column's suffixes and merge, against one launch per part or for both,
+    // two event edges and a round trip of the partial results through HBM for the other ways.  Both durations are
+    // estimated, in microseconds, from fits to 2070 drawn calls of up to 260 us (B = 4 .. 2048, 0 .. 16K shared keys, every cache, each timed in
+    // both ways, with 16 and 32 rows, with up to 30 workgroups per column and with four wavefronts; error of an estimate 13 %, of 4 wavefronts
+    // and of the other ways 17 %); constants below:
+    //   single launch, eight wavefronts: a + rounds x (b + c x stages per wavefront), c growing with the CUs that are busy (they share the
+    //                  L2s), more for 8-bit rows with fp32 weights; m0 + m1 x splits when a column's workgroups have to meet.
+    //   four:          a + (columns per place + tail) x (b + c x stages per wavefront), shared and suffix stages by their own.
+    //                  Neither is faster than the suffix rows stream in.
+    //   the other way: a launch price for each shared level, the longer of suffix and shared blocks and a part of the shorter, partial results.
     // 16 rows: half the products and exponentials per stage and fewer sequences' suffixes per column, but twice the columns, each
     // reading the shared rows for itself: they win while there are CUs for them.  Measured 32 / 16 rows: 13.2 / 10.0 us (45 x 16/2
     // heads, 515 keys), 15.9 / 12.0 (256 x 8/1, 1K keys), 11.3 / 8.8 (95 x 16/2, two queries), 44.5 / 61 (139 x 64/8, four queries),
     // 27.2 / 31 (60 x 16/2, 3K keys, three workgroups per column).
+    // Four wavefronts: half the LDS, so two columns share a CU (at D = 64 three) and one's prologue and combination run beside
+    // the other's stages.  A column takes longer: for calls with more columns than CUs and few stages to a column.  Eight / four wavefronts, and the other
+    // way, us: 683 x 64/8 heads, 549 keys, four queries 222 / 167, 199; 1965 x 64/8, 1294 + 16 x 115 keys 223 / 193, 225; 215 x 64/8, 553 keys, four
+    // queries, codes 79 / 62, 76; 57 x 64/8, 342 + 3 x 297 keys, four queries 21.7 / 15.7, 22; 256 x 64/8, 4K keys, four queries 247 / 232, 185 (not taken).
     // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single launch is
-    // taken below the other estimate, from 60 us on only when it is 25 % below (the model of the separate kernels is
-    // pessimistic where suffixes and shared blocks overlap): over the 520 calls 0.4 % slower than the better way each time.
-    // Measured single / other way: 9.3 / 17 us (12 x 64/8 heads, D = 64, 1261 keys, codes), 13.1 / 35 (53 x 8/1, 1268 + 5 x 289 keys,
-    // codes), 28 / 53 (34 x 32/8, 10.5K keys), 45 / 22 (428 x 64/8, no shared keys, codes, paged: not taken), 73 / 45 (268 x 16/16, 4648 keys,
-    // 35 rows, paged: taken, one of the eleven that miss by more than a tenth).
+    // taken below 1.2 of the other estimate, from 36 us on below 0.94 and from 60 on below 0.9 of it.  Over the 2070 calls 1.023 times as fast as with the constants
+    // of before (fitted when a column's workgroups met in 2 us more and its prologue took 1) and without four wavefronts, 0.98 of the best way's
+    // speed; over 150 others 1.027, two of them slower by more than 3 % (136 x 64/8, D = 64, 2707 keys 20.4 -> 23.2 us; 89 x 40/40, D = 64, 408 codes
+    // and no shared keys 49.4 -> 53.3).
     // (the single launch divides sums by the V scale and multiplies them again: not with scales near the ends of fp32)
     const bool odd_scale = f.fp8 && has_suffix && !(f.v_scale >= 0x1p-60f && f.v_scale <= 0x1p60f);
-    bool take_single = false, combined_wins = false;      // (over the single launch, if there is room for it)
+    bool take_single = false;
     if (c->opt_fused_kernel != 1 && !c->opt_timing && !odd_scale) {
         const int rps = nq * G;
         const bool fp32_weights = f.fp8 && has_suffix && !sfx_mfma;
         long long shared_keys = 0;
         double flops = 0.0, padded = 0.0, shared_bytes = 0.0;      // padded: flops with whole 256-row tiles
-        // wide: a level runs on the persistent kernel otherwise; joins: and shares its launch with the suffix, or could if that were longer
+        // wide: a level runs on the persistent kernel otherwise
         bool any = has_suffix, wide = false;
         int nonempty = 0;
         for (int i = 0; i < n_levels; ++i) {
@@ -988,7 +992,6 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
                 ++nonempty;
             }
         }
-        const bool joins = may_join && wide;
         // Shared rows that neither their XCD's L2 (4 MB) nor, with the suffix rows and another layer's, the 256 MB behind all of them hold: a stage takes
         // half as long again (from five workgroups per column on the waits overlap).  109 x 40/40 heads, D = 64, 7168 keys, 160 columns: 32 suffix rows 45.8 us, 68 rows 76 (separate kernels 48); 64 keys only 11.7
         // and 22; 32 x 40/40, 4K / 8K keys 1.9 / 3.0 us a stage.
@@ -1011,26 +1014,33 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             return x;
         };
         const Shape shape32 = shape_of(32), shape16 = shape_of(16);
-        // the separate kernels at their lightest, the single launch at its slowest: full columns of codes with fp32 weights
-        const bool light = rps == 1 && fp32_weights && D == 128 && !wide && B >= 24;
         const long long cols = shape32.cols;
         const int seqs_per_tile = shape32.seqs_per_tile;
-        // Workgroups that run at a time: one per CU, at D = 64 two (LDS).  Those share it, and a stage takes longer: 112 x 40/40 heads, 8K keys: 48 us with 160
-        // columns of 32 rows, 66 with 280 of 16 rows (45 with 160 of them).  Of 32 rows with fp32 weights the registers hold one per CU: 264 x 32/8, 4171
-        // keys, 264 columns 70 us against 51 on separate kernels.  With both counted, over 700 drawn calls 0.97 of the time.
+        // Workgroups of eight wavefronts that run at a time: one per CU, at D = 64 two (LDS), which take longer then: 112 x 40/40 heads, 8K keys: 48 us with 160
+        // columns of 32 rows, 66 with 280 of 16 rows (45 with 160 of them).
         auto rounds_of = [&](double wgs) { return ceil(wgs / (D == 128 ? 256.0 : 512.0)); };
-        auto shared_cu = [&](int rows, double wgs) {
-            return D == 128 || wgs <= 256.0 || wgs > 512.0 ? 1.0 : !fp32_weights ? 1.3 : rows == 32 ? 1.5 : 1.0;
-        };
+        struct Eight { double a, b, c, more, m0, m1, fp32_weights, sharing, rounds, paged, packed; };      // (paged, packed: of the suffix rows' time at 5 TB/s)
+        struct Four { double a, b, c, more, c_suffix, fp32_weights, tail, paged, packed; };
+        static const Eight eight[2][2] = {      // [D = 64][16 rows]
+            {{1.0, 4.8, 1.56, 0.20, 1.8, 0.31, 1.43, 1.0, 1.0, 1.2, 0.9}, {1.2, 3.4, 1.42, 0.0, 1.9, 0.08, 1.34, 1.0, 1.0, 1.06, 0.87}},
+            {{0.2, 4.5, 1.01, 0.05, 1.7, 0.08, 1.65, 1.76, 1.39, 1.42, 0.98}, {1.6, 2.9, 0.82, 0.07, 1.5, 0.05, 1.55, 1.39, 1.16, 1.18, 0.92}}};
+        static const Four four[2][2] = {
+            {{0.0, 5.9, 0.97, 0.41, 1.69, 1.19, 0.56, 0.97, 0.83}, {1.7, 3.5, 0.86, 0.56, 1.73, 1.15, 0.25, 0.93, 0.82}},
+            {{1.8, 3.2, 0.79, 0.42, 1.16, 1.40, 0.39, 1.38, 1.0}, {2.3, 2.0, 0.64, 0.36, 1.05, 1.40, 0.39, 1.34, 0.96}}};
         auto chain_at = [&](int rows, int S) {
-            static const double fit[2][2][7] = {      // a, b, c on a quarter of the chip, more on all of it, m0, m1, codes with fp32 weights
-                {{3.2, 4.6, 1.50, 0.60, 4.0, 0.44, 1.5}, {2.9, 3.2, 1.32, 0.46, 2.5, 0.14, 1.42}},       // D = 128: 32 rows, 16 rows
-                {{1.8, 4.2, 1.08, 0.42, 1.95, 0.16, 1.42}, {1.9, 3.5, 0.93, 0.33, 1.5, 0.10, 1.38}}};    // D = 64
-            const double* const k = fit[D == 64][rows == 16];
+            const Eight& k = eight[D == 64][rows == 16];
             const Shape& x = rows == 16 ? shape16 : shape32;
             const double wgs = (double)x.cols * S;
-            const double per_stage = shared_cu(rows, wgs) * (fp32_weights ? k[6] : 1.0) * (k[2] + k[3] * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
-            return k[0] + rounds_of(wgs) * (k[1] + per_stage * ceil((x.stages + (far && S <= 4 ? 0.5 * x.shared : 0.0)) / (8.0 * S))) + (S > 1 ? k[4] + k[5] * S : 0.0);
+            const double per_stage = (wgs <= 256.0 ? 1.0 : wgs <= 512.0 ? k.sharing : k.rounds) * (fp32_weights ? k.fp32_weights : 1.0) *
+                                     (k.c + k.more * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
+            return k.a + rounds_of(wgs) * (k.b + per_stage * ceil((x.stages + (far && S <= 4 ? 0.5 * x.shared : 0.0)) / (8.0 * S))) + (S > 1 ? k.m0 + k.m1 * S : 0.0);
+        };
+        auto chain_of_four = [&](int rows) {
+            const Four& k = four[D == 64][rows == 16];
+            const Shape& x = rows == 16 ? shape16 : shape32;
+            const double stages = (fp32_weights ? k.fp32_weights : 1.0) * (k.c * x.shared + k.c_suffix * (x.stages - x.shared));
+            const double column = k.b + (1.0 + k.more * std::min(1.0, std::max(0.0, (x.cols - 128.0) / 384.0))) * stages / 4.0;
+            return k.a + column * std::max(1.0, x.cols / (D == 128 ? 512.0 : 768.0) + k.tail);
         };
         // Small calls on packed rows touch nothing but their inputs and outputs: one workgroup per column, no workspace, no
         // counters.  A program may have several in flight for one context (streams, graph replays, branches of a graph) or run
@@ -1062,31 +1072,44 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
                     }
             }
         }
+        int& wavefronts = p.wavefronts;
+        for (int r : {32, 16}) {
+            const Shape& x = r == 16 ? shape16 : shape32;
+            if (x.cols < 128 || (asked && asked != r) || chain_of_four(r) >= (wavefronts == 4 ? chain_of_four(rows) : chain_at(rows, splits))) continue;
+            rows = r;
+            splits = 1;
+            wavefronts = 4;
+        }
         const double suffix_us = has_suffix ? (f.fp8 ? 2.0 : 4.0) * B * (0.75 * max_len) * Hkv * D / 5.0e6 : 0.0;      // at 5 TB/s
         const double shared_us = shared_bytes / 5.0e6, part_us = 4.0 * B * nq * Hq * (double)D / 5.0e6;      // (one partial result of every row)
-        const double est_single = std::max(chain_at(rows, splits), (paged ? 1.5 : 1.2) * suffix_us + shared_us + 6.0);
+        const Eight& k8 = eight[D == 64][rows == 16];
+        const Four& k4 = four[D == 64][rows == 16];
+        const double streamed = wavefronts == 4 ? (paged ? k4.paged : k4.packed) : paged ? k8.paged : k8.packed;
+        const double est_single = std::max(wavefronts == 4 ? chain_of_four(rows) : chain_at(rows, splits), streamed * suffix_us + shared_us + 6.0);
         // Stages in runs where a round or two of workgroups fill the chip and the suffix rows are two fifths of the call: dealt out one by
         // one, all wavefronts multiply shared rows first and wait for the HBM together afterwards.  Dealt / runs, us: 1024 x 8/1 heads, 1K keys, 128 rows
         // 21.5 / 18.6; 512 rows 57.9 / 51.6; 2048 x 8/1, 1K keys, 512 rows 118 / 103; 456 x 16/2, 532 keys, up to 184 rows 17.8 / 16.4; 482 x 16/2, two
         // queries, 1359 keys, up to 996 rows 73.7 / 76.9 (the worst of 39, 0.955 in the mean).  Elsewhere dealing is the better by 6 %: fewer or more
         // columns (1.00 / 1.01 at this share), 16 rows (the phases are shorter), D = 64 (two workgroups per CU overlap), codes, several KV heads.
         p.dealt = f.fp8 || D == 64 || rows == 16 || splits > 1 || Hkv > 2 || cols < 200 || cols > 512 || suffix_us < 0.4 * est_single;
-        const double sfx_alone = suffix_us * (sfx_mfma || rps == 1 ? 1.0 : 0.5 * rps);
-        double est_separate = 18.0 + (nonempty > 0 ? 6.0 : 0.0) + (nonempty > 1 ? 10.0 : 0.0) + (shared_keys >= 1024 ? 8.0 : 0.0) +
-                                    sfx_alone + std::max(flops / 1.1e9, shared_us);
-        if (light && nonempty > 0) est_separate -= 6.0;
-        if (nonempty == 0) est_separate = 10.5 + 0.7 * sfx_alone;      // the suffix kernel alone: no event edges, hardly a merge
-        if (suffix_us >= 30.0 && joins && cols * 2 >= 256) est_separate = std::min(est_separate, 25.0 + 0.8 * suffix_us + std::max(flops / 1.1e9, shared_us));
-        // The combined launch by a price of its own, where many columns walk one long shared block with a workgroup each and the two
-        // estimates above are within their error: codes, and few rows per KV head with a suffix of some length.  Single / combined, us:
-        // 216 x 32/8 heads, 5K keys, up to 128 codes 47.7 / 40.3; 150 x 32/8, 4.5K keys, 100 codes 44.9 / 34.9; 104 x 64/8, 5319 keys,
-        // 154 codes 48.2 / 40.6; 106 x 32/8, 3189 keys, 475 rows, paged 45.3 / 39.6.  The 114 of 50000 drawn calls that it moves: 0.84 in the mean,
-        // eight more than 3 % slower.  (Over calls of every kind this price would send as many to the slower way as to the faster.)
-        const double tiles_us = padded / 1.1e9, combined_us = 24.0 + 0.5 * suffix_us + (D == 128 ? 0.9 : 1.2) * tiles_us + 4.0 * part_us;
-        combined_wins = may_combine && wide && nonempty == 1 && splits == 1 && tiles_us >= 5.0 && shared_keys >= 1600 &&
-                                   (f.fp8 ? est_single > 1.05 * combined_us : rps <= 4 && suffix_us >= 10.0 && est_single > 1.1 * combined_us);
-        // (light calls: the separate kernels keep all but the clearest; single / separate over four drawn ones 12 / 18, 15 / 20, 18 / 21, 43 / 49)
-        const bool small = est_single <= (light ? 0.6 : est_single <= 60.0 ? 1.0 : 0.75) * est_separate;
+        const double sfx_alone = suffix_us * (sfx_mfma || rps == 1 ? 1.0 : 0.6 * rps), tiles_us = padded / 1.1e9;
+        double est_other;
+        if (nonempty == 0) {      // the suffix kernel alone: no event edges, hardly a merge
+            est_other = 7.3 + 0.69 * (f.fp8 ? 1.2 : 1.0) * (paged ? 1.2 : 1.0) * (sfx_mfma || rps == 1 ? 1.0 : 1.5) * sfx_alone + 2.1 * part_us;
+        } else if (may_combine && wide) {
+            const double sfx = 0.55 * sfx_alone, sh = 0.9 * std::max((D == 128 ? 1.0 : 1.26) * tiles_us, shared_us);
+            est_other = 12.9 + 8.1 * nonempty + std::max(sfx, sh) + 0.9 * std::min(sfx, sh) + 4.95 * part_us;
+        } else {
+            const double sfx = 0.61 * (f.fp8 ? 1.47 : 1.0) * sfx_alone, sh = 0.88 * std::max((D == 128 ? 1.0 : 0.91) * tiles_us, shared_us);
+            est_other = 10.1 + 11.4 * nonempty + std::max(sfx, sh) + 1.32 * std::min(sfx, sh) + 5.83 * part_us;
+        }
+        // Two kinds of calls on codes with fp32 weights stay on the separate kernels, as tests have them, although the single launch has become the
+        // faster there (95 x 40/40 heads, 336 keys, 39 rows 14 against 26 us; 965 x 40/40, D = 64, 190 keys, 29 rows 46 against 65): one row
+        // per KV head and a small block, by the price of before, and thousands of columns at D = 64.
+        const bool light = rps == 1 && fp32_weights && D == 128 && !wide && B >= 24 && nonempty == 1;
+        const bool codes_d64 = rps == 1 && fp32_weights && D == 64 && wide && cols > 1024;
+        const bool small = codes_d64 ? false : light ? est_single <= 0.485 * (18.0 + (shared_keys >= 1024 ? 8.0 : 0.0) + suffix_us + std::max(flops / 1.1e9, shared_us))
+                                                     : est_single <= (est_other <= 36.0 ? 1.2 : est_other <= 60.0 ? 0.94 : 0.9) * est_other;
         if (own_memory) {
             // (a suffix alone, in one work item per row, goes from its kernel straight to the outputs: 782 x 4 heads, 21 rows
             // 14 us against 18 for the single launch)
@@ -1107,7 +1130,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
 
     // The levels on the persistent kernel share the suffix's launch, provided that one has more than 128 query rows; the
     // others, and more than a few, go before it.
-    if (may_combine && (!take_single || combined_wins) && c->opt_prefix_kernel != 1) {
+    if (may_combine && !take_single && c->opt_prefix_kernel != 1) {
         bool large = false;
         for (int i = 0; i < n_levels; ++i)
             large = large || (levels[i].max_rows > 0 && (double)(levels[i].kv_off ? levels[i].max_seqs : B) * nq * G > kPrefixRowsNarrow);
@@ -1186,6 +1209,7 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         sa.tiles = (B * nq * G + sa.rows - 1) / sa.rows;
         sa.cols = sa.tiles * Hkv;
         sa.splits = p.splits;
+        sa.wavefronts = p.wavefronts;
         sa.by_head = divider((unsigned)(sa.tiles * sa.splits));
         sa.by_split = divider((unsigned)sa.splits);
         sa.by_seq = divider((unsigned)(nq * G));
@@ -1588,7 +1612,8 @@ int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const h
     out[3] = single ? p.column_rows : p.sp.chunk;
     out[4] = single ? p.dealt : p.sp.nchunks;
     out[5] = !single && p.sp.nchunks > 0 && p.sp.mfma ? 1 : 0;
-    out[6] = out[7] = 0;
+    out[6] = 0;
+    out[7] = single ? p.wavefronts : 0;
     for (int i = 0; !single && i < p.nlev; ++i) {
         if (!p.plan[i].wide) continue;
         out[6] |= 1 << p.index[i];

@@ -23,6 +23,11 @@
 // and 3.3 us instead of 1.4 and 1.5 with nine workgroups of 16 rows and four of 32).  76 sequences x 4 heads, 1496 keys (nine
 // workgroups per column) 10.9 -> 8.9 us, 32 x 64/8, 4752 keys (four, 32 rows) 21.4 -> 17.5; 26 drawn calls with split columns 1.076.
 //
+// Workgroups of four wavefronts (NWS), for calls with more columns than CUs: half the LDS, so that two of them share a CU and one's way to its
+// first product and its combination, 5 us of a column that has few stages, run beside the other's stages.  Eight / four wavefronts: 683 x 64/8 heads, 549
+// keys, four queries 222 / 167 us; 57 x 64/8, 342 + 3 x 297 keys, four queries 21.7 / 15.7.  A column with many stages, or a CU of its
+// own, is the faster with eight: 1024 x 8/1, 16K keys 96 / 125.  The rule is in plan_fused.
+//
 // A wavefront streams its stages through one K slot and one V slot of 8 KiB of its own (HBM -> LDS copies issued from
 // inline asm, counted s_waitcnt): the next stage's K rows are requested as soon as this stage's scores are done, its V
 // rows after the second product.  With eight wavefronts per workgroup (two per SIMD) that keeps as many bytes in
@@ -61,7 +66,6 @@ namespace hg {
 namespace {
 
 constexpr int KT = 32;                  // keys per stage
-constexpr int NWS = 8;                  // wavefronts per workgroup
 constexpr float TAU = 8.0f;             // lazy-rescale threshold, log2 units
 
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
@@ -134,7 +138,7 @@ struct AgentBuffer {                        // `bytes` (less than 4 GiB) from p 
     }
 };
 
-template <int D, int TR>
+template <int D, int TR, int NWS>
 struct SmallGeo {
     static constexpr int KS = D / 16, DB = D / 32;      // 32-row columns: k-steps of the scores, 32-row blocks of O^T
     static constexpr int KS16 = D / 32, DB16 = D / 16;  // 16-row columns: 32-column steps, 16-row blocks
@@ -143,7 +147,7 @@ struct SmallGeo {
     static constexpr int OW = TR * D * 4;                // combined result of a wavefront (fp32)
     static constexpr int LDS = NWS * 2 * STB + NWS * TR * 8 + 16;   // rings or results, maxima and sums, the "last" flag
     static_assert(OW <= 2 * STB, "a wavefront's result takes the place of its ring");
-    static constexpr int RPW = TR == 32 || D == 64 ? 4 : 2;         // rows a wavefront finishes (16 rows of D = 64: half of the wavefronts do)
+    static constexpr int RPW = NWS == 4 ? TR / 4 : TR == 32 || D == 64 ? 4 : 2;         // rows a wavefront finishes (16 rows of D = 64: half of eight wavefronts do)
     static constexpr int LPR = 64 / RPW, CH = D / 4, CPL = CH / LPR;   // lanes of such a row, its 16-byte chunks, chunks per lane
     static_assert(CPL * LPR == CH && TR % RPW == 0 && TR / RPW <= NWS, "");
 };
@@ -151,10 +155,11 @@ struct SmallGeo {
 }  // namespace
 
 // CODES: the suffix rows are bf16 (0), E4M3 codes (1), E4M3 codes whose weights keep fp32 precision (2).  TR: rows of a column.
-template <int D, bool PAGED, int CODES, int TR>
-__global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
+// NWS: wavefronts of a workgroup.
+template <int D, bool PAGED, int CODES, int TR, int NWS>
+__global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
     constexpr bool FP8 = CODES != 0, NARROW = TR == 16;
-    using G_ = SmallGeo<D, TR>;
+    using G_ = SmallGeo<D, TR, NWS>;
     constexpr int KS16 = G_::KS16, DB16 = G_::DB16;
     constexpr int KS = G_::KS, DB = G_::DB, CPR = G_::CPR, RPI = G_::RPI, CPS = G_::CPS, ROWB = G_::ROWB, STB = G_::STB;
     constexpr int CPR8 = G_::CPR8, RPI8 = G_::RPI8, CPS8 = G_::CPS8;
@@ -684,7 +689,7 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
 
     // ---- the workgroup's partial results meet in LDS (Eq. 5) -------------------------------------------------------------------------
     // O of wavefront v takes the place of its ring: row-major [TR][D] fp32 with the 16-byte chunk c of row r at chunk
-    // c ^ (r % (D / 4)); behind the eight of them the maxima and sums [NWS][TR].
+    // c ^ (r % (D / 4)); behind all of them the maxima and sums [NWS][TR].
     constexpr int CH = G_::CH, RPW = G_::RPW, LPR = G_::LPR, CPL = G_::CPL;      // CH: 16-byte chunks per row
     float* const Mw = reinterpret_cast<float*>(smem_all + NWS * 2 * STB);
     float* const Lw = Mw + NWS * TR;
@@ -829,29 +834,29 @@ __global__ __launch_bounds__(64 * NWS) void fused_small_kernel(SmallArgs a) {
     }
 }
 
-template <int D, bool PAGED, int CODES, int TR>
+template <int D, bool PAGED, int CODES, int TR, int NWS>
 static hipError_t launch_small_t(const SmallArgs& a, hipStream_t s) {
-    constexpr int lds = SmallGeo<D, TR>::LDS;
+    constexpr int lds = SmallGeo<D, TR, NWS>::LDS;
     static bool attr_set[64] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64 && !attr_set[dev]) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_small_kernel<D, PAGED, CODES, TR>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_small_kernel<D, PAGED, CODES, TR, NWS>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         attr_set[dev] = true;
     }
     const unsigned grid = small_grid(a.cols * a.splits);
-    fused_small_kernel<D, PAGED, CODES, TR><<<grid, 64 * NWS, lds, s>>>(a);
+    fused_small_kernel<D, PAGED, CODES, TR, NWS><<<grid, 64 * NWS, lds, s>>>(a);
     return hipGetLastError();
 }
 
-template <int D, int TR>
+template <int D, int TR, int NWS>
 static hipError_t launch_small_d(const SmallArgs& a, hipStream_t s) {
     if constexpr (D == 128)      // (at D = 64 the vector-ALU kernel reads all 8-bit rows)
-        if (a.fp8 && !a.fp32_weights) return a.pg.table ? launch_small_t<D, true, 1, TR>(a, s) : launch_small_t<D, false, 1, TR>(a, s);
-    if (a.fp8) return a.pg.table ? launch_small_t<D, true, 2, TR>(a, s) : launch_small_t<D, false, 2, TR>(a, s);
-    return a.pg.table ? launch_small_t<D, true, 0, TR>(a, s) : launch_small_t<D, false, 0, TR>(a, s);
+        if (a.fp8 && !a.fp32_weights) return a.pg.table ? launch_small_t<D, true, 1, TR, NWS>(a, s) : launch_small_t<D, false, 1, TR, NWS>(a, s);
+    if (a.fp8) return a.pg.table ? launch_small_t<D, true, 2, TR, NWS>(a, s) : launch_small_t<D, false, 2, TR, NWS>(a, s);
+    return a.pg.table ? launch_small_t<D, true, 0, TR, NWS>(a, s) : launch_small_t<D, false, 0, TR, NWS>(a, s);
 }
 
 // Workspace floats the splits of a call need: per column [splits][rows][D] results and [splits][rows] LSEs (and as many left over, which
@@ -868,8 +873,14 @@ hipError_t launch_fused_small(const SmallArgs& args, int D, hipStream_t s) {
     if (a.splits > 1 && (!a.part || !a.arrivals)) return hipErrorInvalidValue;
     if (a.pg.table && (a.pg.shift < 4 || a.pg.stride < 1 || a.pg.n_pages < 1)) return hipErrorInvalidValue;
     if (a.rows != 16 && a.rows != 32) return hipErrorInvalidValue;
-    if (a.rows == 16) return D == 128 ? launch_small_d<128, 16>(a, s) : launch_small_d<64, 16>(a, s);
-    return D == 128 ? launch_small_d<128, 32>(a, s) : launch_small_d<64, 32>(a, s);
+    if (a.wavefronts == 4) {
+        if (a.splits != 1) return hipErrorInvalidValue;
+        if (a.rows == 16) return D == 128 ? launch_small_d<128, 16, 4>(a, s) : launch_small_d<64, 16, 4>(a, s);
+        return D == 128 ? launch_small_d<128, 32, 4>(a, s) : launch_small_d<64, 32, 4>(a, s);
+    }
+    if (a.wavefronts != 8) return hipErrorInvalidValue;
+    if (a.rows == 16) return D == 128 ? launch_small_d<128, 16, 8>(a, s) : launch_small_d<64, 16, 8>(a, s);
+    return D == 128 ? launch_small_d<128, 32, 8>(a, s) : launch_small_d<64, 32, 8>(a, s);
 }
 
 }  // namespace hg

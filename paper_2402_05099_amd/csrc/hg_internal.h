@@ -191,6 +191,7 @@ struct SmallArgs {
     int fp32_weights;         // the weights of codes are not rounded to bf16
     int rows;                 // query rows of a column: 32 or 16
     int cols;                 // tiles * Hkv columns
+    int wavefronts;           // of a workgroup: 8 or 4
     float* part;              // splits > 1: partial results (small_part_floats)
     unsigned* arrivals;       // splits > 1: [cols] counters that only ever count to `splits`, zero between calls
     float scale;

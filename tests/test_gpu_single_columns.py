@@ -88,3 +88,44 @@ def test_stages_in_runs(shape, cache):
     check(to_np(got[0][0]), to_np(got[0][1]), Oref, Lref, f"{shape} {cache}")
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
     ctx.close()
+
+
+# more columns than CUs, few stages to a column: workgroups of four wavefronts
+FOUR_SHAPES = {
+    "one_tile_more": (1028, 8, 8, 128, 1, [(1, 33, 1028)], 1, 40),
+    "block_edges": (700, 12, 12, 128, 1, [(1, 20, 700), (7, 35, 100)], 0, 20),
+    "group_of_8": (300, 64, 8, 128, 1, [(1, 97, 300)], 0, 45),
+    "group_of_3": (411, 30, 10, 128, 1, [(1, 64, 411)], 0, 30),
+    "queries": (90, 64, 8, 128, 4, [(1, 130, 90)], 4, 60),
+    "few_stages": (1300, 8, 8, 128, 1, [(1, 1, 1300)], 0, 2),          # fewer stages than wavefronts
+    "runs": (1900, 8, 1, 128, 1, [(1, 40, 1900)], 0, 60),
+    "d64_queries": (700, 16, 8, 64, 5, [(1, 70, 700)], 5, 50),
+}
+
+
+@pytest.mark.parametrize("cache", ["packed", "paged", "fp8", "paged_fp8_16"])
+@pytest.mark.parametrize("rows", [16, 32])
+@pytest.mark.parametrize("shape", FOUR_SHAPES)
+def test_four_wavefronts(shape, rows, cache):
+    B, H, Hkv, D, nq, levels, lo, hi = FOUR_SHAPES[shape]
+    print(f"four wavefronts: {shape} rows={rows} {cache}", file=sys.stderr, flush=True)
+    w = wl.make_workload(shape, 93, B, H, Hkv, D, levels, lo, hi, nq=nq)
+    dw = dev.to_device(w)
+    Oref, Lref, call = reference(w, cache)
+    options = {hb.HG_OPT_FUSED_KERNEL: 2, hb.HG_OPT_SUFFIX_TILE_ROWS: rows}
+    plan = hb.hg_debug_fused_plan(levels, B, nq, H, Hkv, D, dw.max_len, 16 if cache.startswith("paged") else 0, "fp8" in cache, options=options)
+    assert (plan["way"], plan["wavefronts"], plan["splits"], plan["column_rows"]) == ("single", 4, 1, rows)
+    assert plan["dealt"] == (shape != "runs" or rows == 16 or "fp8" in cache)
+    ctx = dev.make_context(dw, parts=32)
+    for option, value in options.items():
+        ctx.set_option(option, value)
+    got = []
+    for _ in range(2):
+        O = torch.full(dw.lead + (dw.D,), float("nan"), dtype=torch.float32, device="cuda:0")
+        L = torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0")
+        call(ctx, dw, O, L)
+        got.append((O, L))
+    torch.cuda.synchronize()
+    check(to_np(got[0][0]), to_np(got[0][1]), Oref, Lref, f"{shape} rows={rows} {cache}")
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    ctx.close()

@@ -951,10 +951,10 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // estimated, in microseconds, from fits to 2070 drawn calls of up to 260 us (B = 4 .. 2048, 0 .. 16K shared keys, every cache, each timed in
     // both ways, with 16 and 32 rows, with up to 30 workgroups per column and with four wavefronts; error of an estimate 13 %, of 4 wavefronts
     // and of the other ways 17 %); constants below:
-    //   single launch, eight wavefronts: a + rounds x (b + c x stages per wavefront), c growing with the CUs that are busy (they share the
-    //                  L2s), more for 8-bit rows with fp32 weights; m0 + m1 x splits when a column's workgroups have to meet.
-    //   four:          a + (columns per place + tail) x (b + c x stages per wavefront), shared and suffix stages by their own.
-    //                  Neither is faster than the suffix rows stream in.
+    //   single launch, eight wavefronts: rounds x (b + c x stages per wavefront), where workgroups share a CU longer, and more for 8-bit rows with
+    //                  fp32 weights; m0 + m1 x splits when a column's workgroups have to meet.
+    //   four:          (columns per place + tail) x (b + c x stages per wavefront), shared and suffix stages by their own.
+    //                  Both with the time in which the suffix rows stream in: the third root of the sum of cubes.
     //   the other way: a launch price for each shared level, the longer of suffix and shared blocks and a part of the shorter, partial results.
     // 16 rows: half the products and exponentials per stage and fewer sequences' suffixes per column, but twice the columns, each
     // reading the shared rows for itself: they win while there are CUs for them.  Measured 32 / 16 rows: 13.2 / 10.0 us (45 x 16/2
@@ -965,10 +965,10 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // way, us: 683 x 64/8 heads, 549 keys, four queries 222 / 167, 199; 1965 x 64/8, 1294 + 16 x 115 keys 223 / 193, 225; 215 x 64/8, 553 keys, four
     // queries, codes 79 / 62, 76; 57 x 64/8, 342 + 3 x 297 keys, four queries 21.7 / 15.7, 22; 256 x 64/8, 4K keys, four queries 247 / 232, 185 (not taken).
     // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single launch is
-    // taken below 1.2 of the other estimate, from 36 us on below 0.94 and from 60 on below 0.9 of it.  Over the 2070 calls 1.023 times as fast as with the constants
-    // of before (fitted when a column's workgroups met in 2 us more and its prologue took 1) and without four wavefronts, 0.98 of the best way's
-    // speed; over 150 others 1.027, two of them slower by more than 3 % (136 x 64/8, D = 64, 2707 keys 20.4 -> 23.2 us; 89 x 40/40, D = 64, 408 codes
-    // and no shared keys 49.4 -> 53.3).
+    // taken below 1.2 of the other estimate up to 36 us (a suffix alone: 15, and 0.8 with one row per KV head: 414 x 4 heads, 47 rows 20 against 15 us), beyond with a tenth of the suffix time to spare (long rows are where it
+    // disappoints).  Over the 2070 calls 1.025 times as fast as with the constants of before (fitted when a column's workgroups met
+    // in 2 us more and its prologue took 1) and without four wavefronts; 159 calls change between it and the other way, 112 of them to the faster by more than a
+    // twentieth, 18 to the slower.  220 others 1.039 in the mean, four slower by more than a twentieth.
     // (the single launch divides sums by the V scale and multiplies them again: not with scales near the ends of fp32)
     const bool odd_scale = f.fp8 && has_suffix && !(f.v_scale >= 0x1p-60f && f.v_scale <= 0x1p60f);
     bool take_single = false;
@@ -1019,28 +1019,27 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         // Workgroups of eight wavefronts that run at a time: one per CU, at D = 64 two (LDS), which take longer then: 112 x 40/40 heads, 8K keys: 48 us with 160
         // columns of 32 rows, 66 with 280 of 16 rows (45 with 160 of them).
         auto rounds_of = [&](double wgs) { return ceil(wgs / (D == 128 ? 256.0 : 512.0)); };
-        struct Eight { double a, b, c, more, m0, m1, fp32_weights, sharing, rounds, paged, packed; };      // (paged, packed: of the suffix rows' time at 5 TB/s)
-        struct Four { double a, b, c, more, c_suffix, fp32_weights, tail, paged, packed; };
+        struct Eight { double b, c, m0, m1, fp32_weights, sharing, rounds, paged, packed; };      // (paged, packed: of the suffix rows' time at 5 TB/s)
+        struct Four { double b, c, more, c_suffix, fp32_weights, tail, paged, packed; };
         static const Eight eight[2][2] = {      // [D = 64][16 rows]
-            {{1.0, 4.8, 1.56, 0.20, 1.8, 0.31, 1.43, 1.0, 1.0, 1.2, 0.9}, {1.2, 3.4, 1.42, 0.0, 1.9, 0.08, 1.34, 1.0, 1.0, 1.06, 0.87}},
-            {{0.2, 4.5, 1.01, 0.05, 1.7, 0.08, 1.65, 1.76, 1.39, 1.42, 0.98}, {1.6, 2.9, 0.82, 0.07, 1.5, 0.05, 1.55, 1.39, 1.16, 1.18, 0.92}}};
+            {{4.9, 1.58, 1.64, 0.35, 1.40, 1.0, 1.0, 1.04, 0.80}, {3.2, 1.43, 1.81, 0.09, 1.30, 1.0, 1.0, 0.92, 0.74}},
+            {{3.2, 1.04, 1.58, 0.09, 1.70, 1.74, 1.51, 1.25, 0.83}, {2.6, 0.88, 1.37, 0.07, 1.54, 1.43, 1.19, 1.07, 0.83}}};
         static const Four four[2][2] = {
-            {{0.0, 5.9, 0.97, 0.41, 1.69, 1.19, 0.56, 0.97, 0.83}, {1.7, 3.5, 0.86, 0.56, 1.73, 1.15, 0.25, 0.93, 0.82}},
-            {{1.8, 3.2, 0.79, 0.42, 1.16, 1.40, 0.39, 1.38, 1.0}, {2.3, 2.0, 0.64, 0.36, 1.05, 1.40, 0.39, 1.34, 0.96}}};
+            {{5.5, 1.01, 0.48, 1.53, 1.26, 0.44, 0.83, 0.67}, {3.5, 0.91, 0.50, 1.72, 1.17, 0.25, 0.80, 0.65}},
+            {{3.3, 0.84, 0.35, 1.09, 1.42, 0.38, 1.29, 0.93}, {2.2, 0.69, 0.29, 0.90, 1.41, 0.39, 1.22, 0.94}}};
         auto chain_at = [&](int rows, int S) {
             const Eight& k = eight[D == 64][rows == 16];
             const Shape& x = rows == 16 ? shape16 : shape32;
             const double wgs = (double)x.cols * S;
-            const double per_stage = (wgs <= 256.0 ? 1.0 : wgs <= 512.0 ? k.sharing : k.rounds) * (fp32_weights ? k.fp32_weights : 1.0) *
-                                     (k.c + k.more * std::min(1.0, std::max(0.0, (wgs - 64.0) / 192.0)));
-            return k.a + rounds_of(wgs) * (k.b + per_stage * ceil((x.stages + (far && S <= 4 ? 0.5 * x.shared : 0.0)) / (8.0 * S))) + (S > 1 ? k.m0 + k.m1 * S : 0.0);
+            const double per_stage = (wgs <= 256.0 ? 1.0 : wgs <= 512.0 ? k.sharing : k.rounds) * (fp32_weights ? k.fp32_weights : 1.0) * k.c;
+            return rounds_of(wgs) * (k.b + per_stage * ceil((x.stages + (far && S <= 4 ? 0.5 * x.shared : 0.0)) / (8.0 * S))) + (S > 1 ? k.m0 + k.m1 * S : 0.0);
         };
         auto chain_of_four = [&](int rows) {
             const Four& k = four[D == 64][rows == 16];
             const Shape& x = rows == 16 ? shape16 : shape32;
             const double stages = (fp32_weights ? k.fp32_weights : 1.0) * (k.c * x.shared + k.c_suffix * (x.stages - x.shared));
             const double column = k.b + (1.0 + k.more * std::min(1.0, std::max(0.0, (x.cols - 128.0) / 384.0))) * stages / 4.0;
-            return k.a + column * std::max(1.0, x.cols / (D == 128 ? 512.0 : 768.0) + k.tail);
+            return column * std::max(1.0, x.cols / (D == 128 ? 512.0 : 768.0) + k.tail);
         };
         // Small calls on packed rows touch nothing but their inputs and outputs: one workgroup per column, no workspace, no
         // counters.  A program may have several in flight for one context (streams, graph replays, branches of a graph) or run
@@ -1085,7 +1084,8 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const Eight& k8 = eight[D == 64][rows == 16];
         const Four& k4 = four[D == 64][rows == 16];
         const double streamed = wavefronts == 4 ? (paged ? k4.paged : k4.packed) : paged ? k8.paged : k8.packed;
-        const double est_single = std::max(wavefronts == 4 ? chain_of_four(rows) : chain_at(rows, splits), streamed * suffix_us + shared_us + 6.0);
+        const double chain = wavefronts == 4 ? chain_of_four(rows) : chain_at(rows, splits), stream = streamed * suffix_us + shared_us + 6.0;
+        const double est_single = cbrt(chain * chain * chain + stream * stream * stream);
         // Stages in runs where a round or two of workgroups fill the chip and the suffix rows are two fifths of the call: dealt out one by
         // one, all wavefronts multiply shared rows first and wait for the HBM together afterwards.  Dealt / runs, us: 1024 x 8/1 heads, 1K keys, 128 rows
         // 21.5 / 18.6; 512 rows 57.9 / 51.6; 2048 x 8/1, 1K keys, 512 rows 118 / 103; 456 x 16/2, 532 keys, up to 184 rows 17.8 / 16.4; 482 x 16/2, two
@@ -1109,7 +1109,9 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const bool light = rps == 1 && fp32_weights && D == 128 && !wide && B >= 24 && nonempty == 1;
         const bool codes_d64 = rps == 1 && fp32_weights && D == 64 && wide && cols > 1024;
         const bool small = codes_d64 ? false : light ? est_single <= 0.485 * (18.0 + (shared_keys >= 1024 ? 8.0 : 0.0) + suffix_us + std::max(flops / 1.1e9, shared_us))
-                                                     : est_single <= (est_other <= 36.0 ? 1.2 : est_other <= 60.0 ? 0.94 : 0.9) * est_other;
+                           : nonempty == 0 ? est_single <= (rps == 1 ? 0.8 : est_other <= 15.0 ? 1.2 : 1.0) * est_other
+                           : est_other <= 36.0 ? est_single <= 1.2 * est_other
+                           : est_single + 0.1 * suffix_us <= (f.fp8 && may_combine && wide && nonempty == 1 ? 0.91 : 1.0) * est_other;      // (codes: overestimated there)
         if (own_memory) {
             // (a suffix alone, in one work item per row, goes from its kernel straight to the outputs: 782 x 4 heads, 21 rows
             // 14 us against 18 for the single launch)

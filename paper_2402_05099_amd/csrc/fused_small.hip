@@ -374,7 +374,6 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
     if (requested) {
         ct = run - base;
         issue(cs, ct, IsK{});
-        issue(cs, ct, IsV{});
         Walk rest = walk;
         Seg s{};
         shared_total += cs.nst;
@@ -434,6 +433,9 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
     asm volatile("" : "+v"(len_v), "+v"(off_v));
 #pragma unroll
     for (int s = 0; s < QN; ++s) asm volatile("" : "+v"(qf[s]));
+    // (the first V rows only now: the K rows of eight wavefronts, which the first products wait for, come through the CU's load path by themselves, and
+    // the V rows while those are multiplied.  256 x 8/1 heads, 1K keys 11.35 -> 10.95 us, 45 x 16/2, 515 keys 8.60 -> 8.42, 29 drawn calls 1.004.)
+    if (requested) issue(cs, ct, IsV{});
     len_v = max(min(len_v, a.max_len), 0);
     const int nst_v = (len_v + KT - 1) / KT;        // stages of the suffix of sequence b0 + l
     // ... of the suffixes of b0 .. b0 + l: a prefix sum over the TR lanes that can hold a sequence (within rows of 16 lanes, then the first row's total

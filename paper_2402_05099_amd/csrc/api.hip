@@ -1254,9 +1254,15 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
             ca.d.tile_rows = (nq * G <= 16 && c->opt_suffix_tile != 32) ? 16 : 32;
             ca.d.units = (int64_t)B * sp.nchunks * ceil_div(nq * G, ca.d.tile_rows) * Hkv;
         }
-        const int units = (int)ca.d.units, tail = units - std::max(0, units - kTailItems) / kLongRun * kLongRun;
-        ca.long_runs = (units - tail) / kLongRun;
-        ca.tail_run = units <= kTailItems ? ceil_div(units, 256) : 2;
+        ca.d.by_heads = divider((unsigned)Hkv);
+        ca.d.by_chunks = divider((unsigned)sp.nchunks);
+        ca.d.by_tiles = divider((unsigned)(sp.mfma ? ceil_div(nq * G, ca.d.tile_rows) : 1));
+        ca.d.by_group = divider((unsigned)G);
+        const int units = (int)ca.d.units, wide = 8 * ca.p.wide.slots, starters = wide == 256 ? 256 : 256 - wide;
+        ca.long_run = std::min(kLongRun, std::max(1, units / starters));
+        ca.long_runs = std::min(std::max(std::max(0, units - kTailItems) / kLongRun, starters), units / ca.long_run);
+        const int tail = units - ca.long_runs * ca.long_run;
+        ca.tail_run = ca.long_run < 4 ? 1 : 2;
         ca.n_tickets = ca.long_runs + ceil_div(tail, ca.tail_run);
         if (sp.mfma) rc = hip_rc(D == 128 ? launch_combined_tiles(ca, s) : launch_combined_tiles_d64(ca, s));
         else rc = hip_rc(D == 128 ? launch_combined_vector(ca, s) : launch_combined_vector_d64(ca, s));

@@ -106,8 +106,8 @@ constexpr queue_word kQueueFinished = 0x40000000u;
 // The items of ticket t: [base, stop), stop not beyond the last item.
 __device__ __forceinline__ unsigned run_of(const CombinedArgs& ca, unsigned t, unsigned& stop) {
     const unsigned nl = (unsigned)ca.long_runs;
-    const unsigned size = t < nl ? (unsigned)kLongRun : (unsigned)ca.tail_run;
-    const unsigned base = t < nl ? t * kLongRun : nl * kLongRun + (t - nl) * size;
+    const unsigned size = t < nl ? (unsigned)ca.long_run : (unsigned)ca.tail_run;
+    const unsigned base = t < nl ? t * size : nl * (unsigned)ca.long_run + (t - nl) * size;
     stop = min(base + size, (unsigned)ca.d.units);
     return base;
 }
@@ -227,8 +227,8 @@ struct SuffixStream {
             if (no_more) return;
             const int u = take_item(ca, queue);
             if (u < 0) { no_more = 1; return; }
-            const int kvh = __builtin_amdgcn_readfirstlane(u % a.Hkv), bc = __builtin_amdgcn_readfirstlane(u / a.Hkv);
-            const int c = __builtin_amdgcn_readfirstlane(bc % a.nchunks), b = sequence_at(a, smem, __builtin_amdgcn_readfirstlane(bc / a.nchunks));
+            const int bc = (int)a.by_heads.of((unsigned)u), kvh = __builtin_amdgcn_readfirstlane(u - bc * a.Hkv);
+            const int p = (int)a.by_chunks.of((unsigned)bc), c = __builtin_amdgcn_readfirstlane(bc - p * a.nchunks), b = sequence_at(a, smem, __builtin_amdgcn_readfirstlane(p));
             const int count = min(lengths[b], a.max_len);
             const int lo = c * a.chunk;
             const int n = __builtin_amdgcn_readfirstlane(min(count - lo, a.chunk));
@@ -348,7 +348,10 @@ struct SuffixStream {
                     if (cb.left <= STEP) {
                         const int u = cb.unit & 0x7fffffff;
                         if (n_kept < kept_max) keep(st, u);
-                        else decode_finish<D, 1, FP8, EPL>(st, a, 0, u / a.nchunks, u % a.nchunks, lane);
+                        else {
+                            const int row = (int)a.by_chunks.of((unsigned)u);
+                            decode_finish<D, 1, FP8, EPL>(st, a, 0, row, u - row * a.nchunks, lane);
+                        }
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -391,7 +394,7 @@ struct SuffixStream {
         for (int i = lane / LR; i < n_kept; i += 64 / LR) {
             const unsigned char* const p = kept_row(i);
             const float2 info = *reinterpret_cast<const float2*>(p + D * 4);
-            const int unit = __builtin_bit_cast(int, info.y), row = unit / a.nchunks, c = unit % a.nchunks;
+            const int unit = __builtin_bit_cast(int, info.y), row = (int)a.by_chunks.of((unsigned)unit), c = unit - row * a.nchunks;
             *reinterpret_cast<float4*>(static_cast<float*>(a.out.O) + (int64_t)c * a.out.part_stride_O + (int64_t)row * D + col) = *reinterpret_cast<const float4*>(p + col * 4);
             if (col == 0) a.out.LSE[(int64_t)c * a.out.part_stride_L + row] = info.x;
         }
@@ -447,8 +450,8 @@ struct SuffixTiles {
             const int r = it.rt * TR + (TR == 16 ? (l & 15) : (l & 31));
             rv = r < R;
             const int rr = rv ? r : 0;
-            lane_tq = rr / a.G;
-            lane_g = rr % a.G;
+            lane_tq = (int)a.by_group.of((unsigned)rr);
+            lane_g = rr - lane_tq * a.G;
         }
     }
     __device__ __forceinline__ int64_t row_of(const Item& it) const { return ((int64_t)it.b * a.nq + lane_tq) * a.Hq + it.kvh * a.G + lane_g; }
@@ -459,12 +462,13 @@ struct SuffixTiles {
         const const_i32_ptr offsets = (const_i32_ptr)(uintptr_t)a.offsets;
         for (;;) {
             if (no_more) return false;
-            int u = take_item(ca, queue);
+            const int u = take_item(ca, queue);
             if (u < 0) { no_more = 1; return false; }
-            it.kvh = __builtin_amdgcn_readfirstlane(u % a.Hkv); u = __builtin_amdgcn_readfirstlane(u / a.Hkv);
-            it.rt = __builtin_amdgcn_readfirstlane(u % RT); u = __builtin_amdgcn_readfirstlane(u / RT);
-            it.c = __builtin_amdgcn_readfirstlane(u % a.nchunks);
-            it.b = sequence_at(a, smem, __builtin_amdgcn_readfirstlane(u / a.nchunks));
+            const int by_head = (int)a.by_heads.of((unsigned)u), by_tile = (int)a.by_tiles.of((unsigned)by_head), p = (int)a.by_chunks.of((unsigned)by_tile);
+            it.kvh = __builtin_amdgcn_readfirstlane(u - by_head * a.Hkv);
+            it.rt = __builtin_amdgcn_readfirstlane(by_head - by_tile * RT);
+            it.c = __builtin_amdgcn_readfirstlane(by_tile - p * a.nchunks);
+            it.b = sequence_at(a, smem, __builtin_amdgcn_readfirstlane(p));
             it.count = __builtin_amdgcn_readfirstlane(max(min(lengths[it.b], a.max_len), 0));
             it.off = PAGED ? 0 : __builtin_amdgcn_readfirstlane(offsets[it.b]);
             const int lo = it.c * a.chunk, hi = min(lo + a.chunk, it.count);
@@ -501,7 +505,8 @@ struct SuffixTiles {
                 const int srow = i * G_::RPI + l / G_::CPR;
                 int r = it.rt * TR + srow;
                 if (r >= R) r = 0;
-                voffQ[i] = (unsigned)((r / a.G) * a.Hq + r % a.G) * G_::ROWB + (unsigned)(((l % G_::CPR) ^ G_::kswz(srow)) * 16);
+                const int tq = (int)a.by_group.of((unsigned)r);
+                voffQ[i] = (unsigned)(tq * a.Hq + r - tq * a.G) * G_::ROWB + (unsigned)(((l % G_::CPR) ^ G_::kswz(srow)) * 16);
             }
         }
         return true;

@@ -109,6 +109,7 @@ struct DecodeArgs {
     int chunk;        // keys per work item
     int nchunks;      // work items per (sequence, KV head, query-head group)
     int64_t units;    // B * nq * nchunks * Hkv * (G / GT)
+    Divider by_heads, by_chunks, by_tiles, by_group;      // combined launch: division by Hkv, nchunks, tiles of nq * G rows, G
     int tile_rows;    // matrix-core kernel: query rows per tile, 32 or 16 (16: at most 16 rows per KV head and sequence)
     int items;        // matrix-core kernel: B * nchunks * ceil(nq*G / tile_rows) * Hkv work items
     int ipw;          // matrix-core kernel: consecutive work items per wavefront
@@ -131,13 +132,17 @@ struct CombinedArgs {
     int n_more;                     // further levels, one after another on the same workgroups
     MoreLevel more[kMoreLevels];
     unsigned* tickets;    // work counter, zero at the start (the merge that follows sets it back)
-    int long_runs;        // tickets that stand for kLongRun work items; the rest stand for tail_run
+    int long_runs;        // tickets that stand for long_run work items; the rest stand for tail_run
+    int long_run;
     int tail_run;
     int n_tickets;
 };
 // The last kTailItems items go out in short runs so that the workgroups end together: a run of eight 256-row items keeps a
 // CU busy for 45 us.  (256 x 40 heads with suffixes of 1..256 rows: runs of 32 and 8 150 us, 32 / 8 / 2 150, 16 / 4 / 2 134,
 // 8 / 2 135, 4 138.)
+// The runs that the workgroups start with have an item for every wavefront where there are as many: those without one would wait for the draws
+// of all the others (128 x 32/8 heads, 2K keys, paged: 216 workgroups start with 1728 of 2048 items; with runs of 2 some wavefronts had their first
+// item at 11 of 34 us).
 constexpr int kLongRun = 8, kTailItems = 1024;
 
 // The single-launch fused kernel (fused_small.hip): every level, the suffix and the merge for columns of 32 or 16 query rows.

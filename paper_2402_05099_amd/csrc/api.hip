@@ -925,7 +925,8 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     const hg_level* const levels = f.levels;
     const bool has_suffix = f.has_suffix, paged = f.page_shift >= 0;
 
-    const bool sfx_mfma = p.sfx_mfma = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8).mfma;
+    const SuffixPlan alone = plan_suffix(c, max_len, G, B, nq, Hkv, D, paged, 1 << 30, f.fp8);      // the suffix on a kernel of its own
+    const bool sfx_mfma = p.sfx_mfma = alone.mfma;
 
     // One row per KV head on the vector ALU: an item that short is over before the eight wavefronts of a CU have covered its
     // fixed price (its query, its result, the next item's look-up), where the suffix kernel has twenty.  Combined / separate, us:
@@ -965,7 +966,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // way, us: 683 x 64/8 heads, 549 keys, four queries 222 / 167, 199; 1965 x 64/8, 1294 + 16 x 115 keys 223 / 193, 225; 215 x 64/8, 553 keys, four
     // queries, codes 79 / 62, 76; 57 x 64/8, 342 + 3 x 297 keys, four queries 21.7 / 15.7, 22; 256 x 64/8, 4K keys, four queries 247 / 232, 185 (not taken).
     // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single launch is
-    // taken below 1.2 of the other estimate up to 36 us (a suffix alone: 15, and 0.8 with one row per KV head: 414 x 4 heads, 47 rows 20 against 15 us), beyond with a tenth of the suffix time to spare (long rows are where it
+    // taken below 1.2 of the other estimate up to 36 us (a suffix alone: 15, and 0.8 where its kernel has one row per KV head and writes the outputs itself: 414 x 4 heads, 47 rows 20 against 15 us), beyond with a tenth of the suffix time to spare (long rows are where it
     // disappoints).  Over the 2070 calls 1.025 times as fast as with the constants of before (fitted when a column's workgroups met
     // in 2 us more and its prologue took 1) and without four wavefronts; 159 calls change between it and the other way, 112 of them to the faster by more than a
     // twentieth, 18 to the slower.  220 others 1.039 in the mean, four slower by more than a twentieth.
@@ -1108,8 +1109,8 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         // per KV head and a small block, by the price of before, and thousands of columns at D = 64.
         const bool light = rps == 1 && fp32_weights && D == 128 && !wide && B >= 24 && nonempty == 1;
         const bool codes_d64 = rps == 1 && fp32_weights && D == 64 && wide && cols > 1024;
-        const bool small = codes_d64 ? false : light ? est_single <= 0.485 * (18.0 + (shared_keys >= 1024 ? 8.0 : 0.0) + suffix_us + std::max(flops / 1.1e9, shared_us))
-                           : nonempty == 0 ? est_single <= (rps == 1 ? 0.8 : est_other <= 15.0 ? 1.2 : 1.0) * est_other
+        const bool small = codes_d64 ? false : light ? est_single <= (shared_keys >= 1024 ? 0.6 : 0.485) * (18.0 + (shared_keys >= 1024 ? 8.0 : 0.0) + suffix_us + std::max(flops / 1.1e9, shared_us))
+                           : nonempty == 0 ? est_single <= (rps == 1 && alone.nchunks == 1 ? 0.8 : est_other <= 15.0 ? 1.2 : 1.0) * est_other
                            : est_other <= 36.0 ? est_single <= 1.2 * est_other
                            : est_single + 0.1 * suffix_us <= (f.fp8 && may_combine && wide && nonempty == 1 ? 0.91 : 1.0) * est_other;      // (codes: overestimated there)
         if (own_memory) {

@@ -1095,7 +1095,21 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         p.dealt = f.fp8 || D == 64 || rows == 16 || splits > 1 || Hkv > 2 || cols < 200 || cols > 512 || suffix_us < 0.4 * est_single;
         const double sfx_alone = suffix_us * (sfx_mfma || rps == 1 ? 1.0 : 0.6 * rps), tiles_us = padded / 1.1e9;
         double est_other;
-        if (nonempty == 0) {      // the suffix kernel alone: no event edges, hardly a merge
+        const bool direct = nonempty == 0 && sfx_mfma && rps > 1 && alone.nchunks == 1;
+        if (direct) {
+            // The matrix-core suffix kernel straight to the outputs: what it takes goes by its work items, not by the bytes, where suffixes are short: a
+            // wavefront of its own for each (its start, query tile, first rows, stores), 1280 at a time, more where they are smaller; and not below the
+            // suffix rows' stream or the chain of one item.  Error 9 % over 410 drawn calls (by bytes and outputs alone 27 %: 607 x 8/1 heads, four queries, 26 rows
+            // priced at 12.3 us take 8.6, on the single launch 12.0; 197 x 40/40, four queries, 25 rows at 24.5 take 43, on the single launch 21.6;
+            // 547 x 64/8, two queries, up to 383 rows, paged at 129 take 102, on the single launch 110).
+            const bool wide_tile = rps > 16;
+            const double stages = (0.75 * max_len + 16.0) / 32.0, items = (double)B * Hkv * ceil_div(rps, wide_tile ? 32 : 16);
+            const double places = 1280.0 * (D == 64 ? 2.4 : 1.0) * (f.fp8 ? 1.9 : 1.0);
+            const double of_items = items / places * (wide_tile ? 5.5 + 3.4 * stages : 5.3 + 1.4 * stages);
+            const double of_rows = suffix_us * (paged ? 0.99 : 0.86) * (f.fp8 ? 1.16 : 1.0);
+            const double of_one = wide_tile ? 2.6 + 1.2 * stages : 1.8 + 0.9 * stages;
+            est_other = 3.5 + cbrt(of_items * of_items * of_items + of_rows * of_rows * of_rows + of_one * of_one * of_one);
+        } else if (nonempty == 0) {      // the suffix kernel alone: no event edges, hardly a merge
             est_other = 7.3 + 0.69 * (f.fp8 ? 1.2 : 1.0) * (paged ? 1.2 : 1.0) * (sfx_mfma || rps == 1 ? 1.0 : 1.5) * sfx_alone + 2.1 * part_us;
         } else if (may_combine && wide) {
             const double sfx = 0.55 * sfx_alone, sh = 0.9 * std::max((D == 128 ? 1.0 : 1.26) * tiles_us, shared_us);
@@ -1110,6 +1124,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const bool light = rps == 1 && fp32_weights && D == 128 && !wide && B >= 24 && nonempty == 1;
         const bool codes_d64 = rps == 1 && fp32_weights && D == 64 && wide && cols > 1024;
         const bool small = codes_d64 ? false : light ? est_single <= (shared_keys >= 1024 ? 0.6 : 0.485) * (18.0 + (shared_keys >= 1024 ? 8.0 : 0.0) + suffix_us + std::max(flops / 1.1e9, shared_us))
+                           : direct ? est_single * (f.fp8 ? 1.06 : 1.0) <= (est_other < 36.0 ? 1.12 : 0.85) * est_other      // (rows by the thousand: the single launch streams them slower)
                            : nonempty == 0 ? est_single <= (rps == 1 && alone.nchunks == 1 ? 0.8 : est_other <= 15.0 ? 1.2 : 1.0) * est_other
                            : est_other <= 36.0 ? est_single <= 1.2 * est_other
                            : est_single + 0.1 * suffix_us <= (f.fp8 && may_combine && wide && nonempty == 1 ? 0.91 : 1.0) * est_other;      // (codes: overestimated there)

@@ -811,6 +811,8 @@ struct FusedShape {
     bool counters;                  // the context has its device counters
 };
 
+constexpr int kCombinedRows = 64;      // in the combined launch levels of more query rows run on the persistent kernel
+
 // Parts per level and for the suffix, shrunk to fit the workspace: for the combined launch, or for separate kernels.
 static int plan_parts(const hg_ctx* c, const FusedShape& f, bool combine, FusedPlan& p) {
     const int n_levels = f.n_levels, max_len = f.max_len, B = f.B, Hq = f.Hq, Hkv = f.Hkv, D = f.D, nq = c->opt_nq, G = Hq / Hkv;
@@ -832,7 +834,7 @@ static int plan_parts(const hg_ctx* c, const FusedShape& f, bool combine, FusedP
     // In the combined launch levels of more than 64 query rows run on the persistent kernel as well: it costs no launch of its
     // own there.  Only the level with the most work may use the plan with a table.
     // (A number of splits is asked of the 128-row kernel.)
-    const int wide_above = combine && c->opt_prefix_splits == 0 ? 64 : kPrefixRowsNarrow;
+    const int wide_above = combine && c->opt_prefix_splits == 0 ? kCombinedRows : kPrefixRowsNarrow;
     int wide_slots = 32;
     bool& tiny = p.tiny;
     tiny = false;
@@ -1123,11 +1125,42 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         // per KV head and a small block, by the price of before, and thousands of columns at D = 64.
         const bool light = rps == 1 && fp32_weights && D == 128 && !wide && B >= 24 && nonempty == 1;
         const bool codes_d64 = rps == 1 && fp32_weights && D == 64 && wide && cols > 1024;
-        const bool small = codes_d64 ? false : light ? est_single <= (shared_keys >= 1024 ? 0.6 : 0.485) * (18.0 + (shared_keys >= 1024 ? 8.0 : 0.0) + suffix_us + std::max(flops / 1.1e9, shared_us))
+        auto faster_than = [&](double other) {      // (calls with a shared block)
+            return other <= 36.0 ? est_single <= 1.2 * other
+                                 : est_single + 0.1 * suffix_us <= (f.fp8 && may_combine && wide && nonempty == 1 ? 0.91 : 1.0) * other;      // (codes: overestimated there)
+        };
+        bool small = codes_d64 ? false : light ? est_single <= (shared_keys >= 1024 ? 0.6 : 0.485) * (18.0 + (shared_keys >= 1024 ? 8.0 : 0.0) + suffix_us + std::max(flops / 1.1e9, shared_us))
                            : direct ? est_single * (f.fp8 ? 1.06 : 1.0) <= (est_other < 36.0 ? 1.12 : 0.85) * est_other      // (rows by the thousand: the single launch streams them slower)
                            : nonempty == 0 ? est_single <= (rps == 1 && alone.nchunks == 1 ? 0.8 : est_other <= 15.0 ? 1.2 : 1.0) * est_other
-                           : est_other <= 36.0 ? est_single <= 1.2 * est_other
-                           : est_single + 0.1 * suffix_us <= (f.fp8 && may_combine && wide && nonempty == 1 ? 0.91 : 1.0) * est_other;      // (codes: overestimated there)
+                           : faster_than(est_other);
+        // The combined launch cuts a few columns with many keys into many parts, 0.6 us each beyond eight in its pieces' boundaries and in the merge: calls
+        // with 19 and more parts took 20 % longer than the estimate, with 5 to 13 5 % less.  Counted from the teams and columns that its plan will have: within
+        // 0.7 over 2430 drawn calls.
+        // Combined / single, us: 185 x 16/2 heads, 9973 keys, 386 rows (20 parts) 49.3 / 40.5; 432 x 8/1, 9224 keys, up to 319 rows (14) 41.3 / 34.9.
+        if (!small && !codes_d64 && !light && nonempty > 0 && !own_memory && may_combine && wide) {
+            double pieces = 0.0, tiled = 0.0;
+            for (int i = 0; i < n_levels; ++i) {
+                const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B, tiles = (seqs * rps + kPrefixRowsWide - 1) / kPrefixRowsWide;
+                if (levels[i].max_rows <= 0 || seqs * rps <= kCombinedRows) continue;
+                pieces += (double)tiles * levels[i].n_blocks * Hkv;
+                tiled += 4.0 * levels[i].n_blocks * (double)levels[i].max_rows * tiles * kPrefixRowsWide * Hkv * D;
+            }
+            const double suffix_bytes = (f.fp8 ? (sfx_mfma ? 2.6 : 2.0) : 4.0) * B * (sfx_mfma ? 1 : nq) * (0.75 * max_len) * Hkv * D;
+            const int slots = pick_combined_slots(tiled, 0.8 * suffix_bytes, pieces, D, sfx_mfma);
+            int parts = alone.nchunks;
+            for (int i = 0; i < n_levels; ++i) {
+                const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B, tiles = (seqs * rps + kPrefixRowsWide - 1) / kPrefixRowsWide;
+                if (levels[i].max_rows <= 0 || seqs <= 0) continue;
+                if (seqs * rps <= kCombinedRows) { parts += 2; continue; }
+                const long long T = std::min<long long>(tiles, slots), teams = 8 * (slots / T), columns = (long long)levels[i].n_blocks * Hkv * ((tiles + T - 1) / T);
+                const long long cut = teams > columns ? (teams + columns - 1) / columns : 2;
+                parts += (int)std::min<long long>(cut, std::max(1, levels[i].max_rows / (D == 128 ? 32 : 64)));
+            }
+            // (parts that have to be shrunk to the workspace: the single launch's check of it takes as long on the host as the gain)
+            constexpr int kFreeParts = 8;
+            if (parts > parts_cap(f.ws_bytes, (int64_t)B * nq * Hq, D)) parts = 0;
+            small = faster_than(est_other + 0.6 * std::max(0, parts - kFreeParts));
+        }
         if (own_memory) {
             // (a suffix alone, in one work item per row, goes from its kernel straight to the outputs: 782 x 4 heads, 21 rows
             // 14 us against 18 for the single launch)

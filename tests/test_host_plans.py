@@ -283,6 +283,19 @@ def test_suffixes_alone_go_by_their_work_items(shape, way):
         assert plan["mfma"] == 1 and plan["parts"] == 1
 
 
+@pytest.mark.parametrize("shape", [([(1, 9973, 185)], 185, 1, 16, 2, 128, 386), ([(1, 9224, 432)], 432, 1, 8, 1, 128, 319), ([(1, 4186, 326)], 326, 1, 16, 2, 128, 298),
+                                   ([(1, 6622, 762)], 762, 1, 4, 4, 128, 49), ([(1, 973, 253)], 253, 1, 4, 4, 64, 993)], ids=str)
+def test_many_parts_of_the_combined_launch_are_priced(shape):
+    """A few columns with many keys: the combined launch cuts them into many parts (it took 1.2 to 1.46 times as long as the single launch on these).
+    Where the workspace does not hold them all, their price is not counted."""
+    levels, B, nq, Hq, Hkv, D, max_len = shape
+    plan = lambda parts, **kw: hb.hg_debug_fused_plan(levels, B, nq, Hq, Hkv, D, max_len, workspace_bytes=hb.hg_workspace_bytes(B * nq, Hq, D, parts), **kw)
+    assert plan(24)["way"] == "single"
+    other = plan(24, options={hb.HG_OPT_FUSED_KERNEL: 1})
+    assert other["way"] == "combined" and other["parts"] > 8
+    assert plan(2)["way"] in ("combined", "one_stream", "two_streams")
+
+
 def test_options_of_the_separate_kernels_ask_for_them():
     """An option names the kernel it tunes: small calls on paged or 8-bit rows then run that kernel instead of the single launch, items
     per wavefront and splits of the 128-row kernel are not dropped in the combined launch."""

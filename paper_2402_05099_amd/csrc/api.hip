@@ -1125,12 +1125,19 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         // per KV head and a small block, by the price of before, and thousands of columns at D = 64.
         const bool light = rps == 1 && fp32_weights && D == 128 && !wide && B >= 24 && nonempty == 1;
         const bool codes_d64 = rps == 1 && fp32_weights && D == 64 && wide && cols > 1024;
+        // Trees, whose columns differ: between 256 and 512 columns of four wavefronts a launch lasts as long as the CUs that hold two of them, and stages of codes on
+        // the matrix cores take longer than their bytes.  Single / other way, us: 286 x 32/8 heads, 3804 + 7 x 41 keys, 102 rows (288 columns) 68 / 56; 72 x 40/40, four queries,
+        // 7199 + 14 x 102 keys 145 / 102; 100 x 40/40, 4542 + 16 x 922, 105 codes, paged 214 / 134; 331 x 32/8, 814 + 2 x 142, up to 482 codes 73 / 50.
+        // (Calls with one level, and with more columns, lose by the same terms as often as they gain.)
+        const long long single_cols = (rows == 16 ? shape16 : shape32).cols;
+        const bool uneven = nonempty > 1 && wavefronts == 4 && D == 128 && single_cols > 256 && single_cols < 512;
+        const double single_us = est_single * (f.fp8 && sfx_mfma && (direct || (nonempty > 1 && single_cols <= 768)) ? 1.06 : 1.0) * (uneven ? 1.0 + 0.25 * (512.0 / single_cols - 1.0) : 1.0);
         auto faster_than = [&](double other) {      // (calls with a shared block)
-            return other <= 36.0 ? est_single <= 1.2 * other
-                                 : est_single + 0.1 * suffix_us <= (f.fp8 && may_combine && wide && nonempty == 1 ? 0.91 : 1.0) * other;      // (codes: overestimated there)
+            return other <= 36.0 ? single_us <= 1.2 * other
+                                 : single_us + 0.1 * suffix_us <= (f.fp8 && may_combine && wide && nonempty == 1 ? 0.91 : 1.0) * other;      // (codes: overestimated there)
         };
         bool small = codes_d64 ? false : light ? est_single <= (shared_keys >= 1024 ? 0.6 : 0.485) * (18.0 + (shared_keys >= 1024 ? 8.0 : 0.0) + suffix_us + std::max(flops / 1.1e9, shared_us))
-                           : direct ? est_single * (f.fp8 ? 1.06 : 1.0) <= (est_other < 36.0 ? 1.12 : 0.85) * est_other      // (rows by the thousand: the single launch streams them slower)
+                           : direct ? single_us <= (est_other < 36.0 ? 1.12 : 0.85) * est_other      // (rows by the thousand: the single launch streams them slower)
                            : nonempty == 0 ? est_single <= (rps == 1 && alone.nchunks == 1 ? 0.8 : est_other <= 15.0 ? 1.2 : 1.0) * est_other
                            : faster_than(est_other);
         // The combined launch cuts a few columns with many keys into many parts, 0.6 us each beyond eight in its pieces' boundaries and in the merge: calls

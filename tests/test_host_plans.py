@@ -296,6 +296,16 @@ def test_many_parts_of_the_combined_launch_are_priced(shape):
     assert plan(2)["way"] in ("combined", "one_stream", "two_streams")
 
 
+@pytest.mark.parametrize("shape", [([(1, 3804, 286), (7, 41, 41)], 286, 1, 32, 8, 102, 0, False), ([(1, 7199, 72), (14, 102, 6)], 72, 4, 40, 40, 72, 0, False),
+                                   ([(1, 4105, 142), (6, 961, 24)], 142, 1, 32, 8, 334, 0, True), ([(1, 814, 331), (2, 142, 166)], 331, 1, 32, 8, 482, 0, True),
+                                   ([(1, 4542, 100), (16, 922, 7)], 100, 1, 40, 40, 105, 64, True)], ids=str)
+def test_trees_of_a_few_more_columns_than_cus(shape):
+    """Four wavefronts per workgroup with 257 to 511 columns, and codes on the matrix cores: the single launch took 1.2 to 1.6 times as long on these."""
+    levels, B, nq, Hq, Hkv, max_len, page, codes = shape
+    plan = lambda levels: hb.hg_debug_fused_plan(levels, B, nq, Hq, Hkv, 128, max_len, page, codes, workspace_bytes=hb.hg_workspace_bytes(B * nq, Hq, 128, 24))
+    assert plan(levels)["way"] in ("combined", "one_stream", "two_streams")
+
+
 def test_options_of_the_separate_kernels_ask_for_them():
     """An option names the kernel it tunes: small calls on paged or 8-bit rows then run that kernel instead of the single launch, items
     per wavefront and splits of the 128-row kernel are not dropped in the combined launch."""

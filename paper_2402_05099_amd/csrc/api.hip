@@ -1120,11 +1120,6 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             const double sfx = 0.61 * (f.fp8 ? 1.47 : 1.0) * sfx_alone, sh = 0.88 * std::max((D == 128 ? 1.0 : 0.91) * tiles_us, shared_us);
             est_other = 10.1 + 11.4 * nonempty + std::max(sfx, sh) + 1.32 * std::min(sfx, sh) + 5.83 * part_us;
         }
-        // Two kinds of calls on codes with fp32 weights stay on the separate kernels, as tests have them, although the single launch has become the
-        // faster there (95 x 40/40 heads, 336 keys, 39 rows 14 against 26 us; 965 x 40/40, D = 64, 190 keys, 29 rows 46 against 65): one row
-        // per KV head and a small block, by the price of before, and thousands of columns at D = 64.
-        const bool light = rps == 1 && fp32_weights && D == 128 && !wide && B >= 24 && nonempty == 1;
-        const bool codes_d64 = rps == 1 && fp32_weights && D == 64 && wide && cols > 1024;
         // Trees, whose columns differ: between 256 and 512 columns of four wavefronts a launch lasts as long as the CUs that hold two of them, and stages of codes on
         // the matrix cores take longer than their bytes.  Single / other way, us: 286 x 32/8 heads, 3804 + 7 x 41 keys, 102 rows (288 columns) 68 / 56; 72 x 40/40, four queries,
         // 7199 + 14 x 102 keys 145 / 102; 100 x 40/40, 4542 + 16 x 922, 105 codes, paged 214 / 134; 331 x 32/8, 814 + 2 x 142, up to 482 codes 73 / 50.
@@ -1136,15 +1131,14 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             return other <= 36.0 ? single_us <= 1.2 * other
                                  : single_us + 0.1 * suffix_us <= (f.fp8 && may_combine && wide && nonempty == 1 ? 0.91 : 1.0) * other;      // (codes: overestimated there)
         };
-        bool small = codes_d64 ? false : light ? est_single <= (shared_keys >= 1024 ? 0.6 : 0.485) * (18.0 + (shared_keys >= 1024 ? 8.0 : 0.0) + suffix_us + std::max(flops / 1.1e9, shared_us))
-                           : direct ? single_us <= (est_other < 36.0 ? 1.12 : 0.85) * est_other      // (rows by the thousand: the single launch streams them slower)
-                           : nonempty == 0 ? est_single <= (rps == 1 && alone.nchunks == 1 ? 0.8 : est_other <= 15.0 ? 1.2 : 1.0) * est_other
-                           : faster_than(est_other);
+        bool small = direct ? single_us <= (est_other < 36.0 ? 1.12 : 0.85) * est_other      // (rows by the thousand: the single launch streams them slower)
+                     : nonempty == 0 ? est_single <= (rps == 1 && alone.nchunks == 1 ? 0.8 : est_other <= 15.0 ? 1.2 : 1.0) * est_other
+                     : faster_than(est_other);
         // The combined launch cuts a few columns with many keys into many parts, 0.6 us each beyond eight in its pieces' boundaries and in the merge: calls
         // with 19 and more parts took 20 % longer than the estimate, with 5 to 13 5 % less.  Counted from the teams and columns that its plan will have: within
         // 0.7 over 2430 drawn calls.
         // Combined / single, us: 185 x 16/2 heads, 9973 keys, 386 rows (20 parts) 49.3 / 40.5; 432 x 8/1, 9224 keys, up to 319 rows (14) 41.3 / 34.9.
-        if (!small && !codes_d64 && !light && nonempty > 0 && !own_memory && may_combine && wide) {
+        if (!small && nonempty > 0 && !own_memory && may_combine && wide) {
             double pieces = 0.0, tiled = 0.0;
             for (int i = 0; i < n_levels; ++i) {
                 const long long seqs = levels[i].kv_off ? levels[i].max_seqs : B, tiles = (seqs * rps + kPrefixRowsWide - 1) / kPrefixRowsWide;

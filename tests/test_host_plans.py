@@ -243,26 +243,31 @@ def test_separate_kernels_are_planned_for_themselves(levels, options):
 @pytest.mark.parametrize("shape", [([(1, 5766, 576)], 576, 128, 23, False), ([(1, 3028, 867)], 867, 64, 16, False), ([(1, 11315, 179), (15, 91, 12)], 179, 128, 23, False),
                                    ([(1, 190, 965)], 965, 64, 29, True), ([(1, 79, 832)], 832, 64, 71, True), ([(1, 2268, 1802)], 1802, 128, 36, True)], ids=str)
 def test_short_suffixes_of_one_row_do_not_join_the_shared_block(shape):
-    """One query row per KV head and few rows: separate kernels (the combined launch took up to 24 % longer on calls like these)."""
+    """One query row per KV head and few rows: separate kernels (the combined launch took up to 24 % longer on calls like these), or, over codes at
+    D = 64 and few keys, the single launch (64 -> 38 and 69 -> 56 us)."""
     levels, B, D, max_len, fp8 = shape
-    assert hb.hg_debug_fused_plan(levels, B, 1, 40, 40, D, max_len, 0, fp8)["way"] in ("one_stream", "two_streams")
+    separate = hb.hg_debug_fused_plan(levels, B, 1, 40, 40, D, max_len, 0, fp8, options={hb.HG_OPT_FUSED_KERNEL: 1})
+    assert separate["way"] in ("one_stream", "two_streams")
+    assert hb.hg_debug_fused_plan(levels, B, 1, 40, 40, D, max_len, 0, fp8)["way"] == ("single" if fp8 and D == 64 else separate["way"])
     assert hb.hg_debug_fused_plan(levels, B, 1, 40, 40, D, 300, 0, fp8)["way"] == "combined"
     assert hb.hg_debug_fused_plan(levels, B, 1, 40, 40, D, max_len, 0, fp8, options={hb.HG_OPT_FUSED_KERNEL: 1, hb.HG_OPT_WIDE_SLOTS: 16})["way"] == "combined"
 
 
-@pytest.mark.parametrize("shape", [([(1, 299, 30)], 30, 4, 200, 16), ([(1, 336, 95)], 95, 40, 39, 0), ([(1, 219, 37)], 37, 40, 23, 0), ([(1, 3511, 41)], 41, 40, 31, 0)], ids=str)
+@pytest.mark.parametrize("shape", [([(1, 5204, 104)], 104, 40, 26, 0), ([(1, 7000, 120)], 120, 40, 30, 0), ([(1, 12000, 100)], 100, 40, 40, 0), ([(1, 6000, 128)], 128, 40, 300, 0)], ids=str)
 def test_small_calls_on_separate_kernels_where_those_are_faster(shape):
-    """8-bit rows, one query row per KV head: the single launch took 19 to 30 % longer on these (on a few rows it is the faster)."""
+    """8-bit rows, one query row per KV head: the single launch took 8 to 56 % longer on these (on a few rows, or a few keys, it is the faster)."""
     levels, B, H, max_len, page = shape
-    assert hb.hg_debug_fused_plan(levels, B, 1, H, H, 128, max_len, page, True)["way"] == "one_stream"
+    assert hb.hg_debug_fused_plan(levels, B, 1, H, H, 128, max_len, page, True)["way"] in ("one_stream", "two_streams")
     assert hb.hg_debug_fused_plan([(1, 269, 5)], 5, 1, 40, 40, 128, 37, page, True)["way"] == "single"
     assert hb.hg_debug_fused_plan([(1, 95, 14)], 14, 1, 4, 4, 128, 539)["way"] == "single"      # (long rows: matrix cores; 23 against 29 us)
 
 
 @pytest.mark.parametrize("shape", [([(1, 76, 1880)], 1880, 4, 128, 29, 16), ([(1, 156, 155)], 155, 40, 128, 41, 0), ([(1, 6705, 323)], 323, 4, 64, 45, 16),
-                                   ([(1, 660, 171)], 171, 40, 64, 32, 0), ([(1, 1697, 733)], 733, 4, 64, 73, 0), ([(1, 9424, 330)], 330, 4, 64, 93, 0), ([(1, 583, 9)], 9, 4, 128, 350, 16)], ids=str)
+                                   ([(1, 660, 171)], 171, 40, 64, 32, 0), ([(1, 1697, 733)], 733, 4, 64, 73, 0), ([(1, 9424, 330)], 330, 4, 64, 93, 0), ([(1, 583, 9)], 9, 4, 128, 350, 16),
+                                   ([(1, 299, 30)], 30, 4, 128, 200, 16), ([(1, 336, 95)], 95, 40, 128, 39, 0), ([(1, 219, 37)], 37, 40, 128, 23, 0), ([(1, 3511, 41)], 41, 40, 128, 31, 0)], ids=str)
 def test_small_calls_in_one_launch_where_that_is_faster(shape):
-    """8-bit rows, one query row per KV head, a shared block for the persistent kernel, D = 64 or few sequences: 20 to 60 % faster in the single launch."""
+    """8-bit rows, one query row per KV head, a shared block for the persistent kernel, D = 64 or few sequences: 20 to 60 % faster in the single launch.  The
+    last four, small blocks on kernels of their own: 18.7 -> 10.2, 25.2 -> 13.9, 17.6 -> 11.2 and 28.7 -> 22.6 us."""
     levels, B, H, D, max_len, page = shape
     assert hb.hg_debug_fused_plan(levels, B, 1, H, H, D, max_len, page, True)["way"] == "single"
 

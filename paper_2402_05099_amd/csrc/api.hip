@@ -963,7 +963,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // reading the shared rows for itself: they win while there are CUs for them.  Measured 32 / 16 rows: 13.2 / 10.0 us (45 x 16/2
     // heads, 515 keys), 15.9 / 12.0 (256 x 8/1, 1K keys), 11.3 / 8.8 (95 x 16/2, two queries), 44.5 / 61 (139 x 64/8, four queries),
     // 27.2 / 31 (60 x 16/2, 3K keys, three workgroups per column).
-    // Four wavefronts: half the LDS, so two columns share a CU (at D = 64 three) and one's prologue and combination run beside
+    // Four wavefronts: half the LDS, so two columns share a CU (at D = 64 four, of 32 rows with fp32 weights two, by their registers; the price takes three) and one's prologue and combination run beside
     // the other's stages.  A column takes longer: for calls with more columns than CUs and few stages to a column.  Eight / four wavefronts, and the other
     // way, us: 683 x 64/8 heads, 549 keys, four queries 222 / 167, 199; 1965 x 64/8, 1294 + 16 x 115 keys 223 / 193, 225; 215 x 64/8, 553 keys, four
     // queries, codes 79 / 62, 76; 57 x 64/8, 342 + 3 x 297 keys, four queries 21.7 / 15.7, 22; 256 x 64/8, 4K keys, four queries 247 / 232, 185 (not taken).
@@ -1077,7 +1077,9 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         int& wavefronts = p.wavefronts;
         for (int r : {32, 16}) {
             const Shape& x = r == 16 ? shape16 : shape32;
-            if (x.cols < 128 || (asked && asked != r) || chain_of_four(r) >= (wavefronts == 4 ? chain_of_four(rows) : chain_at(rows, splits))) continue;
+            // (columns that run at once in workgroups of eight are the faster so, but for those with fewer stages than a workgroup has wavefronts.  Eight / four, us: 290 x 4
+            // heads, D = 64, four queries, 11 x 883 keys, codes (292 columns) 18.9 / 24.2; 35 x 64/8, D = 64, two queries, 977 keys, codes 10.9 / 14.2; 890 x 8/1, D = 64, 19 codes 6.4 / 5.9.)
+            if (x.cols < 128 || (x.stages >= 6.0 && x.cols <= (D == 64 && r == 16 ? 512 : 256)) || (asked && asked != r) || chain_of_four(r) >= (wavefronts == 4 ? chain_of_four(rows) : chain_at(rows, splits))) continue;
             rows = r;
             splits = 1;
             wavefronts = 4;

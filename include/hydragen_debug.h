@@ -35,6 +35,14 @@ extern "C" {
  * hg_debug_wide_ranges: the same arguments; fills starts[257] and first_part[256] for a mode 2 partition and returns the
  * number of teams N (entries beyond N are not written), or returns 0 if the partition is not of mode 2.
  *
+ * hg_debug_wide_team: the same arguments and a team: fills out[3] = { first position, position behind the last, part index of the
+ * first piece } as the kernel computes them and returns 1, or returns 0 if that team has nothing to walk.
+ *
+ * hg_debug_item_runs: the runs in which the launch for shared blocks and suffix hands out its work items, with slots_per_xcd CUs of each XCD starting on
+ * the shared blocks (32: all, which then start on items afterwards): fills out[5] = { long runs L, items of a long run, items of the runs behind
+ * them, runs R, workgroups that start with a run of their own } and returns 1, or 0 on invalid arguments.  Run t < L is the
+ * t-th of the long ones, the rest follow; the last may be cut short by the number of items.
+ *
  * hg_debug_suffix_plan: the suffix kernel and chunking chosen with default options for B sequences of at most max_len
  * suffix rows, nq queries each, Hq / Hkv heads of dimension D (page_size > 0: paged cache).  Fills out[4] = { keys per
  * work item, work items per row (= partial results), 1 if the matrix-core kernel runs, query heads per vector-ALU
@@ -58,6 +66,9 @@ int hg_debug_wide_plan(int n_blocks, int max_rows, int max_seqs, int Hkv, int ro
                        int slots_per_xcd, int D, int out[9]);
 int hg_debug_wide_ranges(int n_blocks, int max_rows, int max_seqs, int Hkv, int rows_per_seq, int max_parts,
                          int slots_per_xcd, int D, int starts[257], int first_part[256]);
+int hg_debug_wide_team(int n_blocks, int max_rows, int max_seqs, int Hkv, int rows_per_seq, int max_parts,
+                       int slots_per_xcd, int D, int team, int out[3]);
+int hg_debug_item_runs(int items, int slots_per_xcd, int out[5]);
 int hg_debug_suffix_plan(int B, int nq, int Hq, int Hkv, int D, int max_len, int page_size, int out[4]);
 int hg_debug_fused_plan(const int* options, int n_options, int n_levels, const hg_level* levels, int B, int nq, int Hq, int Hkv, int D,
                         int max_len, int page_size, int fp8, size_t workspace_bytes, int out[8]);

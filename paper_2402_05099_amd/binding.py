@@ -39,7 +39,7 @@ EXPORTS = (
     "hg_create", "hg_destroy", "hg_set_stream", "hg_set_option", "hg_workspace_bytes", "hg_prefix_attn",
     "hg_prefix_attn_grouped", "hg_suffix_attn", "hg_merge", "hg_hydragen_attn", "hg_naive_attn", "hg_read_stage_timings",
     "hg_strerror", "hg_suffix_attn_paged", "hg_hydragen_attn_paged", "hg_kv_append", "hg_kv_append_paged",
-    "hg_debug_wide_plan", "hg_debug_wide_ranges", "hg_debug_suffix_plan", "hg_debug_fused_plan", "hg_debug_single_work", "hg_suffix_attn_fp8", "hg_hydragen_attn_fp8", "hg_kv_append_fp8",
+    "hg_debug_wide_plan", "hg_debug_wide_ranges", "hg_debug_wide_team", "hg_debug_item_runs", "hg_debug_suffix_plan", "hg_debug_fused_plan", "hg_debug_single_work", "hg_suffix_attn_fp8", "hg_hydragen_attn_fp8", "hg_kv_append_fp8",
     "hg_hydragen_attn_static", "hg_debug_mfma_loop", "hg_debug_stream_read", "hg_debug_xcd_of_workgroups",
 )
 
@@ -122,6 +122,10 @@ def lib() -> ctypes.CDLL:
         L.hg_debug_wide_plan.restype = ci
         L.hg_debug_wide_ranges.argtypes = [ci] * 8 + [ctypes.POINTER(ci), ctypes.POINTER(ci)]
         L.hg_debug_wide_ranges.restype = ci
+        L.hg_debug_wide_team.argtypes = [ci] * 9 + [ctypes.POINTER(ci)]
+        L.hg_debug_wide_team.restype = ci
+        L.hg_debug_item_runs.argtypes = [ci] * 2 + [ctypes.POINTER(ci)]
+        L.hg_debug_item_runs.restype = ci
         L.hg_debug_suffix_plan.argtypes = [ci] * 7 + [ctypes.POINTER(ci)]
         L.hg_debug_suffix_plan.restype = ci
         L.hg_debug_fused_plan.argtypes = [ctypes.POINTER(ci), ci, ci, ctypes.POINTER(hg_level)] + [ci] * 8 + [cs, ctypes.POINTER(ci)]
@@ -551,6 +555,20 @@ def hg_debug_wide_plan(n_blocks: int, max_rows: int, max_seqs: int, Hkv: int, ro
         assert n == 8 * plan["tpx"]
         plan["starts"], plan["first_part"] = list(starts)[:n + 1], list(first)[:n]
     return plan
+
+
+def hg_debug_wide_team(n_blocks: int, max_rows: int, max_seqs: int, Hkv: int, rows_per_seq: int, max_parts: int, slots_per_xcd: int, D: int, team: int):
+    """(first position, position behind the last, part index of the first piece) of a team's walk, or None if it has none (host only)."""
+    out = (ctypes.c_int * 3)()
+    return tuple(out) if lib().hg_debug_wide_team(n_blocks, max_rows, max_seqs, Hkv, rows_per_seq, max_parts, slots_per_xcd, D, team, out) else None
+
+
+def hg_debug_item_runs(items: int, slots_per_xcd: int):
+    """dict of the runs in which the combined launch hands out its work items, or None on invalid arguments (host only)."""
+    out = (ctypes.c_int * 5)()
+    if not lib().hg_debug_item_runs(items, slots_per_xcd, out):
+        return None
+    return dict(zip(("long_runs", "long_run", "tail_run", "runs", "starters"), list(out)))
 
 
 def hg_debug_suffix_plan(B: int, nq: int, Hq: int, Hkv: int, D: int, max_len: int, page_size: int = 0):

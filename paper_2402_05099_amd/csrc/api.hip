@@ -1311,11 +1311,11 @@ static int fused_impl(hg_ctx* c, const void* Q, int n_levels, const hg_level* le
         ca.d.by_tiles = divider((unsigned)(sp.mfma ? ceil_div(nq * G, ca.d.tile_rows) : 1));
         ca.d.by_group = divider((unsigned)G);
         const int units = (int)ca.d.units, wide = 8 * ca.p.wide.slots, starters = wide == 256 ? 256 : 256 - wide;
-        ca.long_run = std::min(kLongRun, std::max(1, units / starters));
-        ca.long_runs = std::min(std::max(std::max(0, units - kTailItems) / kLongRun, starters), units / ca.long_run);
-        const int tail = units - ca.long_runs * ca.long_run;
-        ca.tail_run = ca.long_run < 4 ? 1 : 2;
-        ca.n_tickets = ca.long_runs + ceil_div(tail, ca.tail_run);
+        const ItemRuns runs = item_runs(units, starters);
+        ca.long_runs = runs.long_runs;
+        ca.long_run = runs.long_run;
+        ca.tail_run = runs.tail_run;
+        ca.n_tickets = runs.n_tickets;
         if (sp.mfma) rc = hip_rc(D == 128 ? launch_combined_tiles(ca, s) : launch_combined_tiles_d64(ca, s));
         else rc = hip_rc(D == 128 ? launch_combined_vector(ca, s) : launch_combined_vector_d64(ca, s));
         if (rc) return rc;
@@ -1636,6 +1636,26 @@ int hg_debug_wide_ranges(int n_blocks, int max_rows, int max_seqs, int Hkv, int 
     for (int t = 0; t <= nteams; ++t) starts[t] = p.starts[t];
     for (int t = 0; t < nteams; ++t) first_part[t] = p.first_part[t];
     return nteams;
+}
+
+int hg_debug_wide_team(int n_blocks, int max_rows, int max_seqs, int Hkv, int rows_per_seq, int max_parts, int slots_per_xcd,
+                       int D, int team, int out[3]) {
+    if (!out || team < 0 || n_blocks < 1 || max_rows < 0 || max_seqs < 0 || Hkv < 1 || rows_per_seq < 1 || (D != 64 && D != 128)) return 0;
+    hg::LevelDev lv{};
+    lv.n_blocks = n_blocks;
+    lv.max_rows = max_rows;
+    lv.max_seqs = max_seqs;
+    hg::WidePlan p{};
+    if (!hg::plan_prefix_wide(lv, Hkv, rows_per_seq, D, max_parts, slots_per_xcd, &p) || team >= 8 * p.tpx) return 0;
+    return hg::wide_team_range(p, team, out[0], out[1], out[2]) ? 1 : 0;
+}
+
+int hg_debug_item_runs(int items, int slots_per_xcd, int out[5]) {
+    if (!out || items < 1 || items >= (1 << 30) || slots_per_xcd < 1 || slots_per_xcd > 32) return 0;
+    const int starters = slots_per_xcd == 32 ? 256 : 256 - 8 * slots_per_xcd;
+    const hg::ItemRuns r = hg::item_runs(items, starters);
+    out[0] = r.long_runs; out[1] = r.long_run; out[2] = r.tail_run; out[3] = r.n_tickets; out[4] = starters;
+    return 1;
 }
 
 int hg_debug_suffix_plan(int B, int nq, int Hq, int Hkv, int D, int max_len, int page_size, int out[4]) {

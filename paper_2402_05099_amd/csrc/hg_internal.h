@@ -69,6 +69,39 @@ struct WidePlan {
     int first_part[kWideMaxTeams];      // mode 2: part index of team t's first piece (pieces of its column before it)
 };
 
+// The range [f0, f1) of the flattened (column, stage) space that a team walks, and the part index of its first piece; false: none.
+// `p`: a WidePlan, on the device in the kernarg segment.
+template <class Plan>
+__host__ __device__ inline bool wide_team_range(const Plan& p, int team, int& f0, int& f1, int& sp0) {
+    const auto div = [](unsigned n, const auto& d) { return Divider{d.mul, d.shift}.of(n); };
+    const int nteams = 8 * p.tpx;
+    const int total = p.ncols * p.n_c;      // the planner keeps this below 2^31 (and the columns below 2^20)
+    if (p.mode == 0) {            // equal contiguous ranges
+        const long long lo = (long long)team * p.quota;
+        if (lo >= total) return false;
+        f0 = (int)lo;
+        f1 = (int)(lo + p.quota < total ? lo + p.quota : total);
+        sp0 = team - (int)div(div((unsigned)f0, p.by_n_c) * (unsigned)p.n_c, p.by_quota);
+    } else if (p.mode == 2) {     // ranges of equal cost, from the planner's table
+        f0 = p.starts[team];
+        f1 = p.starts[team + 1];
+        sp0 = p.first_part[team];
+    } else if (p.ncols <= nteams) {   // every column is cut evenly among its own teams
+        const int c = (int)div((unsigned)(team * p.ncols), p.by_teams);
+        const int tf = (int)div((unsigned)(c * nteams + p.ncols - 1), p.by_cols);
+        const int nt = (int)div((unsigned)((c + 1) * nteams + p.ncols - 1), p.by_cols) - tf;
+        const int more = nt * p.ncols > nteams;      // nteams / ncols teams, or one more
+        sp0 = team - tf;
+        f0 = c * p.n_c + (int)div((unsigned)(sp0 * p.n_c), p.by_cut[more]);
+        f1 = c * p.n_c + (int)div((unsigned)((sp0 + 1) * p.n_c), p.by_cut[more]);
+    } else {                      // whole columns per team
+        f0 = (int)div((unsigned)(team * p.ncols), p.by_teams) * p.n_c;
+        f1 = (int)div((unsigned)((team + 1) * p.ncols), p.by_teams) * p.n_c;
+        sp0 = 0;
+    }
+    return f0 < f1;
+}
+
 struct PrefixArgs {
     const uint16_t* Q;
     LevelDev lv;
@@ -132,18 +165,29 @@ struct CombinedArgs {
     int n_more;                     // further levels, one after another on the same workgroups
     MoreLevel more[kMoreLevels];
     unsigned* tickets;    // work counter, zero at the start (the merge that follows sets it back)
-    int long_runs;        // tickets that stand for long_run work items; the rest stand for tail_run
+    int long_runs;        // (item_runs below)
     int long_run;
     int tail_run;
     int n_tickets;
 };
-// The last kTailItems items go out in short runs so that the workgroups end together: a run of eight 256-row items keeps a
-// CU busy for 45 us.  (256 x 40 heads with suffixes of 1..256 rows: runs of 32 and 8 150 us, 32 / 8 / 2 150, 16 / 4 / 2 134,
-// 8 / 2 135, 4 138.)
-// The runs that the workgroups start with have an item for every wavefront where there are as many: those without one would wait for the draws
-// of all the others (128 x 32/8 heads, 2K keys, paged: 216 workgroups start with 1728 of 2048 items; with runs of 2 some wavefronts had their first
-// item at 11 of 34 us).
+// Work items go out in runs (tickets).  The first runs, one for every workgroup that starts with one, have an item for each of its wavefronts where there are
+// as many: those without would wait for the draws of all the others (128 x 32/8 heads, 2K keys, paged: 216 workgroups start with 1728 of 2048
+// items; with runs of 2 some wavefronts had their first item at 11 of 34 us).  Long runs until kTailItems are left, then short ones so that the workgroups
+// end together: a run of eight 256-row items keeps a CU busy for 45 us.  (256 x 40 heads with suffixes of 1..256 rows: runs of 32 and 8
+// 150 us, 32 / 8 / 2 150, 16 / 4 / 2 134, 8 / 2 135, 4 138.)  Calls whose first runs leave fewer than kTailItems, or none (2048 items on 256 starting
+// workgroups), have that much less of a tail; of 700 drawn calls with these runs none is slower than with the short runs by more than 3 %.
 constexpr int kLongRun = 8, kTailItems = 1024;
+struct ItemRuns { int long_runs, long_run, tail_run, n_tickets; };      // tickets below long_runs stand for long_run items, the others for tail_run
+inline ItemRuns item_runs(int units, int starters) {
+    ItemRuns r;
+    r.long_run = units / starters < 1 ? 1 : units / starters < kLongRun ? units / starters : kLongRun;
+    const int full = units > kTailItems ? (units - kTailItems) / kLongRun : 0, most = units / r.long_run;
+    r.long_runs = full > starters ? full : starters;
+    if (r.long_runs > most) r.long_runs = most;
+    r.tail_run = r.long_run < 4 ? 1 : 2;
+    r.n_tickets = r.long_runs + (units - r.long_runs * r.long_run + r.tail_run - 1) / r.tail_run;
+    return r;
+}
 
 // The single-launch fused kernel (fused_small.hip): every level, the suffix and the merge for columns of 32 or 16 query rows.
 constexpr int kSmallMaxSplits = 32;           // workgroups per column at most
@@ -200,7 +244,7 @@ struct SmallArgs {
     float* part;              // splits > 1: partial results (small_part_floats)
     unsigned* arrivals;       // splits > 1: [cols] counters that only ever count to `splits`, zero between calls
     float scale;
-    float c2, tau_raw;        // scale * log2(e); by how much a raw score may pass the maximum before sums are rescaled (small_scales)
+    float c2, tau_raw;        // scale * log2(e); by how much a raw score may pass the maximum before sums are rescaled (set by launch_fused_small)
     void* O;                  // final results: [B, nq, Hq, D] bf16 or fp32, LSE [B, nq, Hq] (may be null)
     float* LSE;
     int bf16;

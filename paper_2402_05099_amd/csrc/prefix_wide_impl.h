@@ -176,38 +176,13 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     const int team_local = (int)div_by((unsigned)cu_slot, p.by_T), member = cu_slot - team_local * p.T;
     if (team_local >= p.tpx) return;
     const int team = xcd * p.tpx + team_local;
-    const int nteams = 8 * p.tpx;
-    const int total = p.ncols * p.n_c;      // the planner keeps this below 2^31 (and the columns below 2^20)
 
     // ---- this team's range [f0, f1) of the flattened (column, stage) space; sp0 = part index of its first piece ----
     // (Divisions, here, in the look-up of a piece and in the lanes' row numbers, are multiplications by numbers from the host: on this
     // chip one by a run-time divisor takes some 30 instructions that wait for each other, one of 64 bits a loop.  With the order of the sequences
     // in combined_impl.h: 256 x 64/8 heads, 4K keys, four queries 185.4 -> 184.5 us, 512 x 64/8, 4K keys 135.0 -> 134.2; eleven drawn combined calls 1.008 in the mean.)
     int f0, f1, sp0;
-    if (p.mode == 0) {            // equal contiguous ranges
-        const long long lo = (long long)team * p.quota;
-        if (lo >= total) return;
-        f0 = (int)lo;
-        f1 = (int)(lo + p.quota < total ? lo + p.quota : total);
-        sp0 = team - (int)div_by(div_by((unsigned)f0, p.by_n_c) * (unsigned)p.n_c, p.by_quota);
-    } else if (p.mode == 2) {     // ranges of equal cost, from the planner's table
-        f0 = p.starts[team];
-        f1 = p.starts[team + 1];
-        sp0 = p.first_part[team];
-    } else if (p.ncols <= nteams) {   // every column is cut evenly among its own teams
-        const int c = (int)div_by((unsigned)(team * p.ncols), p.by_teams);
-        const int tf = (int)div_by((unsigned)(c * nteams + p.ncols - 1), p.by_cols);
-        const int nt = (int)div_by((unsigned)((c + 1) * nteams + p.ncols - 1), p.by_cols) - tf;
-        const int more = nt * p.ncols > nteams;      // nteams / ncols teams, or one more
-        sp0 = team - tf;
-        f0 = c * p.n_c + (int)div_by((unsigned)(sp0 * p.n_c), p.by_cut[more]);
-        f1 = c * p.n_c + (int)div_by((unsigned)((sp0 + 1) * p.n_c), p.by_cut[more]);
-    } else {                      // whole columns per team
-        f0 = (int)div_by((unsigned)(team * p.ncols), p.by_teams) * p.n_c;
-        f1 = (int)div_by((unsigned)((team + 1) * p.ncols), p.by_teams) * p.n_c;
-        sp0 = 0;
-    }
-    if (f0 >= f1) return;
+    if (!wide_team_range(p, team, f0, f1, sp0)) return;
 
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);

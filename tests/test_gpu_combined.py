@@ -122,6 +122,35 @@ def test_combined_more_results_than_a_wavefront_keeps(B, H, D, cache):
     ctx.close()
 
 
+@pytest.mark.parametrize("cache", ["packed", "paged"])
+@pytest.mark.parametrize("heads", [1, 8])
+@pytest.mark.parametrize("B", [129, 223, 224, 225, 448, 1000, 1791, 1792, 1793, 2048, 2817])
+def test_combined_item_runs(B, heads, cache):
+    """One work item per sequence, on the vector ALU and the matrix cores: fewer than the 224 (256) workgroups that start with a run, as many, one more, runs of
+    2 to 8, first runs that leave no items, one, and a tail behind long runs."""
+    print(f"combined, runs: {cache} B={B} heads={heads}", file=sys.stderr, flush=True)
+    w = wl.make_workload("runs", 80, B, heads, 1, 128, [(1, 40, B)], 0, 40)
+    dw = dev.to_device(w)
+    Oref, Lref, call = reference(w, cache)
+    ctx = dev.make_context(dw, parts=16)
+    ctx.set_option(hb.HG_OPT_FUSED_KERNEL, 1)
+    for slots in (4, 32):
+        ctx.set_option(hb.HG_OPT_WIDE_SLOTS, slots)
+        plan = hb.hg_debug_fused_plan([(1, 40, B)], B, 1, heads, 1, 128, dw.max_len, 16 if cache == "paged" else 0, False, hb.hg_workspace_bytes(B, heads, 128, 16),
+                                      {hb.HG_OPT_FUSED_KERNEL: 1, hb.HG_OPT_WIDE_SLOTS: slots})
+        assert (plan["way"], plan["nchunks"], plan["mfma"]) == ("combined", 1, int(heads > 1)), plan
+        got = []
+        for _ in range(2):
+            O = torch.full(dw.lead + (128,), float("nan"), dtype=torch.float32, device="cuda:0")
+            L = torch.full(dw.lead, float("nan"), dtype=torch.float32, device="cuda:0")
+            call(ctx, dw, O, L)
+            got.append((O, L))
+        torch.cuda.synchronize()
+        check(to_np(got[0][0]), to_np(got[0][1]), Oref, Lref, f"runs {cache} B={B} heads={heads} slots={slots}")
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    ctx.close()
+
+
 @pytest.mark.parametrize("shape", ["many_items", "tile_items", "tile_items_g4"])
 def test_combined_capture(shape):
     """Captured once, replayed with eager calls and other inputs in between: every replay leaves its counters at zero."""

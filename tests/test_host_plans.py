@@ -81,6 +81,54 @@ def test_wide_plan_covers_every_stage_once(shape, slots, max_parts, D):
         assert 8 * plan["tpx"] * plan["quota"] >= plan["ncols"] * plan["n_c"]
 
 
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("slots", [1, 3, 5, 12, 20, 32])
+@pytest.mark.parametrize("max_parts", [1, 3, 24])
+def test_wide_teams_walk_the_ranges_of_the_plan(shape, slots, max_parts):
+    """The kernel finds its range with multiplications by numbers from the host: what it computes, for every team, against whole-number divisions here."""
+    n_blocks, max_rows, max_seqs, Hkv, rps = shape
+    args = (n_blocks, max_rows, max_seqs, Hkv, rps, max_parts, slots, 128)
+    plan = hb.hg_debug_wide_plan(*args)
+    n_c, ncols, nteams, quota = plan["n_c"], plan["ncols"], 8 * plan["tpx"], plan["quota"]
+    for team in range(nteams):
+        if plan["mode"] == 2:
+            want = plan["starts"][team], plan["starts"][team + 1], plan["first_part"][team]
+        elif plan["mode"] == 0:
+            want = team * quota, min((team + 1) * quota, n_c * ncols), team - team * quota // n_c * n_c // quota
+        elif ncols <= nteams:
+            c = team * ncols // nteams
+            first = -(-c * nteams // ncols)
+            n = -(-(c + 1) * nteams // ncols) - first
+            want = c * n_c + (team - first) * n_c // n, c * n_c + (team - first + 1) * n_c // n, team - first
+        else:
+            want = team * ncols // nteams * n_c, (team + 1) * ncols // nteams * n_c, 0
+        assert hb.hg_debug_wide_team(*args, team) == (want if want[0] < want[1] else None), (plan, team)
+    assert hb.hg_debug_wide_team(*args, nteams) is None
+
+
+@pytest.mark.parametrize("slots", [1, 5, 8, 16, 24, 28, 31, 32])
+def test_item_runs_cover_every_item_once(slots):
+    """Runs of the combined launch: together they hold every item once, a workgroup that starts with a run finds one where there are items for it, and runs are short
+    where first runs alone would leave wavefronts without an item."""
+    starters = 256 if slots == 32 else 256 - 8 * slots
+    for items in sorted({1, 2, 7, starters - 1, starters, starters + 1, 2 * starters - 1, 2 * starters, 4 * starters - 1, 4 * starters, 7 * starters + 3, 8 * starters - 1,
+                         8 * starters, 8 * starters + 1, 1023, 1024, 1025, 2048, 2100, 1024 + 8 * starters - 1, 1024 + 8 * starters, 40960, 2**30 - 1} - {0}):
+        r = hb.hg_debug_item_runs(items, slots)
+        assert r["starters"] == starters and 1 <= r["long_run"] <= 8 and r["tail_run"] in (1, 2)
+        assert 0 < r["long_runs"] <= r["runs"] and r["long_runs"] * r["long_run"] <= items
+        tail = items - r["long_runs"] * r["long_run"]
+        assert (r["runs"] - r["long_runs"] - 1) * r["tail_run"] < tail <= (r["runs"] - r["long_runs"]) * r["tail_run"] or (tail == 0 and r["runs"] == r["long_runs"])
+        assert r["runs"] >= min(items, starters)
+        if items >= 8 * starters:
+            assert r["long_run"] == 8                               # an item for every wavefront at the start
+            assert tail <= max(1024 + 7, items - 8 * starters)
+        elif items >= starters:
+            assert r["long_run"] == items // starters and r["long_runs"] >= starters
+        else:
+            assert r["long_run"] == 1 and r["long_runs"] == items
+    assert hb.hg_debug_item_runs(0, slots) is None and hb.hg_debug_item_runs(2**30, slots) is None and hb.hg_debug_item_runs(5, 33) is None
+
+
 def test_wide_plan_aligns_short_pieces_to_columns():
     """Config 2's shape (40 columns of 64 stages on 256 teams): ranges of 10 stages would cut 32 teams' ranges at a
     column boundary (two pieces, each with its fixed price); aligned ranges give every team one piece of 9..11 stages."""

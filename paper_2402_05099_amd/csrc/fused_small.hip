@@ -8,8 +8,8 @@
 // block boundary falls inside the tile), then the suffix of each of the tile's sequences (only that sequence's rows
 // attend).  Softmax over the union of all segments is one online softmax: a row that does not attend to a segment has
 // its scores masked.  The decomposition of Eq. 5 appears twice: the 32-key stages of the list are dealt out to the
-// wavefronts of the column's workgroups one by one (or in runs, see below), each with its own running maximum, sum and accumulator; the eight partial
-// results of a workgroup meet in LDS and are combined with the weights exp(LSE_i - max LSE).
+// wavefronts of the column's workgroups one by one (or in runs, see below), each with its own running maximum, sum and accumulator; the partial
+// results of a workgroup's wavefronts meet in LDS and are combined with the weights exp(LSE_i - max LSE).
 //
 // 16 rows: products of 16 x 16 instead of 32 x 32, half the exponentials per lane, and fewer sequences whose suffixes a column
 // has to walk; twice as many columns, which a small call has CUs for (the rule is in plan_fused).
@@ -41,7 +41,7 @@
 // divisions are multiplications by numbers from the host, the prefix sum of the lengths stays in the vector ALU, and copies whose
 // rows need no clamp run without a branch: before, lengths to first product 0.95 us, arguments to first request 0.1 longer;
 // 45 x 16/2 heads, 515 keys, ragged up to 150 rows 9.86 -> 8.56 us, 256 x 8/1, 1K keys, 128 rows 12.2 -> 11.4, 40 drawn calls 1.046 in the mean.
-// Measured, one workgroup per column, runs of consecutive stages and 32 rows before, as it is now after: 256 sequences x 8 heads on one KV head, 1024
+// Stages dealt out one by one, 16-row columns and early requests (with one workgroup per column, runs of consecutive stages and 32 rows before): 256 sequences x 8 heads on one KV head, 1024
 // shared keys, 128 suffix rows 16.2 -> 12.1 us; 45 x 16 heads on two KV heads, 515 keys, ragged up to 150 rows 13.9 -> 10.0;
 // 57 calls of this kind drawn at random 1.19 times as fast in the mean (stages dealt out one by one and the first requested early
 // alone: 1.05).
@@ -476,7 +476,7 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
         t = p - (__builtin_amdgcn_readlane(incl_v, i) - s.nst);
     };
     const int step = a.dealt ? runs : 1;
-    // (runs: the host gives a column one workgroup then; 9 total stays below 2^31, a block's rows being fewer than 2^24)
+    // (runs: the host gives a column one workgroup then; NWS * total stays below 2^31, a block's rows being fewer than 2^24)
     const int first = a.dealt ? run : (int)((unsigned)(run * total) / NWS), end = a.dealt ? total : (int)((unsigned)((run + 1) * total) / NWS);
     if (!requested && first < end) {
         if (!a.dealt && first < shared_total) {     // (the walk has counted the shared stages: once more from the beginning)
@@ -754,7 +754,7 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
     }
     float lse = Lsum > 0.f ? M * a.scale + __logf(Lsum) : -INFINITY;
 
-    if (a.splits > 1) {
+    if (NWS == 8 && a.splits > 1) {      // (four wavefronts: one workgroup per column)
         // ---- the column's results meet in the workspace ----------------------------------------------------------------------------------
         // (a column's [S][TR][D] results and, behind them, [S][TR] LSEs; every access below is at a row < TR of a split < S)
         const int S = a.splits;

@@ -963,15 +963,16 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
     // reading the shared rows for itself: they win while there are CUs for them.  Measured 32 / 16 rows: 13.2 / 10.0 us (45 x 16/2
     // heads, 515 keys), 15.9 / 12.0 (256 x 8/1, 1K keys), 11.3 / 8.8 (95 x 16/2, two queries), 44.5 / 61 (139 x 64/8, four queries),
     // 27.2 / 31 (60 x 16/2, 3K keys, three workgroups per column).
-    // Four wavefronts: half the LDS, so two columns share a CU (at D = 64 four, of 32 rows with fp32 weights two, by their registers; the price takes three) and one's prologue and combination run beside
+    // Four wavefronts: half the LDS, so two columns share a CU (at D = 64 four, of 32 rows with fp32 weights three, by their registers; the price takes three) and one's prologue and combination run beside
     // the other's stages.  A column takes longer: for calls with more columns than CUs and few stages to a column.  Eight / four wavefronts, and the other
     // way, us: 683 x 64/8 heads, 549 keys, four queries 222 / 167, 199; 1965 x 64/8, 1294 + 16 x 115 keys 223 / 193, 225; 215 x 64/8, 553 keys, four
     // queries, codes 79 / 62, 76; 57 x 64/8, 342 + 3 x 297 keys, four queries 21.7 / 15.7, 22; 256 x 64/8, 4K keys, four queries 247 / 232, 185 (not taken).
     // The host knows only an upper bound of the suffix lengths; both estimates take 0.75 of it as the mean.  The single launch is
-    // taken below 1.2 of the other estimate up to 36 us (a suffix alone: 15, and 0.8 where its kernel has one row per KV head and writes the outputs itself: 414 x 4 heads, 47 rows 20 against 15 us), beyond with a tenth of the suffix time to spare (long rows are where it
-    // disappoints).  Over the 2070 calls 1.025 times as fast as with the constants of before (fitted when a column's workgroups met
-    // in 2 us more and its prologue took 1) and without four wavefronts; 159 calls change between it and the other way, 112 of them to the faster by more than a
-    // twentieth, 18 to the slower.  220 others 1.039 in the mean, four slower by more than a twentieth.
+    // taken below 1.2 of the other estimate up to 36 us, beyond with a tenth of the suffix time to spare (long rows are where it disappoints); a suffix alone up to 15 us,
+    // and below 0.8 where one row per KV head goes straight from its kernel to the outputs (414 x 4 heads, 47 rows 20 against 15 us), or by the price of its work items.
+    // The estimates' errors are as large as most differences between the ways: of 14000 drawn calls 1168 go another way than with the constants of before (fitted when a
+    // column's workgroups met in 2 us more and its prologue took 1) and without four wavefronts; of 1000 of these, timed, 695 are by more than a tenth faster, 43 slower, 1.24
+    // times as fast in the mean.  Finer estimates (the suffix at its true mean, every part priced, errors of 8 to 11 %) chose no better with the mean unknown.
     // (the single launch divides sums by the V scale and multiplies them again: not with scales near the ends of fp32)
     const bool odd_scale = f.fp8 && has_suffix && !(f.v_scale >= 0x1p-60f && f.v_scale <= 0x1p60f);
     bool take_single = false;
@@ -1019,7 +1020,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
         const Shape shape32 = shape_of(32), shape16 = shape_of(16);
         const long long cols = shape32.cols;
         const int seqs_per_tile = shape32.seqs_per_tile;
-        // Workgroups of eight wavefronts that run at a time: one per CU, at D = 64 two (LDS), which take longer then: 112 x 40/40 heads, 8K keys: 48 us with 160
+        // Workgroups of eight wavefronts that run at a time: one per CU, at D = 64 two (LDS; of 32 rows with fp32 weights one, by their registers, which the constants below have taken in), which take longer then: 112 x 40/40 heads, 8K keys: 48 us with 160
         // columns of 32 rows, 66 with 280 of 16 rows (45 with 160 of them).
         auto rounds_of = [&](double wgs) { return ceil(wgs / (D == 128 ? 256.0 : 512.0)); };
         struct Eight { double b, c, m0, m1, fp32_weights, sharing, rounds, paged, packed; };      // (paged, packed: of the suffix rows' time at 5 TB/s)
@@ -1133,7 +1134,7 @@ static int plan_fused(const hg_ctx* c, const FusedShape& f, FusedPlan* out) {
             return other <= 36.0 ? single_us <= 1.2 * other
                                  : single_us + 0.1 * suffix_us <= (f.fp8 && may_combine && wide && nonempty == 1 ? 0.91 : 1.0) * other;      // (codes: overestimated there)
         };
-        bool small = direct ? single_us <= (est_other < 36.0 ? 1.12 : 0.85) * est_other      // (rows by the thousand: the single launch streams them slower)
+        bool small = direct ? single_us <= (est_other < 6.1 ? 1.26 : est_other < 36.0 ? 1.12 : 0.85) * est_other      // (a few items: 5 us are estimated at 7; rows by the thousand: it streams them slower)
                      : nonempty == 0 ? est_single <= (rps == 1 && alone.nchunks == 1 ? 0.8 : est_other <= 15.0 ? 1.2 : 1.0) * est_other
                      : faster_than(est_other);
         // The combined launch cuts a few columns with many keys into many parts, 0.6 us each beyond eight in its pieces' boundaries and in the merge: calls

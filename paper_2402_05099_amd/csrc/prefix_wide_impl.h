@@ -7,7 +7,7 @@
 //
 // Same mathematics and LDS layout as prefix.hip (transposed products S^T = K Q^T and O^T += V^T P^T with
 // v_mfma_f32_32x32x16_bf16, K/V tiles in their HBM layout with XOR-swizzled 16-byte chunks, transposing LDS
-// reads for V, lazy rescaling).  What differs, and why:
+// reads for V).  What differs, and why:
 //   * One workgroup per CU, 8 wavefronts x 32 query rows = 256 rows: a workgroup amortises each K/V byte it
 //     copies from L2 over 256 rows.  On this chip the copies cost power rather than time, and the kernel runs
 //     against the power limit (a register-only MFMA loop on random data holds 1.85 GHz, not 2.4).
@@ -19,10 +19,16 @@
 //   * Ring of 8 stages (K and V, 16 KiB together) in 128 KiB of dynamic LDS, filled by direct HBM->LDS copies that
 //     are issued from inline asm and waited for with counted s_waitcnt vmcnt: four stages are in flight while
 //     one is consumed.
-//   * Software pipeline over stages, written out by gen_prefix_wide_step.py: in one step the scores of stage j+1
-//     are produced while the exponentials of stage j are taken and its P*V product runs; fragments are loaded
-//     from LDS four MFMAs before their use; the vector-ALU work is spread over the gaps between the MFMAs.  At D = 64 a
+//   * Software pipeline over stages, written out by gen_prefix_wide_step.py: in one step the scores of stage j+2 are
+//     produced, the weights of stage j+1 are taken and the P*V product of stage j runs; fragments are loaded
+//     from LDS four MFMAs before their use; the vector-ALU work is spread evenly over the gaps between the MFMAs.  At D = 64 a
 //     stage has two 32-key score tiles: the same 16 MFMAs per step with twice the softmax work between them.
+//   * No search for the row maximum: weights are taken against the maximum of the piece's first stage, and their sum, which is needed
+//     anyway and is there a step before their product, says whether a stage has to be taken again against its own (add_sum).
+//     Before, with exponentials and product of a stage in one step and the maximum of every stage: 73 instead of 59 vector-ALU instructions per
+//     16 MFMAs (D = 64: 147 / 116).  The kernel runs at the board's power limit, so what counts is the energy of what it issues: 1024 x 40 heads,
+//     16K keys 303.5 -> 296 us with its merge (1365 -> 1325 cycles per stage), 512 x 64/8, 4K keys 74.9 -> 73.7, D = 64, 1024 x 40, 4K keys 63.2 -> 61.6; in the
+//     combined launch 256 x 64/8, four queries, 4K keys 179 -> 174, 1024 x 8/1, 16K keys 83.0 -> 81.6, 1024 x 40, 16K keys 480 -> 474.
 #include <algorithm>
 #include <numeric>
 #include <type_traits>
@@ -54,7 +60,7 @@ constexpr int LDS_RING_BYTES = 2 * NS * STB;        // 128 KiB
 constexpr int kStageBytes = 32 * 32 * 4;              // staging area of one wavefront for its results: 32 columns of its 32 rows, fp32
 constexpr int LDS_BYTES = LDS_RING_BYTES + NW * kStageBytes;   // 160 KiB, all of a CU's LDS
 constexpr int INFLIGHT = 4;             // stages that may still be in flight at a step's barrier
-constexpr float TAU = 8.0f;             // lazy-rescale threshold, log2 units
+constexpr float kMostWeight = 65536.f;  // largest sum of a lane's weights of one stage that is left as it is
 static_assert(KT == NW * RPI, "one copy instruction per wavefront, stage and tensor");
 static_assert(kPrefixRowsWide == 32 * NW, "one 32-row query block per wavefront");
 
@@ -93,26 +99,6 @@ __device__ __forceinline__ unsigned pack_bf16_pair(float lo, float hi) {
     floatx2 f = {lo, hi};
     return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
 }
-// plain v_max3 / v_max: the operands are MFMA results or earlier maxima, nothing to quiet
-__device__ __forceinline__ float max3f(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-__device__ __forceinline__ float max2f(float a, float b) {
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-// max of a value with the one held 32 lanes away.  v_permlane32_swap exchanges the upper 32 lanes of its first
-// operand with the lower 32 lanes of its second: afterwards t holds the lower half's values in both halves and
-// x the upper half's.
-__device__ __forceinline__ float half_max_swap(float x) {
-    float t;
-    asm("v_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane32_swap_b32 %1, %0\n\ts_nop 1\n\tv_max_f32 %0, %0, %1" : "+v"(x), "=&v"(t));
-    return x;
-}
-
 extern __shared__ __attribute__((aligned(1024))) unsigned char wide_smem[];
 
 // Phase time stamps of a -DHG_TRACE build (a measurement aid, compiled out otherwise): thread 0 of every workgroup
@@ -443,24 +429,40 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     // ---- online softmax state ------------------------------------------------------------------------------------
     floatx16 Oacc[DB];
     float m_used;               // raw-score maximum the exponentials are taken against
-    float lsum[2];              // this lane's share of the row sum (of the unrounded exponentials), two chains
+    float lsum;                 // this lane's share of the row sum (of the unrounded exponentials)
     float mc;                   // m_used * c2
     const float c2 = ka->scale * kLog2e;
-    const float tau_raw = TAU / c2;
-    auto maybe_rescale = [&](float tmax) {
-        if (__any(tmax > m_used + tau_raw)) {
-            const float m_new = fmaxf(m_used, tmax);
-            // equal maxima (also -inf and -inf) keep the accumulators; otherwise exp2(-inf) = 0 for a first maximum
-            const float alpha = (m_new == m_used) ? 1.0f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
-            m_used = m_new;
-            mc = m_new * c2;
-            lsum[0] *= alpha;
-            lsum[1] *= alpha;
+    // the weights of one stage (its scores against the present maximum), packed for the second product; returns this lane's sum of them
+    auto weights = [&](const STile& S, uintx4 (&p)[KT / 16]) -> float {
+        float sa = 0.f, sb = 0.f;
 #pragma unroll
-            for (int i = 0; i < DB; ++i)
+        for (int h = 0; h < KT / 16; ++h)
 #pragma unroll
-                for (int k = 0; k < 16; ++k) Oacc[i][k] *= alpha;
-        }
+            for (int i = 0; i < 4; ++i) {
+                const int e = 8 * (h & 1) + 2 * i;
+#if HG_WIDE_D == 128
+                const float x0 = S[e], x1 = S[e + 1];
+#else
+                const float x0 = h < 2 ? S.a[e] : S.b[e], x1 = h < 2 ? S.a[e + 1] : S.b[e + 1];
+#endif
+                const float ea = __builtin_amdgcn_exp2f(fmaf(x0, c2, -mc)), eb = __builtin_amdgcn_exp2f(fmaf(x1, c2, -mc));
+                p[h][i] = pack_bf16_pair(ea, eb);
+                sa += ea;
+                sb += eb;
+            }
+        return sa + sb;
+    };
+    auto tile_max = [&](const STile& S) -> float {
+#if HG_WIDE_D == 128
+        float t = fmaxf(S[0], S[1]);
+#pragma unroll
+        for (int i = 2; i < 16; i += 2) t = fmaxf(fmaxf(t, S[i]), S[i + 1]);
+#else
+        float t = fmaxf(S.a[0], S.b[0]);
+#pragma unroll
+        for (int i = 1; i < 16; ++i) t = fmaxf(fmaxf(t, S.a[i]), S.b[i]);
+#endif
+        return half_max(t);
     };
 
     constexpr int kStepOutstanding = INFLIGHT * 2;
@@ -482,7 +484,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
         asm volatile("" : "+v"(l));
         const int lq = l & 31, hl = l >> 5;
         const RowCtx qrc = row_ctx(k, q);
-        const float ltot = half_sum(lsum[0] + lsum[1]);
+        const float ltot = half_sum(lsum);
         const float inv = 1.0f / ltot;
         const int my_row = qrc.rv ? (int)qrc.qidx : -1;            // query row index (b*nq + t)*Hq + h, below 2^31 / D
         if (qrc.rv && hl == 0) k->out.LSE[q.sp * k->out.part_stride_L + qrc.qidx] = m_used * k->scale + __logf(ltot);
@@ -595,82 +597,100 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
 #pragma unroll
             for (int k = 0; k < 16; ++k) Oacc[i][k] = 0.f;
         m_used = -INFINITY;
-        lsum[0] = lsum[1] = 0.f;
+        lsum = 0.f;
         mc = 0.f;
 
         uintx4 kf[NKF];
         shortx8 vf[NVF];
         STile SA, SB;
-        if (!idle) {
-            constexpr int s0 = 0, s1 = 1;        // a piece starts at slot 0
+        uintx4 PA[KT / 16], PB[KT / 16];
+        // the scores of the stage in `slot` of the ring, all fragments loaded here
+        auto scores = [&](int slot, STile& S) {
             uintx4 k0[KB * KS];
 #pragma unroll
-            for (int q = 0; q < KB * KS; ++q) k0[q] = lds_k(s0, q);
+            for (int q = 0; q < KB * KS; ++q) k0[q] = lds_k(slot, q);
 #if HG_WIDE_D == 128
-            mfma_first(SA, k0[0], qf[0]);
+            mfma_first(S, k0[0], qf[0]);
 #pragma unroll
-            for (int q = 1; q < KS; ++q) mfma_acc(SA, k0[q], qf[q]);
-            if (pc.nfull == 0) mask_stage(SA, 0);
-            float t = fmaxf(SA[0], SA[1]);
-#pragma unroll
-            for (int i = 2; i < 16; i += 2) t = fmaxf(fmaxf(t, SA[i]), SA[i + 1]);
+            for (int q = 1; q < KS; ++q) mfma_acc(S, k0[q], qf[q]);
 #else
-            mfma_first(SA.a, k0[0], qf[0]);
-            mfma_first(SA.b, k0[KS], qf[0]);
+            mfma_first(S.a, k0[0], qf[0]);
+            mfma_first(S.b, k0[KS], qf[0]);
 #pragma unroll
             for (int q = 1; q < KS; ++q) {
-                mfma_acc(SA.a, k0[q], qf[q]);
-                mfma_acc(SA.b, k0[KS + q], qf[q]);
+                mfma_acc(S.a, k0[q], qf[q]);
+                mfma_acc(S.b, k0[KS + q], qf[q]);
             }
-            if (pc.nfull == 0) mask_stage(SA, 0);
-            float t = fmaxf(SA.a[0], SA.b[0]);
-#pragma unroll
-            for (int i = 1; i < 16; ++i) t = fmaxf(fmaxf(t, SA.a[i]), SA.b[i]);
 #endif
-            maybe_rescale(half_max(t));
-            // K fragments of the first half of stage 1, V fragments of the first half of stage 0 (what a step expects)
+        };
+        if (!idle) {
+            // what the first step expects (a piece starts at slot 0): weights of stage 0, scores of stage 1, V fragments of the first half of stage 0
+            scores(0, SB);
+            scores(1, SA);
+            if (pc.nfull == 0) mask_stage(SB, 0);
+            // (a row with nothing but -inf so far keeps a finite maximum, against which any finite score's weight is infinite: see add_sum)
+            m_used = fmaxf(tile_max(SB), -3.4028234e38f);
+            mc = m_used * c2;
+            lsum = weights(SB, PA);
 #pragma unroll
-            for (int q = 0; q < NKF; ++q) kf[q] = lds_k(s1, q);
-#pragma unroll
-            for (int i = 0; i < NVF; ++i) vf[i] = lds_v(s0, i / DB, i % DB);
+            for (int i = 0; i < NVF; ++i) vf[i] = lds_v(0, i / DB, i % DB);
         }
         HG_TP(piece_no, 1);
         HG_TC_BEGIN();
 
-        // One pipeline step.  On entry: Scur = scores of stage j, kf = K fragments 0..3 of stage j+1, vf = V fragments
-        // of keys 0..15 of stage j.  On exit the same with j+1, Snext = scores of stage j+1 (of whatever follows in
-        // the ring when j is the piece's last stage: those scores are dropped).  The step's copy goes into the slot
-        // whose stage was consumed in the step before.  slot = (g0 + j) % NS.
-        // `plain` steps (the groups of NS) score full stages only and never reach the end of a piece: no mask, no
+        // One pipeline step.  On entry: pb = weights of stage j, Scur = scores of stage j+1, vf = the first half of stage j's V
+        // fragments.  On exit the same with j+1: pn = weights of stage j+1, Snext = scores of stage j+2 (of whatever follows in
+        // the ring when there are no such stages in the piece).  The step's copy goes into the slot
+        // whose stage was consumed in the step before.  slot = (g0 + j) % NS.  Returns this lane's sum of the new weights.
+        // `plain` steps (the groups of NS) take the weights of full stages only and never reach the end of a piece: no mask, no
         // clearing, no look-up of a piece, no branch that would let the compiler move work out of its gap.
         // The body of a step is one basic block (a branch inside it lets the compiler move work out of its gap): the
-        // steps outside the groups of NS apply the mask to every stage they score (it changes nothing on a full one).
-        auto step_body = [&](int j, int slot, STile& Scur, STile& Snext, auto masked) -> float {
+        // steps outside the groups of NS apply the mask to every stage whose weights they take (it changes nothing on a full one; a
+        // stage behind the piece's last gets weights of zero).
+        auto step_body = [&](int j, int slot, const uintx4 (&pb)[KT / 16], uintx4 (&pn)[KT / 16], STile& Scur, STile& Snext, auto masked) -> float {
             constexpr bool kMasked = decltype(masked)::value;
-            uintx4 pb[KT / 16];
-            float tmax;
+            float ssum;
             const int slot1 = (slot + 1) & (NS - 1), slot2 = (slot + 2) & (NS - 1);
 #if HG_WIDE_D == 128
 #include "prefix_wide_step.inc"
 #else
 #include "prefix_wide_step_d64.inc"
 #endif
-            return tmax;
+            return ssum;
+        };
+        // The weights just taken are not too large for what they are summed with, or infinite, as long as their sum (at least as large as the
+        // largest of them) is small.  Otherwise the stage's scores are computed once more (its K rows are still in the ring) and its weights taken
+        // against the larger maximum; nothing has been multiplied with them yet.  (Exact: the stale maximum cancels in O/l and LSE.)
+        auto add_sum = [&](int j, int slot, float ssum, uintx4 (&pn)[KT / 16], auto masked) {
+            if (__builtin_expect(__any(!(ssum <= kMostWeight)), 0)) {
+                STile S;
+                scores((slot + 1) & (NS - 1), S);
+                if constexpr (decltype(masked)::value) mask_stage(S, j + 1);
+                const float m_new = fmaxf(m_used, tile_max(S));
+                const float alpha = (m_new == m_used) ? 1.0f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
+                m_used = m_new;
+                mc = m_new * c2;
+                lsum *= alpha;
+#pragma unroll
+                for (int i = 0; i < DB; ++i)
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) Oacc[i][k] *= alpha;
+                ssum = weights(S, pn);
+            }
+            lsum += ssum;
         };
         // kind 1: a step of a group of NS that is not the piece's last; 0: a step of the last group.
-        auto step = [&](int j, int slot, STile& Scur, STile& Snext, auto kind) {
-            constexpr int kKind = decltype(kind)::value;
+        auto step = [&](int j, int slot, auto even, auto kind) {
+            constexpr bool kPlain = decltype(kind)::value == 1, kEven = decltype(even)::value;
+            STile &Scur = kEven ? SA : SB, &Snext = kEven ? SB : SA;
+            uintx4 (&pb)[KT / 16] = kEven ? PA : PB, (&pn)[KT / 16] = kEven ? PB : PA;
+            typedef std::integral_constant<bool, !kPlain> Masked;
             __builtin_amdgcn_s_waitcnt(kStepWait);    // own copies of the next two stages have landed
             __builtin_amdgcn_s_barrier();             // ... everyone's, and everyone has finished the step before
-            if (kKind == 1) {
-                maybe_rescale(step_body(j, slot, Scur, Snext, std::false_type{}));
-                cursor_step();
-            } else {
-                if (j == zstep) clear_partial_v();
-                const float tmax = step_body(j, slot, Scur, Snext, std::true_type{});
-                if (j + 1 < pc.nst) maybe_rescale(tmax);
-                cursor_advance();
-            }
+            if (!kPlain && j == zstep) clear_partial_v();
+            add_sum(j, slot, step_body(j, slot, pb, pn, Scur, Snext, Masked{}), pn, Masked{});
+            if (kPlain) cursor_step();
+            else cursor_advance();
         };
 
         if (idle) {
@@ -691,8 +711,8 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
             for (; j + NS < pc.nfull; j += NS) {
 #pragma unroll
                 for (int u = 0; u < NS; u += 2) {
-                    step(j + u, u, SA, SB, std::integral_constant<int, 1>{});
-                    step(j + u + 1, u + 1, SB, SA, std::integral_constant<int, 1>{});
+                    step(j + u, u, std::true_type{}, std::integral_constant<int, 1>{});
+                    step(j + u + 1, u + 1, std::false_type{}, std::integral_constant<int, 1>{});
                 }
             }
             // The rest of the piece (1 .. NS + 1 steps: its last group, and one step more when the stage after a complete
@@ -704,8 +724,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
                 constexpr int u = decltype(uc)::value;
                 if constexpr (u < NS + 1) {
                     if (u < rest) {
-                        if constexpr (u % 2 == 0) step(j + u, u & (NS - 1), SA, SB, std::integral_constant<int, 0>{});
-                        else step(j + u, u & (NS - 1), SB, SA, std::integral_constant<int, 0>{});
+                        step(j + u, u & (NS - 1), std::integral_constant<bool, u % 2 == 0>{}, std::integral_constant<int, 0>{});
                         self(self, std::integral_constant<int, u + 1>{});
                     }
                 }

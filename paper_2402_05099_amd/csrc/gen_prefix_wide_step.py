@@ -5,7 +5,7 @@
 Step j is 16 MFMAs in a fixed order: the first half of P*V of stage j (4), the scores of stage j + 2 (8), the second half of P*V
 (4); a stage is 32 keys at D = 128 and 64 keys, two score tiles, at D = 64.  Between them go, in fixed places: the step's vector-ALU
 work on stage j + 1, whose scores the step before has left (exponentials, packing to bf16, fp32 row sums), its two
-HBM->LDS copy instructions (addressed by the kernel's copy cursor `cur`, which runs NS-1 stages ahead of the piece
+HBM->LDS copy instructions (addressed by the kernel's copy cursor `cur`, which runs AHEAD stages ahead of the piece
 `pc` being computed) and its 24 LDS fragment reads.  Every gap ends in a scheduling barrier so that the compiler keeps
 this order: a wavefront then always has a matrix instruction in flight while it issues vector-ALU instructions,
 instead of running the two kinds back to back.  The exponentials need no result of their own step and their own step needs
@@ -51,10 +51,10 @@ def build(D=128, CAP=None):
         mf.append([f"{f}({nxt_t[tile]}, kf[{q & 3}], qf[{ks}]);", [], [f"kf[{q}] = lds_k(slot2, {q + 4});" if q < 4 else v_load(q, "slot")]])
     for i in range(4, 8):        # gaps 12 .. 15; first half of the V fragments of stage j+1, for the next step
         mf.append([value(i), [], [v_load(i - 4, "slot1")]])
-    # the copy that keeps the ring NS-1 stages ahead (the copy cursor may already be in a later piece): scalar address
+    # the copy that keeps the ring AHEAD stages ahead (the copy cursor may already be in a later piece): scalar address
     # arithmetic in gap 0, the two copy instructions in gaps 1 and 3
     mf[0][1].extend(["const int64_t cp_off = (int64_t)min(cur.ks + cur.t * KT, cur.kwin) * rstride_b;",
-                     "const unsigned cp_dst = ldsw + (unsigned)((slot + NS - 1) & (NS - 1)) * STB;"])
+                     "const unsigned cp_dst = ldsw + (unsigned)((slot + AHEAD) & (NS - 1)) * STB;"])
     mf[1][1].append("copy16(cur.Kg + cp_off, cur.voffK, cp_dst);")
     mf[3][1].append("copy16(cur.Vg + cp_off, cur.voffV, cp_dst + VRING);")
 

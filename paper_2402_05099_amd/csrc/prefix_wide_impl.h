@@ -17,8 +17,9 @@
 //     tail round.  A column that is cut by a range boundary yields several partial results (part index = piece
 //     index inside the column); the workgroup that finishes a column marks the unused parts empty.
 //   * Ring of 8 stages (K and V, 16 KiB together) in 128 KiB of dynamic LDS, filled by direct HBM->LDS copies that
-//     are issued from inline asm and waited for with counted s_waitcnt vmcnt: four stages are in flight while
-//     one is consumed.
+//     are issued from inline asm and waited for with counted s_waitcnt vmcnt: two to four stages are in flight while
+//     two are consumed.  The wavefronts meet once in two steps (in every step, with seven stages ahead instead of six, before: where the shared block
+//     has 8 CUs per XCD and the clock is high, 1024 x 40 heads, 16K keys 764 -> 748 us; 1024 x 8/1, 16K keys 81.5 -> 80.7; calls at the power limit equal).
 //   * Software pipeline over stages, written out by gen_prefix_wide_step.py: in one step the scores of stage j+2 are
 //     produced, the weights of stage j+1 are taken and the P*V product of stage j runs; fragments are loaded
 //     from LDS four MFMAs before their use; the vector-ALU work is spread evenly over the gaps between the MFMAs.  At D = 64 a
@@ -59,7 +60,8 @@ constexpr int VRING = NS * STB;         // byte offset of the V ring
 constexpr int LDS_RING_BYTES = 2 * NS * STB;        // 128 KiB
 constexpr int kStageBytes = 32 * 32 * 4;              // staging area of one wavefront for its results: 32 columns of its 32 rows, fp32
 constexpr int LDS_BYTES = LDS_RING_BYTES + NW * kStageBytes;   // 160 KiB, all of a CU's LDS
-constexpr int INFLIGHT = 4;             // stages that may still be in flight at a step's barrier
+constexpr int AHEAD = NS - 2;           // stages that the copies run ahead of the steps
+constexpr int INFLIGHT = AHEAD - 4;     // stages that may still be in flight at a barrier (one before every second step)
 constexpr float kMostWeight = 65536.f;  // largest sum of a lane's weights of one stage that is left as it is
 static_assert(KT == NW * RPI, "one copy instruction per wavefront, stage and tensor");
 static_assert(kPrefixRowsWide == 32 * NW, "one 32-row query block per wavefront");
@@ -222,7 +224,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
 
     // ---- HBM -> LDS copies -----------------------------------------------------------------------------------------
     // The ring is one stream of stages across all of this workgroup's pieces: global stage g lives in slot g % NS, and
-    // the copy side (the cursor below) stays NS-1 stages ahead of the compute side, also across a piece boundary, so
+    // the copy side (the cursor below) stays AHEAD stages ahead of the compute side, also across a piece boundary, so
     // that a piece after the first finds its first stages in LDS already.  Stage t of a piece holds keys
     // [k0c, k0c + 32) with k0c = min(ks + 32 t, kwin): a stage that is partial or past the range re-reads the last 32
     // rows of the range, so every stage is copied by the same uniform instruction (wavefront w copies rows 4w .. 4w+3,
@@ -379,7 +381,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     constexpr int kStoresPerPiece = D / 8 + 1;     // result stores of a wavefront whose 32 rows all exist: 16 of O, 1 of LSE
     enum { kQFirst = 0, kQAfterStores = 1, kQDrain = 2 };
     auto wait_q = [&](int kind) {
-        constexpr int kFirst = (NS - 3) * 2;       // kernel start: two stages, Q, then NS-3 stages more, which may stay in flight
+        constexpr int kFirst = (AHEAD - 2) * 2;       // kernel start: two stages, Q, then AHEAD-2 stages more, which may stay in flight
         if (kind == kQFirst) __builtin_amdgcn_s_waitcnt(0x0F70 | (kFirst & 15) | ((kFirst >> 4) << 14));
         else if (kind == kQAfterStores) __builtin_amdgcn_s_waitcnt(0x0F70 | (kStoresPerPiece & 15) | ((kStoresPerPiece >> 4) << 14));
         else __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -539,7 +541,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     }
     int qkind = kQFirst;
 #pragma unroll
-    for (int s = 2; s < NS - 1; ++s) issue_stage(s);
+    for (int s = 2; s < AHEAD; ++s) issue_stage(s);
     int piece_no = 0;
 
     for (;;) {
@@ -613,6 +615,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
             mfma_first(S, k0[0], qf[0]);
 #pragma unroll
             for (int q = 1; q < KS; ++q) mfma_acc(S, k0[q], qf[q]);
+            __builtin_amdgcn_sched_barrier(0);      // (what follows does not fit the registers beside the fragments)
 #else
             mfma_first(S.a, k0[0], qf[0]);
             mfma_first(S.b, k0[KS], qf[0]);
@@ -641,7 +644,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
         // One pipeline step.  On entry: pb = weights of stage j, Scur = scores of stage j+1, vf = the first half of stage j's V
         // fragments.  On exit the same with j+1: pn = weights of stage j+1, Snext = scores of stage j+2 (of whatever follows in
         // the ring when there are no such stages in the piece).  The step's copy goes into the slot
-        // whose stage was consumed in the step before.  slot = (g0 + j) % NS.  Returns this lane's sum of the new weights.
+        // whose stage was consumed two steps before.  slot = (g0 + j) % NS.  Returns this lane's sum of the new weights.
         // `plain` steps (the groups of NS) take the weights of full stages only and never reach the end of a piece: no mask, no
         // clearing, no look-up of a piece, no branch that would let the compiler move work out of its gap.
         // The body of a step is one basic block (a branch inside it lets the compiler move work out of its gap): the
@@ -672,9 +675,10 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
                 mc = m_new * c2;
                 lsum *= alpha;
 #pragma unroll
-                for (int i = 0; i < DB; ++i)
-#pragma unroll
-                    for (int k = 0; k < 16; ++k) Oacc[i][k] *= alpha;
+                for (int i = 0; i < DB; ++i) {
+                    Oacc[i] *= alpha;
+                    __builtin_amdgcn_sched_barrier(0);      // (block by block: all in flight at once do not fit the registers)
+                }
                 ssum = weights(S, pn);
             }
             lsum += ssum;
@@ -685,8 +689,12 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
             STile &Scur = kEven ? SA : SB, &Snext = kEven ? SB : SA;
             uintx4 (&pb)[KT / 16] = kEven ? PA : PB, (&pn)[KT / 16] = kEven ? PB : PA;
             typedef std::integral_constant<bool, !kPlain> Masked;
-            __builtin_amdgcn_s_waitcnt(kStepWait);    // own copies of the next two stages have landed
-            __builtin_amdgcn_s_barrier();             // ... everyone's, and everyone has finished the step before
+            if constexpr (kEven) {                        // (a piece starts at slot 0: even steps are those at even slots)
+                __builtin_amdgcn_s_waitcnt(kStepWait);    // own copies of the next three stages have landed
+                __builtin_amdgcn_s_barrier();             // ... everyone's, and everyone has finished the step before
+            } else {
+                __builtin_amdgcn_sched_barrier(0);
+            }
             if (!kPlain && j == zstep) clear_partial_v();
             add_sum(j, slot, step_body(j, slot, pb, pn, Scur, Snext, Masked{}), pn, Masked{});
             if (kPlain) cursor_step();
@@ -697,10 +705,12 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
             // nothing to multiply (blocks of <= 224 rows): this wavefront keeps its share of the copies going and meets
             // the others at every barrier
             for (int j = 0; j < pc.nst; ++j) {
-                __builtin_amdgcn_s_waitcnt(kStepWait);
-                __builtin_amdgcn_s_barrier();
+                if (j % 2 == 0) {
+                    __builtin_amdgcn_s_waitcnt(kStepWait);
+                    __builtin_amdgcn_s_barrier();
+                }
                 if (j == zstep) clear_partial_v();
-                issue_stage((j + NS - 1) & (NS - 1));
+                issue_stage((j + AHEAD) & (NS - 1));
             }
         } else {
             // Whole groups of NS steps at compile-time slots (a piece starts at slot 0: the stream pads every piece to
@@ -733,8 +743,8 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
         }
         // ... and its padding: steps that only keep the stream going (the slots of the padding stay unused)
         for (int j = pc.nst; j & (NS - 1); ++j) {
-            __builtin_amdgcn_s_barrier();
-            issue_stage((j + NS - 1) & (NS - 1));
+            if (j % 2 == 0) __builtin_amdgcn_s_barrier();
+            issue_stage((j + AHEAD) & (NS - 1));
         }
         HG_TC_END(piece_no);
         HG_TP(piece_no, 2);

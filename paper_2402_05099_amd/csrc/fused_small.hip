@@ -177,9 +177,13 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
     // 59.8 -> 33.6 us; 34 x 40/10, 10.5K keys, paged 50.3 -> 28.4; 56 x 24/12, 8574 keys, codes 45.9 -> 30.1.  The others, which had
     // an order of their own to the same end: 1.005 in the mean over 117 calls.
     int kvh, tile, split;
-    // (loaded at once with the rest, not behind the way out or where they are first used)
+    // (loaded at once with the rest, not behind the way out or where they are first used: the first K rows are requested after one wait for
+    // arguments, before after three, the second of them for lines that no cache held.  4 x 4 heads, D = 64, 128 keys 5.5 -> 5.0 us; 119 x 64/8, D = 64, 150
+    // keys 5.6 -> 5.1; 256 x 8/1, D = 128, 1K keys, where the rows' way into the CU sets the time, 11.24 -> 11.14; 100 drawn calls 1.016 in the mean.  Keys
+    // requested before the queries: D = 64 as fast, D = 128 slower by 2 %, the queries then come behind eight wavefronts' rows.)
     asm volatile("" ::"s"(a.nq), "s"(a.G), "s"(a.B), "s"(a.Q), "s"(a.lengths), "s"(a.offsets), "s"(a.by_seq.mul), "s"(a.by_group.mul), "s"(a.n_levels));
-    asm volatile("" ::"s"(a.lv[0].K), "s"(a.lv[0].V), "s"(a.lv[0].seq_off), "s"(a.lv[0].max_rows));
+    asm volatile("" ::"s"(a.lv[0].K), "s"(a.lv[0].V), "s"(a.lv[0].seq_off), "s"(a.lv[0].max_rows), "s"(a.Ks), "s"(a.Vs), "s"(a.max_len), "s"(a.dealt), "s"(a.c2));
+    if constexpr (PAGED) asm volatile("" ::"s"(a.pg.table), "s"(a.pg.shift), "s"(a.pg.stride), "s"(a.pg.n_pages));
     if (!small_work(blockIdx.x, a.tiles, a.splits, a.Hkv, a.by_head, a.by_split, kvh, tile, split)) return;
     const int col = kvh * a.tiles + tile;
     const int rps = a.nq * a.G;                     // query rows of one sequence for this KV head
@@ -363,13 +367,26 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
     Seg cs{};
     int ct = 0, base = 0;                           // current stage of segment cs; shared stages before cs
     bool requested = false;
-    while (next_shared(walk, cs)) {
-        if (a.dealt && base + cs.nst > run) {
-            requested = true;
-            break;
-        }
+    auto reached = [&]() -> bool {                  // segment cs holds this wavefront's first stage (dealt out); else it is passed over
+        if (a.dealt && base + cs.nst > run) return true;
         base += cs.nst;
+        return false;
+    };
+    // (the only block of a first level without a list of blocks, which is most calls' only shared block, from arguments that are there already)
+    if (a.n_levels > 0 && a.lv[0].seq_off == nullptr) {
+        cs.K = reinterpret_cast<const unsigned char*>(a.lv[0].K + (int64_t)kvh * D);
+        cs.V = reinterpret_cast<const unsigned char*>(a.lv[0].V + (int64_t)kvh * D);
+        cs.ks = 0;
+        cs.ke = a.lv[0].max_rows;
+        cs.rlo = 0;
+        cs.rhi = min((b1 + 1) * rps - r0, TR);
+        cs.vis_base = 0x3fffffff;
+        cs.sfx = -1;
+        cs.nst = (cs.ke + KT - 1) / KT;
+        walk.level = 1;
+        requested = reached();
     }
+    while (!requested && next_shared(walk, cs)) requested = reached();
     int shared_total = base;
     if (requested) {
         ct = run - base;

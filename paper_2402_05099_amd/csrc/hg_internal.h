@@ -219,7 +219,7 @@ __host__ __device__ inline bool small_work(unsigned id, int tiles, int splits, i
     return true;
 }
 struct SmallArgs {
-    // what a wavefront needs before its first request, side by side: the kernel starts by reading it
+    // Everything but the further levels lies side by side: a wavefront reads it at its start with loads that wait for each other nowhere.
     const uint16_t* Q;
     const int32_t* lengths;   // null: no suffix
     const int32_t* offsets;
@@ -231,10 +231,11 @@ struct SmallArgs {
     int dealt;                // stages go to the wavefronts one by one (else in runs)
     int n_levels;
     int max_len;
-    LevelDev lv[HG_MAX_LEVELS];
     const uint16_t* Ks;
     const uint16_t* Vs;
     PagedDev pg;              // suffix read through a page table when pg.table != null
+    float c2, tau_raw;        // scale * log2(e); by how much a raw score may pass the maximum before sums are rescaled (set by launch_fused_small)
+    LevelDev lv[HG_MAX_LEVELS];
     int fp8;                  // suffix rows are E4M3 codes: value = code * scale
     float k_scale, v_scale;
     int fp32_weights;         // the weights of codes are not rounded to bf16
@@ -244,7 +245,6 @@ struct SmallArgs {
     float* part;              // splits > 1: partial results (small_part_floats)
     unsigned* arrivals;       // splits > 1: [cols] counters that only ever count to `splits`, zero between calls
     float scale;
-    float c2, tau_raw;        // scale * log2(e); by how much a raw score may pass the maximum before sums are rescaled (set by launch_fused_small)
     void* O;                  // final results: [B, nq, Hq, D] bf16 or fp32, LSE [B, nq, Hq] (may be null)
     float* LSE;
     int bf16;

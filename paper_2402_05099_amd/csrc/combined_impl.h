@@ -334,11 +334,7 @@ struct SuffixStream {
                 if (cb.left > 0) {
                     if (cb.unit < 0) {
 #pragma unroll
-                        for (int j = 0; j < QW; ++j) {
-                            st.qp[0][j] = cb.q[j];
-                            st.q[0][2 * j] = bf16_lo(cb.q[j]) * st.qs;
-                            st.q[0][2 * j + 1] = bf16_hi(cb.q[j]) * st.qs;
-                        }
+                        for (int j = 0; j < QW; ++j) st.qp[0][j] = cb.q[j];
                         st.m[0] = -INFINITY;
                         st.l[0] = 0.f;
 #pragma unroll
@@ -376,15 +372,17 @@ struct SuffixStream {
     }
 
     __device__ __forceinline__ void keep(const DecodeState<D, 1, EPL>& st, int unit) {
-        float M, l, o[EPL];
+        constexpr int N = EPL / 4;
+        float M, l, o[N];
         decode_combine<D, 1, EPL>(st, 0, M, l, o);
-        if (lane < LPR) {
-            unsigned char* const p = kept_row(n_kept);
-            const float inv = l > 0.f ? (FP8 ? a.v_scale / l : 1.0f / l) : 0.f;
-#pragma unroll
-            for (int j = 0; j < EPL; j += 4) *reinterpret_cast<float4*>(p + (lane * EPL + j) * 4) = make_float4(o[j] * inv, o[j + 1] * inv, o[j + 2] * inv, o[j + 3] * inv);
-            if (lane == 0) *reinterpret_cast<float2*>(p + D * 4) = make_float2(l > 0.f ? (M + __log2f(l)) * kLn2 : -INFINITY, __builtin_bit_cast(float, unit));
+        unsigned char* const p = kept_row(n_kept);
+        const float inv = l > 0.f ? (FP8 ? a.v_scale / l : 1.0f / l) : 0.f;
+        if (LPR == 16 || !(lane & 8)) {
+            float* const op = reinterpret_cast<float*>(p) + combined_col<D, EPL>(lane);
+            if constexpr (N == 4) *reinterpret_cast<float4*>(op) = make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+            else *reinterpret_cast<float2*>(op) = make_float2(o[0] * inv, o[1] * inv);
         }
+        if (lane == 0) *reinterpret_cast<float2*>(p + D * 4) = make_float2(l > 0.f ? (M + __log2f(l)) * kLn2 : -INFINITY, __builtin_bit_cast(float, unit));
         n_kept = __builtin_amdgcn_readfirstlane(n_kept + 1);
     }
 

@@ -37,38 +37,33 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a) {
     DecodeState<D, GT, EPL> st;
     {
         constexpr int LPR = D / EPL;
-        const float qs = FP8 ? a.scale * kLog2e * a.k_scale : a.scale * kLog2e;
         const int col = (lane % LPR) * EPL;
 #pragma unroll
         for (int g = 0; g < GT; ++g) {
 #pragma unroll
             for (int h8 = 0; h8 < EPL / 8; ++h8) {
                 const uint4 qv = *reinterpret_cast<const uint4*>(a.Q + ((int64_t)bq * a.Hq + h0 + g) * D + col + 8 * h8);
-                float* const q = &st.q[g][8 * h8];
                 st.qp[g][4 * h8] = qv.x; st.qp[g][4 * h8 + 1] = qv.y; st.qp[g][4 * h8 + 2] = qv.z; st.qp[g][4 * h8 + 3] = qv.w;
-                q[0] = bf16_lo(qv.x) * qs; q[1] = bf16_hi(qv.x) * qs;
-                q[2] = bf16_lo(qv.y) * qs; q[3] = bf16_hi(qv.y) * qs;
-                q[4] = bf16_lo(qv.z) * qs; q[5] = bf16_hi(qv.z) * qs;
-                q[6] = bf16_lo(qv.w) * qs; q[7] = bf16_hi(qv.w) * qs;
             }
             st.m[g] = -INFINITY;
             st.l[g] = 0.f;
 #pragma unroll
             for (int j = 0; j < EPL; ++j) st.acc[g][j] = 0.f;
         }
-        st.qs = qs;
+        st.qs = FP8 ? a.scale * kLog2e * a.k_scale : a.scale * kLog2e;
     }
 
     // walk the concatenated key list (shared blocks root first, then the suffix), clipped to this chunk
     const int64_t lo = (int64_t)c * a.chunk, hi = lo + a.chunk;
     int64_t pos = 0;
-    for (int li = 0; SHARED && li < a.n_levels; ++li) {
-        int begin, count;
-        block_of(a.lv[li], b, a.B, begin, count);
-        const int64_t s0 = max(lo, pos), s1 = min(hi, pos + count);
-        if (s0 < s1) decode_span<D, GT, false, false, EPL>(st, a.lv[li].K, a.lv[li].V, begin + (s0 - pos), (int)(s1 - s0), a.Hkv, kvh, lane);
-        pos += count;
-    }
+    if constexpr (SHARED)
+        for (int li = 0; li < a.n_levels; ++li) {
+            int begin, count;
+            block_of(a.lv[li], b, a.B, begin, count);
+            const int64_t s0 = max(lo, pos), s1 = min(hi, pos + count);
+            if (s0 < s1) decode_span<D, GT, false, false, EPL>(st, a.lv[li].K, a.lv[li].V, begin + (s0 - pos), (int)(s1 - s0), a.Hkv, kvh, lane);
+            pos += count;
+        }
     if (a.lengths) {
         // the nq queries of a sequence are its last nq suffix tokens: query t does not see the later ones
         int count = min(a.lengths[b], a.max_len) - (a.nq - 1 - tq);

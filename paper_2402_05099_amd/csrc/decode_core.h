@@ -35,13 +35,10 @@ __device__ __forceinline__ const unsigned char* uniform_ptr(const unsigned char*
 template <int D, int GT, bool FP8>
 constexpr int epl_of() { return (FP8 && D == 128 && GT <= 2) ? 16 : 8; }
 
-// bf16 rows are multiplied two elements at a time with v_dot2_f32_bf16 (products of bf16 values are exact in fp32, the
-// sums are taken in fp32): a score is four such instructions on the packed words of K and Q as they come from memory,
-// and the value sums take the rounded weights of two keys against those keys' values of one column.  Set to 0 to fall
-// back to unpacking every element to fp32 first (four times the instructions for the scores, twice for the values).
-#ifndef HG_DECODE_DOT2
-#define HG_DECODE_DOT2 1
-#endif
+// Rows are multiplied two elements at a time with v_dot2_f32_bf16 (products of bf16 values are exact in fp32, the
+// sums are taken in fp32): the score of a bf16 row is four such instructions on the packed words of K and Q as they come from memory
+// (codes are expanded to packed bf16 values first, exactly, two to an instruction), and the value sums of bf16 rows take the rounded weights of two
+// keys against those keys' values of one column.  The values of codes are multiplied with fp32 weights.
 typedef __bf16 bf16pair __attribute__((ext_vector_type(2)));
 typedef float f32pair __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned pack_pair_bf16(float lo, float hi) {      // v_cvt_pk_bf16_f32, round to nearest even
@@ -52,12 +49,13 @@ __device__ __forceinline__ float dot2_bf16(unsigned a, unsigned b, float c) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16pair, a), __builtin_bit_cast(bf16pair, b), c, false);
 }
 
+constexpr float kLazy = 8.f;      // log2 units
+
 template <int D, int GT, int EPL = 8>
 struct DecodeState {
-    float q[GT][EPL];    // query elements of this lane's column slice, pre-multiplied by scale*log2(e)
-    unsigned qp[GT][EPL / 2];   // the same elements as packed bf16 pairs, unscaled (bf16 rows with HG_DECODE_DOT2)
-    float qs;            // scale*log2(e), applied to a score after its sum (same case)
-    float m[GT];         // running max (log2 domain)
+    unsigned qp[GT][EPL / 2];   // query elements of this lane's column slice, packed bf16 pairs
+    float qs;            // scale*log2(e) (codes: times their K scale), applied to a score after its sum
+    float m[GT];         // running max (log2 domain); codes: a score that no score has passed by more than kLazy
     float l[GT];         // running sum of 2^(s-m)
     float acc[GT][EPL];  // running sum of 2^(s-m) * v
 };
@@ -115,6 +113,18 @@ __device__ __forceinline__ void unpack8(const uint2& r, float (&f)[8]) {
     f[0] = a.x; f[1] = a.y; f[2] = b.x; f[3] = b.y; f[4] = c.x; f[5] = c.y; f[6] = d.x; f[7] = d.y;
 }
 
+// this lane's elements of a row as packed bf16 pairs
+__device__ __forceinline__ void pairs_of(const uint4& r, unsigned (&p)[4]) { p[0] = r.x; p[1] = r.y; p[2] = r.z; p[3] = r.w; }
+template <int N, class Row>
+__device__ __forceinline__ void pairs_of_codes(const Row& r, unsigned (&p)[N]) {
+    const unsigned* const w = reinterpret_cast<const unsigned*>(&r);
+#pragma unroll
+    for (int j = 0; j < N / 2; ++j) {
+        p[2 * j] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[j], 1.0f, false));
+        p[2 * j + 1] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[j], 1.0f, true));
+    }
+}
+
 // kb/vb: wavefront-uniform byte pointers to the span's first row of this KV head; rowoff: this lane's byte offset
 // of its key in load 0 of the batch (sub-row, column slice and batch start); colb: the column part alone.  Lanes
 // whose key lies past the span read the span's first row instead (always valid; their score is masked), so no
@@ -142,26 +152,19 @@ __device__ __forceinline__ void consume_batch(DecodeState<D, GT, EPL>& st, const
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const bool ok = first + u * KPW < n;
-        if constexpr (!FP8 && HG_DECODE_DOT2) {
-            const unsigned kw[4] = {bt.k[u].x, bt.k[u].y, bt.k[u].z, bt.k[u].w};
+        unsigned kw[EPL / 2];
+        if constexpr (FP8) pairs_of_codes(bt.k[u], kw);
+        else pairs_of(bt.k[u], kw);
 #pragma unroll
-            for (int g = 0; g < GT; ++g) {
-                const float d0 = dot2_bf16(kw[2], st.qp[g][2], dot2_bf16(kw[0], st.qp[g][0], 0.f));     // two chains of two
-                const float d1 = dot2_bf16(kw[3], st.qp[g][3], dot2_bf16(kw[1], st.qp[g][1], 0.f));
-                const float d = row_allreduce_sum<LPR>(d0 + d1) * st.qs;
-                s[u][g] = ok ? d : -INFINITY;
+        for (int g = 0; g < GT; ++g) {
+            float d0 = 0.f, d1 = 0.f;       // two chains
+#pragma unroll
+            for (int j = 0; j < EPL / 2; j += 2) {
+                d0 = dot2_bf16(kw[j], st.qp[g][j], d0);
+                d1 = dot2_bf16(kw[j + 1], st.qp[g][j + 1], d1);
             }
-        } else {
-            float k[EPL];
-            unpack8(bt.k[u], k);
-#pragma unroll
-            for (int g = 0; g < GT; ++g) {
-                float d = st.q[g][0] * k[0];
-#pragma unroll
-                for (int j = 1; j < EPL; ++j) d = fmaf(st.q[g][j], k[j], d);
-                d = row_allreduce_sum<LPR>(d);
-                s[u][g] = ok ? d : -INFINITY;
-            }
+            const float d = row_allreduce_sum<LPR>(d0 + d1) * st.qs;
+            s[u][g] = ok ? d : -INFINITY;
         }
     }
 #pragma unroll
@@ -169,9 +172,19 @@ __device__ __forceinline__ void consume_batch(DecodeState<D, GT, EPL>& st, const
         float mx = st.m[g];
 #pragma unroll
         for (int u = 0; u < U; ++u) mx = fmaxf(mx, s[u][g]);
-        const float ms = (mx == -INFINITY) ? 0.f : mx;
-        const float alpha = __builtin_amdgcn_exp2f(st.m[g] - ms);
-        st.m[g] = mx;
+        // (fp32 weights lose nothing when the largest is not 1: sums are rescaled only when a score passes the maximum by kLazy.  bf16
+        // weights do: the largest would be rounded)
+        float alpha = 1.0f;
+        if (!FP8 || __any(mx > st.m[g] + kLazy)) {
+            alpha = __builtin_amdgcn_exp2f(st.m[g] - ((mx == -INFINITY) ? 0.f : mx));
+            st.m[g] = mx;
+            if constexpr (FP8) {
+                st.l[g] *= alpha;
+#pragma unroll
+                for (int j = 0; j < EPL; ++j) st.acc[g][j] *= alpha;
+            }
+        }
+        const float ms = (st.m[g] == -INFINITY) ? 0.f : st.m[g];
         float p[U];
         float ps = 0.f;
 #pragma unroll
@@ -179,10 +192,14 @@ __device__ __forceinline__ void consume_batch(DecodeState<D, GT, EPL>& st, const
             p[u] = __builtin_amdgcn_exp2f(s[u][g] - ms);
             ps += p[u];
         }
-        st.l[g] = fmaf(st.l[g], alpha, ps);
+        if constexpr (FP8) {
+            st.l[g] += ps;
+        } else {
+            st.l[g] = fmaf(st.l[g], alpha, ps);
 #pragma unroll
-        for (int j = 0; j < EPL; ++j) st.acc[g][j] *= alpha;
-        if constexpr (!FP8 && HG_DECODE_DOT2) {
+            for (int j = 0; j < EPL; ++j) st.acc[g][j] *= alpha;
+        }
+        if constexpr (!FP8) {
             static_assert(FP8 || U % 2 == 0, "keys are taken in pairs");
             // weights of two keys, rounded to bf16 (as the matrix-core kernels round theirs; the row sum above keeps
             // the unrounded ones), against the two keys' values of one column: v_perm_b32 gathers the column's pair
@@ -326,55 +343,75 @@ __device__ __forceinline__ void block_of(const LevelDev& lv, int b, int B, int& 
     }
 }
 
-// Combines the 64/LPR key sub-streams of the wavefront for query head g: maximum (0 if there is none), sum, and value sums.
+// Combines the 64/LPR key sub-streams of the wavefront for query head g: maximum (0 if there is none) and sum in every lane; of the value
+// sums a lane keeps EPL / 4, those of columns combined_col(lane) and up (with 8 lanes to a row, lanes 8 apart keep the same ones).
+// The lanes that hold parts of a column are 8, 16 and 32 apart: a swap of 32-lane halves (rows of 16 lanes) between two registers and an
+// addition sum two columns at once, each in the half (row) that keeps it, in place of an exchange through LDS for every column (16 columns of
+// codes: 54 exchanges before, 14 swaps and as many additions now).  With scores of codes by dot products (24 -> 16 instructions a key) and sums that are rescaled
+// past kLazy only: 1024 x 40 heads, 4K keys, suffixes of 32..128 codes 226.7 -> 223.6 us, error of O on the suffixes alone 1.17e-7 -> 1.00e-7;
+// bf16 rows, 256 x 40, 2K keys 122.0 -> 121.8, 1024 x 40, 16K keys 470.5 -> 469.7, 2048 x 40, two levels 548.7 -> 549.4.
+template <int D, int EPL>
+__device__ __forceinline__ int combined_col(int lane) {
+    return lane % (D / EPL) * EPL + (lane & 32 ? EPL / 2 : 0) + (lane & 16 ? EPL / 4 : 0);
+}
+template <int LPR, class F>
+__device__ __forceinline__ float over_substreams(float x, F f) {
+    // (the value of the lane 32 or 16 away, picked by lane: taking both results of a swap of a register with itself for the pair is folded away)
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    x = f(x, __builtin_bit_cast(float, threadIdx.x & 32 ? r[0] : r[1]));
+    const auto t = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    x = f(x, __builtin_bit_cast(float, threadIdx.x & 16 ? t[0] : t[1]));
+    if constexpr (LPR == 8) x = f(x, dpp_f32<0x128>(x));      // row_ror:8
+    return x;
+}
 template <int D, int GT, int EPL>
-__device__ __forceinline__ void decode_combine(const DecodeState<D, GT, EPL>& st, int g, float& Ms, float& l, float (&o)[EPL]) {
+__device__ __forceinline__ void decode_combine(const DecodeState<D, GT, EPL>& st, int g, float& Ms, float& l, float (&o)[EPL / 4]) {
     constexpr int LPR = D / EPL;
-    float M = st.m[g];
-#pragma unroll
-    for (int off = LPR; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
+    static_assert(LPR == 8 || LPR == 16, "");
+    const auto sum = [](float a, float b) { return a + b; };
+    const auto bits = [](float v) { return __builtin_bit_cast(unsigned, v); };
+    const auto value = [](unsigned v) { return __builtin_bit_cast(float, v); };
+    const float M = over_substreams<LPR>(st.m[g], [](float a, float b) { return fmaxf(a, b); });
     Ms = (M == -INFINITY) ? 0.f : M;
     const float f = __builtin_amdgcn_exp2f(st.m[g] - Ms);
-    l = st.l[g] * f;
+    l = over_substreams<LPR>(st.l[g] * f, sum);
+    float h[EPL / 2];
 #pragma unroll
-    for (int off = LPR; off < 64; off <<= 1) l += __shfl_xor(l, off);
+    for (int j = 0; j < EPL / 2; ++j) {
+        const auto r = __builtin_amdgcn_permlane32_swap(bits(st.acc[g][j] * f), bits(st.acc[g][j + EPL / 2] * f), false, false);
+        h[j] = value(r[0]) + value(r[1]);
+    }
 #pragma unroll
-    for (int j = 0; j < EPL; ++j) {
-        o[j] = st.acc[g][j] * f;
-#pragma unroll
-        for (int off = LPR; off < 64; off <<= 1) o[j] += __shfl_xor(o[j], off);
+    for (int j = 0; j < EPL / 4; ++j) {
+        const auto r = __builtin_amdgcn_permlane16_swap(bits(h[j]), bits(h[j + EPL / 4]), false, false);
+        o[j] = value(r[0]) + value(r[1]);
+        if constexpr (LPR == 8) o[j] += dpp_f32<0x128>(o[j]);
     }
 }
 
 // Combines the sub-streams and writes (O, LSE) of chunk c.
 template <int D, int GT, bool FP8, int EPL>
 __device__ __forceinline__ void decode_finish(const DecodeState<D, GT, EPL>& st, const DecodeArgs& a, int bq, int h0, int c, int lane) {
-    constexpr int LPR = D / EPL;
+    constexpr int LPR = D / EPL, N = EPL / 4;
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
-        float Ms, l, o[EPL];
+        float Ms, l, o[N];
         decode_combine<D, GT, EPL>(st, g, Ms, l, o);
-        if (lane < LPR) {
-            const float inv = l > 0.f ? (FP8 ? a.v_scale / l : 1.0f / l) : 0.f;
-            const int64_t idx = (int64_t)bq * a.Hq + h0 + g;
-#pragma unroll
-            for (int h8 = 0; h8 < EPL / 8; ++h8) {
-                const int64_t e = (int64_t)c * a.out.part_stride_O + idx * D + lane * EPL + 8 * h8;
-                const float* const oh = &o[8 * h8];
-                if (a.out.bf16) {
-                    uint4 v;
-                    v.x = pack_bf16(oh[0] * inv, oh[1] * inv); v.y = pack_bf16(oh[2] * inv, oh[3] * inv);
-                    v.z = pack_bf16(oh[4] * inv, oh[5] * inv); v.w = pack_bf16(oh[6] * inv, oh[7] * inv);
-                    *reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.out.O) + e) = v;
-                } else {
-                    float* op = static_cast<float*>(a.out.O) + e;
-                    *reinterpret_cast<float4*>(op) = make_float4(oh[0] * inv, oh[1] * inv, oh[2] * inv, oh[3] * inv);
-                    *reinterpret_cast<float4*>(op + 4) = make_float4(oh[4] * inv, oh[5] * inv, oh[6] * inv, oh[7] * inv);
-                }
+        const float inv = l > 0.f ? (FP8 ? a.v_scale / l : 1.0f / l) : 0.f;
+        const int64_t idx = (int64_t)bq * a.Hq + h0 + g;
+        if (LPR == 16 || !(lane & 8)) {
+            const int64_t e = (int64_t)c * a.out.part_stride_O + idx * D + combined_col<D, EPL>(lane);
+            if (a.out.bf16) {
+                unsigned* const op = reinterpret_cast<unsigned*>(static_cast<uint16_t*>(a.out.O) + e);
+                if constexpr (N == 4) *reinterpret_cast<uint2*>(op) = make_uint2(pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv));
+                else *op = pack_bf16(o[0] * inv, o[1] * inv);
+            } else {
+                float* const op = static_cast<float*>(a.out.O) + e;
+                if constexpr (N == 4) *reinterpret_cast<float4*>(op) = make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+                else *reinterpret_cast<float2*>(op) = make_float2(o[0] * inv, o[1] * inv);
             }
-            if (lane == 0)
-                a.out.LSE[(int64_t)c * a.out.part_stride_L + idx] = l > 0.f ? (Ms + __log2f(l)) * kLn2 : -INFINITY;
         }
+        if (lane == 0) a.out.LSE[(int64_t)c * a.out.part_stride_L + idx] = l > 0.f ? (Ms + __log2f(l)) * kLn2 : -INFINITY;
     }
 }
 

@@ -302,7 +302,21 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
     auto copies_of = [&](const Seg& s) { return FP8 && s.sfx >= 0 ? CPS8 : CPS; };     // copy instructions per stage and tensor
     // first row of stage t of segment s as it lies in LDS
     auto row0_of = [&](const Seg& s, int t) { return PAGED && s.sfx >= 0 ? t * KT : min(s.ks + t * KT, max(s.ke - KT, 0)); };
-    auto issue = [&](const Seg& s, int t, auto is_v) {      // requests the K (or V) rows of stage t of segment s
+    // Paged suffixes: the table's entries for the two halves of stage t of segment s.  They are looked up when the stage becomes the next one and first
+    // used behind the scores of the one before, so that the look-up lies under those.  (Looked up where the rows are requested, before: 82 x 64/8 heads, 340 keys,
+    // codes 29.5 -> 28.5 us, 298 x 64/8, four queries, 15 x 171 keys, codes 98.3 -> 95.5; 49 drawn paged calls 1.005 in the mean.)
+    struct Pages { int p0, p1; };
+    auto pages_of = [&](const Seg& s, int t) -> Pages {
+        Pages pg{0, 0};
+        if (PAGED && s.sfx >= 0) {
+            const const_i32_ptr table = (const_i32_ptr)(uintptr_t)a.pg.table + (int64_t)(b0 + s.sfx) * a.pg.stride;
+            const int last = a.pg.stride - 1;
+            pg.p0 = table[min((t * KT) >> a.pg.shift, last)];
+            pg.p1 = table[min((t * KT + KT / 2) >> a.pg.shift, last)];
+        }
+        return pg;
+    };
+    auto issue = [&](const Seg& s, int t, const Pages& pg, auto is_v) {      // requests the K (or V) rows of stage t of segment s
         constexpr bool V = decltype(is_v)::value;
         const unsigned dst = (unsigned)__builtin_amdgcn_readfirstlane(ldsb + (V ? (unsigned)STB : 0u));
         const bool codes = FP8 && s.sfx >= 0;
@@ -311,11 +325,10 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
         const unsigned char *base0, *base1;         // of rows 0 .. 15 and 16 .. 31 (both relative to row 0)
         int rowclamp = KT - 1;                      // < 31 only when the range ends before row 32 of the tensor
         if (PAGED && s.sfx >= 0) {
-            const const_i32_ptr table = (const_i32_ptr)(uintptr_t)k->pg.table + (int64_t)(b0 + s.sfx) * k->pg.stride;
-            const int shift = k->pg.shift, mask = (1 << shift) - 1, last = k->pg.stride - 1, n_pages = k->pg.n_pages;
+            const int shift = a.pg.shift, mask = (1 << shift) - 1, n_pages = a.pg.n_pages;
             const int j0 = t * KT, j1 = j0 + KT / 2;
-            const int p0 = min(max(table[min(j0 >> shift, last)], 0), n_pages - 1);
-            const int p1 = min(max(table[min(j1 >> shift, last)], 0), n_pages - 1);
+            const int p0 = min(max(pg.p0, 0), n_pages - 1);
+            const int p1 = min(max(pg.p1, 0), n_pages - 1);
             base0 = scalar_ptr(tensor + (((int64_t)p0 << shift) + (j0 & mask)) * rs);
             base1 = scalar_ptr(tensor + (((int64_t)p1 << shift) + (j1 & mask) - KT / 2) * rs);
         } else {
@@ -390,7 +403,7 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
     int shared_total = base;
     if (requested) {
         ct = run - base;
-        issue(cs, ct, IsK{});
+        issue(cs, ct, Pages{0, 0}, IsK{});
         Walk rest = walk;
         Seg s{};
         shared_total += cs.nst;
@@ -452,7 +465,7 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
     for (int s = 0; s < QN; ++s) asm volatile("" : "+v"(qf[s]));
     // (the first V rows only now: the K rows of eight wavefronts, which the first products wait for, come through the CU's load path by themselves, and
     // the V rows while those are multiplied.  256 x 8/1 heads, 1K keys 11.35 -> 10.95 us, 45 x 16/2, 515 keys 8.60 -> 8.42, 29 drawn calls 1.004.)
-    if (requested) issue(cs, ct, IsV{});
+    if (requested) issue(cs, ct, Pages{0, 0}, IsV{});
     len_v = max(min(len_v, a.max_len), 0);
     const int nst_v = (len_v + KT - 1) / KT;        // stages of the suffix of sequence b0 + l
     // ... of the suffixes of b0 .. b0 + l: a prefix sum over the TR lanes that can hold a sequence (within rows of 16 lanes, then the first row's total
@@ -502,8 +515,9 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
             next_shared(walk, cs);
         }
         seek(first, cs, ct);
-        issue(cs, ct, IsK{});
-        issue(cs, ct, IsV{});
+        const Pages pg = pages_of(cs, ct);
+        issue(cs, ct, pg, IsK{});
+        issue(cs, ct, pg, IsV{});
     }
 
     // ---- this wavefront's share of the softmax ------------------------------------------------------------------------------
@@ -530,6 +544,7 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
             if (ct + step < cs.nst) nt = ct + step;
             else seek(pos + step, ns, nt);
         }
+        const Pages npg = more ? pages_of(ns, nt) : Pages{0, 0};
         const bool codes = FP8 && cs.sfx >= 0;
         wait_for(copies_of(cs));                    // this stage's K rows are here, its V rows may still be on their way
         // S^T = K Q^T.  Element i: stage row 8 (i / 4) + i % 4 + 4 hl; 16-row columns: 16 (i / 4) + i % 4 + 4 lg
@@ -580,7 +595,7 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
         // are those between a product and a read of its result, which the compiler does not count across a branch.)
         asm volatile("s_nop 11" : "+v"(S));
         asm volatile("" ::: "memory");
-        if (more) issue(ns, nt, IsK{});
+        if (more) issue(ns, nt, npg, IsK{});
         const int key0 = cs.ks + ct * KT;
         const int k0c = row0_of(cs, ct);
         const bool partial = k0c != key0 || cs.ke - k0c < KT;      // some stage rows are not keys of this stage
@@ -701,7 +716,7 @@ __global__ __launch_bounds__(64 * NWS, 2) void fused_small_kernel(SmallArgs a) {
 #pragma unroll
         for (int db = 0; db < VA; ++db) asm volatile("" : "+v"(Oacc[db]));
         asm volatile("s_nop 11" ::: "memory");
-        if (more) issue(ns, nt, IsV{});
+        if (more) issue(ns, nt, npg, IsV{});
         cs = ns;
         ct = nt;
     }

@@ -629,6 +629,12 @@ struct TileRole {
 template <class Role>
 __global__ __launch_bounds__(64 * NW, 1) void combined_kernel(CombinedArgs c) {
     unsigned char* const smem = wide_smem;
+    // The arguments that either role reads on its way to the first request: their lines, which no cache holds at the start of a launch (0.4 us each), are
+    // loaded at once instead of one behind the other.  1024 x 8/1 heads, 16K keys 79.5 -> 79.1 us, others equal.
+    asm volatile("" ::"s"(c.p.lv.K), "s"(c.p.Hkv), "s"(c.p.by_heads.mul), "s"(c.p.scale), "s"(c.p.out.O), "s"(c.p.out.part_stride_L), "s"(c.p.wide.n_c),
+                 "s"(c.p.wide.mode), "s"(c.p.wide.by_teams.mul), "s"(c.p.wide.by_cut[1].mul));
+    asm volatile("" ::"s"(c.d.Q), "s"(c.d.Ks), "s"(c.d.lengths), "s"(c.d.pg.table), "s"(c.d.max_len), "s"(c.d.nchunks), "s"(c.d.by_heads.mul),
+                 "s"(c.d.by_group.mul), "s"(c.d.scale), "s"(c.d.out.O), "s"(c.d.out.part_stride_L), "s"(c.n_more), "s"(c.tickets), "s"(c.n_tickets));
     if (blockIdx.x < 8 * c.p.wide.slots) {
         const wide_args_ptr first = (wide_args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
         for (int i = 0; i <= c.n_more; ++i) {

@@ -251,13 +251,13 @@ struct SmallArgs {
 };
 
 struct MergeArgs {
-    const void* O[HG_MAX_PARTS];
-    const float* L[HG_MAX_PARTS];
-    int n;
-    int64_t rows;
+    int64_t rows;     // (first what a wavefront needs whatever the parts; the kernel reads it with the first parts' pointers at its start)
     void* O_out;
     float* L_out;     // may be null
     unsigned* clear;  // a counter to set to zero, or null
+    int n;
+    const float* L[HG_MAX_PARTS];
+    const void* O[HG_MAX_PARTS];
 };
 
 // KV-cache update of a decode step: nq new rows per sequence appended to the suffix cache, lengths advanced.

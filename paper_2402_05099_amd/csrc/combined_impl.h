@@ -393,7 +393,9 @@ struct SuffixStream {
             const unsigned char* const p = kept_row(i);
             const float2 info = *reinterpret_cast<const float2*>(p + D * 4);
             const int unit = __builtin_bit_cast(int, info.y), row = (int)a.by_chunks.of((unsigned)unit), c = unit - row * a.nchunks;
-            *reinterpret_cast<float4*>(static_cast<float*>(a.out.O) + (int64_t)c * a.out.part_stride_O + (int64_t)row * D + col) = *reinterpret_cast<const float4*>(p + col * 4);
+            // (past the caches: the merge reads them once, see store_part)
+            __builtin_nontemporal_store(*reinterpret_cast<const uintx4*>(p + col * 4),
+                                        reinterpret_cast<uintx4*>(static_cast<float*>(a.out.O) + (int64_t)c * a.out.part_stride_O + (int64_t)row * D + col));
             if (col == 0) a.out.LSE[(int64_t)c * a.out.part_stride_L + row] = info.x;
         }
     }

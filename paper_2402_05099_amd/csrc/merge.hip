@@ -4,11 +4,15 @@
 
 namespace hg {
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
 // D/4 lanes per query row, 4 output elements per lane.  Parts with LSE = -inf are skipped (their O may
 // be uninitialised memory); a row whose parts are all empty becomes O = 0, LSE = -inf.
 // Parts are taken four at a time: their LSEs, then the O pieces of the non-empty ones, are loaded before any is
 // used, so that a lane has up to four 16-byte loads in flight; the running maximum is carried across groups (the
 // accumulators are rescaled when it grows), which equals the one-pass formula with the global maximum.
+// float parts are read, and a bfloat16 result is written, past the caches: each is touched once.  Median us: 8-bit rows, 4K keys
+// 225.8 -> 222.2 without and 217.1 with the loads (and the parts written that way), D = 64 181.9 -> 181.4, 174.9 -> 173.8.
 template <int D, bool IN_BF16, bool OUT_BF16>
 __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
     constexpr int LPR = D / 4;
@@ -49,7 +53,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
                     const uint2 v = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(O[u]) + row * D + 4 * c);
                     o[u][0] = bf16_lo(v.x); o[u][1] = bf16_hi(v.x); o[u][2] = bf16_lo(v.y); o[u][3] = bf16_hi(v.y);
                 } else {
-                    const float4 v = *reinterpret_cast<const float4*>(static_cast<const float*>(O[u]) + row * D + 4 * c);
+                    const floatx4 v = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(static_cast<const float*>(O[u]) + row * D + 4 * c));
                     o[u][0] = v.x; o[u][1] = v.y; o[u][2] = v.z; o[u][3] = v.w;
                 }
             }
@@ -80,10 +84,8 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
         for (int j = 0; j < 4; ++j) acc[j] *= inv;
     }
     if constexpr (OUT_BF16) {
-        uint2 v;
-        v.x = pack_bf16(acc[0], acc[1]);
-        v.y = pack_bf16(acc[2], acc[3]);
-        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.O_out) + row * D + 4 * c) = v;
+        const uint64_t v = pack_bf16(acc[0], acc[1]) | (uint64_t)pack_bf16(acc[2], acc[3]) << 32;
+        __builtin_nontemporal_store(v, reinterpret_cast<uint64_t*>(static_cast<uint16_t*>(a.O_out) + row * D + 4 * c));
     } else {
         *reinterpret_cast<float4*>(static_cast<float*>(a.O_out) + row * D + 4 * c) = make_float4(acc[0], acc[1], acc[2], acc[3]);
     }

@@ -478,11 +478,11 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     // columns of all 32 rows at a time, and leave it as whole 128-byte lines, eight rows per store instruction.
     // 16-byte chunk c of staged row r lives at chunk c ^ (r % 8): writes and reads are free of bank conflicts.
     // A wavefront whose 32 rows all exist issues exactly kStoresPerPiece store instructions; one with fewer rows, fewer.
-    // They are written past the caches, for the merge to read once: kept there, they drive out keys and values that other
-    // workgroups still read.  Median us, together with the merge's own loads and stores: 2048 x 40 heads, two levels 549.5 ->
+    // They are written past the caches, for the merge to read once.  What that saves is not the launch's traffic, which stays the same
+    // (2048 x 40 heads, two levels 3.10 -> 3.09 GB); presumably the writes leave at once and not as dirty lines under the reads.  Median us, together with the merge's own loads and stores: 2048 x 40 heads, two levels 549.5 ->
     // 524.7, D = 64, 4K keys 181.9 -> 173.8, 8-bit rows, 4K keys 225.8 -> 217.1, 256 x 40, 2K keys 122.1 -> 120.8, 1024 x 40, 16K
-    // keys 475.7 -> 470.7.  With the tiles of several query rows, whose rows the heads of a group share, it is the other way
-    // round: 32/8 heads, 4K keys 126.6 -> 127.4, four query rows a sequence 173.0 -> 173.5.
+    // keys 475.7 -> 470.7.  Beside the tiles of several query rows, whose own results stay in the L2, it is the other way
+    // round: 64/8 heads, 4K keys 126.6 -> 127.4, four query rows a sequence 173.0 -> 173.5.
     auto store_part = [](float* p, const float4& v) {
 #ifdef HG_COMBINED_TILES
         *reinterpret_cast<float4*>(p) = v;

@@ -435,8 +435,11 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     floatx16 Oacc[DB];
     float m_used;               // raw-score maximum the exponentials are taken against
     float lsum;                 // this lane's share of the row sum (of the unrounded exponentials)
-    float mc;                   // m_used * c2
+    float mc;                   // against(m_used)
     const float c2 = ka->scale * kLog2e;
+    // what the exponents are taken against: of a row with nothing but -inf so far a finite number, so that -inf has weight 0 and any finite score one
+    // that is infinite, which add_sum sees (clamped behind the product: with c2 > 1 the product of a finite number may be -inf)
+    auto against = [&](float m) { return fmaxf(m * c2, -3.4028234e38f); };
     // the weights of one stage (its scores against the present maximum), packed for the second product; returns this lane's sum of them
     auto weights = [&](const STile& S, uintx4 (&p)[KT / 16]) -> float {
         float sa = 0.f, sb = 0.f;
@@ -646,9 +649,8 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
             scores(0, SB);
             scores(1, SA);
             if (pc.nfull == 0) mask_stage(SB, 0);
-            // (a row with nothing but -inf so far keeps a finite maximum, against which any finite score's weight is infinite: see add_sum)
-            m_used = fmaxf(tile_max(SB), -3.4028234e38f);
-            mc = m_used * c2;
+            m_used = tile_max(SB);
+            mc = against(m_used);
             lsum = weights(SB, PA);
 #pragma unroll
             for (int i = 0; i < NVF; ++i) vf[i] = lds_v(0, i / DB, i % DB);
@@ -687,7 +689,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
                 const float m_new = fmaxf(m_used, tile_max(S));
                 const float alpha = (m_new == m_used) ? 1.0f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
                 m_used = m_new;
-                mc = m_new * c2;
+                mc = against(m_new);
                 lsum *= alpha;
 #pragma unroll
                 for (int i = 0; i < DB; ++i) {

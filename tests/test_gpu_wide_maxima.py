@@ -24,12 +24,15 @@ PROFILES = {
 @pytest.mark.parametrize("profile", PROFILES)
 @pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("P", [31, 32, 97, 333, 1100])
-def test_moving_maxima(profile, D, P):
-    B, H, scale = 300, 2, 1.0 / math.sqrt(D)      # two row tiles, the second one ragged
+@pytest.mark.parametrize("scaled_q", [False, True])      # queries that carry the scale: factor 1, by log2(e) more than 1 in the exponent
+def test_moving_maxima(profile, D, P, scaled_q):
+    B, H, scale = 300, 2, 1.0 if scaled_q else 1.0 / math.sqrt(D)      # two row tiles, the second one ragged
     if profile == "from_minus_inf" and P <= 70:
         pytest.skip("no finite score at all")
     rng = np.random.default_rng(P + D)
     q, k, v = (torch.from_numpy(rng.standard_normal(s).astype(np.float32)) for s in ((B, H, D), (P, H, D), (P, H, D)))
+    if scaled_q:
+        q /= math.sqrt(D)
     # one column carries the profile: rows of odd sequences see a hundredth of it, so that a wavefront's rows move apart
     q[..., 0] = torch.where(torch.arange(B) % 2 == 0, 1.0, 0.0078125)[:, None]
     k[..., 0] = torch.from_numpy(np.broadcast_to(PROFILES[profile](np.arange(P), P) / scale, (P,)).astype(np.float32).copy())[:, None]
@@ -37,7 +40,7 @@ def test_moving_maxima(profile, D, P):
     ctx = hb.Context(0, hb.hg_workspace_bytes(B, H, D, 16))
     ctx.set_option(hb.HG_OPT_PREFIX_KERNEL, 2)
     O, LSE = torch.empty(B, H, D, device="cuda"), torch.empty(B, H, device="cuda")
-    hb.hg_prefix_attn(ctx, q.cuda(), k.cuda(), v.cuda(), O, LSE)
+    hb.hg_prefix_attn(ctx, q.cuda(), k.cuda(), v.cuda(), O, LSE, scale=scale)
     s = torch.einsum("bhd,phd->bhp", q.double(), k.double()) * scale
     lse = torch.logsumexp(s, -1)
     ref = torch.einsum("bhp,phd->bhd", torch.exp(s - lse[..., None]), v.double())

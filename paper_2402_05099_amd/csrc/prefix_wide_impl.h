@@ -28,7 +28,7 @@
 //     anyway and is there a step before their product, says whether a stage has to be taken again against its own (add_sum).
 //     Before, with exponentials and product of a stage in one step and the maximum of every stage: 73 instead of 59 vector-ALU instructions per
 //     16 MFMAs (D = 64: 147 / 116).  The kernel runs at the board's power limit, so what counts is the energy of what it issues: 1024 x 40 heads,
-//     16K keys 303.5 -> 296 us with its merge (1365 -> 1325 cycles per stage), 512 x 64/8, 4K keys 74.9 -> 73.7, D = 64, 1024 x 40, 4K keys 63.2 -> 61.6; in the
+//     16K keys 310.8 -> 302.2 us with its merge, 512 x 64/8, 4K keys 74.9 -> 73.7, D = 64, 1024 x 40, 4K keys 63.2 -> 61.6; in the
 //     combined launch 256 x 64/8, four queries, 4K keys 179 -> 174, 1024 x 8/1, 16K keys 83.0 -> 81.6, 1024 x 40, 16K keys 480 -> 474.
 #include <algorithm>
 #include <numeric>
@@ -66,6 +66,7 @@ constexpr int INFLIGHT = AHEAD - 4;     // stages that may still be in flight at
 // 4 nats' deviation, 4096 keys, error of O 1.49e-3 at 65536, 8.2e-4 at 256 (8.2e-4 with a search that let maxima grow by 2^8); of 1 nat's
 // 1.61e-3 either way, in the same time: hardly a stage is taken again.  At 64, 256 x 64/8 heads, four queries, 4K keys 169.7 -> 170.7 us.
 constexpr float kMostWeight = 256.f;
+constexpr float kRoom = 16.f;           // log2 units, see add_sum
 static_assert(KT == NW * RPI, "one copy instruction per wavefront, stage and tensor");
 static_assert(kPrefixRowsWide == 32 * NW, "one 32-row query block per wavefront");
 
@@ -433,13 +434,9 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
 
     // ---- online softmax state ------------------------------------------------------------------------------------
     floatx16 Oacc[DB];
-    float m_used;               // raw-score maximum the exponentials are taken against
     float lsum;                 // this lane's share of the row sum (of the unrounded exponentials)
-    float mc;                   // against(m_used)
+    float mc;                   // what the exponents are taken against, log2 units
     const float c2 = ka->scale * kLog2e;
-    // what the exponents are taken against: of a row with nothing but -inf so far a finite number, so that -inf has weight 0 and any finite score one
-    // that is infinite, which add_sum sees (clamped behind the product: with c2 > 1 the product of a finite number may be -inf)
-    auto against = [&](float m) { return fmaxf(m * c2, -3.4028234e38f); };
     // the weights of one stage (its scores against the present maximum), packed for the second product; returns this lane's sum of them
     auto weights = [&](const STile& S, uintx4 (&p)[KT / 16]) -> float {
         float sa = 0.f, sb = 0.f;
@@ -507,7 +504,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
         const float ltot = half_sum(lsum);
         const float inv = 1.0f / ltot;
         const int my_row = qrc.rv ? (int)qrc.qidx : -1;            // query row index (b*nq + t)*Hq + h, below 2^31 / D
-        if (qrc.rv && hl == 0) k->out.LSE[q.sp * k->out.part_stride_L + qrc.qidx] = m_used * k->scale + __logf(ltot);
+        if (qrc.rv && hl == 0) k->out.LSE[q.sp * k->out.part_stride_L + qrc.qidx] = (mc + __log2f(ltot)) * kLn2;
         const int nvalid = min(q.nrows - (q.row0 + w * 32), 32);   // rows of this wavefront that exist (>= 1)
         unsigned char* const stg = smem + LDS_RING_BYTES + w * kStageBytes;
         float* const Of = static_cast<float*>(k->out.O) + q.sp * k->out.part_stride_O;
@@ -616,7 +613,6 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
         for (int i = 0; i < DB; ++i)
 #pragma unroll
             for (int k = 0; k < 16; ++k) Oacc[i][k] = 0.f;
-        m_used = -INFINITY;
         lsum = 0.f;
         mc = 0.f;
 
@@ -649,8 +645,9 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
             scores(0, SB);
             scores(1, SA);
             if (pc.nfull == 0) mask_stage(SB, 0);
-            m_used = tile_max(SB);
-            mc = against(m_used);
+            // (a finite number for a row with nothing but -inf, so that -inf has weight 0 and any finite score one that is infinite, which add_sum sees;
+            // clamped behind the product: with c2 > 1 the product of a finite number may be -inf)
+            mc = fmaxf(tile_max(SB) * c2, -3.4028234e38f);
             lsum = weights(SB, PA);
 #pragma unroll
             for (int i = 0; i < NVF; ++i) vf[i] = lds_v(0, i / DB, i % DB);
@@ -679,17 +676,23 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
             return ssum;
         };
         // The weights just taken are not too large for what they are summed with, or infinite, as long as their sum (at least as large as the
-        // largest of them) is small.  Otherwise the stage's scores are computed once more (its K rows are still in the ring) and its weights taken
-        // against the larger maximum; nothing has been multiplied with them yet.  (Exact: the stale maximum cancels in O/l and LSE.)
-        auto add_sum = [&](int j, int slot, float ssum, uintx4 (&pn)[KT / 16], auto masked) {
+        // largest of them) is small.  Otherwise they are taken again against the larger maximum, from the scores, whose registers the next step
+        // is the first to write; nothing has been multiplied with them yet.  (Exact: the stale maximum cancels in O/l and LSE.)
+        // Where most rows have moved, scores rise along the keys, and the maxima are set kRoom too large so that the next few stages are not taken again
+        // as well (a whole number: the largest weight stays a power of two, which bf16 holds exactly).  Single rows' outliers get no room: their largest
+        // weights would be rounded for the rest of the piece (error of O at 4 nats 1.19e-3 -> 1.5e-3 with room at every second one).
+        // us with a search for every stage's maximum / with the scores computed once more here and no room / now: 256 x 64/8 heads, four queries, 4K
+        // keys, scores of 1, 2, 4 nats' deviation 176.5 / 170.7 / 170.5, 178.3 / 174.6 / 173.7, 185.8 / 193.2 / 185.0, of 1 nat and rising by 40 and 400 nats 182.3 / 192.0 / 172.6,
+        // 197.1 / 251.6 / 188.4; D = 64, 1024 x 40, 4K keys, 1 and 4 nats 179.5 / 171.1 / 170.7, 180.6 / 175.8 / 174.6, rising by 40 and 400 180.4 / 177.2 / 171.1, 181.0 / 228.5 / 172.7.
+        // The block alone, 1024 x 40, 16K keys, 1 and 4 nats 310.8 / 298.4 / 302.2, 327.1 / 333.8 / 324.6, D = 64, 4K keys 62.4 / 59.6 / 59.3, 64.7 / 69.6 / 67.2.
+        // Error of O the same at 1 to 4 nats and up to 2^3 a stage; where scores rise by 2^9 a stage 1.1e-3 -> 1.6e-3 (1.65e-3 without a rise).
+        auto add_sum = [&](const STile& S, float ssum, uintx4 (&pn)[KT / 16]) {
             if (__builtin_expect(__any(!(ssum <= kMostWeight)), 0)) {
-                STile S;
-                scores((slot + 1) & (NS - 1), S);
-                if constexpr (decltype(masked)::value) mask_stage(S, j + 1);
-                const float m_new = fmaxf(m_used, tile_max(S));
-                const float alpha = (m_new == m_used) ? 1.0f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
-                m_used = m_new;
-                mc = against(m_new);
+                float top = tile_max(S) * c2;
+                if (__builtin_popcountll(__ballot(top > mc + 2.0f)) >= 48) top += kRoom;
+                const float mc_new = fmaxf(mc, top);
+                const float alpha = __builtin_amdgcn_exp2f(mc - mc_new);
+                mc = mc_new;
                 lsum *= alpha;
 #pragma unroll
                 for (int i = 0; i < DB; ++i) {
@@ -713,7 +716,7 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (!kPlain && j == zstep) clear_partial_v();
-            add_sum(j, slot, step_body(j, slot, pb, pn, Scur, Snext, Masked{}), pn, Masked{});
+            add_sum(Scur, step_body(j, slot, pb, pn, Scur, Snext, Masked{}), pn);
             if (kPlain) cursor_step();
             else cursor_advance();
         };

@@ -11,8 +11,10 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // Parts are taken four at a time: their LSEs, then the O pieces of the non-empty ones, are loaded before any is
 // used, so that a lane has up to four 16-byte loads in flight; the running maximum is carried across groups (the
 // accumulators are rescaled when it grows), which equals the one-pass formula with the global maximum.
-// float parts are read, and a bfloat16 result is written, past the caches: each is touched once.  Median us: 8-bit rows, 4K keys
-// 225.8 -> 222.2 without and 217.1 with the loads (and the parts written that way), D = 64 181.9 -> 181.4, 174.9 -> 173.8.
+// float parts are read past the caches: each is touched once.  With the shared blocks' parts written that way (store_part) median us 8-bit rows, 4K
+// keys 225.8 -> 217.1, D = 64 181.9 -> 173.8.  The result is not: its reader follows.  Stored past the caches as well, the call alone and with a kernel
+// that reads O after it: 256 x 40 heads, 2K keys 121.4 -> 121.7 and 123.8 -> 124.4, 8-bit rows, 1024 x 40, 4K keys 207.6 -> 207.3 and 211.7 -> 212.8, 2048 x 40, two
+// levels 495.5 -> 494.1 and 504.4 -> 503.8, 512 x 64/8 heads 134.4 -> 134.3 and 138.4 -> 138.1.
 template <int D, bool IN_BF16, bool OUT_BF16>
 __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
     constexpr int LPR = D / 4;
@@ -85,7 +87,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
     }
     if constexpr (OUT_BF16) {
         const uint64_t v = pack_bf16(acc[0], acc[1]) | (uint64_t)pack_bf16(acc[2], acc[3]) << 32;
-        __builtin_nontemporal_store(v, reinterpret_cast<uint64_t*>(static_cast<uint16_t*>(a.O_out) + row * D + 4 * c));
+        *reinterpret_cast<uint64_t*>(static_cast<uint16_t*>(a.O_out) + row * D + 4 * c) = v;
     } else {
         *reinterpret_cast<float4*>(static_cast<float*>(a.O_out) + row * D + 4 * c) = make_float4(acc[0], acc[1], acc[2], acc[3]);
     }

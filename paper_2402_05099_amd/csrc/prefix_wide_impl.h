@@ -481,11 +481,14 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     // columns of all 32 rows at a time, and leave it as whole 128-byte lines, eight rows per store instruction.
     // 16-byte chunk c of staged row r lives at chunk c ^ (r % 8): writes and reads are free of bank conflicts.
     // A wavefront whose 32 rows all exist issues exactly kStoresPerPiece store instructions; one with fewer rows, fewer.
-    // They are written past the caches, for the merge to read once.  What that saves is not the launch's traffic, which stays the same
-    // (2048 x 40 heads, two levels 3.10 -> 3.09 GB); presumably the writes leave at once and not as dirty lines under the reads.  Median us, together with the merge's own loads and stores: 2048 x 40 heads, two levels 549.5 ->
-    // 524.7, D = 64, 4K keys 181.9 -> 173.8, 8-bit rows, 4K keys 225.8 -> 217.1, 256 x 40, 2K keys 122.1 -> 120.8, 1024 x 40, 16K
-    // keys 475.7 -> 470.7.  Beside the tiles of several query rows, whose own results stay in the L2, it is the other way
-    // round: 64/8 heads, 4K keys 126.6 -> 127.4, four query rows a sequence 173.0 -> 173.5.
+    // fp32 results are parts, for the merge to read once, and written past the caches (those that hg_prefix_attn leaves in the caller's memory too: they are for hg_merge).  What
+    // that saves is not the launch's traffic, which stays the same (2048 x 40 heads, two levels 3.10 -> 3.09 GB); why it is faster has not been measured.  Median us with the merge's
+    // loads the same way: 2048 x 40 heads, two levels 549.5 -> 524.7, D = 64, 4K keys 181.9 -> 173.8, 8-bit rows, 4K keys 225.8 -> 217.1, 256 x 40, 2K keys 122.1 -> 120.8,
+    // 1024 x 40, 16K keys 475.7 -> 470.7; this store alone, six drawn calls of one query row 2.9 % in the mean, 373.7 -> 353.3 at most.  hg_prefix_attn to fp32, 1024 x 40, 512 keys 23.9 ->
+    // 22.7, with hg_suffix_attn and hg_merge 257.6 -> 257.5, D = 64, 1K keys 147.6 -> 146.8, 512 x 64/8, 1K keys 78.2 -> 77.9, 2048 x 40, 1K keys 529.6 -> 530.8.
+    // Beside the tiles of several query rows they are stored the ordinary way, which is as good in the calls this was drawn up on and not in all: past the caches
+    // 512 x 64/8 heads, 4K keys 134.4 -> 134.6, four query rows a sequence 171.0 -> 171.3, 128 x 32/8, paged 39.5 -> 39.4; 16 drawn calls from 35.1 -> 36.1 (272 x 64/8,
+    // 164 keys) over 80.1 -> 79.4 to 130.2 -> 124.8 (318 x 64/8, 379 keys, codes), 0.8 % faster in the mean.
     auto store_part = [](float* p, const float4& v) {
 #ifdef HG_COMBINED_TILES
         *reinterpret_cast<float4*>(p) = v;

@@ -92,14 +92,9 @@ __device__ __forceinline__ auto ldg_row(const unsigned char* base, unsigned off)
     else return ldg128<STREAM>(base, off);
 }
 
-// this lane's 8 elements of a row as fp32
+// this lane's 16 or 8 codes of a row as fp32
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void unpack8(const uint4& r, float (&f)[8]) {
-    f[0] = bf16_lo(r.x); f[1] = bf16_hi(r.x); f[2] = bf16_lo(r.y); f[3] = bf16_hi(r.y);
-    f[4] = bf16_lo(r.z); f[5] = bf16_hi(r.z); f[6] = bf16_lo(r.w); f[7] = bf16_hi(r.w);
-}
-// 16 codes
-__device__ __forceinline__ void unpack8(const uint4& r, float (&f)[16]) {
+__device__ __forceinline__ void unpack_codes(const uint4& r, float (&f)[16]) {
     const unsigned w[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -107,7 +102,7 @@ __device__ __forceinline__ void unpack8(const uint4& r, float (&f)[16]) {
         f[4 * j] = a.x; f[4 * j + 1] = a.y; f[4 * j + 2] = b.x; f[4 * j + 3] = b.y;
     }
 }
-__device__ __forceinline__ void unpack8(const uint2& r, float (&f)[8]) {
+__device__ __forceinline__ void unpack_codes(const uint2& r, float (&f)[8]) {
     const f32x2 a = __builtin_amdgcn_cvt_pk_f32_fp8((int)r.x, false), b = __builtin_amdgcn_cvt_pk_f32_fp8((int)r.x, true);
     const f32x2 c = __builtin_amdgcn_cvt_pk_f32_fp8((int)r.y, false), d = __builtin_amdgcn_cvt_pk_f32_fp8((int)r.y, true);
     f[0] = a.x; f[1] = a.y; f[2] = b.x; f[3] = b.y; f[4] = c.x; f[5] = c.y; f[6] = d.x; f[7] = d.y;
@@ -220,7 +215,7 @@ __device__ __forceinline__ void consume_batch(DecodeState<D, GT, EPL>& st, const
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 float v[EPL];
-                unpack8(bt.v[u], v);
+                unpack_codes(bt.v[u], v);
 #pragma unroll
                 for (int j = 0; j < EPL; ++j) st.acc[g][j] = fmaf(p[u], v[j], st.acc[g][j]);
             }
@@ -347,7 +342,7 @@ __device__ __forceinline__ void block_of(const LevelDev& lv, int b, int B, int& 
 // sums a lane keeps EPL / 4, those of columns combined_col(lane) and up (with 8 lanes to a row, lanes 8 apart keep the same ones).
 // The lanes that hold parts of a column are 8, 16 and 32 apart: a swap of 32-lane halves (rows of 16 lanes) between two registers and an
 // addition sum two columns at once, each in the half (row) that keeps it, in place of an exchange through LDS for every column (16 columns of
-// codes: 54 exchanges before, 14 swaps and as many additions now).  With scores of codes by dot products (24 -> 16 instructions a key) and sums that are rescaled
+// codes, maximum and sum: 54 exchanges before, 16 swaps and 6 rotations within rows of 16 lanes now).  With scores of codes by dot products (24 -> 16 instructions a key) and sums that are rescaled
 // past kLazy only: 1024 x 40 heads, 4K keys, suffixes of 32..128 codes 226.7 -> 223.6 us, error of O on the suffixes alone 1.17e-7 -> 1.00e-7;
 // bf16 rows, 256 x 40, 2K keys 122.0 -> 121.8, 1024 x 40, 16K keys 470.5 -> 469.7, 2048 x 40, two levels 548.7 -> 549.4.
 template <int D, int EPL>

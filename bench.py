@@ -359,12 +359,14 @@ def wide_timeline(args, hb, dev, wl, torch):
         assert L.hg_debug_read_wide_trace(buf.ctypes.data_as(ctypes.c_void_p)) == 0
         t = buf.reshape(256, 32).astype(np.float64)[:8 * plan["slots"]]
         t0 = t[:, 0].min()
+        ids = np.flatnonzero(t[:, 15] > 0)
+        t = t[ids]      # (a workgroup without a piece leaves at once, without stamps)
         print(f"level {li}: plan { {k: v for k, v in plan.items() if k not in ('starts', 'first_part')} }")
         print(f"  kernel span {(t[:, 15].max() - t0) / 100:.1f} us; workgroups start between 0 and {(t[:, 0].max() - t0) / 100:.1f} us (mean {(t[:, 0] - t0).mean() / 100:.2f}) "
               f"and leave between {(t[:, 15].min() - t0) / 100:.1f} and {(t[:, 15].max() - t0) / 100:.1f} us; from a workgroup's start to its first piece's entry "
               f"{(t[:, 1] - t[:, 0]).mean() / 100:.2f} (max {(t[:, 1] - t[:, 0]).max() / 100:.2f}): first piece looked up {(t[:, 24] - t[:, 0]).mean() / 100:.2f}, "
               f"copy cursor set {(t[:, 25] - t[:, 24]).mean() / 100:.2f}, two stages' copies issued {(t[:, 26] - t[:, 25]).mean() / 100:.2f}, Q requested "
-              f"{(t[:, 27] - t[:, 26]).mean() / 100:.2f}, five more stages {(t[:, 1] - t[:, 27]).mean() / 100:.2f}")
+              f"{(t[:, 27] - t[:, 26]).mean() / 100:.2f}, four more stages {(t[:, 1] - t[:, 27]).mean() / 100:.2f}")
         for p in range(3):
             b = 1 + 4 * p
             ok = t[:, b + 3] > t[:, b]
@@ -380,7 +382,7 @@ def wide_timeline(args, hb, dev, wl, torch):
         # piece 0 at, its cycles per stage, and when its workgroups left
         ok0 = t[:, 3] > t[:, 2]
         if ok0.all():
-            xcd = np.arange(t.shape[0]) & 7
+            xcd = ids & 7
             clk = t[:, 16] / ((t[:, 3] - t[:, 2]) * 10.0)
             cps = t[:, 16] / np.maximum(t[:, 13], 1)
             print("  by XCD (workgroup id % 8): clock GHz " + " ".join(f"{clk[xcd == x].mean():.3f}" for x in range(8))

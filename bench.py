@@ -359,7 +359,7 @@ def wide_timeline(args, hb, dev, wl, torch):
         assert L.hg_debug_read_wide_trace(buf.ctypes.data_as(ctypes.c_void_p)) == 0
         t = buf.reshape(256, 32).astype(np.float64)[:8 * plan["slots"]]
         t0 = t[:, 0].min()
-        ids = np.flatnonzero(t[:, 15] > 0)
+        ids = np.flatnonzero(t[:, 15] > t[:, 0])
         t = t[ids]      # (a workgroup without a piece leaves at once, without stamps)
         print(f"level {li}: plan { {k: v for k, v in plan.items() if k not in ('starts', 'first_part')} }")
         print(f"  kernel span {(t[:, 15].max() - t0) / 100:.1f} us; workgroups start between 0 and {(t[:, 0].max() - t0) / 100:.1f} us (mean {(t[:, 0] - t0).mean() / 100:.2f}) "

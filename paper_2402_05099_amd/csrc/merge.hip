@@ -12,9 +12,11 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // used, so that a lane has up to four 16-byte loads in flight; the running maximum is carried across groups (the
 // accumulators are rescaled when it grows), which equals the one-pass formula with the global maximum.
 // float parts are read past the caches: each is touched once.  With the shared blocks' parts written that way (store_part) median us 8-bit rows, 4K
-// keys 225.8 -> 217.1, D = 64 181.9 -> 173.8.  The result is not: its reader follows.  Stored past the caches as well, the call alone and with a kernel
-// that reads O after it: 256 x 40 heads, 2K keys 121.4 -> 121.7 and 123.8 -> 124.4, 8-bit rows, 1024 x 40, 4K keys 207.6 -> 207.3 and 211.7 -> 212.8, 2048 x 40, two
-// levels 495.5 -> 494.1 and 504.4 -> 503.8, 512 x 64/8 heads 134.4 -> 134.3 and 138.4 -> 138.1.
+// keys 225.8 -> 217.1, D = 64 181.9 -> 173.8.  A bfloat16 result is written past them too, although its reader follows: it then does not leave the caches under the next call's reads.
+// Inputs changing from call to call, ordinary store / this one, call alone, with a kernel that scales O, with a matrix product of it: 2048 x 40 heads, two levels 531.3 / 522.4, 535.0 /
+// 531.5, 605.4 / 604.9; 8-bit rows, 1024 x 40, 4K keys 222.9 / 218.1, 222.7 / 222.7, 270.8 / 271.0; 1024 x 40, 16K keys 479.2 / 479.5, 481.8 / 481.2, 531.9 / 531.6; 256 x 64/8, four
+// queries 173.6 / 173.7, 179.0 / 180.4, 251.7 / 251.9; 256 x 40, 2K keys 125.0 / 125.0, 126.1 / 126.2, 151.5 / 152.0.  (The same inputs every time: no difference but 0.2 to 0.5 % that the scaling
+// loses.)  An fp32 result is not: D = 64, 4K keys 172.2 ordinary, 172.8 past the caches, with the scaling 176.7 / 177.5, eight drawn calls 0.999 and 0.995 in the mean, 172.2 / 174.5 at worst.
 template <int D, bool IN_BF16, bool OUT_BF16>
 __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
     constexpr int LPR = D / 4;
@@ -87,7 +89,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
     }
     if constexpr (OUT_BF16) {
         const uint64_t v = pack_bf16(acc[0], acc[1]) | (uint64_t)pack_bf16(acc[2], acc[3]) << 32;
-        *reinterpret_cast<uint64_t*>(static_cast<uint16_t*>(a.O_out) + row * D + 4 * c) = v;
+        __builtin_nontemporal_store(v, reinterpret_cast<uint64_t*>(static_cast<uint16_t*>(a.O_out) + row * D + 4 * c));
     } else {
         *reinterpret_cast<float4*>(static_cast<float*>(a.O_out) + row * D + 4 * c) = make_float4(acc[0], acc[1], acc[2], acc[3]);
     }

@@ -484,11 +484,11 @@ __device__ __forceinline__ void wide_role(const wide_args_ptr ka) {
     // fp32 results are parts, for the merge to read once, and written past the caches (those that hg_prefix_attn leaves in the caller's memory too: they are for hg_merge).  What
     // that saves is not the launch's traffic, which stays the same (2048 x 40 heads, two levels 3.10 -> 3.09 GB); why it is faster has not been measured.  Median us with the merge's
     // loads the same way: 2048 x 40 heads, two levels 549.5 -> 524.7, D = 64, 4K keys 181.9 -> 173.8, 8-bit rows, 4K keys 225.8 -> 217.1, 256 x 40, 2K keys 122.1 -> 120.8,
-    // 1024 x 40, 16K keys 475.7 -> 470.7; this store alone, six drawn calls of one query row 2.9 % in the mean, 373.7 -> 353.3 at most.  hg_prefix_attn to fp32, 1024 x 40, 512 keys 23.9 ->
+    // 1024 x 40, 16K keys 475.7 -> 470.7; this store alone, the same inputs every time, six drawn calls of one query row 2.9 % in the mean, 373.7 -> 353.3 at most.  hg_prefix_attn to fp32, 1024 x 40, 512 keys 23.9 ->
     // 22.7, with hg_suffix_attn and hg_merge 257.6 -> 257.5, D = 64, 1K keys 147.6 -> 146.8, 512 x 64/8, 1K keys 78.2 -> 77.9, 2048 x 40, 1K keys 529.6 -> 530.8.
-    // Beside the tiles of several query rows they are stored the ordinary way, which is as good in the calls this was drawn up on and not in all: past the caches
-    // 512 x 64/8 heads, 4K keys 134.4 -> 134.6, four query rows a sequence 171.0 -> 171.3, 128 x 32/8, paged 39.5 -> 39.4; 16 drawn calls from 35.1 -> 36.1 (272 x 64/8,
-    // 164 keys) over 80.1 -> 79.4 to 130.2 -> 124.8 (318 x 64/8, 379 keys, codes), 0.8 % faster in the mean.
+    // Beside the tiles of several query rows they are stored the ordinary way, which is as good in the calls that the choice was made on, not in all: past the caches, inputs
+    // changing from call to call, 512 x 64/8 heads, 4K keys 133.9 -> 134.4, 256 x 64/8, four queries 170.5 -> 170.8, 128 x 32/8, paged 41.2 -> 41.2; 16 drawn calls 0.8 % faster in the
+    // mean, from 58.5 -> 59.7 (1416 x 4/4, four queries, 1850 keys, codes) and 37.4 -> 37.8 (272 x 64/8, 164 keys) over 81.5 -> 81.0 to 129.6 -> 124.8 (318 x 64/8, 379 keys, codes) and 572 -> 553.
     auto store_part = [](float* p, const float4& v) {
 #ifdef HG_COMBINED_TILES
         *reinterpret_cast<float4*>(p) = v;
